@@ -21,8 +21,9 @@ SOURCES = {
     "api.hip": [],
     "decode.hip": [],
     "cache.hip": [],
-    # the softmax bookkeeping never sees NaNs (masked scores are -inf): drop the NaN-quieting copies around max
-    "prefill.hip": ["-fno-honor-nans"],
+    # the softmax bookkeeping never sees NaNs (masked scores are -inf): drop the NaN-quieting copies around max.
+    # Matrix results in ordinary registers: the accumulation half belongs to the accumulators the source names.
+    "prefill.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
     "project.hip": [],
     # bit-exact k-means: no fused multiply-add, no reassociation
     "kmeans.hip": ["-ffp-contract=off", "-fno-fast-math"],

@@ -13,7 +13,7 @@
 // probabilities is already in the B-operand layout of O^T += V^T P^T.  That second product runs in fp16 (P in
 // [0,256] keeps 11 bits instead of bf16's 8).  Its A operand needs 8 keys of one value column per lane, which a
 // row-major V cache cannot deliver, so a first kernel writes V^T once per call: fp16 (exact from bf16 inside
-// the fp16 range, |v| <= 65504), in blocks of 32 keys x 128 columns, keys permuted inside every group of 16 into
+// the fp16 range, |v| <= 65504), in blocks of 64 keys x 128 columns, keys permuted inside every group of 16 into
 // the order the probability registers have, zero beyond the last key.  The main kernel then stages K and V^T
 // tiles in LDS with 16-byte direct loads and feeds every MFMA operand with one ds_read_b128.  (The LDS transpose
 // reads of this chip could hand the operand over from a row-major bf16 tile and make the pre-pass unnecessary,
@@ -26,18 +26,15 @@
 #include <hip/hip_ext.h>
 
 #include <type_traits>
+#include <utility>
 
 namespace chai {
 
 namespace {
 
 constexpr int kGroup = 2;          // member heads that share one score tile
-constexpr int kPairedRounds = 4;     // launches of fewer rounds of 256 paired workgroups send single tiles instead
-constexpr int kRec = 2 + kGroup;   // ints per work-list record: cluster, member count, members
-constexpr int kQWave = 32;         // query rows per wave
-constexpr int kPWaves = 8;         // waves per workgroup (two per SIMD: one's MFMAs overlap the other's VALU work)
-constexpr int kPBlock = kPWaves * 64;
-constexpr int kQTile = kQWave * kPWaves;   // 256 query rows per workgroup
+constexpr int kRec = 2 + kGroup;   // ints per work-list record: cluster and member count, members, representative
+constexpr int kRecCount = 24;      // the member count stands above this bit of a record's first word
 constexpr int kKTile = 64;         // keys per tile
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kRescaleSlack = 8.0f;      // log2 units a tile may exceed the running maximum before a rescale
@@ -68,15 +65,78 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
 __device__ __forceinline__ int key_slot16(int r16) { return 8 * ((r16 & 7) >> 2) + 4 * (r16 >> 3) + (r16 & 3); }
 
 // ---------------------------------------------------------------------------------------------------------
-// V^T in blocks of 32 keys: vt[b][h][t/32][dd][16*((t%32)/16) + key_slot16(t%16)] = fp16(V[b][h][t][dd]) for
-// t < n_keys, 0 up to Tp (a multiple of 64).  A block is 8 KB of consecutive memory, so the main kernels stage it
-// with fully coalesced 16-byte loads.  grid (Tp/64, H, B), 256 threads; a 64 x 128 tile goes through LDS.
+// Work list: the heads of every cluster, in ascending order, cut into groups of at most kGroup members.
+// groups[b][g] = {cluster | n << kRecCount, head_0 .., representative}, kRec ints per record; clusters in ascending order.  One
+// workgroup per batch row: the membership row is copied to LDS, thread j counts cluster j, thread h ranks head h among
+// the heads of its cluster, and every head writes its own slot.  Heads that name no live cluster are left out.
+// lds: (H + 2k) ints.
 // ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void vt_kernel(const char *__restrict__ v, int H, int T_cap, int n_keys, int Tp,
-                                                 _Float16 *__restrict__ vt)
+__device__ __forceinline__ void plan_row(const int32_t *__restrict__ h2c, const int32_t *__restrict__ rep, int H, int k,
+                                         int max_groups, int32_t *__restrict__ groups, int32_t *__restrict__ n_groups,
+                                         int b, int32_t *lds)
 {
-    __shared__ _Float16 tile[kHeadDim][kKTile + 2];
-    const int tid = threadIdx.x, t0 = blockIdx.x * kKTile, h = blockIdx.y, b = blockIdx.z;
+    int32_t *member = lds, *count = lds + H, *base = count + k;
+    const int tid = threadIdx.x, n_thr = blockDim.x;
+    for (int h = tid; h < H; h += n_thr) {
+        const int c = h2c[(size_t)b * H + h];
+        member[h] = (c >= 0 && c < k && rep[(size_t)b * k + c] >= 0) ? c : -1;
+    }
+    __syncthreads();
+    for (int j = tid; j < k; j += n_thr) {
+        int n = 0;
+        for (int h = 0; h < H; ++h) n += member[h] == j;
+        count[j] = n;
+    }
+    __syncthreads();
+    for (int j = tid; j < k; j += n_thr) {
+        int first = 0;
+        for (int i = 0; i < j; ++i) first += (count[i] + kGroup - 1) / kGroup;
+        base[j] = first;
+        if (j == k - 1) {
+            const int ng = first + (count[j] + kGroup - 1) / kGroup;
+            n_groups[b] = ng < max_groups ? ng : max_groups;
+        }
+    }
+    __syncthreads();
+    int32_t *g = groups + (size_t)b * max_groups * kRec;
+    for (int h = tid; h < H; h += n_thr) {
+        const int c = member[h];
+        if (c < 0) continue;
+        int rank = 0;
+        for (int i = 0; i < h; ++i) rank += member[i] == c;
+        const int gi = base[c] + rank / kGroup, slot = rank % kGroup;
+        if (gi >= max_groups) continue;
+        g[gi * kRec + 1 + slot] = h;
+        if (slot == 0) {
+            const int left = count[c] - rank;
+            g[gi * kRec] = c | (left < kGroup ? left : kGroup) << kRecCount;
+            g[gi * kRec + 1 + kGroup] = min(rep[(size_t)b * k + c], H - 1);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Pre-pass, one launch.  V^T in blocks of 64 keys: vt[b][h][t/64][dd][16*((t%64)/16) + key_slot16(t%16)] =
+// fp16(V[b][h][t][dd]) for t < n_keys, 0 up to Tp (a multiple of 64).  A block is 16 KB of consecutive memory with whole
+// cache lines per value column, which is what the main kernels' direct loads to LDS ask for (rows of 64 bytes in blocks
+// of 32 keys made each of those loads touch twice as many lines).  grid (Tp/64 + 1, H, B), 256 threads; a 64 x 128 tile
+// goes through LDS.  The workgroups with blockIdx.x = 0 make the work list, one per batch row (h2c != NULL; a launch of
+// its own took 5 us for a few thousand instructions); dynamic LDS: the tile, or what
+// plan_row needs if that is more.
+// ---------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v, int H, int T_cap, int n_keys, int Tp,
+                                                      _Float16 *__restrict__ vt, const int32_t *__restrict__ h2c,
+                                                      const int32_t *__restrict__ rep, int k, int max_groups,
+                                                      int32_t *__restrict__ groups, int32_t *__restrict__ n_groups)
+{
+    extern __shared__ __attribute__((aligned(16))) char pre_lds[];
+    _Float16 (*tile)[kKTile + 2] = reinterpret_cast<_Float16 (*)[kKTile + 2]>(pre_lds);
+    const int tid = threadIdx.x, h = blockIdx.y, b = blockIdx.z;
+    if (blockIdx.x == 0) {
+        if (h == 0 && h2c != nullptr) plan_row(h2c, rep, H, k, max_groups, groups, n_groups, b, reinterpret_cast<int32_t *>(pre_lds));
+        return;
+    }
+    const int block = (int)blockIdx.x - 1, t0 = block * kKTile;
     const char *vhead = v + ((size_t)b * H + h) * (size_t)T_cap * (kHeadDim * 2);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -90,243 +150,349 @@ __global__ __launch_bounds__(256) void vt_kernel(const char *__restrict__ v, int
         for (int e = 0; e < 8; ++e) tile[c8 * 8 + e][slot] = (_Float16)(float)x.bf[e];
     }
     __syncthreads();
-    _Float16 *dst = vt + (((size_t)b * H + h) * (Tp / 32) + t0 / 32) * (size_t)(kHeadDim * 32);
+    _Float16 *dst = vt + (((size_t)b * H + h) * (Tp / kKTile) + block) * (size_t)(kHeadDim * kKTile);
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-        const int idx = tid + i * 256, c8 = idx & 7, dd = (idx >> 3) & (kHeadDim - 1), blk = idx >> 10;   // 4 keys each
-        const unsigned int lo = *reinterpret_cast<const unsigned int *>(&tile[dd][blk * 32 + c8 * 4]);
-        const unsigned int hi = *reinterpret_cast<const unsigned int *>(&tile[dd][blk * 32 + c8 * 4 + 2]);
-        *reinterpret_cast<uint2 *>(dst + ((size_t)blk * kHeadDim + dd) * 32 + c8 * 4) = make_uint2(lo, hi);
+        const int idx = tid + i * 256, c4 = idx & 15, dd = idx >> 4;                                       // 4 keys each
+        const unsigned int lo = *reinterpret_cast<const unsigned int *>(&tile[dd][c4 * 4]);
+        const unsigned int hi = *reinterpret_cast<const unsigned int *>(&tile[dd][c4 * 4 + 2]);
+        *reinterpret_cast<uint2 *>(dst + (size_t)dd * kKTile + c4 * 4) = make_uint2(lo, hi);
     }
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Work list: the heads of every cluster, in ascending order, cut into groups of at most `gsize` (<= kGroup).
-// groups[b][g] = {cluster, n, head_0 .. }, kRec ints per record; clusters in ascending order.  One workgroup per
-// batch row: the membership row is copied to LDS, thread j counts cluster j, thread h ranks head h among the
-// heads of its cluster, and every head writes its own slot.  Heads that name no live cluster are left out.
-// Dynamic LDS: (H + 2k) ints.
-// ---------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void prefill_plan_kernel(const int32_t *__restrict__ h2c,
-                                                           const int32_t *__restrict__ rep, int H, int k, int gsize,
-                                                           int max_groups, int32_t *__restrict__ groups,
-                                                           int32_t *__restrict__ n_groups)
-{
-    extern __shared__ int32_t plan_lds[];
-    int32_t *member = plan_lds, *count = plan_lds + H, *base = count + k;
-    const int b = blockIdx.x, tid = threadIdx.x;
-    for (int h = tid; h < H; h += blockDim.x) {
-        const int c = h2c[(size_t)b * H + h];
-        member[h] = (c >= 0 && c < k && rep[(size_t)b * k + c] >= 0) ? c : -1;
-    }
-    __syncthreads();
-    for (int j = tid; j < k; j += blockDim.x) {
-        int n = 0;
-        for (int h = 0; h < H; ++h) n += member[h] == j;
-        count[j] = n;
-    }
-    __syncthreads();
-    for (int j = tid; j < k; j += blockDim.x) {
-        int first = 0;
-        for (int i = 0; i < j; ++i) first += (count[i] + gsize - 1) / gsize;
-        base[j] = first;
-        if (j == k - 1) {
-            const int ng = first + (count[j] + gsize - 1) / gsize;
-            n_groups[b] = ng < max_groups ? ng : max_groups;
-        }
-    }
-    __syncthreads();
-    int32_t *g = groups + (size_t)b * max_groups * kRec;
-    for (int h = tid; h < H; h += blockDim.x) {
-        const int c = member[h];
-        if (c < 0) continue;
-        int rank = 0;
-        for (int i = 0; i < h; ++i) rank += member[i] == c;
-        const int gi = base[c] + rank / gsize, slot = rank % gsize;
-        if (gi >= max_groups) continue;
-        g[gi * kRec + 2 + slot] = h;
-        if (slot == 0) {
-            const int left = count[c] - rank;
-            g[gi * kRec] = c;
-            g[gi * kRec + 1] = left < gsize ? left : gsize;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------------------------
-// Main kernel.  1-D grid of ceil(n_qt / 2) * n_slots * B workgroups of 512 threads; IDENT: every head is its own cluster
-// (dense attention) and the work list is not read.
+// Main kernel.  Workgroups of four waves, one per SIMD; a wave owns U (2 or 1) streams of 32 query rows and the
+// accumulators of up to kGroup member heads for them (256 or 128 accumulation registers).
 //
-// A score block is shared by the TWO members whose accumulators one wave can hold.  Two wider schemes were built,
-// passed the same parity tests and measured no faster on the LLaMa-7B shape, so neither is kept:
-//  * four members through LDS -- the two waves of a SIMD own the same 32 query rows and two members each, take
-//    turns producing the probabilities of a 32-key block and hand them over in the B-operand layout, one barrier
-//    per block: 670-840 us per 8-cluster layer in three schedules against 578 us for pairs (128 query rows per
-//    workgroup double the staging per flop, and the producer's chain scores -> softmax -> publish is not hidden
-//    by its partner);
-//  * three members in ONE wave -- four waves per workgroup, one per SIMD, 192 accumulation registers of
-//    accumulators (a fourth member does not fit: the compiler keeps every MFMA result, the score block's
-//    included, in the accumulation half), the loop software-pipelined by hand (value products of block i-1, score
-//    product of block i+1 and softmax of block i interleaved instruction by instruction, LDS fragments four
-//    MFMAs ahead, rings of three 32-key blocks): equal to pairs when every cluster has exactly three heads
-//    (592 against 596 us), 630 us against 553 us on the benchmark's membership and 1000 against 730 us when
-//    every head is its own cluster.  A single wave per SIMD issues about eight vector instructions per MFMA and
-//    nothing else fills its waits.
+// Per 32-key block i of its keys a wave has three independent pieces of work, from three successive blocks: the value
+// products of block i-1, the softmax of block i, the score products of block i+1.  One straight stretch of code (`body`)
+// interleaves them instruction by instruction: a SLOT is one 16-byte LDS fragment and the U MFMAs that multiply with
+// it (both streams of a wave use every fragment, which halves the LDS reads per MFMA: 24 KB instead of 48 KB per 64 rows
+// and block), value and score slots alternate so that no MFMA waits for the one before it, the maxima stand behind the
+// first MFMAs and the exponentials behind the others (OpSchedule).  Fragments are requested kAhead slots ahead, also
+// across the end of a block: the next block's keys and values are always in LDS already.
 //
-// Workgroup -> work item: the hardware deals consecutive workgroup ids round-robin to the 8 XCDs, each with an L2
-// of its own.  The ids are therefore re-numbered so that every XCD owns a contiguous range of (batch row, group)
-// pairs with all their query tiles (largest first): the tiles of one group stream the same keys and values and
-// now find them in the same L2.
+// What bounds it, two members, U = 2 (cycles of one wave per 64-key tile; the MFMAs alone are 96 x 32 = 3072): 4500 to
+// 4600 on a chip with free CUs -- the replayed body is 2 x 1940 (MFMA only 1536, + LDS reads 1570, + vector work 1700,
+// all of it 1940: issue slots), the 12 direct loads to LDS about 25 each, the barrier 40 to 150 -- and about 5000 with every
+// CU busy, at 1.8 to 1.9 GHz instead of 2.4: the chip lowers its clock on this data (the matrix pipe alone reaches 64 % of
+// its nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
+// tile adds 11 us for its start, the diagonal that the four waves finish one after the other, and the output rows.
+// Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls: 16 rows x 2043
+// positions, 32 heads in 8 clusters 632 -> 616 us; 4 rows x 4000, 4 clusters 520 -> 472 us (with the balanced numbering
+// below); 1 row x 2043 94 -> 61 us; 256 positions behind 1792 keys, 4 rows x 52 heads 131 -> 97 us.
 //
-// LDS (dynamic): three K tiles and two V^T tiles per member.  K runs one tile ahead of V^T because the scores of
-// a 32-key block are issued one block before its softmax (the matrix pipe works on the next block's scores while
-// the vector ALUs exponentiate this one), and the extra buffer of each kind lets tile t+2 / t+1 be written while
-// tile t is read: ONE barrier per 64-key tile.
+// U = 1 halves a workgroup's rows for launches that leave CUs without work (rule in launch_prefill): a wave's LDS
+// reads per MFMA double, but twice as many CUs work, on half as long a chain.
+//
+// LDS: rings of three K and three V^T tiles (64 keys).  While tile t is computed, K(t+2) and V(t+1) are loaded with
+// direct loads, requested in the first half of the tile; K runs ahead of V because the scores of a block are issued one
+// block before its softmax, and V lags because its products come one block after.  ONE barrier per tile.
+//
+// A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
+// through LDS (670-840 against 578 us per 8-cluster LLaMa-7B layer), three members in one wave (630 against 553 us).
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kKBufs = 3, kVBufs = 2;
+constexpr int kWaves = 4, kThreads = kWaves * 64;
+constexpr int kBufs = 3;
 constexpr size_t kKBufBytes = (size_t)kKTile * kHeadDim * 2;        // 64 rows of 256 B (16 pieces), swizzled
 constexpr size_t kVBufBytes = (size_t)kHeadDim * kKTile * 2;        // one member: 128 rows of 128 B (8 pieces), swizzled
-constexpr size_t prefill_lds_bytes(bool ident) { return kKBufs * kKBufBytes + kVBufs * (ident ? 1 : kGroup) * kVBufBytes; }
+constexpr size_t kLdsBytes = kBufs * (kKBufBytes + kGroup * kVBufBytes);
 
+// ---------------------------------------------------------------------------------------------------------
+// Which query tiles of which (batch row, group) a workgroup takes.  The hardware deals consecutive workgroup ids
+// round-robin to the 8 XCDs, each with an L2 of its own, and hands the next id of an XCD to the first of its 32 CUs
+// that is free (one workgroup fits a CU).  The unit is a PAIR of query tiles of one group, the p-th largest and the
+// p-th smallest: under the causal mask tile q walks q+1 key tiles' worth of work, so all pairs cost the same.  The
+// pairs that EXIST (the groups of all rows, counted here from the plan) are dealt to the XCDs in equal contiguous
+// ranges, so that the pairs of one group share its keys and values in one L2.  Within an XCD whole rounds of 32 pairs
+// go out first; the last 32 to 63 pairs go out as single tiles, the largest first, which fills the last round.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kXcds = 8, kXcdCus = 32;
+constexpr int kSmallTiles = 600;
+struct PrefillWork {
+    int b, gi;           // batch row, group (identity: head)
+    int qt0, qt1, n_pass;   // query tiles
+};
 template <bool IDENT>
-__global__ __launch_bounds__(kPBlock) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
-                                                          const _Float16 *__restrict__ vt,
-                                                          const int32_t *__restrict__ rep,
-                                                          const int32_t *__restrict__ groups,
-                                                          const int32_t *__restrict__ n_groups, int H, int k, int Tq,
-                                                          int q_start, int Tc_cap, int Tp, int n_qt_arg, int n_slots,
-                                                          int n_rows, float scale, float *__restrict__ out)
+__device__ __forceinline__ bool find_work(const int32_t *__restrict__ n_groups, int n_rows, int H, int n_qt, PrefillWork &work)
 {
-    constexpr int G = IDENT ? 1 : kGroup;
-    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
-    char *const k_lds = lds_raw;                                   // [kKBufs][kKTile][128] bf16, swizzled rows
-    char *const v_lds = lds_raw + kKBufs * kKBufBytes;             // [kVBufs][G][kHeadDim][kKTile] fp16, swizzled rows
-
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r = lane & 31, hl = lane >> 5;
-
-    // A work item is a PAIR of query tiles, the p-th largest and the p-th smallest of a group: under the causal
-    // mask tile q walks q+1 key tiles' worth of work, so every pair costs the same and the workgroups of a launch
-    // finish together instead of leaving a tail of long ones.
-    // (n_qt < 0: a small launch; every tile is then an item of its own, see the numbering above.  On launches of
-    // many rounds single tiles measured 3-8 % SLOWER than pairs: the tiles of a group no longer run side by side and
-    // stop sharing its keys and values in L2.)
-    const bool paired = n_qt_arg > 0;
-    const int n_qt = paired ? n_qt_arg : -n_qt_arg;
-    const int n_pairs = paired ? (n_qt + 1) / 2 : n_qt;
-    int pi, gi, b;
-    if (paired) {
-        const unsigned n = blockIdx.x, N = gridDim.x;
-        const unsigned x = n & 7u, per = N >> 3, rem = N & 7u;
-        const unsigned item = x * per + min(x, rem) + (n >> 3);
-        pi = (int)(item % (unsigned)n_pairs);
-        const unsigned rest = item / (unsigned)n_pairs;
-        gi = (int)(rest % (unsigned)n_slots);
-        b = (int)(rest / (unsigned)n_slots);
-    } else {
-        // single tiles, the largest first: XCD x owns `per_xcd` consecutive (batch row, group) slots, and its
-        // workgroups come in the order tile n_qt-1 of every slot, then tile n_qt-2 of every slot, ...; the hardware
-        // hands the next workgroup to the first CU that is free, which is longest-job-first list scheduling
-        const unsigned n = blockIdx.x, x = n & 7u, local = n >> 3;
-        const unsigned per_xcd = gridDim.x / (8u * (unsigned)n_qt);
-        const unsigned slot = x * per_xcd + local % per_xcd;
-        if (slot >= (unsigned)(n_slots * n_rows)) return;
-        pi = (int)(local / per_xcd);
-        gi = (int)(slot % (unsigned)n_slots);
-        b = (int)(slot / (unsigned)n_slots);
+    const int lane = threadIdx.x & 63;
+    const int n_pairs = (n_qt + 1) / 2;
+    long long total = 0;
+    if (IDENT) total = (long long)n_rows * H;
+    else {
+        for (int r0 = 0; r0 < n_rows; r0 += 64) {
+            int c = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
+            total += c;
+        }
     }
-
-    int cluster, n_mem, heads[G];
+    const int xcd = blockIdx.x % kXcds;
+    const long long local = blockIdx.x / kXcds, pairs = total * n_pairs;
+    const long long lo = pairs * xcd / kXcds, hi = pairs * (xcd + 1) / kXcds;
+    const long long rounds = (hi - lo) / kXcdCus - 1;
+    const long long mid = lo + (rounds > 0 ? rounds * kXcdCus : 0);          // pairs lo .. mid-1, then single tiles
+    long long group;
+    if (local < mid - lo) {
+        const long long at = lo + local;
+        group = at / n_pairs;
+        const int pi = (int)(at % n_pairs);
+        work.qt0 = n_qt - 1 - pi;
+        work.qt1 = pi;
+        work.n_pass = work.qt0 > pi ? 2 : 1;                               // the middle tile of an odd count is alone
+    } else {
+        if (mid >= hi) return false;
+        const long long first = mid / n_pairs, n_first = (hi - 1) / n_pairs - first + 1, m = n_first * n_pairs;
+        long long j = local - (mid - lo);
+        if (j >= 2 * m) return false;
+        const bool large = j < m;
+        if (!large) j -= m;
+        const int pi = large ? (int)(j / n_first) : n_pairs - 1 - (int)(j / n_first);
+        group = first + j % n_first;
+        const long long at = group * n_pairs + pi;
+        if (at < mid || at >= hi || (!large && n_qt - 1 - pi == pi)) return false;
+        work.qt0 = large ? n_qt - 1 - pi : pi;
+        work.qt1 = 0;
+        work.n_pass = 1;
+    }
     if (IDENT) {
-        cluster = gi; n_mem = 1;
-        heads[0] = gi;
-    } else {
-        if (gi >= n_groups[b]) return;
-        const int32_t *gr = groups + ((size_t)b * n_slots + gi) * kRec;
-        cluster = min(max(gr[0], 0), k - 1);
-        n_mem = min(max(gr[1], 1), kGroup);
-#pragma unroll
-        for (int g = 0; g < G; ++g) heads[g] = min(max(gr[2 + min(g, n_mem - 1)], 0), H - 1);
+        work.b = (int)(group / H);
+        work.gi = (int)(group % H);
+        return true;
     }
-    const int rhead = IDENT ? cluster : min(max(rep[(size_t)b * k + cluster], 0), H - 1);
-
-    const float scale2 = scale * kLog2e;
-    const int n_pass = (paired && (n_qt - 1 - pi) > pi) ? 2 : 1;     // the middle tile of an odd count is alone
-    for (int pass = 0; pass < n_pass; ++pass) {
-    const int qt = pass == 0 ? n_qt - 1 - pi : pi;
-    const int i0 = qt * kQTile + w * kQWave;                 // first query row of this wave (relative)
-    const int my_i = i0 + r;                                 // this lane's query row
-    const int q_abs = q_start + min(my_i, Tq - 1);           // its sequence position (clamped for padding rows)
-    const int wave_first = q_start + min(i0, Tq - 1);
-    const int wave_last = q_start + min(i0 + kQWave - 1, Tq - 1);     // last position any lane of the wave sees
-    const int wg_last = q_start + min(qt * kQTile + kQTile - 1, Tq - 1);
-    const int n_tiles = wg_last / kKTile + 1;                // key tiles 0 .. n_tiles-1 cover positions <= wg_last
-    const int n_hb = i0 < Tq ? wave_last / 32 + 1 : 0;       // 32-key blocks this wave works on (0: padding wave)
-    const int n_keys = q_start + Tq;                         // keys that exist (rows past them are never read)
-
-    // query fragments (B operand of S^T = K Q^T): Q[my_i][16*ks + 8*hl .. +7]
-    Frag16 qf[kHeadDim / 16];
-    {
-        const char *qrow = q + (((size_t)b * H + rhead) * Tq + min(my_i, Tq - 1)) * (kHeadDim * 2) + hl * 16;
+    for (int r0 = 0; r0 < n_rows; r0 += 64) {
+        const int c = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
+        int upto = c;
 #pragma unroll
-        for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[ks].raw = *reinterpret_cast<const u32x4 *>(qrow + ks * 32);
+        for (int o = 1; o < 64; o <<= 1) {
+            const int other = __shfl_up(upto, o);
+            upto += lane >= o ? other : 0;
+        }
+        const int all = __shfl(upto, 63);
+        if (group < all) {
+            const int row = __popcll(__ballot(upto <= group));
+            work.b = r0 + row;
+            work.gi = (int)group - (row > 0 ? __shfl(upto, row > 0 ? row - 1 : 0) : 0);
+            return true;
+        }
+        group -= all;
     }
+    return false;
+}
 
-    // Staging with direct loads to LDS: one instruction moves 64 pieces of 16 bytes into 1 KB of consecutive LDS
-    // (lane l's piece lands at base + 16 l), no registers and no LDS write instructions.  The BUFFER form of the
-    // instruction is used: with the global form in a loop the compiler gives up counting LDS reads and waits for
-    // all of them (lgkmcnt(0)) before every MFMA; with the buffer form it waits for exactly the fragment it needs
-    // (measured 4-5 % faster, and the register allocation no longer spills).  Rows are unpadded, and bank
-    // conflicts of the fragment reads are avoided by a swizzle instead: piece c of K row R sits in slot
-    // c ^ (R & 15) of the row, piece c of V^T row R in slot c ^ ((R >> 1) & 7); 16 consecutive rows read at one
-    // piece index then touch 16 different 16-byte slots of the 256-byte bank window.  A lane fetches whichever
-    // piece belongs in the slot it fills.  Wave w fills K rows 4w..4w+3 and 32+4w.. (two instructions per tile)
-    // and V^T rows 8w..8w+7 and 64+8w.. of every member (two instructions per member and tile).
-    // Requesting the tiles one iteration earlier still (rings of six K half-tiles and three V^T tiles, the wait
-    // before the barrier leaving the newest requests in flight) was measured too: no gain (565 against 553 us),
-    // the loop does not wait for these loads.
-    const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
-    const char *vsrc[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        vsrc[g] = reinterpret_cast<const char *>(vt + ((size_t)b * H + heads[g]) * (size_t)kHeadDim * Tp);
-    const int k_row = 4 * w + (lane >> 4), k_piece = (lane & 15) ^ (k_row & 15);
-    const int v_row = 8 * w + (lane >> 3), v_piece = (lane & 7) ^ ((v_row >> 1) & 7);
-    // V^T in memory: blocks of 32 keys, [block][row][32 keys]; piece c of a 64-key row = block c/4, 16 B piece c%4
-    const unsigned int v_off = (unsigned int)(((v_piece >> 2) * kHeadDim + v_row) * 64 + (v_piece & 3) * 16);
-    // (the instruction exists only in the device pass of the compiler; the host pass sees an empty body)
+// Accumulator tile T of the kernel below: registers a[16 T .. 16 T + 15] of the accumulation half, BY NAME.  The compiler
+// never sees the accumulators as values (offered as operands it carried them through ordinary registers at every branch,
+// 688 spills); it has no other use for that half in this file (matrix results are kept in ordinary registers by the
+// build's -amdgpu-mfma-vgpr-form), and the clobbers keep it from finding one.  What the compiler would insert
+// between dependent instructions stands here: two idle slots between an ordinary write and a matrix read
+// (acc_written), twenty between a matrix write and an ordinary read (acc_settle).
+template <int T>
+struct AccTile;
 #if defined(__HIP_DEVICE_COMPILE__)
-    typedef __amdgpu_buffer_rsrc_t Rsrc;
+#define CHAI_ACC_ZERO(r) asm volatile("v_accvgpr_write_b32 " r ", 0" ::: r)
+#define CHAI_ACC_SCALE(r)                                                                                              \
+    asm volatile("v_accvgpr_read_b32 %0, " r "\n\tv_mul_f32 %0, %1, %0\n\tv_accvgpr_write_b32 " r ", %0"               \
+                 : "=&v"(t)                                                                                            \
+                 : "v"(alpha)                                                                                          \
+                 : r)
+#define CHAI_ACC_READ(i, r) asm volatile("v_accvgpr_read_b32 %0, " r : "=v"(x[i]))
+#define CHAI_ACC_MFMA(range, ...)                                                                                      \
+    asm volatile("v_mfma_f32_32x32x16_f16 " range ", %0, %1, " range ::"v"(a), "v"(b) : __VA_ARGS__)
+#else
+#define CHAI_ACC_ZERO(r) (void)0
+#define CHAI_ACC_SCALE(r) (void)0
+#define CHAI_ACC_READ(i, r) x[i] = 0.f
+#define CHAI_ACC_MFMA(range, ...) (void)0
+#endif
+#define CHAI_ACC_TILE(T, range, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                   \
+    template <>                                                                                                        \
+    struct AccTile<T> {                                                                                                \
+        static __device__ __forceinline__ void mfma(const f16x8 &a, const f16x8 &b)                                    \
+        {                                                                                                              \
+            CHAI_ACC_MFMA(range, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15);                 \
+        }                                                                                                              \
+        static __device__ __forceinline__ void zero()                                                                  \
+        {                                                                                                              \
+            CHAI_ACC_ZERO(r0); CHAI_ACC_ZERO(r1); CHAI_ACC_ZERO(r2); CHAI_ACC_ZERO(r3);                                 \
+            CHAI_ACC_ZERO(r4); CHAI_ACC_ZERO(r5); CHAI_ACC_ZERO(r6); CHAI_ACC_ZERO(r7);                                 \
+            CHAI_ACC_ZERO(r8); CHAI_ACC_ZERO(r9); CHAI_ACC_ZERO(r10); CHAI_ACC_ZERO(r11);                               \
+            CHAI_ACC_ZERO(r12); CHAI_ACC_ZERO(r13); CHAI_ACC_ZERO(r14); CHAI_ACC_ZERO(r15);                             \
+        }                                                                                                              \
+        static __device__ __forceinline__ void scale(float alpha)                                                      \
+        {                                                                                                              \
+            float t = alpha;                                                                                           \
+            (void)t;                                                                                                   \
+            CHAI_ACC_SCALE(r0); CHAI_ACC_SCALE(r1); CHAI_ACC_SCALE(r2); CHAI_ACC_SCALE(r3);                             \
+            CHAI_ACC_SCALE(r4); CHAI_ACC_SCALE(r5); CHAI_ACC_SCALE(r6); CHAI_ACC_SCALE(r7);                             \
+            CHAI_ACC_SCALE(r8); CHAI_ACC_SCALE(r9); CHAI_ACC_SCALE(r10); CHAI_ACC_SCALE(r11);                           \
+            CHAI_ACC_SCALE(r12); CHAI_ACC_SCALE(r13); CHAI_ACC_SCALE(r14); CHAI_ACC_SCALE(r15);                         \
+        }                                                                                                              \
+        static __device__ __forceinline__ void read(float (&x)[16])                                                    \
+        {                                                                                                              \
+            CHAI_ACC_READ(0, r0); CHAI_ACC_READ(1, r1); CHAI_ACC_READ(2, r2); CHAI_ACC_READ(3, r3);                     \
+            CHAI_ACC_READ(4, r4); CHAI_ACC_READ(5, r5); CHAI_ACC_READ(6, r6); CHAI_ACC_READ(7, r7);                     \
+            CHAI_ACC_READ(8, r8); CHAI_ACC_READ(9, r9); CHAI_ACC_READ(10, r10); CHAI_ACC_READ(11, r11);                 \
+            CHAI_ACC_READ(12, r12); CHAI_ACC_READ(13, r13); CHAI_ACC_READ(14, r14); CHAI_ACC_READ(15, r15);             \
+        }                                                                                                              \
+    };
+CHAI_ACC_TILE(0, "a[0:15]", "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15")
+CHAI_ACC_TILE(1, "a[16:31]", "a16", "a17", "a18", "a19", "a20", "a21", "a22", "a23", "a24", "a25", "a26", "a27", "a28", "a29", "a30", "a31")
+CHAI_ACC_TILE(2, "a[32:47]", "a32", "a33", "a34", "a35", "a36", "a37", "a38", "a39", "a40", "a41", "a42", "a43", "a44", "a45", "a46", "a47")
+CHAI_ACC_TILE(3, "a[48:63]", "a48", "a49", "a50", "a51", "a52", "a53", "a54", "a55", "a56", "a57", "a58", "a59", "a60", "a61", "a62", "a63")
+CHAI_ACC_TILE(4, "a[64:79]", "a64", "a65", "a66", "a67", "a68", "a69", "a70", "a71", "a72", "a73", "a74", "a75", "a76", "a77", "a78", "a79")
+CHAI_ACC_TILE(5, "a[80:95]", "a80", "a81", "a82", "a83", "a84", "a85", "a86", "a87", "a88", "a89", "a90", "a91", "a92", "a93", "a94", "a95")
+CHAI_ACC_TILE(6, "a[96:111]", "a96", "a97", "a98", "a99", "a100", "a101", "a102", "a103", "a104", "a105", "a106", "a107", "a108", "a109", "a110", "a111")
+CHAI_ACC_TILE(7, "a[112:127]", "a112", "a113", "a114", "a115", "a116", "a117", "a118", "a119", "a120", "a121", "a122", "a123", "a124", "a125", "a126", "a127")
+CHAI_ACC_TILE(8, "a[128:143]", "a128", "a129", "a130", "a131", "a132", "a133", "a134", "a135", "a136", "a137", "a138", "a139", "a140", "a141", "a142", "a143")
+CHAI_ACC_TILE(9, "a[144:159]", "a144", "a145", "a146", "a147", "a148", "a149", "a150", "a151", "a152", "a153", "a154", "a155", "a156", "a157", "a158", "a159")
+CHAI_ACC_TILE(10, "a[160:175]", "a160", "a161", "a162", "a163", "a164", "a165", "a166", "a167", "a168", "a169", "a170", "a171", "a172", "a173", "a174", "a175")
+CHAI_ACC_TILE(11, "a[176:191]", "a176", "a177", "a178", "a179", "a180", "a181", "a182", "a183", "a184", "a185", "a186", "a187", "a188", "a189", "a190", "a191")
+CHAI_ACC_TILE(12, "a[192:207]", "a192", "a193", "a194", "a195", "a196", "a197", "a198", "a199", "a200", "a201", "a202", "a203", "a204", "a205", "a206", "a207")
+CHAI_ACC_TILE(13, "a[208:223]", "a208", "a209", "a210", "a211", "a212", "a213", "a214", "a215", "a216", "a217", "a218", "a219", "a220", "a221", "a222", "a223")
+CHAI_ACC_TILE(14, "a[224:239]", "a224", "a225", "a226", "a227", "a228", "a229", "a230", "a231", "a232", "a233", "a234", "a235", "a236", "a237", "a238", "a239")
+CHAI_ACC_TILE(15, "a[240:255]", "a240", "a241", "a242", "a243", "a244", "a245", "a246", "a247", "a248", "a249", "a250", "a251", "a252", "a253", "a254", "a255")
+#undef CHAI_ACC_TILE
+#undef CHAI_ACC_ZERO
+#undef CHAI_ACC_SCALE
+#undef CHAI_ACC_READ
+#undef CHAI_ACC_MFMA
+
+__device__ __forceinline__ void acc_written()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 3");
+#endif
+}
+__device__ __forceinline__ void acc_settle()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("s_nop 15\n\ts_nop 3");
+#endif
+}
+
+// Two probabilities to fp16, nearest even, HERE: the empty statement pins the place (the compiler would gather all
+// conversions at the end of a block).  The conversion itself is left to the compiler, which knows how long an exponential
+// takes to arrive.
+__device__ __forceinline__ unsigned int pack_f16(float lo, float hi)
+{
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    union {
+        f16x2 h;
+        unsigned int u;
+    } x;
+    x.h[0] = (_Float16)lo;
+    x.h[1] = (_Float16)hi;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x.u));
+#endif
+    return x.u;
+}
+
+// f(integral_constant 0), f(1), .. f(N - 1): loops whose index names registers
+template <typename F, int... I>
+__device__ __forceinline__ void unroll_seq(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F &&f)
+{
+    unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
+
+// Which of the 34 * 4 softmax operations of a block stand behind which of its MFMAs: by cost (quarter cycles: a vector
+// instruction 18, an exponential 32), a step with an LDS request takes a quarter of what the step without takes.
+template <int STEPS, int ELEMS, int EVEN, int ODD>
+struct OpSchedule {
+    int first[STEPS + 1];
+    constexpr OpSchedule() : first{}
+    {
+        auto cost = [](int i) {
+            const int g = i / 4, kind = i % 4;
+            if (kind == 0) return g < ELEMS ? 18 : 0;
+            if (kind == 1) return g >= 1 && g <= ELEMS ? 32 : 0;
+            if (kind == 2) return g >= 2 ? 18 : 0;
+            return g >= 2 && (g & 1) ? 18 : 0;
+        };
+        constexpr int kOps = (ELEMS + 2) * 4, kTotal = ELEMS * (18 + 32 + 18) + ELEMS / 2 * 18;
+        int i = 0, spent = 0, share = 0;
+        for (int n = 0; n < STEPS; ++n) {
+            first[n] = i;
+            share += n % 2 == 0 ? EVEN : ODD;
+            while (i < kOps && (n == STEPS - 1 || (spent + cost(i) / 2) * (STEPS / 2) * (EVEN + ODD) <= kTotal * share))
+                spent += cost(i++);
+        }
+        first[STEPS] = kOps;
+    }
+};
+
+// One query tile (4 waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
+template <int NM, int U>
+__device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
+                                          const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
+                                          int qt, int rhead, float scale2, float *__restrict__ out)
+{
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, hl = lane >> 5;
+    const int n_keys = q_start + Tq;
+    const int i0 = (qt * kWaves + w) * (32 * U);                // first query row of this wave
+    const int wave_first = q_start + min(i0, Tq - 1);
+    const int wave_last = q_start + min(i0 + 32 * U - 1, Tq - 1);
+    const int wg_last = q_start + min((qt + 1) * (kWaves * 32 * U) - 1, Tq - 1);
+    const int n_tiles = wg_last / kKTile + 1;
+    const int n_hb = i0 < Tq ? wave_last / 32 + 1 : -1;      // 32-key blocks of this wave (-1: a padding wave)
+
+    Frag16 qf[U][kHeadDim / 16];
+    int q_abs[U];                                            // sequence position of this lane's row in every stream
+
+    // Staging with direct loads to LDS: one instruction moves 64 pieces of 16 bytes into 1 KB of consecutive LDS (lane l's
+    // piece lands at base + 16 l), no registers and no LDS write instructions.  The BUFFER form of the instruction is
+    // used: with the global form in a loop the compiler gives up counting LDS reads and waits for all of them before
+    // every MFMA.  Rows are unpadded, and bank conflicts of the fragment reads are avoided by a swizzle instead: piece c
+    // of K row R sits in slot c ^ (R & 15) of the row, piece c of V^T row R in slot c ^ ((R >> 1) & 7); 16 consecutive rows
+    // read at one piece index then touch 16 different 16-byte slots of the 256-byte bank window (measured: 16 cycles per
+    // read with four waves reading, the same as for linear addresses).  A lane fetches whichever piece belongs in the
+    // slot it fills.  Instruction i of wave w fills K rows 4w + 16i .. +3, or V^T rows 8w + 32i .. +7 of a member.
+    const int k_row = 4 * w + (lane >> 4);
+    const int v_row = 8 * w + (lane >> 3);
+#if defined(__HIP_DEVICE_COMPILE__)
     auto make_rsrc = [](const char *base) {
         return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00020000);
     };
-    auto load_to_lds = [](Rsrc rs, unsigned int off, char *dst) {
+    auto load_to_lds = [](__amdgpu_buffer_rsrc_t rs, unsigned int off, char *dst) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16, (int)off, 0, 0, 0);
     };
 #else
-    typedef const char *Rsrc;
     auto make_rsrc = [](const char *base) { return base; };
-    auto load_to_lds = [](Rsrc, unsigned int, char *) {};
+    auto load_to_lds = [](const char *, unsigned int, char *) {};
 #endif
-    const Rsrc k_rs = make_rsrc(ksrc);
-    Rsrc v_rs[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) v_rs[g] = make_rsrc(vsrc[g]);
+    const auto k_rs = make_rsrc(ksrc);
+    const auto v_rs0 = make_rsrc(vsrc[0]);
+    const auto v_rs1 = make_rsrc(vsrc[NM - 1]);
+    auto dma_k1 = [&](int kt, int buf, int i) {              // instruction i (of 4) of a K tile
+        const int row = k_row + 16 * i;
+        load_to_lds(k_rs, (unsigned int)(min(kt * kKTile + row, n_keys - 1) * (kHeadDim * 2) + (((lane & 15) ^ (row & 15)) << 4)),
+                    k_lds + buf * kKBufBytes + (w + 4 * i) * 1024);
+    };
+    const int v_piece = (lane & 7) ^ ((v_row >> 1) & 7);     // rows 32 apart share the swizzle
+    const unsigned int v_off = (unsigned int)(v_row * (kKTile * 2) + v_piece * 16);
+    auto dma_v1 = [&](int kt, int buf, int g, int i) {       // instruction i (of 4) of member g's V^T tile
+        load_to_lds(g == 0 ? v_rs0 : v_rs1, (unsigned int)kt * (unsigned int)kVBufBytes + v_off + i * 32 * (kKTile * 2),
+                    v_lds + (buf * kGroup + g) * kVBufBytes + (w + 4 * i) * 1024);
+    };
     auto dma_k = [&](int kt, int buf) {
-        const int key0 = kt * kKTile;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            load_to_lds(k_rs, (unsigned int)(min(key0 + k_row + 32 * i, n_keys - 1) * (kHeadDim * 2) + k_piece * 16),
-                        k_lds + buf * kKBufBytes + (w + 8 * i) * 1024);
+        for (int i = 0; i < 4; ++i) dma_k1(kt, buf, i);
     };
-    auto dma_v = [&](int kt, int g, int buf) {
+    auto dma_v = [&](int kt, int buf) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            load_to_lds(v_rs[g], (unsigned int)kt * (2 * kHeadDim * 64) + v_off + i * 64 * 64,
-                        v_lds + (buf * G + g) * kVBufBytes + (w + 8 * i) * 1024);
+        for (int g = 0; g < NM; ++g)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) dma_v1(kt, buf, g, i);
     };
-    // The barrier of the tile loop: every wave first waits for its own requests (the compiler does not track loads
-    // that land in LDS), then a bare s_barrier -- __syncthreads() would add fences the loads-to-LDS do not need.
+    // every wave waits for its own requests (the compiler does not track loads that land in LDS), then a bare s_barrier:
+    // __syncthreads() would add fences that the loads to LDS do not need
     auto tile_barrier = [&]() {
 #if defined(__HIP_DEVICE_COMPILE__)
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -334,209 +500,297 @@ __global__ __launch_bounds__(kPBlock) void prefill_kernel(const char *__restrict
         asm volatile("" ::: "memory");
 #endif
     };
-    // fragment read offsets: this lane's row r of a 32-row block, piece index p -> byte offset inside the block
+    // fragments: this lane's row r of a 32-row block of K, fragment p = 8 * member + 4 * (16 keys) + 32-column block of V^T
     const int k_sw = r & 15, v_sw = (r >> 1) & 7;
-
-    f32x16 acc[G][kHeadDim / 32];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int blk = 0; blk < kHeadDim / 32; ++blk)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[g][blk][e] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;          // running maximum (log2 units) and denominator of this query
-
-    // S^T block: 32 keys (rows half*32 .. +31 of K buffer `buf`) x 32 queries
-    auto score_block = [&](int buf, int half) {
-        f32x16 st;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) st[e] = 0.f;
-        const char *kb = k_lds + buf * kKBufBytes + (half * 32 + r) * (kHeadDim * 2);
-#pragma unroll
-        for (int ks = 0; ks < kHeadDim / 16; ++ks) {
-            Frag16 kf;
-            kf.raw = *reinterpret_cast<const u32x4 *>(kb + (((2 * ks + hl) ^ k_sw) << 4));
-            st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.bf, qf[ks].bf, st, 0, 0, 0);
-        }
-        return st;
+    auto k_frag = [&](const char *kb, int ks) { return *reinterpret_cast<const u32x4 *>(kb + (((2 * ks + hl) ^ k_sw) << 4)); };
+    auto v_frag = [&](const char *vb, int half, int p) {
+        const int j = p & 7;
+        return *reinterpret_cast<const u32x4 *>(vb + (p >> 3) * kVBufBytes + (j & 3) * 32 * (kKTile * 2) +
+                                                (((4 * half + 2 * (j >> 2) + hl) ^ v_sw) << 4));
     };
 
-    // One block (keys kbase .. kbase+31, scores st): online softmax and the product with the members' values from
-    // V^T buffer vbuf.  HAS_NEXT: the scores of the wave's next block (K buffer nbuf, half nhalf) are issued in the
-    // same stretch of code as the exponentials, one MFMA per handful of vector instructions, so that the matrix
-    // pipe is busy while this wave exponentiates; they are returned.
-    // Wave priority: raised while a wave is in the stretch that mixes vector work with score MFMAs, so that the
-    // SIMD's arbiter favours it over the other wave's back-to-back value MFMAs, which lose nothing by waiting a
-    // few cycles (measured: 1.5-4 % faster).
-    auto wave_priority = [](bool high) {
-#if defined(__HIP_DEVICE_COMPILE__)
-        if (high) __builtin_amdgcn_s_setprio(2);
-        else __builtin_amdgcn_s_setprio(0);
-#else
-        (void)high;
-#endif
+    unroll<4 * U * NM>([&](auto t) { AccTile<t.value>::zero(); });           // tile (stream * NM + member) * 4 + block
+    acc_written();
+    float m_run[U], l_run[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        m_run[u] = -INFINITY;
+        l_run[u] = 0.f;
+    }
+
+    struct Prob {
+        Frag16 f[U][2];                                      // [stream][16 keys]
     };
-    auto block = [&](f32x16 st, int kbase, int vbuf, int half, auto has_next, int nbuf, int nhalf) {
-        constexpr bool HAS_NEXT = decltype(has_next)::value;
-        // causal mask: only blocks that reach past the wave's first query need it (a real branch, uniform per
-        // wave -- the empty asm keeps the compiler from turning it into 32 selects on every block)
-        if (kbase + 31 > wave_first) {
+    struct Score {
+        f32x16 s[U];
+    };
+
+    // products of block hb-1's probabilities with its values
+    auto pv_only = [&](const Prob &pp, const char *vb, int vhalf) {
+        acc_written();
+        unroll<8 * NM>([&](auto pc) {
+            constexpr int p = pc.value;
+            Frag16 vf;
+            vf.raw = v_frag(vb, vhalf, p);
+            unroll<U>([&](auto uc) {
+                constexpr int u = uc.value;
+                AccTile<(u * NM + (p >> 3)) * 4 + (p & 3)>::mfma(vf.h, pp.f[u][(p >> 2) & 1].h);
+            });
+        });
+    };
+
+    // slots of a block: 8 NM value fragments and 8 key fragments, every third (NM = 2) or second one a key fragment
+    constexpr int kSlots = 8 * NM + 8, kAhead = 4, kHead = 5, kMaxSteps = 4 * U;
+    struct Carry {
+        Frag16 f[kAhead];
+    };
+    auto frag_of = [&](auto sl, const char *kb, const char *vb, int vhalf) {
+        constexpr int s = sl.value;
+        constexpr bool qk = NM == 2 ? s % 3 == 2 : s % 2 == 1;
+        if constexpr (qk) return k_frag(kb, NM == 2 ? s / 3 : s / 2);
+        else return v_frag(vb, vhalf, NM == 2 ? s - s / 3 : s / 2);
+    };
+    // Block kbase .. kbase+31: softmax of its scores sc into pn; scores of the next block (keys kb) into sn; products of the
+    // block before (probabilities pp, values vb, half vhalf).  carry: the first fragments, and then those of the next call.
+    auto body = [&](Score &sc, Score &sn, const Prob &pp, Prob &pn, int kbase, const char *kb, const char *vb, int vhalf,
+                    const char *kb_next, const char *vb_next, int vhalf_next, Carry &carry, auto dma) {
+        // causal mask: only blocks that reach past the wave's first query need it (a branch uniform per wave; out of line,
+        // like the rescaling below: a taken branch costs a lone wave 40 cycles)
+        if (__builtin_expect(kbase + 31 > wave_first, 0)) {
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int key = kbase + (e >> 2) * 8 + hl * 4 + (e & 3);
-                st[e] = key <= q_abs ? st[e] : -INFINITY;
-            }
-        }
-        // maximum of the raw scores (scale > 0 is required); the scale, times log2 e, is folded into the
-        // exponent: p = exp2(s * scale2 - m)
-        float ext = st[0];
+            for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int e = 1; e < 16; ++e) ext = fmaxf(ext, st[e]);
-        float mx_lo, mx_hi;
-        both_halves(ext * scale2, mx_lo, mx_hi);
-        const float mx = fmaxf(mx_lo, mx_hi);
-        // lazy reference: the running maximum only moves when a block exceeds it by more than kRescaleSlack, so
-        // most blocks skip the rescaling of the accumulators (p < 2^slack)
-        const bool need = mx > m_run + kRescaleSlack;
-        const float m_new = need ? mx : m_run;
-        const float alpha = need ? __builtin_amdgcn_exp2f(m_run - m_new) : 1.0f;   // exp2(-inf) = 0 at the start
-        if (__any(need)) {
-            l_run *= alpha;
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (g < n_mem)
-#pragma unroll
-                    for (int blk = 0; blk < kHeadDim / 32; ++blk)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) acc[g][blk][e] *= alpha;
-        }
-        m_run = m_new;
-
-        wave_priority(true);
-        f32x16 s_next = st;
-        float rs = 0.f;
-        Frag16 pf[2];
-        if (HAS_NEXT) {
-            // Exponentials of this block and scores of the next one, written out in the issue order wanted: per
-            // step one MFMA of the next block's scores (its K fragment was requested two steps earlier) and the
-            // vector work of two probabilities.  The scheduling barriers keep the compiler from regrouping it
-            // into "all MFMAs, then all exponentials", which would leave the matrix pipe idle during the latter.
-#pragma unroll
-            for (int e = 0; e < 16; ++e) s_next[e] = 0.f;
-            const char *kb = k_lds + nbuf * kKBufBytes + (nhalf * 32 + r) * (kHeadDim * 2);
-            Frag16 kf[kHeadDim / 16];
-            kf[0].raw = *reinterpret_cast<const u32x4 *>(kb + ((hl ^ k_sw) << 4));
-            kf[1].raw = *reinterpret_cast<const u32x4 *>(kb + (((2 + hl) ^ k_sw) << 4));
-#pragma unroll
-            for (int i = 0; i < kHeadDim / 16; ++i) {
-                if (i + 2 < kHeadDim / 16)
-                    kf[i + 2].raw = *reinterpret_cast<const u32x4 *>(kb + (((2 * (i + 2) + hl) ^ k_sw) << 4));
-                s_next = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i].bf, qf[i].bf, s_next, 0, 0, 0);
-#pragma unroll
-                for (int e = 2 * i; e < 2 * i + 2; ++e) {
-                    const float p = __builtin_amdgcn_exp2f(fmaf(st[e], scale2, -m_run));
-                    rs += p;
-                    pf[e >> 3].h[e & 7] = (_Float16)p;
+                for (int e = 0; e < 16; ++e) {
+                    const int key = kbase + (e >> 2) * 8 + hl * 4 + (e & 3);
+                    sc.s[u][e] = key <= q_abs[u] ? sc.s[u][e] : -INFINITY;
                 }
+        }
+        Frag16 fr[kSlots + kAhead];
+        unroll<kAhead>([&](auto i) { fr[i.value] = carry.f[i.value]; });
+        auto fetch = [&](auto sl) {
+            constexpr int s = sl.value;
+            if constexpr (s < kSlots) fr[s].raw = frag_of(sl, kb, vb, vhalf);
+            else fr[s].raw = frag_of(std::integral_constant<int, s - kSlots>{}, kb_next, vb_next, vhalf_next);
+        };
+        // step j: MFMA of stream j % U of slot j / U
+        auto step = [&](auto jc) {
+            constexpr int s = jc.value / U, u = jc.value % U;
+            if constexpr (s < kSlots) {
+                constexpr bool qk = NM == 2 ? s % 3 == 2 : s % 2 == 1;
+                if constexpr (u == 0) fetch(std::integral_constant<int, s + kAhead>{});
+                if constexpr (u == U - 1 && s % 2 == 0) dma(s / 2);
+                if constexpr (qk) {
+                    constexpr int ks = NM == 2 ? s / 3 : s / 2;
+                    f32x16 c;
+                    if constexpr (ks == 0) {
+#pragma unroll
+                        for (int e = 0; e < 16; ++e) c[e] = 0.f;
+                    } else
+                        c = sn.s[u];
+                    sn.s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s].bf, qf[u][ks].bf, c, 0, 0, 0);
+                } else {
+                    constexpr int p = NM == 2 ? s - s / 3 : s / 2;
+                    AccTile<(u * NM + (p >> 3)) * 4 + (p & 3)>::mfma(fr[s].h, pp.f[u][(p >> 2) & 1].h);
+                }
+            }
+        };
+        acc_written();
+        float ext[U];
+        // maxima, two vector instructions behind every MFMA
+        unroll<U * kHead>([&](auto jc) {
+            constexpr int j = jc.value, u = j / 4, c = j % 4;
+            step(jc);
+            if constexpr (j < kMaxSteps) {
+                if constexpr (c == 0) ext[u] = sc.s[u][0];
+#pragma unroll
+                for (int e = c == 0 ? 1 : c * 4; e < c * 4 + 4; ++e) ext[u] = fmaxf(ext[u], sc.s[u][e]);
+                if constexpr (c == 3) ext[u] *= scale2;
                 __builtin_amdgcn_sched_barrier(0);
             }
-        } else {
+        });
+        // Lazy reference: the running maximum (log2 units, of the raw scores times scale2; scale > 0 is required) only
+        // moves when a block exceeds it by more than kRescaleSlack, so p < 2^slack and most blocks skip the rescaling.
+        // A lane sees half of its row's keys; the halves are compared only when one of them is over.
+        bool over = ext[0] > m_run[0] + kRescaleSlack;
+        if constexpr (U == 2) over = over || ext[1] > m_run[1] + kRescaleSlack;
+        const bool moved = __any(over);
+        float alpha[U];
 #pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const float p = __builtin_amdgcn_exp2f(fmaf(st[e], scale2, -m_run));
-                rs += p;
-                pf[e >> 3].h[e & 7] = (_Float16)p;
+        for (int u = 0; u < U; ++u) alpha[u] = 1.f;
+        if (__builtin_expect(moved, 0)) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float lo, hi;
+                both_halves(ext[u], lo, hi);
+                const float mx = fmaxf(lo, hi);
+                const bool need = mx > m_run[u] + kRescaleSlack;
+                const float m_new = need ? mx : m_run[u];
+                alpha[u] = need ? __builtin_amdgcn_exp2f(m_run[u] - m_new) : 1.0f;
+                l_run[u] *= alpha[u];
+                m_run[u] = m_new;
             }
-        }
-        float rs_lo, rs_hi;
-        both_halves(rs, rs_lo, rs_hi);
-        l_run += rs_lo + rs_hi;
-        wave_priority(false);
-        // O^T[d][query] += V^T P^T for every member head: fragment j = (blk, s) of a member, requested
-        // kVAhead MFMAs before its use so that the LDS latency hides behind the matrix pipe
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (g < n_mem) {
-                const char *vb = v_lds + (vbuf * G + g) * kVBufBytes + r * (kKTile * 2);
-                constexpr int kBlks = kHeadDim / 32, kFrags = 2 * kBlks, kVAhead = 3;
-                // fragment j: value rows 32 * (j % kBlks) .., keys 16 * (j / kBlks) .. of the block (piece
-                // 4 * half + 2 * (j / kBlks) + hl of the row); the two MFMAs that add into the same accumulator are
-                // kBlks apart
-                auto v_frag = [&](int j) {
-                    return *reinterpret_cast<const u32x4 *>(vb + (j % kBlks) * 32 * (kKTile * 2) +
-                                                            (((4 * half + 2 * (j / kBlks) + hl) ^ v_sw) << 4));
-                };
-                Frag16 vf[kFrags];
-#pragma unroll
-                for (int j = 0; j < kVAhead; ++j) vf[j].raw = v_frag(j);
-#pragma unroll
-                for (int j = 0; j < kFrags; ++j) {
-                    if (j + kVAhead < kFrags) vf[j + kVAhead].raw = v_frag(j + kVAhead);
-                    acc[g][j % kBlks] =
-                        __builtin_amdgcn_mfma_f32_32x32x16_f16(vf[j].h, pf[j / kBlks].h, acc[g][j % kBlks], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-        }
-        return s_next;
-    };
-    const std::true_type with_next;
-    const std::false_type last_block;
-
-    // prologue: K(0), K(1), V(0) requested together; the previous pass's last barrier has freed every buffer
-    dma_k(0, 0);
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-        if (g < n_mem) dma_v(0, g, 0);
-    if (n_tiles > 1) dma_k(1, 1);
-    tile_barrier();
-    // every wave, padding waves included: the first use of the query fragments is then outside the loop
-    f32x16 s_cur = score_block(0, 0);
-
-    // Iteration kt computes tile kt while K(kt+2) and V(kt+1) stream into the buffers that tile kt-1 has left
-    // (its readers passed the barrier that ended iteration kt-1); they must have landed by the barrier that ends
-    // this iteration.
-    int kb3 = 0, vb2 = 0;                      // kt % 3, kt % 2
-    for (int kt = 0; kt < n_tiles; ++kt) {
-        const int kb3_1 = kb3 == 2 ? 0 : kb3 + 1, kb3_2 = kb3_1 == 2 ? 0 : kb3_1 + 1;
-        if (kt + 2 < n_tiles) dma_k(kt + 2, kb3_2);
-        if (kt + 1 < n_tiles) {
-#pragma unroll
-            for (int g = 0; g < G; ++g)
-                if (g < n_mem) dma_v(kt + 1, g, vb2 ^ 1);
         }
         __builtin_amdgcn_sched_barrier(0);
-
-        const int hb = 2 * kt;                             // blocks hb (first half of the tile) and hb + 1
-        if (hb + 1 < n_hb) s_cur = block(s_cur, hb * 32, vb2, 0, with_next, kb3, 1);
-        else if (hb < n_hb) s_cur = block(s_cur, hb * 32, vb2, 0, last_block, 0, 0);
-        if (hb + 2 < n_hb) s_cur = block(s_cur, hb * 32 + 32, vb2, 1, with_next, kb3_1, 0);
-        else if (hb + 1 < n_hb) s_cur = block(s_cur, hb * 32 + 32, vb2, 1, last_block, 0, 0);
-        tile_barrier();                                    // tile kt is done with; tiles kt+1 / kt+2 are in LDS
-        kb3 = kb3_1;
-        vb2 ^= 1;
-    }
-
-    if (n_hb != 0 && my_i < Tq) {
-        const float inv = 1.0f / l_run;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            if (g < n_mem) {
-                float *orow = out + (((size_t)b * H + heads[g]) * Tq + my_i) * kHeadDim;
-#pragma unroll
-                for (int blk = 0; blk < kHeadDim / 32; ++blk)
-#pragma unroll
-                    for (int v4 = 0; v4 < 4; ++v4) {
-                        float4 o;
-                        o.x = acc[g][blk][v4 * 4 + 0] * inv; o.y = acc[g][blk][v4 * 4 + 1] * inv;
-                        o.z = acc[g][blk][v4 * 4 + 2] * inv; o.w = acc[g][blk][v4 * 4 + 3] * inv;
-                        *reinterpret_cast<float4 *>(orow + blk * 32 + v4 * 8 + hl * 4) = o;
-                    }
+        // probabilities: element n's exponent, element n-1's exponential and element n-2's sum and conversion together, so
+        // that no instruction waits for the one before it
+        constexpr int kRest = U * (kSlots - kHead), kElems = 16 * U;
+        float x[kElems], pe[kElems];
+        // operation i: group i / 4 holds element g's exponent, g-1's exponential, g-2's sum, (odd g-2) the conversion
+        auto op = [&](auto ic) {
+            constexpr int g = ic.value / 4, kind = ic.value % 4;
+            if constexpr (kind == 0 && g < kElems) x[g] = fmaf(sc.s[g >> 4][g & 15], scale2, -m_run[g >> 4]);
+            if constexpr (kind == 1 && g >= 1 && g <= kElems) pe[g - 1] = __builtin_amdgcn_exp2f(x[g - 1]);
+            if constexpr (kind == 2 && g >= 2) l_run[(g - 2) >> 4] += pe[g - 2];
+            if constexpr (kind == 3 && g >= 2 && (g & 1)) {
+                constexpr int e = g - 2;
+                pn.f[e >> 4][(e >> 3) & 1].raw[(e & 7) >> 1] = pack_f16(pe[e - 1], pe[e]);
             }
+        };
+        constexpr OpSchedule<kRest, kElems, 1, U == 2 ? 3 : 1> sched{};
+        unroll<kRest>([&](auto nc) {
+            constexpr int n = nc.value;
+            step(std::integral_constant<int, U * kHead + n>{});
+            unroll<sched.first[n + 1] - sched.first[n]>(
+                [&](auto q) { op(std::integral_constant<int, sched.first[n] + q.value>{}); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        unroll<kAhead>([&](auto i) { carry.f[i.value] = fr[kSlots + i.value]; });
+        if (__builtin_expect(moved && kbase > 0, 0)) {
+            acc_settle();
+            unroll<4 * U * NM>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
+        }
+    };
+
+    dma_k(0, 0);
+    dma_v(0, 0);
+    if (n_tiles > 1) dma_k(1, 1);
+    // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]; padding rows repeat the last one
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int i = min(i0 + u * 32 + r, Tq - 1);
+        q_abs[u] = q_start + i;
+        const char *qrow = q + ((brow * H + rhead) * Tq + i) * (kHeadDim * 2) + hl * 16;
+#pragma unroll
+        for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[u][ks].raw = *reinterpret_cast<const u32x4 *>(qrow + ks * 32);
+    }
+    tile_barrier();
+    Score sa, sb;
+    Prob pa, pb;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            pb.f[u][i].raw = u32x4{0u, 0u, 0u, 0u};
+#if defined(__HIP_DEVICE_COMPILE__)
+            // keeps the zeros in these registers: as a known constant they were written again right before a product,
+            // closer than the matrix unit allows
+            asm volatile("" : "+v"(pb.f[u][i].raw));
+#endif
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) sa.s[u][e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) {
+            Frag16 kf;
+            kf.raw = k_frag(k_lds + r * (kHeadDim * 2), ks);
+            sa.s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.bf, qf[u][ks].bf, sa.s[u], 0, 0, 0);
         }
     }
-    }   // the two query tiles of the pair
+    const char *kb_lane = k_lds + r * (kHeadDim * 2), *vb_lane = v_lds + r * (kKTile * 2);
+    Carry carry;
+    unroll<kAhead>([&](auto i) { carry.f[i.value].raw = frag_of(i, kb_lane + 32 * (kHeadDim * 2), vb_lane, 0); });
+    // Tile kt: blocks 2 kt (keys already multiplied; scores of the tile's second half, values of the block before) and
+    // 2 kt + 1.  The first block multiplies zero probabilities with the first tile's values.
+    int b3 = 0, b3p = 0;                                     // buffers of tile kt and of the values before it
+    for (int kt = 0; kt < n_tiles; ++kt) {
+        const int b3n = b3 == 2 ? 0 : b3 + 1, b3nn = b3n == 2 ? 0 : b3n + 1;
+        const int kt2 = min(kt + 2, n_tiles - 1), kt1 = min(kt + 1, n_tiles - 1);      // past the end: requested, not read
+        const int hb = 2 * kt;
+        const char *vprev = vb_lane + b3p * (kGroup * kVBufBytes), *vcur = vb_lane + b3 * (kGroup * kVBufBytes);
+        const char *k_odd = kb_lane + b3 * kKBufBytes + 32 * (kHeadDim * 2), *k_even = kb_lane + b3n * kKBufBytes;
+        auto dma0 = [&](int i) {                             // the next tiles' 4 + 4 NM requests, early in this one
+            if (i < 4) dma_v1(kt1, b3n, 0, i);
+            else if (i < 4 * NM) dma_v1(kt1, b3n, 1, i - 4);
+            else if (i < 4 * NM + 4) dma_k1(kt2, b3nn, i - 4 * NM);
+        };
+        auto dma1 = [&](int) {};
+        if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0);
+        else {
+            unroll<4 * NM + 4>([&](auto i) { dma0(i.value); });
+            if (hb == n_hb) pv_only(pb, vprev, 1);
+        }
+        if (hb + 1 < n_hb)
+            body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1);
+        else if (hb + 1 == n_hb) pv_only(pa, vcur, 0);
+        tile_barrier();
+        b3p = b3;
+        b3 = b3n;
+    }
+    if (n_hb == 2 * n_tiles) pv_only(pb, vb_lane + b3p * (kGroup * kVBufBytes), 1);
+
+    if (n_hb > 0) {
+        acc_settle();
+        float inv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float lo, hi;
+            both_halves(l_run[u], lo, hi);
+            inv[u] = 1.0f / (lo + hi);
+        }
+        unroll<4 * U * NM>([&](auto tc) {
+            constexpr int t = tc.value, u = t / (4 * NM), g = t / 4 % NM, blk = t % 4;
+            const int my_i = i0 + u * 32 + r;
+            float x[16];
+            AccTile<t>::read(x);
+            if (my_i < Tq) {
+                float *orow = out + ((brow * H + heads[g]) * Tq + my_i) * kHeadDim + blk * 32 + hl * 4;
+#pragma unroll
+                for (int v4 = 0; v4 < 4; ++v4)
+                    *reinterpret_cast<float4 *>(orow + v4 * 8) = make_float4(x[v4 * 4] * inv[u], x[v4 * 4 + 1] * inv[u],
+                                                                            x[v4 * 4 + 2] * inv[u], x[v4 * 4 + 3] * inv[u]);
+            }
+        });
+    }
+}
+
+template <int U, bool IDENT>
+__global__ __launch_bounds__(kThreads, 1) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
+                                                                  const _Float16 *__restrict__ vt,
+                                                                  const int32_t *__restrict__ groups,
+                                                                  const int32_t *__restrict__ n_groups, int H, int k,
+                                                                  int Tq, int q_start, int Tc_cap, int Tp, int n_qt,
+                                                                  int n_slots, int n_rows, float scale,
+                                                                  float *__restrict__ out)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+    PrefillWork work;
+    if (!find_work<IDENT>(n_groups, n_rows, H, n_qt, work)) return;
+    const int gi = __builtin_amdgcn_readfirstlane(work.gi), b = __builtin_amdgcn_readfirstlane(work.b);
+    int cluster = gi, n_mem = 1, rhead = gi, heads[kGroup] = {gi, gi};
+    if (!IDENT) {
+        const int32_t *gr = groups + ((size_t)b * n_slots + gi) * kRec;
+        cluster = min(gr[0] & ((1 << kRecCount) - 1), k - 1);
+        n_mem = min(max(gr[0] >> kRecCount, 1), kGroup);
+#pragma unroll
+        for (int g = 0; g < kGroup; ++g) heads[g] = min(max(gr[1 + min(g, n_mem - 1)], 0), H - 1);
+        rhead = min(max(gr[1 + kGroup], 0), H - 1);
+    }
+    const char *vsrc[kGroup];
+#pragma unroll
+    for (int g = 0; g < kGroup; ++g)
+        vsrc[g] = reinterpret_cast<const char *>(vt + ((size_t)b * H + heads[g]) * (size_t)kHeadDim * Tp);
+    const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
+    for (int pass = 0; pass < work.n_pass; ++pass) {
+        const int qt = __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1);
+        if (pass != 0) __syncthreads();
+        if (!IDENT && n_mem == 2)
+            prefill_tile<2, U>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
+                         scale * kLog2e, out);
+        else
+            prefill_tile<1, U>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
+                         scale * kLog2e, out);
+    }
 }
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
@@ -566,36 +820,32 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     int32_t *n_groups = reinterpret_cast<int32_t *>(ws);
     ws += round256((size_t)B * sizeof(int32_t));
     _Float16 *vt = reinterpret_cast<_Float16 *>(ws);
-    const int n_qt = (Tq + kQTile - 1) / kQTile;
 
-    hipError_t e = launch_kernel(vt_kernel, dim3(Tp / kKTile, H, B), dim3(256), 0, stream, KernelEvents(),
-                                 static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt);
+    const size_t tile_lds = (size_t)kHeadDim * (kKTile + 2) * sizeof(_Float16), plan_lds = (size_t)(H + 2 * k) * sizeof(int32_t);
+    hipError_t e = launch_kernel(prepass_kernel, dim3(Tp / kKTile + 1, H, B), dim3(256),
+                                 identity || plan_lds < tile_lds ? tile_lds : plan_lds, stream, KernelEvents(),
+                                 static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt, h2c, rep, k, max_groups, groups,
+                                 n_groups);
     if (e != hipSuccess) return (int)e;
-    static DeviceFlags lds_ident, lds_clustered;
-    e = identity ? allow_dynamic_lds(reinterpret_cast<const void *>(&prefill_kernel<true>), prefill_lds_bytes(true), lds_ident)
-                 : allow_dynamic_lds(reinterpret_cast<const void *>(&prefill_kernel<false>), prefill_lds_bytes(false),
-                                     lds_clustered);
+    // Two streams of 32 rows per wave, or one (tiles of 256 or 128 rows): one where the wide tiles would leave CUs without
+    // work or end in a ragged last round.  The line lies at kSmallTiles 256-row tiles of the most groups the maps can
+    // have; whole calls with tiles of 256 / 128 rows: at 384 of them 164 / 153 us, at 416 73 / 71 us, dense at 576 88 / 84 us,
+    // at 840 656 / 676 us, at 1280 472 / 567 us.
+    const long long tiles = (long long)((Tq + 255) / 256) * max_groups * B;
+    const int U = tiles <= kSmallTiles ? 1 : 2;
+    auto *kernel = U == 1 ? (identity ? prefill_kernel<1, true> : prefill_kernel<1, false>)
+                          : (identity ? prefill_kernel<2, true> : prefill_kernel<2, false>);
+    static DeviceFlags lds_allowed[4];
+    e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsBytes, lds_allowed[2 * (U - 1) + (identity ? 1 : 0)]);
     if (e != hipSuccess) return (int)e;
-    // A workgroup takes a large and a small query tile (equal work for all), unless the launch is small: below
-    // kPairedRounds rounds of the chip a partly filled last round of equal workgroups costs more than pairing
-    // gains, and the tiles go out singly, the largest first.
-    const bool paired = (long long)((n_qt + 1) / 2) * max_groups * B >= (long long)kPairedRounds * 256;
-    const int n_qt_arg = paired ? n_qt : -n_qt;
-    const long long slots = (long long)max_groups * B;
-    const long long n_wg_ll = paired ? (long long)((n_qt + 1) / 2) * slots : 8LL * n_qt * ((slots + 7) / 8);
-    if (n_wg_ll > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    const unsigned int n_wg = (unsigned int)n_wg_ll;
-    if (identity) {
-        return (int)launch_kernel(prefill_kernel<true>, dim3(n_wg), dim3(kPBlock), prefill_lds_bytes(true), stream, ev,
-                                  static_cast<const char *>(q), static_cast<const char *>(kc), vt, nullptr, nullptr,
-                                  nullptr, H, k, Tq, q_start, Tc_cap, Tp, n_qt_arg, max_groups, B, scale, out);
-    }
-    e = launch_kernel(prefill_plan_kernel, dim3(B), dim3(256), (size_t)(H + 2 * k) * sizeof(int32_t), stream,
-                      KernelEvents(), h2c, rep, H, k, kGroup, max_groups, groups, n_groups);
-    if (e != hipSuccess) return (int)e;
-    return (int)launch_kernel(prefill_kernel<false>, dim3(n_wg), dim3(kPBlock), prefill_lds_bytes(false), stream, ev,
-                              static_cast<const char *>(q), static_cast<const char *>(kc), vt, rep, groups, n_groups, H, k,
-                              Tq, q_start, Tc_cap, Tp, n_qt_arg, max_groups, B, scale, out);
+    const int n_qt = (Tq + kWaves * 32 * U - 1) / (kWaves * 32 * U);
+    // the most workgroups an XCD can need (find_work): its pairs, the last of them as single tiles of padded groups
+    const long long n_pairs = (n_qt + 1) / 2, most = ((long long)max_groups * B * n_pairs + kXcds - 1) / kXcds + 1;
+    const long long n_wg = kXcds * (most + (most < 2 * kXcdCus ? most : 2 * kXcdCus) + 4 * n_pairs);
+    if (n_wg > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
+    return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(kThreads), kLdsBytes, stream, ev,
+                              static_cast<const char *>(q), static_cast<const char *>(kc), vt, groups, n_groups, H, k, Tq,
+                              q_start, Tc_cap, Tp, n_qt, max_groups, B, scale, out);
 }
 
 }  // namespace chai

@@ -1,0 +1,80 @@
+"""GPU parity of the prefill kernel at the edges of its tiles and of the rules that number its workgroups: 128-row tiles
+(small launches) and 256-row tiles, pairs and single tiles, more batch rows than one wave counts, unused cluster slots,
+a running maximum that keeps moving."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2403_08058_amd as C
+import workloads as W
+from oracle import chai_oracle as O
+
+import gpu_util as G
+from gpu_util import dev
+from test_gpu_prefill import RTOL_PREFILL, run_case
+
+SCALE = float(np.float32(1 / math.sqrt(128)))
+
+
+@pytest.mark.parametrize("B,H,kk,Tq,q_start", [
+    (1, 4, 2, 127, 0), (1, 4, 2, 128, 1), (1, 4, 2, 129, 63), (1, 4, 2, 33, 31), (1, 4, 2, 32, 32),   # one, two 128-row tiles
+    (2, 6, 3, 385, 64),                                    # four of them, the last with one row
+    (66, 4, 2, 70, 5),                                     # more batch rows than one wave adds up at a time
+    (40, 32, 8, 65, 130),                                  # 960 tiles of 256 rows: the wide kernel with one ragged tile
+    (14, 32, 8, 257, 3), (14, 32, 8, 512, 0),              # 672: two tiles per group, pairs and singles
+    (66, 4, 2, 769, 5),                                    # wide, four tiles, 66 rows
+    (5, 24, 24, 1000, 30),                                 # wide, every head alone
+])
+def test_prefill_tile_edges(B, H, kk, Tq, q_start):
+    print(f"[prefill] B={B} H={H} k={kk} Tq={Tq} q_start={q_start}", flush=True)
+    run_case(B, H, kk, Tq, q_start, q_start + Tq + 3, seed=B + 5 * H + 7 * kk + Tq + q_start)
+
+
+@pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5)])
+def test_dense_prefill_tiles(B, H, Tq, q_start):
+    """Dense entry point, 128-row and 256-row tiles."""
+    g = np.random.default_rng(B)
+    T = q_start + Tq
+    q, k, v = (W.normal(g, (B, H, n, 128), W.BF16) for n in (Tq, T, T))
+    out = torch.full((B, H, Tq, 128), float("nan"), dtype=torch.float32, device="cuda")
+    ws = torch.empty((C.chai_prefill_workspace_bytes(B, H, H, T),), dtype=torch.uint8, device="cuda")
+    C.chai_dense_prefill_attention(dev(q), dev(k), dev(v), q_start, SCALE, out, ws)
+    torch.cuda.synchronize()
+    ident = np.tile(np.arange(H, dtype=np.int32), (B, 1))
+    ok, worst = G.rows_close(out.cpu().numpy(), O.clustered_prefill(q, k, v, ident, ident, q_start, SCALE), RTOL_PREFILL)
+    assert ok, worst
+
+
+@pytest.mark.parametrize("B,Tq", [(1, 200), (24, 300)])
+def test_prefill_moving_maximum_and_unused_slot(B, Tq):
+    """Keys that grow with their position move the running maximum in block after block (the accumulators are rescaled);
+    one slot of the first row is unused and its heads' rows stay untouched."""
+    H, kk, q_start = 24, 5, 40
+    T = q_start + Tq
+    g = np.random.default_rng(Tq)
+    q, v = W.normal(g, (B, H, Tq, 128), W.BF16), W.normal(g, (B, H, T, 128), W.BF16)
+    k = W.store(g.standard_normal((B, H, T, 128), dtype=np.float32) * (1 + np.arange(T, dtype=np.float32) / 8)[:, None], W.BF16)
+    h2c, rep = W.random_membership(g, B, H, kk)
+    kc = torch.zeros((B, kk, T, 128), dtype=torch.bfloat16, device="cuda")
+    C.chai_compact_kcache(dev(k), dev(rep), kc, T)
+    ref = O.clustered_prefill(q, k, v, h2c, rep, q_start, SCALE)
+    used = rep.copy()
+    used[0, kk - 1] = -1
+    out = torch.full((B, H, Tq, 128), 7.0, dtype=torch.float32, device="cuda")
+    ws = torch.full((C.chai_prefill_workspace_bytes(B, H, kk, T),), 0xFF, dtype=torch.uint8, device="cuda")
+    C.chai_prefill_attention(dev(q), kc, dev(v), dev(h2c), dev(used), q_start, SCALE, out, ws)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    dead = h2c[0] == kk - 1
+    assert dead.any() and np.all(got[0][dead] == 7.0)
+    got[0][dead] = ref[0][dead]
+    # one key dominates a row here: its probability, 1 before the last rescaling, is exact in fp16; the others carry 2^-11
+    ok, worst = G.rows_close(got, ref, RTOL_PREFILL)
+    assert ok, worst

@@ -50,7 +50,7 @@ int check_sizes(int B, int H, int k, int T, int Tc_cap, int T_cap, int d, int dt
     if (bad_dtype(dtype)) return CHAI_ERR_DTYPE;
     if (B < 0 || H < 1 || k < 1 || k > H || T < 1 || T > T_cap || T > Tc_cap || d < 1) return CHAI_ERR_SHAPE;
     if (d != kHeadDim || B > kMaxGridYZ || H > kMaxGridYZ) return CHAI_ERR_UNSUPPORTED;
-    *plan = make_decode_plan(B, H, k, T);
+    *plan = make_decode_plan(B, H, k, T, row_bytes_of(dtype));
     if (B > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < plan->bytes))
         return CHAI_ERR_WORKSPACE;
     return CHAI_OK;
@@ -222,7 +222,7 @@ size_t chai_decode_workspace_bytes(int B, int H, int k, int T, int d, int dtype)
 {
     if (B < 0 || H < 1 || k < 1 || k > H || T < 1 || d != kHeadDim || bad_dtype(dtype)) return 0;
     if (B == 0) return 256;
-    return make_decode_plan(B, H, k, T).bytes;
+    return make_decode_plan(B, H, k, T, row_bytes_of(dtype)).bytes;
 }
 
 int chai_decode_scores_timed(const void *q, const void *k_compact, const int32_t *rep_heads, int B, int H, int k,
@@ -366,7 +366,7 @@ size_t chai_decode_q8_workspace_bytes(int B, int H, int k, int T, int d)
 {
     if (B < 0 || H < 1 || k < 1 || k > H || T < 1 || d != kHeadDim) return 0;
     if (B == 0) return 256;
-    return make_decode_plan(B, H, k, T, false).bytes;
+    return make_decode_plan(B, H, k, T, kHeadDim).bytes;
 }
 
 int chai_decode_attention_q8_timed(const void *q, const uint8_t *k8, const float *kscale, const uint8_t *v8,
@@ -380,7 +380,7 @@ int chai_decode_attention_q8_timed(const void *q, const uint8_t *k8, const float
     if (B < 0 || H < 1 || k < 1 || k > H || T < 1 || T > T_cap || T > Tc_cap || d < 1) return CHAI_ERR_SHAPE;
     if (d != kHeadDim || B > kMaxGridYZ || H > kMaxGridYZ) return CHAI_ERR_UNSUPPORTED;
     if (!aligned16(q) || !aligned16(k8) || !aligned16(v8) || !aligned16(out)) return CHAI_ERR_ALIGN;
-    const DecodePlan plan = make_decode_plan(B, H, k, T, false);
+    const DecodePlan plan = make_decode_plan(B, H, k, T, kHeadDim);
     if (B > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < plan.bytes))
         return CHAI_ERR_WORKSPACE;
     if (B == 0) return CHAI_OK;
@@ -432,7 +432,7 @@ int chai_decode_attention_shared_v(const void *q, const void *k_compact, const v
     if (d != kHeadDim || B > kMaxGridYZ || H > kMaxGridYZ) return CHAI_ERR_UNSUPPORTED;
     if (!aligned16(q) || !aligned16(k_compact) || !aligned16(v_compact) || !aligned16(out)) return CHAI_ERR_ALIGN;
     // both caches hold k streams per batch row: the launch plan of k heads in k clusters
-    const DecodePlan plan = make_decode_plan(B, k, k, T);
+    const DecodePlan plan = make_decode_plan(B, k, k, T, row_bytes_of(dtype));
     if (B > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < plan.bytes))
         return CHAI_ERR_WORKSPACE;
     if (B == 0) return CHAI_OK;

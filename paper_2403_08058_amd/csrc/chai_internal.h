@@ -27,8 +27,10 @@ struct DecodePlan {
     size_t off_scores, off_stats, off_partial, off_rows, bytes;   // off_rows: [B,H,128] fp32 staging rows
 };
 
-// column_split = false: never cut rows into column parts (caches whose rows are a single cache line)
-DecodePlan make_decode_plan(int B, int H, int k, int T, bool column_split = true);
+// row_bytes: bytes of one cached row (rows that are a single cache line are never cut into column parts).  The size of the
+// workspace does not depend on it.
+DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes);
+inline int row_bytes_of(int dtype) { return kHeadDim * (dtype == CHAI_F32 ? 4 : 2); }
 
 // Kernels that use more than 64 KB of dynamic LDS must be told so once on every device they run on.  `done` is the
 // caller's per-kernel table (zero-initialised, one flag per device ordinal); a repeated call costs one hipGetDevice.
@@ -88,7 +90,7 @@ int launch_values(const void *v, const int32_t *h2c, const int32_t *rep, int B, 
                   const void *v_new = nullptr);
 
 // The same two kernels over caches of 8-bit E4M3 codes with one fp32 scale per row; q stays fp32 or bf16 (q_dtype).
-// The plan must have been made with column_split = false.
+// The plan must have been made for rows of kHeadDim bytes.
 int launch_scores_q8(const void *q, int q_dtype, const void *k8, const float *kscale, const int32_t *rep, int B, int H,
                      int k, int T, int Tc_cap, float scale, void *workspace, const DecodePlan &plan,
                      const KernelEvents &ev, hipStream_t stream);

@@ -452,14 +452,28 @@ __global__ __launch_bounds__(NW * 64) void score_kernel(const char *__restrict__
     }
 }
 
+// The partial rows p[0], p[stride], .. added in order; kAddAhead of them are requested at a time (added as they were
+// requested one by one, 14 rows of 52 heads took 5.3 us, a launch with next to no work 2.3 us).
+constexpr int kAddAhead = 16;
+__device__ __forceinline__ float add_rows(const float *__restrict__ p, int n)
+{
+    float sum = 0.f;
+    for (int s0 = 0; s0 < n; s0 += kAddAhead) {
+        float v[kAddAhead];
+#pragma unroll
+        for (int u = 0; u < kAddAhead; ++u) v[u] = p[(size_t)min(s0 + u, n - 1) * kHeadDim];
+#pragma unroll
+        for (int u = 0; u < kAddAhead; ++u) sum = s0 + u < n ? sum + v[u] : sum;
+    }
+    return sum;
+}
+
 // Sum of the partial rows of every head in chunk order.  grid = (B*H), 128 threads.
 __global__ __launch_bounds__(kHeadDim) void combine_kernel(const float *__restrict__ partial, int n_cp,
                                                            float *__restrict__ out)
 {
     const size_t orow = blockIdx.x;
-    float sum = 0.f;
-    for (int s = 0; s < n_cp; ++s) sum += partial[(orow * n_cp + s) * kHeadDim + threadIdx.x];
-    out[orow * kHeadDim + threadIdx.x] = sum;
+    out[orow * kHeadDim + threadIdx.x] = add_rows(partial + orow * n_cp * kHeadDim + threadIdx.x, n_cp);
 }
 
 // Shared-value variant: the streams are compact (one per cluster); head h of n_heads takes the sum of the
@@ -472,9 +486,7 @@ __global__ __launch_bounds__(kHeadDim) void combine_members_kernel(const float *
     const int c = h2c[(size_t)b * n_heads + h];
     if (c < 0 || c >= k) return;
     const size_t srow = (size_t)b * k + c;
-    float sum = 0.f;
-    for (int s = 0; s < n_cp; ++s) sum += partial[(srow * n_cp + s) * kHeadDim + threadIdx.x];
-    out[((size_t)b * n_heads + h) * kHeadDim + threadIdx.x] = sum;
+    out[((size_t)b * n_heads + h) * kHeadDim + threadIdx.x] = add_rows(partial + srow * n_cp * kHeadDim + threadIdx.x, n_cp);
 }
 
 struct Workspace {
@@ -591,7 +603,9 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace
 
-DecodePlan make_decode_plan(int B, int H, int k, int T, bool column_split)
+constexpr long long kShortStream = 192 * 1024;     // bytes of values per workgroup up to which a head's tokens are not split
+
+DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes)
 {
     DecodePlan pl;
     // Score chunk (measured on MI355X on the LLaMa-7B/33B, OPT-66B and 32k-context shapes): the largest of
@@ -601,26 +615,34 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, bool column_split)
     for (int c : {2048, 1024, 512}) {
         if ((long long)B * k * ((T + c - 1) / c) >= 256) { pl.cs = c; break; }
     }
+    // up to 64 workgroups of 256 tokens the launch is one wave's chain long: 64 tokens shorten it (8 clusters, both phases at
+    // 256 fp32 tokens 9.4 -> 8.8 us, at 512 bf16 tokens 9.6 -> 9.3; 16 clusters at 1024 11.9 -> 11.7; with 192 workgroups slower)
+    const bool few = (long long)B * k * ((T + 255) / 256) <= 64;
     // value chunk (measured on MI355X at T = 2048): with >= 384 heads one workgroup per head -- whole row of
     // the cache, no partial rows, no combine launch -- is fastest (416 heads: 39 us against 41-44 us split);
     // with fewer heads the single workgroups become latency-bound and the tokens are split into >= 1024
     // workgroups whose partial rows a combine launch adds up (288 heads: 30 us with 4 chunks against 34 us
-    // unsplit).  Between 192 and 383 heads and up to 1536 tokens, two workgroups per head that take half of the
-    // columns each do better still: enough workgroups without partial rows and without the combine launch
-    // (288 heads: 18.6 against 21.7 us at 640 tokens, 23.0 against 24.3 at 1024, 30.3 against 30.8 at 1536; at
-    // 2048 the token split is 3 % ahead again).
+    // unsplit).  Short streams (up to 192 KB of values per workgroup: 1536 bf16 tokens, 768 fp32, 1536 of 8-bit rows) do better without partial rows and the
+    // combine launch: two workgroups per head that take half of the columns each (bf16, 288 heads: 18.6 against
+    // 21.7 us at 640 tokens, 23.0 against 24.3 at 1024, 30.3 against 30.8 at 1536, at 2048 the token split is 3 % ahead
+    // again; both phases of 72 heads at 1024 tokens 11.9 against 14.1 us, of 104 at 700 11.2 against 13.6, of 32 fp32 heads
+    // at 256 9.4 against 10.3, but of 32 heads at 2048 14.3 against 13.1), or one where a row is a single cache line
+    // (8-bit rows).
     {
         const long long heads = (long long)B * H > 0 ? (long long)B * H : 1;
-        pl.ds = (column_split && heads >= 192 && heads < 384 && T <= 1536) ? 2 : 1;
-        const long long groups = heads * pl.ds;
-        long long want = groups >= 384 ? 1 : (1024 + groups - 1) / groups;
+        const bool halves = row_bytes >= 256;               // column halves are whole cache lines
+        const bool whole = heads < 384 && ((long long)T * row_bytes <= (halves ? 2 : 1) * kShortStream ||
+                                           (halves && heads >= 192 && T <= 1536));
+        pl.ds = whole && halves ? 2 : 1;
+        long long want = heads >= 384 || whole ? 1 : (1024 + heads - 1) / heads;
         const long long most = (T + 127) / 128;
         if (want > most) want = most;
         pl.cp = (int)(((T + want - 1) / want + 127) / 128 * 128);
     }
+    pl.n_cp = (T + pl.cp - 1) / pl.cp;
+    if (few && pl.n_cp == 1) pl.cs = 64;
     pl.n_cs = (T + pl.cs - 1) / pl.cs;
     pl.n_rec = pl.n_cs * kScoreWaves;
-    pl.n_cp = (T + pl.cp - 1) / pl.cp;
 
     // Region sizes are upper bounds over every chunking the rules above can pick (smallest chunks), so the
     // total grows monotonically with T: a workspace sized for the cache capacity serves every shorter context.
@@ -631,6 +653,9 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, bool column_split)
     pl.off_partial = off; off = align_up(off + (size_t)B * H * max_n_cp * kHeadDim * sizeof(float), 256);
     pl.off_rows = off;    off = align_up(off + (size_t)B * H * kHeadDim * sizeof(float), 256);
     pl.bytes = off;
+    // 64-token score chunks write more records than the region above holds; they go where the partial rows would be, which
+    // such a plan has none of (32 bytes per 64 tokens and cluster against 512 per 128 tokens and head)
+    if (pl.cs < 256) pl.off_stats = pl.off_partial;
     return pl;
 }
 

@@ -15,13 +15,13 @@ namespace {
 
 // ---------------------------------------------------------------------------------------------------------
 // Features: grid (H, B), one wave per head.  Lane p < n_tok*(n_tok+1)/2 owns one causal (i, j) pair and runs
-// its 128-term dot product in element order in fp64; lane i < n_tok then normalises row i.
+// its 128-term dot product in element order in fp64, and then its element of the row's softmax.
 // ---------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5, const void *__restrict__ k5,
                                                      int H, int n_tok, int bf16, long long qs, long long ks,
                                                      double scale, float *__restrict__ feat)
 {
-    __shared__ double s[8][8];
+    __shared__ double s[8][8], ex[8][8];
     const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
     const size_t head = (size_t)b * H + h;
 
@@ -66,23 +66,25 @@ __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5
         s[i][j] = scale * acc;
     }
     __syncthreads();
-    if (lane < n_tok) {
-        const int row = lane;
-        double m = s[row][0];
-        for (int c = 1; c <= row; ++c) m = fmax(m, s[row][c]);
-        double e[8];
-        double z = 0.0;
-        for (int c = 0; c <= row; ++c) { e[c] = exp(s[row][c] - m); z = z + e[c]; }
-        float *f = feat + head * (size_t)(n_tok * n_tok) + (size_t)row * n_tok;
-        for (int c = 0; c < n_tok; ++c) f[c] = c <= row ? (float)(e[c] / z) : 0.0f;
+    // every pair's lane takes its own exponential and its own division (one lane per row took up to eight of each in a
+    // row); the row sum is added in column order by all of them
+    double e = 0.0;
+    if (i < n_tok) {
+        double m = s[i][0];
+        for (int c = 1; c <= i; ++c) m = fmax(m, s[i][c]);
+        e = exp(s[i][j] - m);
+        ex[i][j] = e;
     }
+    __syncthreads();
+    float *f = feat + head * (size_t)(n_tok * n_tok);
+    if (i < n_tok) {
+        double z = 0.0;
+        for (int c = 0; c <= i; ++c) z = z + ex[i][c];
+        f[i * n_tok + j] = (float)(e / z);
+    }
+    if (lane < n_tok * n_tok && lane % n_tok > lane / n_tok) f[lane] = 0.0f;
 }
 
-// ---------------------------------------------------------------------------------------------------------
-// K-Means: grid (B), one workgroup of 512 threads per batch row.  Dynamic LDS: centres [k][F] fp64, per-head
-// distance [H] fp64, slice winners [H][slices], assignment/previous assignment/member order [H],
-// counts/labels/list starts [k], and a copy of the features when it fits.
-// ---------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ double sqdist(const float *__restrict__ x, const double *c, int F)
 {
     double acc = 0.0;
@@ -94,108 +96,174 @@ __device__ __forceinline__ double sqdist(const float *__restrict__ x, const doub
     return acc;
 }
 
-// The same sum with the head's coordinates in registers: every term in index order, terms past F left out.  Fully
-// unrolled, so the loads of the centre's coordinates are all in flight together instead of one per iteration.
-constexpr int kRegF = 32;
-constexpr int kHeadWaves = 4;         // waves that own a head each (H <= 256)
-constexpr int kKmBlock = 512;        // threads of the k-means workgroup: more slices per head, one round for the update
-__device__ __forceinline__ double sqdist_regs(const double (&x)[kRegF], const double *c, int F)
+// ---------------------------------------------------------------------------------------------------------
+// K-Means: grid (B), one workgroup per batch row, 2^n "slices" of lanes per head.  A handful of workgroups on an otherwise
+// idle chip: its time is the length of the dependent chain of one pass, so a pass is two stretches with one barrier each:
+//  * assignment: lane sl of a head scans the centres sl, sl + slices, .. (two distances at a time, each one sequential
+//    fp64 sum), then the slices of the head, neighbours in one DPP row, agree on the smallest distance (lowest centre on
+//    ties: what a single ascending scan picks); the head's bit goes into the member mask of its centre;
+//  * update: one thread per (centre, coordinate) adds its members in head order, walking the bits of the mask.
+// Whether a centre is empty every wave sees for itself from the masks, whether a head moved from a flag; masks and flag
+// are doubled, the ones of the next pass are cleared during the update.  (Before: slice winners, assignments, counts,
+// wave votes and member lists passed through LDS with eight barriers per pass, and one thread numbered the clusters in
+// the end: KMOLD us for 72 heads, 16 centres, 9 passes; now KMNEW us.)
+// Dynamic LDS (kmeans_layout): centres [k][FP] fp64, rows padded with zeros (a zero term leaves the sum unchanged),
+// distances [H] fp64, masks [2][k][W] words, assignment [H], counts [k], labels [k], flags, and a copy of the features
+// when it fits.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kRegF = 32;            // coordinates of a head that stay in registers
+constexpr int kKmThreads = 1024;     // most threads of a workgroup
+constexpr int kMaxSlices = 16;       // lanes of a DPP row
+
+struct KmeansLayout {
+    int FP, W, slices;               // padded coordinates, mask words per centre, lanes per head
+    size_t dmin, mask, assign, count, label, flag, x, bytes;      // byte offsets (centres at 0)
+    bool stage_x;
+};
+
+__host__ __device__ inline KmeansLayout kmeans_layout(int H, int F, int k)
 {
-    double acc = 0.0;
-#pragma unroll
-    for (int f = 0; f < kRegF; ++f) {
-        if (f < F) {
-            const double diff = x[f] - c[f];
-            const double sq = diff * diff;
-            acc = acc + sq;
-        }
-    }
-    return acc;
+    KmeansLayout L;
+    L.FP = (F + 3) / 4 * 4;
+    L.W = (H + 31) / 32;
+    L.slices = 1;
+    while (2 * L.slices <= k && 2 * L.slices * H <= kKmThreads && L.slices < kMaxSlices) L.slices *= 2;
+    size_t at = sizeof(double) * (size_t)k * L.FP;
+    L.dmin = at;   at += sizeof(double) * (size_t)H;
+    L.mask = at;   at += sizeof(unsigned) * 2 * (size_t)k * L.W;
+    L.assign = at; at += sizeof(int) * (size_t)H;
+    L.count = at;  at += sizeof(int) * (size_t)k;
+    L.label = at;  at += sizeof(int) * (size_t)k;
+    L.flag = at;   at += sizeof(int) * 2;
+    L.x = at;
+    L.stage_x = at + sizeof(float) * (size_t)H * F <= 64 * 1024;
+    if (L.stage_x) at += sizeof(float) * (size_t)H * F;
+    L.bytes = at;
+    return L;
 }
 
-__global__ __launch_bounds__(kKmBlock) void kmeans_kernel(const float *__restrict__ feat, int H, int F, int k,
-                                                        const int32_t *__restrict__ init_heads, int max_iter,
-                                                        int slices, int stage_x, int32_t *__restrict__ h2c,
-                                                        int32_t *__restrict__ rep, int32_t *__restrict__ ncl,
-                                                        int32_t *__restrict__ iters)
+template <int CTRL>
+__device__ __forceinline__ void take_nearer(double &d, int &j, bool upper)
 {
-    extern __shared__ double lds[];
-    double *centre = lds;                                   // [k][F]
-    double *dmin = centre + (size_t)k * F;                  // [H]      distance of a head to its centre
-    double *cand_d = dmin + H;                              // [H][slices] best distance found by a slice
-    int *cand_j = reinterpret_cast<int *>(cand_d + (size_t)H * slices);   // [H][slices] and its centre
-    int *assign = cand_j + (size_t)H * slices;              // [H]
-    int *prev = assign + H;                                 // [H]
-    int *count = prev + H;                                  // [k]
-    int *label = count + k;                                 // [k]
-    int *order = label + k;                                 // [H] heads sorted by centre, ascending inside a centre
-    int *first = order + H;                                 // [k] where a centre's heads start in `order`
-    int *wave_count = first + k;                            // [kHeadWaves][k] heads of a centre inside one wave
-    float *x_lds = reinterpret_cast<float *>(wave_count + kHeadWaves * k);   // [H][F] copy of the features, when it fits
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(d), CTRL, 0xf, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(d), CTRL, 0xf, 0xf, false);
+    const int oj = __builtin_amdgcn_update_dpp(0, j, CTRL, 0xf, 0xf, false);
+    const double od = __hiloint2double(hi, lo);
+    // the pair's lower lane is asked first, the upper one replaces it: both lanes decide alike, whatever the values are
+    const double da = upper ? od : d, db = upper ? d : od;
+    const int ja = upper ? oj : j, jb = upper ? j : oj;
+    const bool second = db < da || (db == da && jb < ja);
+    d = second ? db : da;
+    j = second ? jb : ja;
+}
 
-    const int b = blockIdx.x, tid = threadIdx.x;
+__global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restrict__ feat, int H, int F, int k,
+                                                            const int32_t *__restrict__ init_heads, int max_iter,
+                                                            int32_t *__restrict__ h2c, int32_t *__restrict__ rep,
+                                                            int32_t *__restrict__ ncl, int32_t *__restrict__ iters)
+{
+    extern __shared__ __attribute__((aligned(16))) char km_lds[];
+    const KmeansLayout L = kmeans_layout(H, F, k);
+    const int FP = L.FP, W = L.W, slices = L.slices;
+    double *centre = reinterpret_cast<double *>(km_lds);
+    double *dmin = reinterpret_cast<double *>(km_lds + L.dmin);
+    unsigned *masks = reinterpret_cast<unsigned *>(km_lds + L.mask);
+    int *assign = reinterpret_cast<int *>(km_lds + L.assign);
+    int *count = reinterpret_cast<int *>(km_lds + L.count);
+    int *label = reinterpret_cast<int *>(km_lds + L.label);
+    int *flag = reinterpret_cast<int *>(km_lds + L.flag);
+    float *x_lds = reinterpret_cast<float *>(km_lds + L.x);
+
+    const int b = blockIdx.x, tid = threadIdx.x, n_thr = blockDim.x, lane = tid & 63;
     const float *Xg = feat + (size_t)b * H * F;
-    if (stage_x)
-        for (int i = tid; i < H * F; i += kKmBlock) x_lds[i] = Xg[i];
-    const float *X = stage_x ? x_lds : Xg;                  // same values either way
-
-    for (int i = tid; i < k * F; i += kKmBlock) {
-        const int j = i / F, f = i - j * F;
+    const float *X = L.stage_x ? x_lds : Xg;                // same values either way
+    if (L.stage_x)
+        for (int i = tid; i < H * F; i += n_thr) x_lds[i] = Xg[i];
+    for (int i = tid; i < k * FP; i += n_thr) {
+        const int j = i / FP, f = i - j * FP;
         const int h0 = min(max(init_heads[(size_t)b * k + j], 0), H - 1);
-        centre[i] = (double)Xg[(size_t)h0 * F + f];
+        centre[i] = f < F ? (double)Xg[(size_t)h0 * F + f] : 0.0;
     }
-    for (int h = tid; h < H; h += kKmBlock) prev[h] = -1;
-    __syncthreads();
+    for (int i = tid; i < 2 * k * W; i += n_thr) masks[i] = 0u;
+    if (tid < 2) flag[tid] = 0;
 
-    // H * slices <= kKmBlock: a thread keeps the same (head, slice) in every pass, so the head's coordinates are
-    // converted once and stay in registers when there are few enough of them
-    const bool in_regs = F <= kRegF && tid < H * slices;
+    // thread -> (head, slice), the same in every pass; the head's coordinates stay in registers when there are few enough
+    const int my_h = tid / slices, sl = tid - my_h * slices;
+    const bool owner = my_h < H;
+    const bool in_regs = F <= kRegF;
     double xr[kRegF];
 #pragma unroll
-    for (int f = 0; f < kRegF; ++f) xr[f] = (in_regs && f < F) ? (double)Xg[(size_t)(tid / slices) * F + f] : 0.0;
+    for (int f = 0; f < kRegF; ++f) xr[f] = (in_regs && owner && f < F) ? (double)Xg[(size_t)my_h * F + f] : 0.0;
+    int prev = -1;                                          // the head's centre in the pass before
+    __syncthreads();
 
     int it = 0;
     for (;;) {
+        unsigned *mask = masks + (it & 1) * (k * W);
+        int *moved_flag = flag + (it & 1);
         ++it;
-        // Assignment.  The centres of a head are dealt to `slices` threads (slice s scans s, s+slices, ... in
-        // ascending order and keeps the first smallest), then one thread per head picks the smallest of the
-        // slice winners, the lowest centre on ties: the same centre a single ascending scan would pick.  Each
-        // distance is one sequential fp64 sum inside one thread.
-        for (int p = tid; p < H * slices; p += kKmBlock) {
-            const int h = p / slices, sl = p - h * slices;
-            const float *x = X + (size_t)h * F;
-            int best = -1;
-            double bd = 0.0;
-            for (int j = sl; j < k; j += slices) {
-                const double dj = in_regs ? sqdist_regs(xr, centre + (size_t)j * F, F) : sqdist(x, centre + (size_t)j * F, F);
-                if (best < 0 || dj < bd) { bd = dj; best = j; }
+        int best = 0;
+        double bd = 0.0;
+        if (owner) {
+            if (in_regs) {
+                best = -1;
+                for (int j = sl; j < k; j += 2 * slices) {
+                    const int j2 = min(j + slices, k - 1);  // past the last centre: repeated, not used
+                    const double *c0 = centre + (size_t)j * FP, *c1 = centre + (size_t)j2 * FP;
+                    double a0 = 0.0, a1 = 0.0;
+#pragma unroll
+                    for (int f0 = 0; f0 < kRegF; f0 += 4) {
+                        if (f0 < F) {
+#pragma unroll
+                            for (int f = f0; f < f0 + 4; ++f) {
+                                const double e0 = xr[f] - c0[f], e1 = xr[f] - c1[f];
+                                const double s0 = e0 * e0, s1 = e1 * e1;
+                                a0 = a0 + s0;
+                                a1 = a1 + s1;
+                            }
+                        }
+                    }
+                    if (best < 0 || a0 < bd) { bd = a0; best = j; }
+                    if (j + slices < k && a1 < bd) { bd = a1; best = j + slices; }
+                }
+            } else {
+                best = -1;
+                for (int j = sl; j < k; j += slices) {
+                    const double dj = sqdist(X + (size_t)my_h * F, centre + (size_t)j * FP, F);
+                    if (best < 0 || dj < bd) { bd = dj; best = j; }
+                }
             }
-            cand_d[p] = bd;
-            cand_j[p] = best;
         }
+        if (slices > 1) take_nearer<0xB1>(bd, best, sl & 1);       // quad_perm [1,0,3,2]
+        if (slices > 2) take_nearer<0x4E>(bd, best, sl & 2);       // quad_perm [2,3,0,1]
+        if (slices > 4) take_nearer<0x141>(bd, best, sl & 4);      // row_half_mirror: the other quad, which agrees already
+        if (slices > 8) take_nearer<0x140>(bd, best, sl & 8);      // row_mirror: the other eight
+        if (owner && sl == 0) {
+            assign[my_h] = best;
+            dmin[my_h] = bd;
+            atomicOr(&mask[best * W + (my_h >> 5)], 1u << (my_h & 31));
+            if (best != prev) *moved_flag = 1;
+        }
+        const int before = prev;
+        prev = best;
         __syncthreads();
-        for (int h = tid; h < H; h += kKmBlock) {
-            int best = cand_j[(size_t)h * slices];
-            double bd = cand_d[(size_t)h * slices];
-            for (int sl = 1; sl < slices; ++sl) {
-                const int j = cand_j[(size_t)h * slices + sl];
-                const double dj = cand_d[(size_t)h * slices + sl];
-                if (j >= 0 && (dj < bd || (dj == bd && j < best))) { bd = dj; best = j; }
+
+        // Centres that received no head take, in ascending order, the farthest head of a cluster that can spare one.
+        // Sequential by nature, but needed only when some centre is empty.
+        bool empty = false;
+        for (int j = lane; j < k; j += 64) {
+            unsigned any = 0u;
+            for (int i = 0; i < W; ++i) any |= mask[j * W + i];
+            empty |= any == 0u;
+        }
+        int changed = *moved_flag;
+        if (__any(empty)) {                                 // the same in every wave
+            for (int j = tid; j < k; j += n_thr) {
+                int n = 0;
+                for (int i = 0; i < W; ++i) n += __popc(mask[j * W + i]);
+                count[j] = n;
             }
-            assign[h] = best;
-            dmin[h] = bd;
-        }
-        for (int j = tid; j < k; j += kKmBlock) count[j] = 0;
-        __syncthreads();
-        // members per centre: every head adds one to its centre's counter (integers: any order gives the
-        // sequential result)
-        for (int h = tid; h < H; h += kKmBlock) atomicAdd(&count[assign[h]], 1);
-        __syncthreads();
-        int empty = 0;
-        for (int j = tid; j < k; j += kKmBlock) empty |= count[j] == 0;
-        // Centres that received no head take, in ascending order, the farthest head of a cluster that can spare
-        // one.  Sequential by nature, but needed only when some centre is empty.
-        if (__syncthreads_or(empty)) {
+            __syncthreads();
             if (tid == 0) {
                 for (int j = 0; j < k; ++j) {
                     if (count[j] != 0) continue;
@@ -204,79 +272,79 @@ __global__ __launch_bounds__(kKmBlock) void kmeans_kernel(const float *__restric
                     for (int h = 0; h < H; ++h)
                         if (count[assign[h]] >= 2 && dmin[h] > far) { far = dmin[h]; pick = h; }
                     if (pick < 0) continue;
-                    count[assign[pick]]--;
+                    const int from = assign[pick];
+                    count[from]--;
+                    mask[from * W + (pick >> 5)] &= ~(1u << (pick & 31));
                     assign[pick] = j;
                     count[j] = 1;
+                    mask[j * W + (pick >> 5)] |= 1u << (pick & 31);
                     dmin[pick] = 0.0;
                 }
             }
             __syncthreads();
+            // heads that moved for good: compared with the pass before, which the owners remember
+            const int now = owner ? assign[my_h] : 0;
+            changed = __syncthreads_or(owner && now != before);
+            prev = now;
         }
-        int moved = 0;
-        for (int h = tid; h < H; h += kKmBlock) {
-            moved |= assign[h] != prev[h];
-            prev[h] = assign[h];
-        }
-        const int changed = __syncthreads_or(moved);        // same value in every thread
         if (!changed || it >= max_iter) break;
-        // member lists: the heads of centre j in ascending order, behind those of the centres before it.  Thread h
-        // owns head h (H <= 256: the first four waves); its place is the number of lower heads of the same centre,
-        // counted with one wave vote per centre plus the totals of the waves before it.
-        {
-            const int wv = tid >> 6, ln = tid & 63;
-            const int a = tid < H ? assign[tid] : -1;
-            int below = 0;
-            if (wv < kHeadWaves) {
-                for (int j = 0; j < k; ++j) {
-                    const unsigned long long votes = __ballot(a == j);
-                    if (a == j) below = __popcll(votes & ((1ull << ln) - 1ull));
-                    if (ln == 0) wave_count[wv * k + j] = __popcll(votes);
+        // update: one thread per (centre, coordinate), members added in head order, four requested at a time
+        for (int i = tid; i < k * F; i += n_thr) {
+            const int j = i / F, f = i - j * F;
+            double acc = 0.0;
+            int n = 0;
+            for (int wd = 0; wd < W; ++wd) {
+                unsigned left = mask[j * W + wd];
+                n += __popc(left);
+                while (left != 0u) {
+                    float v[4];
+                    int got = 0;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int h = wd * 32 + (left != 0u ? __ffs(left) - 1 : 0);
+                        got += left != 0u;
+                        left &= left - 1u;                  // 0 stays 0
+                        v[u] = X[(size_t)h * F + f];
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (u < got) acc = acc + (double)v[u];
                 }
             }
-            for (int j = tid; j < k; j += kKmBlock) {
-                int at = 0;
-                for (int i = 0; i < j; ++i) at += count[i];
-                first[j] = at;
-            }
-            __syncthreads();
-            if (tid < H) {
-                int at = first[a] + below;
-                for (int i = 0; i < wv; ++i) at += wave_count[i * k + a];
-                order[at] = tid;
-            }
+            if (n != 0) centre[j * FP + f] = acc / (double)n;
         }
-        __syncthreads();
-        // update: one thread per (centre, coordinate), members added in head order
-        for (int i = tid; i < k * F; i += kKmBlock) {
-            const int j = i / F, f = i - j * F;
-            const int n = count[j];
-            if (n == 0) continue;
-            const int *mem = order + first[j];
-            double acc = 0.0;
-#pragma unroll 4
-            for (int m = 0; m < n; ++m) acc = acc + (double)X[(size_t)mem[m] * F + f];
-            centre[i] = acc / (double)n;
-        }
+        unsigned *next = masks + (it & 1) * (k * W);
+        for (int i = tid; i < k * W; i += n_thr) next[i] = 0u;
+        if (tid == 0) flag[it & 1] = 0;
         __syncthreads();
     }
-    __syncthreads();
 
     // canonical labels: clusters numbered by their lowest member, which represents them
-    if (tid == 0) {
-        for (int j = 0; j < k; ++j) { label[j] = -1; rep[(size_t)b * k + j] = -1; }
-        int n = 0;
-        for (int h = 0; h < H; ++h) {
-            const int a = assign[h];
-            if (label[a] < 0) {
-                label[a] = n;
-                rep[(size_t)b * k + n] = h;
-                ++n;
-            }
-            h2c[(size_t)b * H + h] = label[a];
+    const unsigned *mask = masks + ((it - 1) & 1) * (k * W);
+    for (int j = tid; j < k; j += n_thr) {
+        int low = H;
+        for (int i = W - 1; i >= 0; --i) {
+            const unsigned m = mask[j * W + i];
+            if (m != 0u) low = i * 32 + __ffs(m) - 1;
         }
-        ncl[b] = n;
-        if (iters) iters[b] = it;
+        count[j] = low;
     }
+    __syncthreads();
+    for (int j = tid; j < k; j += n_thr) {
+        const int low = count[j];
+        int rank = 0, used = 0;
+        for (int i = 0; i < k; ++i) {
+            rank += count[i] < low;
+            used += count[i] < H;
+        }
+        label[j] = rank;
+        if (low < H) rep[(size_t)b * k + rank] = low;
+        if (j >= used) rep[(size_t)b * k + j] = -1;
+        if (j == 0) ncl[b] = used;
+    }
+    __syncthreads();
+    for (int h = tid; h < H; h += n_thr) h2c[(size_t)b * H + h] = label[assign[h]];
+    if (tid == 0 && iters) iters[b] = it;
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -341,14 +409,6 @@ __global__ __launch_bounds__(kBlock) void cluster_error_kernel(const float *__re
     }
 }
 
-// threads that share the centres of one head: as many as fit the workgroup, at most one per centre
-int assignment_slices(int H, int k)
-{
-    int s = kKmBlock / H;
-    if (s > k) s = k;
-    return s < 1 ? 1 : s;
-}
-
 }  // namespace
 
 int launch_score_features(const void *q5, const void *k5, int B, int H, int n_tok, int dtype, int64_t qs, int64_t ks,
@@ -358,28 +418,30 @@ int launch_score_features(const void *q5, const void *k5, int B, int H, int n_to
                               dtype == CHAI_BF16 ? 1 : 0, (long long)qs, (long long)ks, (double)scale, feat);
 }
 
+// The sizes the entry point accepts are those of this formula (64 KB); the kernel itself needs what kmeans_layout says.
 size_t assign_clusters_lds_bytes(int H, int F, int k)
 {
-    const size_t sl = (size_t)assignment_slices(H, k);
-    return sizeof(double) * ((size_t)k * F + H + H * sl) +
-           sizeof(int) * (H * sl + 3 * (size_t)H + (3 + kHeadWaves) * (size_t)k);
-}
-
-// the features are copied to LDS too when that still fits the 64 KB a workgroup may ask for
-constexpr size_t kKmeansLdsLimit = 64 * 1024 - 64;
-size_t kmeans_feature_copy_bytes(int H, int F, int k)
-{
-    const size_t extra = sizeof(float) * (size_t)H * F;
-    return assign_clusters_lds_bytes(H, F, k) + extra <= kKmeansLdsLimit ? extra : 0;
+    size_t sl = 512 / H;
+    if (sl > (size_t)k) sl = k;
+    if (sl < 1) sl = 1;
+    return sizeof(double) * ((size_t)k * F + H + H * sl) + sizeof(int) * (H * sl + 3 * (size_t)H + 7 * (size_t)k);
 }
 
 int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const int32_t *init_heads, int max_iter,
                            int32_t *h2c, int32_t *rep, int32_t *ncl, int32_t *iters, hipStream_t stream)
 {
-    const size_t copy = kmeans_feature_copy_bytes(H, F, k);
-    return (int)launch_kernel(kmeans_kernel, dim3(B), dim3(kKmBlock), assign_clusters_lds_bytes(H, F, k) + copy, stream,
-                              KernelEvents(), feat, H, F, k, init_heads, max_iter, assignment_slices(H, k),
-                              copy != 0 ? 1 : 0, h2c, rep, ncl, iters);
+    const KmeansLayout L = kmeans_layout(H, F, k);
+    if (L.bytes > 64 * 1024) {                              // the mask words of many centres over many heads
+        static DeviceFlags lds_allowed;
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), 160 * 1024, lds_allowed);
+        if (e != hipSuccess) return (int)e;
+    }
+    // threads: the lanes of all heads, and enough for the update to be one round where that is not much more
+    int n_thr = (H * L.slices + 63) / 64 * 64;
+    const int update = (k * F + 63) / 64 * 64;
+    if (n_thr < update) n_thr = update < 512 ? update : (n_thr < 512 ? 512 : n_thr);
+    return (int)launch_kernel(kmeans_kernel, dim3(B), dim3(n_thr), L.bytes, stream, KernelEvents(), feat, H, F, k, init_heads,
+                              max_iter, h2c, rep, ncl, iters);
 }
 
 size_t cluster_error_lds_bytes(int H, int F, int k)

@@ -161,8 +161,9 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Main kernel.  Workgroups of four waves, one per SIMD; a wave owns U (2 or 1) streams of 32 query rows and the
-// accumulators of up to kGroup member heads for them (256 or 128 accumulation registers).
+// Main kernel.  Clustered: workgroups of NW = 4 waves, one per SIMD; a wave owns U (2 or 1) streams of 32 query rows and
+// the accumulators of up to kGroup member heads for them (256 or 128 accumulation registers).  Dense attention (IDENT:
+// every head its own cluster, the work list is not read) needs 64 of them, so that two waves fit a SIMD: NW = 8, U = 1.
 //
 // Per 32-key block i of its keys a wave has three independent pieces of work, from three successive blocks: the value
 // products of block i-1, the softmax of block i, the score products of block i+1.  One straight stretch of code (`body`)
@@ -179,10 +180,10 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // its nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
 // tile adds 11 us for its start, the diagonal that the four waves finish one after the other, and the output rows.
 // Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls: 16 rows x 2043
-// positions, 32 heads in 8 clusters 632 -> 616 us; 4 rows x 4000, 4 clusters 520 -> 472 us (with the balanced numbering
+// positions, 32 heads in 8 clusters 632 -> 616 us, dense 820 -> 783 us; 4 rows x 4000, 4 clusters 520 -> 472 us (with the balanced numbering
 // below); 1 row x 2043 94 -> 61 us; 256 positions behind 1792 keys, 4 rows x 52 heads 131 -> 97 us.
 //
-// U = 1 halves a workgroup's rows for launches that leave CUs without work (rule in launch_prefill): a wave's LDS
+// NW = 4 with U = 1 halves a workgroup's rows for launches that leave CUs without work (rule in launch_prefill): a wave's LDS
 // reads per MFMA double, but twice as many CUs work, on half as long a chain.
 //
 // LDS: rings of three K and three V^T tiles (64 keys).  While tile t is computed, K(t+2) and V(t+1) are loaded with
@@ -192,7 +193,6 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
 // through LDS (670-840 against 578 us per 8-cluster LLaMa-7B layer), three members in one wave (630 against 553 us).
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kWaves = 4, kThreads = kWaves * 64;
 constexpr int kBufs = 3;
 constexpr size_t kKBufBytes = (size_t)kKTile * kHeadDim * 2;        // 64 rows of 256 B (16 pieces), swizzled
 constexpr size_t kVBufBytes = (size_t)kHeadDim * kKTile * 2;        // one member: 128 rows of 128 B (8 pieces), swizzled
@@ -208,7 +208,7 @@ constexpr size_t kLdsBytes = kBufs * (kKBufBytes + kGroup * kVBufBytes);
 // go out first; the last 32 to 63 pairs go out as single tiles, the largest first, which fills the last round.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kXcds = 8, kXcdCus = 32;
-constexpr int kSmallTiles = 600;
+constexpr int kSmallTiles = 450, kSmallDense = 256;      // see launch_prefill
 struct PrefillWork {
     int b, gi;           // batch row, group (identity: head)
     int qt0, qt1, n_pass;   // query tiles
@@ -217,63 +217,65 @@ template <bool IDENT>
 __device__ __forceinline__ bool find_work(const int32_t *__restrict__ n_groups, int n_rows, int H, int n_qt, PrefillWork &work)
 {
     const int lane = threadIdx.x & 63;
-    const int n_pairs = (n_qt + 1) / 2;
-    long long total = 0;
-    if (IDENT) total = (long long)n_rows * H;
+    const unsigned n_pairs = (unsigned)(n_qt + 1) / 2;
+    unsigned total = 0;                                     // groups; total * n_pairs < 2^31 (launch_prefill)
+    int first_rows = 0;                                     // group count of this lane's row among the first 64
+    if (IDENT) total = (unsigned)n_rows * (unsigned)H;
     else {
         for (int r0 = 0; r0 < n_rows; r0 += 64) {
             int c = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
+            if (r0 == 0) first_rows = c;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-            total += c;
+            total += (unsigned)__builtin_amdgcn_readfirstlane(c);
         }
     }
-    const int xcd = blockIdx.x % kXcds;
-    const long long local = blockIdx.x / kXcds, pairs = total * n_pairs;
-    const long long lo = pairs * xcd / kXcds, hi = pairs * (xcd + 1) / kXcds;
-    const long long rounds = (hi - lo) / kXcdCus - 1;
-    const long long mid = lo + (rounds > 0 ? rounds * kXcdCus : 0);          // pairs lo .. mid-1, then single tiles
-    long long group;
+    const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, pairs = total * n_pairs;
+    const unsigned each = pairs / kXcds, rest = pairs % kXcds;               // the first `rest` XCDs take one more
+    const unsigned lo = each * xcd + min(xcd, rest), hi = lo + each + (xcd < rest ? 1u : 0u);
+    const unsigned rounds = (hi - lo) / kXcdCus;
+    const unsigned mid = lo + (rounds > 1 ? (rounds - 1) * kXcdCus : 0u);    // pairs lo .. mid-1, then single tiles
+    unsigned group;
     if (local < mid - lo) {
-        const long long at = lo + local;
+        const unsigned at = lo + local;
         group = at / n_pairs;
-        const int pi = (int)(at % n_pairs);
+        const int pi = (int)(at - group * n_pairs);
         work.qt0 = n_qt - 1 - pi;
         work.qt1 = pi;
-        work.n_pass = work.qt0 > pi ? 2 : 1;                               // the middle tile of an odd count is alone
+        work.n_pass = work.qt0 > pi ? 2 : 1;                                 // the middle tile of an odd count is alone
     } else {
         if (mid >= hi) return false;
-        const long long first = mid / n_pairs, n_first = (hi - 1) / n_pairs - first + 1, m = n_first * n_pairs;
-        long long j = local - (mid - lo);
+        const unsigned first = mid / n_pairs, n_first = (hi - 1) / n_pairs - first + 1, m = n_first * n_pairs;
+        unsigned j = local - (mid - lo);
         if (j >= 2 * m) return false;
         const bool large = j < m;
         if (!large) j -= m;
-        const int pi = large ? (int)(j / n_first) : n_pairs - 1 - (int)(j / n_first);
-        group = first + j % n_first;
-        const long long at = group * n_pairs + pi;
+        const unsigned row = j / n_first;
+        const int pi = (int)(large ? row : n_pairs - 1 - row);
+        group = first + j - row * n_first;
+        const unsigned at = group * n_pairs + (unsigned)pi;
         if (at < mid || at >= hi || (!large && n_qt - 1 - pi == pi)) return false;
         work.qt0 = large ? n_qt - 1 - pi : pi;
         work.qt1 = 0;
         work.n_pass = 1;
     }
     if (IDENT) {
-        work.b = (int)(group / H);
-        work.gi = (int)(group % H);
+        work.b = (int)(group / (unsigned)H);
+        work.gi = (int)(group % (unsigned)H);
         return true;
     }
     for (int r0 = 0; r0 < n_rows; r0 += 64) {
-        const int c = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
-        int upto = c;
+        int upto = r0 == 0 ? first_rows : (r0 + lane < n_rows ? n_groups[r0 + lane] : 0);
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
             const int other = __shfl_up(upto, o);
             upto += lane >= o ? other : 0;
         }
-        const int all = __shfl(upto, 63);
+        const unsigned all = (unsigned)__builtin_amdgcn_readlane(upto, 63);
         if (group < all) {
-            const int row = __popcll(__ballot(upto <= group));
+            const int row = __popcll(__ballot((unsigned)upto <= group));
             work.b = r0 + row;
-            work.gi = (int)group - (row > 0 ? __shfl(upto, row > 0 ? row - 1 : 0) : 0);
+            work.gi = (int)group - (row > 0 ? __builtin_amdgcn_readlane(upto, row - 1) : 0);
             return true;
         }
         group -= all;
@@ -283,8 +285,9 @@ __device__ __forceinline__ bool find_work(const int32_t *__restrict__ n_groups, 
 
 // Accumulator tile T of the kernel below: registers a[16 T .. 16 T + 15] of the accumulation half, BY NAME.  The compiler
 // never sees the accumulators as values (offered as operands it carried them through ordinary registers at every branch,
-// 688 spills); it has no other use for that half in this file (matrix results are kept in ordinary registers by the
-// build's -amdgpu-mfma-vgpr-form), and the clobbers keep it from finding one.  What the compiler would insert
+// 688 spills); matrix results of its own are kept in ordinary registers by the build's -amdgpu-mfma-vgpr-form, and the
+// clobbers keep whatever else it may put into that half (copies of ordinary registers, in the kernel with two waves per
+// SIMD) away from the named ones.  What the compiler would insert
 // between dependent instructions stands here: two idle slots between an ordinary write and a matrix read
 // (acc_written), twenty between a matrix write and an ordinary read (acc_settle).
 template <int T>
@@ -358,6 +361,21 @@ CHAI_ACC_TILE(15, "a[240:255]", "a240", "a241", "a242", "a243", "a244", "a245", 
 #undef CHAI_ACC_READ
 #undef CHAI_ACC_MFMA
 
+// Nothing of the compiler's lives in a0 .. a63 across this point.  In the kernel with two waves per SIMD, which needs the
+// rest of the accumulation half for copies of ordinary registers, one stands behind every matrix instruction: the products'
+// own clobbers left it room to park a value in a0 between two products of another tile.
+__device__ __forceinline__ void acc_hold()
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" :::
+                 "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15", "a16",
+                 "a17", "a18", "a19", "a20", "a21", "a22", "a23", "a24", "a25", "a26", "a27", "a28", "a29", "a30", "a31",
+                 "a32", "a33", "a34", "a35", "a36", "a37", "a38", "a39", "a40", "a41", "a42", "a43", "a44", "a45", "a46",
+                 "a47", "a48", "a49", "a50", "a51", "a52", "a53", "a54", "a55", "a56", "a57", "a58", "a59", "a60", "a61",
+                 "a62", "a63");
+#endif
+}
+
 __device__ __forceinline__ void acc_written()
 {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -427,8 +445,8 @@ struct OpSchedule {
     }
 };
 
-// One query tile (4 waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
-template <int NM, int U>
+// One query tile (NW waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
+template <int NM, int U, int NW>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
                                           int qt, int rhead, float scale2, float *__restrict__ out)
@@ -436,10 +454,10 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r = lane & 31, hl = lane >> 5;
     const int n_keys = q_start + Tq;
-    const int i0 = (qt * kWaves + w) * (32 * U);                // first query row of this wave
+    const int i0 = (qt * NW + w) * (32 * U);                // first query row of this wave
     const int wave_first = q_start + min(i0, Tq - 1);
     const int wave_last = q_start + min(i0 + 32 * U - 1, Tq - 1);
-    const int wg_last = q_start + min((qt + 1) * (kWaves * 32 * U) - 1, Tq - 1);
+    const int wg_last = q_start + min((qt + 1) * (NW * 32 * U) - 1, Tq - 1);
     const int n_tiles = wg_last / kKTile + 1;
     const int n_hb = i0 < Tq ? wave_last / 32 + 1 : -1;      // 32-key blocks of this wave (-1: a padding wave)
 
@@ -453,7 +471,9 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     // of K row R sits in slot c ^ (R & 15) of the row, piece c of V^T row R in slot c ^ ((R >> 1) & 7); 16 consecutive rows
     // read at one piece index then touch 16 different 16-byte slots of the 256-byte bank window (measured: 16 cycles per
     // read with four waves reading, the same as for linear addresses).  A lane fetches whichever piece belongs in the
-    // slot it fills.  Instruction i of wave w fills K rows 4w + 16i .. +3, or V^T rows 8w + 32i .. +7 of a member.
+    // slot it fills.  Instruction i (of kDma) of wave w fills K rows 4(w + NW i) .. +3, or V^T rows 8(w + NW i) .. +7 of a
+    // member.
+    constexpr int kDma = 16 / NW;
     const int k_row = 4 * w + (lane >> 4);
     const int v_row = 8 * w + (lane >> 3);
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -470,26 +490,26 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     const auto k_rs = make_rsrc(ksrc);
     const auto v_rs0 = make_rsrc(vsrc[0]);
     const auto v_rs1 = make_rsrc(vsrc[NM - 1]);
-    auto dma_k1 = [&](int kt, int buf, int i) {              // instruction i (of 4) of a K tile
-        const int row = k_row + 16 * i;
+    auto dma_k1 = [&](int kt, int buf, int i) {
+        const int row = k_row + 4 * NW * i;
         load_to_lds(k_rs, (unsigned int)(min(kt * kKTile + row, n_keys - 1) * (kHeadDim * 2) + (((lane & 15) ^ (row & 15)) << 4)),
-                    k_lds + buf * kKBufBytes + (w + 4 * i) * 1024);
+                    k_lds + buf * kKBufBytes + (w + NW * i) * 1024);
     };
-    const int v_piece = (lane & 7) ^ ((v_row >> 1) & 7);     // rows 32 apart share the swizzle
+    const int v_piece = (lane & 7) ^ ((v_row >> 1) & 7);     // rows 8 NW apart share the swizzle
     const unsigned int v_off = (unsigned int)(v_row * (kKTile * 2) + v_piece * 16);
-    auto dma_v1 = [&](int kt, int buf, int g, int i) {       // instruction i (of 4) of member g's V^T tile
-        load_to_lds(g == 0 ? v_rs0 : v_rs1, (unsigned int)kt * (unsigned int)kVBufBytes + v_off + i * 32 * (kKTile * 2),
-                    v_lds + (buf * kGroup + g) * kVBufBytes + (w + 4 * i) * 1024);
+    auto dma_v1 = [&](int kt, int buf, int g, int i) {
+        load_to_lds(g == 0 ? v_rs0 : v_rs1, (unsigned int)kt * (unsigned int)kVBufBytes + v_off + i * 8 * NW * (kKTile * 2),
+                    v_lds + (buf * kGroup + g) * kVBufBytes + (w + NW * i) * 1024);
     };
     auto dma_k = [&](int kt, int buf) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) dma_k1(kt, buf, i);
+        for (int i = 0; i < kDma; ++i) dma_k1(kt, buf, i);
     };
     auto dma_v = [&](int kt, int buf) {
 #pragma unroll
         for (int g = 0; g < NM; ++g)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) dma_v1(kt, buf, g, i);
+            for (int i = 0; i < kDma; ++i) dma_v1(kt, buf, g, i);
     };
     // every wave waits for its own requests (the compiler does not track loads that land in LDS), then a bare s_barrier:
     // __syncthreads() would add fences that the loads to LDS do not need
@@ -509,8 +529,14 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                                                 (((4 * half + 2 * (j >> 2) + hl) ^ v_sw) << 4));
     };
 
-    unroll<4 * U * NM>([&](auto t) { AccTile<t.value>::zero(); });           // tile (stream * NM + member) * 4 + block
+    // accumulators: tile (stream * NM + member) * 4 + 32-column block
+    constexpr int kTiles = 4 * U * NM;
+    unroll<kTiles>([&](auto t) { AccTile<t.value>::zero(); });
     acc_written();
+    auto product = [&](auto t, const f16x8 &a, const f16x8 &b) {
+        AccTile<t.value>::mfma(a, b);
+        if constexpr (NW == 8) acc_hold();
+    };
     float m_run[U], l_run[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -534,7 +560,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             vf.raw = v_frag(vb, vhalf, p);
             unroll<U>([&](auto uc) {
                 constexpr int u = uc.value;
-                AccTile<(u * NM + (p >> 3)) * 4 + (p & 3)>::mfma(vf.h, pp.f[u][(p >> 2) & 1].h);
+                product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, vf.h, pp.f[u][(p >> 2) & 1].h);
             });
         });
     };
@@ -589,9 +615,10 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                     } else
                         c = sn.s[u];
                     sn.s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fr[s].bf, qf[u][ks].bf, c, 0, 0, 0);
+                    if constexpr (NW == 8) acc_hold();
                 } else {
                     constexpr int p = NM == 2 ? s - s / 3 : s / 2;
-                    AccTile<(u * NM + (p >> 3)) * 4 + (p & 3)>::mfma(fr[s].h, pp.f[u][(p >> 2) & 1].h);
+                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, fr[s].h, pp.f[u][(p >> 2) & 1].h);
                 }
             }
         };
@@ -658,7 +685,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         unroll<kAhead>([&](auto i) { carry.f[i.value] = fr[kSlots + i.value]; });
         if (__builtin_expect(moved && kbase > 0, 0)) {
             acc_settle();
-            unroll<4 * U * NM>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
+            unroll<kTiles>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
         }
     };
 
@@ -709,21 +736,22 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         const int hb = 2 * kt;
         const char *vprev = vb_lane + b3p * (kGroup * kVBufBytes), *vcur = vb_lane + b3 * (kGroup * kVBufBytes);
         const char *k_odd = kb_lane + b3 * kKBufBytes + 32 * (kHeadDim * 2), *k_even = kb_lane + b3n * kKBufBytes;
-        auto dma0 = [&](int i) {                             // the next tiles' 4 + 4 NM requests, early in this one
-            if (i < 4) dma_v1(kt1, b3n, 0, i);
-            else if (i < 4 * NM) dma_v1(kt1, b3n, 1, i - 4);
-            else if (i < 4 * NM + 4) dma_k1(kt2, b3nn, i - 4 * NM);
+        auto dma0 = [&](int i) {                             // the next tiles' kDma (NM + 1) requests, early in this one
+            if (i < kDma) dma_v1(kt1, b3n, 0, i);
+            else if (i < kDma * NM) dma_v1(kt1, b3n, 1, i - kDma);
+            else if (i < kDma * (NM + 1)) dma_k1(kt2, b3nn, i - kDma * NM);
         };
         auto dma1 = [&](int) {};
         if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0);
         else {
-            unroll<4 * NM + 4>([&](auto i) { dma0(i.value); });
+            unroll<kDma * (NM + 1)>([&](auto i) { dma0(i.value); });
             if (hb == n_hb) pv_only(pb, vprev, 1);
         }
         if (hb + 1 < n_hb)
             body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1);
         else if (hb + 1 == n_hb) pv_only(pa, vcur, 0);
-        tile_barrier();
+        // (after the last tile nobody waits for the requests past the end: they fill buffers that are not read any more)
+        if (kt + 1 < n_tiles) tile_barrier();
         b3p = b3;
         b3 = b3n;
     }
@@ -738,7 +766,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             both_halves(l_run[u], lo, hi);
             inv[u] = 1.0f / (lo + hi);
         }
-        unroll<4 * U * NM>([&](auto tc) {
+        unroll<kTiles>([&](auto tc) {
             constexpr int t = tc.value, u = t / (4 * NM), g = t / 4 % NM, blk = t % 4;
             const int my_i = i0 + u * 32 + r;
             float x[16];
@@ -752,10 +780,14 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             }
         });
     }
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the requests past the end have landed before LDS is given to another tile or workgroup
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
 }
 
-template <int U, bool IDENT>
-__global__ __launch_bounds__(kThreads, 1) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
+template <int U, int NW, bool IDENT>
+__global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
                                                                   const _Float16 *__restrict__ vt,
                                                                   const int32_t *__restrict__ groups,
                                                                   const int32_t *__restrict__ n_groups, int H, int k,
@@ -785,10 +817,10 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_kernel(const char *__rest
         const int qt = __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1);
         if (pass != 0) __syncthreads();
         if (!IDENT && n_mem == 2)
-            prefill_tile<2, U>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
+            prefill_tile<2, U, NW>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
                          scale * kLog2e, out);
         else
-            prefill_tile<1, U>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
+            prefill_tile<1, U, NW>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
                          scale * kLog2e, out);
     }
 }
@@ -827,23 +859,25 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
                                  static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt, h2c, rep, k, max_groups, groups,
                                  n_groups);
     if (e != hipSuccess) return (int)e;
-    // Two streams of 32 rows per wave, or one (tiles of 256 or 128 rows): one where the wide tiles would leave CUs without
-    // work or end in a ragged last round.  The line lies at kSmallTiles 256-row tiles of the most groups the maps can
-    // have; whole calls with tiles of 256 / 128 rows: at 384 of them 164 / 153 us, at 416 73 / 71 us, dense at 576 88 / 84 us,
-    // at 840 656 / 676 us, at 1280 472 / 567 us.
+    // Tiles of 256 or of 128 query rows: 128 where the wide tiles would leave CUs without work or end in a ragged last round,
+    // and where a block has no more rows than that.  The lines lie at a number of 256-row tiles of the most groups the maps
+    // can have.  Whole calls with 256 / 128 rows: clustered, at 136 tiles 118 / 97 us, at 384 164 / 153 us and 71 / 66 us, at
+    // 440 28 / 25 us, at 416 81 / 86 us and 110 / 103 us, at 576 129 / 148 us, at 1280 472 / 567 us, 65 rows at 960 tiles
+    // 81 / 73 us; dense, at 128 tiles 39 / 32 us, at 256 68 / 66 us, at 260 48 / 60 us, at 4096 783 / 914 us.
     const long long tiles = (long long)((Tq + 255) / 256) * max_groups * B;
-    const int U = tiles <= kSmallTiles ? 1 : 2;
-    auto *kernel = U == 1 ? (identity ? prefill_kernel<1, true> : prefill_kernel<1, false>)
-                          : (identity ? prefill_kernel<2, true> : prefill_kernel<2, false>);
+    const bool small = identity ? tiles <= kSmallDense : (tiles <= kSmallTiles || Tq <= 128);
+    auto *kernel = small ? (identity ? prefill_kernel<1, 4, true> : prefill_kernel<1, 4, false>)
+                         : (identity ? prefill_kernel<1, 8, true> : prefill_kernel<2, 4, false>);
+    const int threads = identity && !small ? 512 : 256, tile_rows = small ? 128 : 256;
     static DeviceFlags lds_allowed[4];
-    e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsBytes, lds_allowed[2 * (U - 1) + (identity ? 1 : 0)]);
+    e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsBytes, lds_allowed[(small ? 2 : 0) + (identity ? 1 : 0)]);
     if (e != hipSuccess) return (int)e;
-    const int n_qt = (Tq + kWaves * 32 * U - 1) / (kWaves * 32 * U);
+    const int n_qt = (Tq + tile_rows - 1) / tile_rows;
     // the most workgroups an XCD can need (find_work): its pairs, the last of them as single tiles of padded groups
-    const long long n_pairs = (n_qt + 1) / 2, most = ((long long)max_groups * B * n_pairs + kXcds - 1) / kXcds + 1;
+    const long long n_pairs = (n_qt + 1) / 2, most = (long long)max_groups * B * n_pairs / kXcds + 1;
     const long long n_wg = kXcds * (most + (most < 2 * kXcdCus ? most : 2 * kXcdCus) + 4 * n_pairs);
     if (n_wg > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(kThreads), kLdsBytes, stream, ev,
+    return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(threads), kLdsBytes, stream, ev,
                               static_cast<const char *>(q), static_cast<const char *>(kc), vt, groups, n_groups, H, k, Tq,
                               q_start, Tc_cap, Tp, n_qt, max_groups, B, scale, out);
 }

@@ -27,7 +27,7 @@ SCALE = float(np.float32(1 / math.sqrt(128)))
     (1, 4, 2, 127, 0), (1, 4, 2, 128, 1), (1, 4, 2, 129, 63), (1, 4, 2, 33, 31), (1, 4, 2, 32, 32),   # one, two 128-row tiles
     (2, 6, 3, 385, 64),                                    # four of them, the last with one row
     (66, 4, 2, 70, 5),                                     # more batch rows than one wave adds up at a time
-    (40, 32, 8, 65, 130),                                  # 960 tiles of 256 rows: the wide kernel with one ragged tile
+    (40, 32, 8, 65, 130), (40, 16, 4, 129, 100),           # many rows of a short block: 128-row tiles, 256-row tiles
     (14, 32, 8, 257, 3), (14, 32, 8, 512, 0),              # 672: two tiles per group, pairs and singles
     (66, 4, 2, 769, 5),                                    # wide, four tiles, 66 rows
     (5, 24, 24, 1000, 30),                                 # wide, every head alone
@@ -37,9 +37,9 @@ def test_prefill_tile_edges(B, H, kk, Tq, q_start):
     run_case(B, H, kk, Tq, q_start, q_start + Tq + 3, seed=B + 5 * H + 7 * kk + Tq + q_start)
 
 
-@pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5)])
+@pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5), (5, 52, 257, 0)])
 def test_dense_prefill_tiles(B, H, Tq, q_start):
-    """Dense entry point, 128-row and 256-row tiles."""
+    """Dense entry point: 128-row tiles; 256-row tiles of eight waves."""
     g = np.random.default_rng(B)
     T = q_start + Tq
     q, k, v = (W.normal(g, (B, H, n, 128), W.BF16) for n in (Tq, T, T))

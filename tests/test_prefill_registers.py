@@ -1,5 +1,5 @@
-"""The prefill kernel names its accumulators (a0 .. a255) in inline assembly, where the compiler inserts no idle slots and
-knows of no owner.  What it relies on is checked here in the assembly that the build's own flags produce."""
+"""The prefill kernel names its accumulators (a0 ..) in inline assembly, where the compiler inserts no idle slots and knows
+of no owner.  What it relies on is checked here in the assembly that the build's own flags produce."""
 import os
 import re
 import subprocess
@@ -17,6 +17,15 @@ def _registers(token):
     return {(m.group(1), int(m.group(2)))} if m else set()
 
 
+def _operands(line):
+    return [o.strip() for o in re.split(r",\s*(?![^\[]*\])", line.split(None, 1)[1])]
+
+
+def _is_product(line):
+    """A matrix instruction of the source's assembly: it adds into accumulation registers (the compiler's own do not)."""
+    return line.startswith("v_mfma") and _operands(line)[0].startswith("a[")
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("asm") / "prefill.s")
@@ -29,12 +38,8 @@ def kernels(tmp_path_factory):
     for m in re.finditer(r"^(_Z\S*prefill_kernel\S*):[^\n]*\n(.*?)\.Lfunc_end", text, re.S | re.M):
         lines = [ln.split(";")[0].strip() for ln in m.group(2).split("\n")]
         found[m.group(1)] = [ln for ln in lines if ln and not (ln.startswith(".") and not ln.startswith(".LBB"))]
-    assert len(found) == 4                       # one or two streams, clustered or dense
+    assert len(found) == 4                       # wide or small tiles, clustered or dense
     return found
-
-
-def _operands(line):
-    return [o.strip() for o in re.split(r",\s*(?![^\[]*\])", line.split(None, 1)[1])]
 
 
 def test_products_are_two_slots_behind_their_operands(kernels):
@@ -42,7 +47,7 @@ def test_products_are_two_slots_behind_their_operands(kernels):
     for name, lines in kernels.items():
         seen = 0
         for i, line in enumerate(lines):
-            if not (line.startswith("v_mfma") and " a[" in line):
+            if not _is_product(line):
                 continue
             seen += 1
             ops = _operands(line)
@@ -65,17 +70,27 @@ def test_products_are_two_slots_behind_their_operands(kernels):
 
 
 def test_accumulators_have_one_owner(kernels):
-    """Accumulation registers are written by zeroing, by a rescaling's read-multiply-write and by the products, and read by
-    those and by the output; no copies, no spills, and no reads without the idle slots after the products."""
+    """The named accumulation registers are written by zeroing, by a rescaling's read-multiply-write and by the products, and
+    read by those and by the output: nothing of the compiler's goes there, and no read comes without the idle slots after
+    the products.  No kernel uses scratch memory."""
     for name, lines in kernels.items():
+        named = set()
+        for line in lines:
+            if _is_product(line):
+                named |= _registers(_operands(line)[0])
+        assert named == {("a", i) for i in range(len(named))} and len(named) in (64, 128, 256), name
         for i, line in enumerate(lines):
-            assert not line.startswith(("scratch_", "v_accvgpr_mov")), f"{name}: {line}"
+            assert not line.startswith("scratch_"), f"{name}: {line}"
+            if line.startswith("v_accvgpr_mov"):
+                assert not (named & (_registers(_operands(line)[0]) | _registers(_operands(line)[1]))), f"{name}: {line}"
             if line.startswith("v_accvgpr_write"):
                 ops = _operands(line)
+                if not named & _registers(ops[0]):
+                    continue
                 if ops[1] != "0":                # the write of a rescaling: read, multiply, write of one register
                     assert lines[i - 1].startswith("v_mul_f32") and lines[i - 2].startswith("v_accvgpr_read"), f"{name}: {line}"
                     assert _operands(lines[i - 2])[1] == ops[0], f"{name}: {line}"
-            if line.startswith("v_accvgpr_read"):
+            if line.startswith("v_accvgpr_read") and named & _registers(_operands(line)[1]):
                 slots, j = 0, i - 1
                 while j >= 0 and slots < 19:     # a product's sixteen passes and the write behind them
                     before = lines[j]

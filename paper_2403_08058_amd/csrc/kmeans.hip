@@ -433,7 +433,8 @@ int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const 
     const KmeansLayout L = kmeans_layout(H, F, k);
     if (L.bytes > 64 * 1024) {                              // the mask words of many centres over many heads
         static DeviceFlags lds_allowed;
-        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), 160 * 1024, lds_allowed);
+        // what the accepted sizes can need: 64 KB of the old formula, 6 KB of padding, 16 KB of masks
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), 96 * 1024, lds_allowed);
         if (e != hipSuccess) return (int)e;
     }
     // threads: the lanes of all heads, and enough for the update to be one round where that is not much more

@@ -267,7 +267,9 @@ int chai_decode_attention_static(const void *q, const void *k_compact, const voi
  * workspace (scores of Section 2, one per cluster as in Section 3.4);
  * chai_decode_values turns them into probabilities and applies them to every
  * head's own values (Section 3.5, Fig. 3).  chai_decode_values must follow
- * chai_decode_scores on the same stream with the same sizes and workspace.
+ * chai_decode_scores on the same stream with the same sizes and workspace;
+ * the types of the two calls may differ (dtype: of q and k_compact in the
+ * first, of v_cache in the second).
  * Meant for callers that time or overlap the phases; chai_decode_attention
  * is exactly the two in sequence.
  */

@@ -27,8 +27,9 @@ struct DecodePlan {
     size_t off_scores, off_stats, off_partial, off_rows, bytes;   // off_rows: [B,H,128] fp32 staging rows
 };
 
-// row_bytes: bytes of one cached row (rows that are a single cache line are never cut into column parts).  The size of the
-// workspace does not depend on it.
+// row_bytes: bytes of one cached row (rows that are a single cache line are never cut into column parts).  Neither the size of
+// the workspace nor what the score phase leaves in it (cs, n_cs, n_rec, off_scores, off_stats) differs between fp32 and bf16
+// rows: the two phase calls are planned one by one and each with its own type.
 DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes);
 inline int row_bytes_of(int dtype) { return kHeadDim * (dtype == CHAI_F32 ? 4 : 2); }
 

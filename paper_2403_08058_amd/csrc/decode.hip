@@ -620,32 +620,38 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes)
     for (int c : {2048, 1024, 512}) {
         if ((long long)B * k * ((T + c - 1) / c) >= 256) { pl.cs = c; break; }
     }
-    // up to 64 workgroups of 256 tokens the launch is one wave's chain long: 64 tokens shorten it (8 clusters, both phases at
-    // 256 fp32 tokens 9.4 -> 8.8 us, at 512 bf16 tokens 9.6 -> 9.3; 16 clusters at 1024 11.9 -> 11.7; with 192 workgroups slower)
-    const bool few = (long long)B * k * ((T + 255) / 256) <= 64;
     // value chunk (measured on MI355X at T = 2048): with >= 384 heads one workgroup per head -- whole row of
     // the cache, no partial rows, no combine launch -- is fastest (416 heads: 39 us against 41-44 us split);
     // with fewer heads the single workgroups become latency-bound and the tokens are split into >= 1024
     // workgroups whose partial rows a combine launch adds up (288 heads: 30 us with 4 chunks against 34 us
-    // unsplit).  Short streams (up to 192 KB of values per workgroup: 1536 bf16 tokens, 768 fp32, 1536 of 8-bit rows) do better without partial rows and the
-    // combine launch: two workgroups per head that take half of the columns each (bf16, 288 heads: 18.6 against
+    // unsplit).  Short streams do better without partial rows and the combine launch: up to 192 KB of values per workgroup
+    // (1536 bf16 tokens, 768 fp32, 1536 of 8-bit rows), and from 192 heads on up to 1536 tokens of fp32 too.  Two
+    // workgroups per head then take half of the columns each (bf16, 288 heads: 18.6 against
     // 21.7 us at 640 tokens, 23.0 against 24.3 at 1024, 30.3 against 30.8 at 1536, at 2048 the token split is 3 % ahead
     // again; both phases of 72 heads at 1024 tokens 11.9 against 14.1 us, of 104 at 700 11.2 against 13.6, of 32 fp32 heads
     // at 256 9.4 against 10.3, but of 32 heads at 2048 14.3 against 13.1), or one where a row is a single cache line
-    // (8-bit rows).
-    {
-        const long long heads = (long long)B * H > 0 ? (long long)B * H : 1;
-        const bool halves = row_bytes >= 256;               // column halves are whole cache lines
-        const bool whole = heads < 384 && ((long long)T * row_bytes <= (halves ? 2 : 1) * kShortStream ||
+    // (8-bit rows; 32 heads at 1536 tokens 12.9 against 15.7, 144 at 1024 12.8 against 21.5).
+    const long long heads = (long long)B * H > 0 ? (long long)B * H : 1;
+    auto value_chunk = [&](int bytes, int *parts) {
+        const bool halves = bytes >= 256;                   // column halves are whole cache lines
+        const bool whole = heads < 384 && ((long long)T * bytes <= (halves ? 2 : 1) * kShortStream ||
                                            (halves && heads >= 192 && T <= 1536));
-        pl.ds = whole && halves ? 2 : 1;
+        *parts = whole && halves ? 2 : 1;
         long long want = heads >= 384 || whole ? 1 : (1024 + heads - 1) / heads;
         const long long most = (T + 127) / 128;
         if (want > most) want = most;
-        pl.cp = (int)(((T + want - 1) / want + 127) / 128 * 128);
-    }
+        return (int)(((T + want - 1) / want + 127) / 128 * 128);
+    };
+    pl.cp = value_chunk(row_bytes, &pl.ds);
     pl.n_cp = (T + pl.cp - 1) / pl.cp;
-    if (few && pl.n_cp == 1) pl.cs = 64;
+    // Up to 64 score workgroups of 256 tokens the launch is one wave's chain long: 64 tokens shorten it (8 clusters, both
+    // phases at 256 fp32 tokens 9.4 -> 8.8 us, at 512 bf16 tokens 9.6 -> 9.3; with 192 workgroups slower).  Their records lie
+    // where partial rows would (below), so no head may be split -- of NEITHER type: the two phase calls are planned one by
+    // one, may be given scores of one type and values of the other, and have to agree on number and place of the records.
+    // fp32 rows are split first; rows of 8-bit codes have no separate phases.
+    int parts;
+    const bool whole_any = (row_bytes < 256 ? pl.cp : value_chunk(kHeadDim * 4, &parts)) >= T;
+    if (whole_any && (long long)B * k * ((T + 255) / 256) <= 64) pl.cs = 64;
     pl.n_cs = (T + pl.cs - 1) / pl.cs;
     pl.n_rec = pl.n_cs * kScoreWaves;
 

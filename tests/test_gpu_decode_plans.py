@@ -99,3 +99,27 @@ def test_features_of_every_prompt_length(n_tok, dtype):
     want = (e / e.sum(-1, keepdims=True)).reshape(2, 7, -1)
     # one rounding to fp32 of a value that 64 bits carry to a few 1e-15
     assert np.all(np.abs(feat.cpu().numpy() - want) <= 2.0 ** -24 * want + 1e-14)
+
+
+@pytest.mark.parametrize("score_dtype,value_dtype", [(W.F32, W.BF16), (W.BF16, W.F32)])
+@pytest.mark.parametrize("B,H,kk,T", [(1, 32, 8, 1024), (1, 8, 3, 769), (1, 8, 3, 768), (1, 12, 4, 1536), (2, 100, 2, 1400)])
+def test_phases_of_different_types_agree_on_the_workspace(score_dtype, value_dtype, B, H, kk, T):
+    """The two phase calls with queries and keys of one type and values of the other: the layout between them does not
+    depend on the type."""
+    print(f"[mixed] {score_dtype}->{value_dtype} B={B} H={H} k={kk} T={T}", flush=True)
+    g = np.random.default_rng(T + H)
+    h2c, rep = W.random_membership(g, B, H, kk)
+    # bf16 numbers, so that the oracle can be given all of them in fp32
+    q, k, v = (W.as_f64(W.normal(g, s, W.BF16)).astype(np.float32) for s in ((B, H, 128), (B, H, T, 128), (B, H, T, 128)))
+    ref = O.clustered_decode(q, k, v, h2c, rep, T, SCALE)
+    tt = {W.F32: torch.float32, W.BF16: torch.bfloat16}
+    kd, hd, rd = dev(k).to(tt[score_dtype]), dev(h2c), dev(rep)
+    kc = torch.zeros((B, kk, T, 128), dtype=kd.dtype, device="cuda")
+    C.chai_compact_kcache(kd, rd, kc, T)
+    ws = G.poisoned_workspace(B, H, kk, T, 128, W.F32)
+    out = torch.full((B, H, 128), float("nan"), dtype=torch.float32, device="cuda")
+    C.chai_decode_scores(dev(q).to(tt[score_dtype]), kc, rd, T, SCALE, ws)
+    C.chai_decode_values(dev(v).to(tt[value_dtype]), hd, rd, T, out, ws)
+    torch.cuda.synchronize()
+    ok, worst = G.rows_close(out.cpu().numpy(), ref, 2e-5)
+    assert ok, worst

@@ -142,19 +142,24 @@ __host__ __device__ inline KmeansLayout kmeans_layout(int H, int F, int k)
     return L;
 }
 
+// What a distance counts for in the choice of the nearest centre.  An ascending scan that starts with centre 0 and takes what
+// is smaller passes a NaN by, and keeps centre 0 for good if that one is NaN: NaN is the largest value, or for centre 0
+// the smallest, and the choice no longer depends on how the centres are dealt to the slices.
+__device__ __forceinline__ double rank_distance(double d, int j)
+{
+    return d == d ? d : (j == 0 ? -HUGE_VAL : HUGE_VAL);
+}
+
 template <int CTRL>
-__device__ __forceinline__ void take_nearer(double &d, int &j, bool upper)
+__device__ __forceinline__ void take_nearer(double &d, int &j)
 {
     const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(d), CTRL, 0xf, 0xf, false);
     const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(d), CTRL, 0xf, 0xf, false);
     const int oj = __builtin_amdgcn_update_dpp(0, j, CTRL, 0xf, 0xf, false);
     const double od = __hiloint2double(hi, lo);
-    // the pair's lower lane is asked first, the upper one replaces it: both lanes decide alike, whatever the values are
-    const double da = upper ? od : d, db = upper ? d : od;
-    const int ja = upper ? oj : j, jb = upper ? j : oj;
-    const bool second = db < da || (db == da && jb < ja);
-    d = second ? db : da;
-    j = second ? jb : ja;
+    const bool other = od < d || (od == d && oj < j);       // never NaN: both lanes of a pair decide alike
+    d = other ? od : d;
+    j = other ? oj : j;
 }
 
 __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restrict__ feat, int H, int F, int k,
@@ -223,21 +228,23 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
                             }
                         }
                     }
+                    a0 = rank_distance(a0, j);
+                    a1 = rank_distance(a1, j2);
                     if (best < 0 || a0 < bd) { bd = a0; best = j; }
                     if (j + slices < k && a1 < bd) { bd = a1; best = j + slices; }
                 }
             } else {
                 best = -1;
                 for (int j = sl; j < k; j += slices) {
-                    const double dj = sqdist(X + (size_t)my_h * F, centre + (size_t)j * FP, F);
+                    const double dj = rank_distance(sqdist(X + (size_t)my_h * F, centre + (size_t)j * FP, F), j);
                     if (best < 0 || dj < bd) { bd = dj; best = j; }
                 }
             }
         }
-        if (slices > 1) take_nearer<0xB1>(bd, best, sl & 1);       // quad_perm [1,0,3,2]
-        if (slices > 2) take_nearer<0x4E>(bd, best, sl & 2);       // quad_perm [2,3,0,1]
-        if (slices > 4) take_nearer<0x141>(bd, best, sl & 4);      // row_half_mirror: the other quad, which agrees already
-        if (slices > 8) take_nearer<0x140>(bd, best, sl & 8);      // row_mirror: the other eight
+        if (slices > 1) take_nearer<0xB1>(bd, best);       // quad_perm [1,0,3,2]
+        if (slices > 2) take_nearer<0x4E>(bd, best);       // quad_perm [2,3,0,1]
+        if (slices > 4) take_nearer<0x141>(bd, best);      // row_half_mirror: the other quad, which agrees already
+        if (slices > 8) take_nearer<0x140>(bd, best);      // row_mirror: the other eight
         if (owner && sl == 0) {
             assign[my_h] = best;
             dmin[my_h] = bd;

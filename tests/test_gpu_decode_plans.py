@@ -123,3 +123,24 @@ def test_phases_of_different_types_agree_on_the_workspace(score_dtype, value_dty
     torch.cuda.synchronize()
     ok, worst = G.rows_close(out.cpu().numpy(), ref, 2e-5)
     assert ok, worst
+
+
+@pytest.mark.parametrize("H,F,k,bad", [(32, 25, 8, (2,)), (32, 25, 8, (0,)), (72, 25, 16, (2, 5)), (40, 40, 12, (3, 9)),
+                                       (33, 3, 1, (0,)), (24, 9, 24, (1, 6, 22))])
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+def test_kmeans_with_features_that_are_not_finite(H, F, k, bad, value):
+    """Heads whose features are NaN or infinite are starting centres `bad`: the distances to them are NaN, which an ascending
+    scan passes by (or keeps, if it met it first)."""
+    g = np.random.default_rng(H + F + k)
+    B = 2
+    feat = g.random((B, H, F)).astype(np.float32)
+    init = np.stack([g.choice(H, size=k, replace=False) for _ in range(B)]).astype(np.int32)
+    for b in range(B):
+        for j in bad:
+            feat[b, init[b, j], :: 2] = value
+    for max_iter in (1, 2, 50):
+        got = C.chai_assign_clusters(dev(feat), dev(init), max_iter)
+        torch.cuda.synchronize()
+        want = O.kmeans(feat, init, max_iter=max_iter)
+        for a, b in zip(got, want):
+            assert np.array_equal(a.cpu().numpy(), b)

@@ -529,10 +529,8 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                                                 (((4 * half + 2 * (j >> 2) + hl) ^ v_sw) << 4));
     };
 
-    // accumulators: tile (stream * NM + member) * 4 + 32-column block
+    // accumulators: tile (stream * NM + member) * 4 + 32-column block; zeroed at the end of the first block
     constexpr int kTiles = 4 * U * NM;
-    unroll<kTiles>([&](auto t) { AccTile<t.value>::zero(); });
-    acc_written();
     auto product = [&](auto t, const f16x8 &a, const f16x8 &b) {
         AccTile<t.value>::mfma(a, b);
         if constexpr (NW == 8) acc_hold();
@@ -577,9 +575,10 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         else return v_frag(vb, vhalf, NM == 2 ? s - s / 3 : s / 2);
     };
     // Block kbase .. kbase+31: softmax of its scores sc into pn; scores of the next block (keys kb) into sn; products of the
-    // block before (probabilities pp, values vb, half vhalf).  carry: the first fragments, and then those of the next call.
+    // block before (probabilities pp, values vb, half vhalf).  carry: the first fragments, and then those of the next call;
+    // even: block 0 may be among them.
     auto body = [&](Score &sc, Score &sn, const Prob &pp, Prob &pn, int kbase, const char *kb, const char *vb, int vhalf,
-                    const char *kb_next, const char *vb_next, int vhalf_next, Carry &carry, auto dma) {
+                    const char *kb_next, const char *vb_next, int vhalf_next, Carry &carry, auto dma, auto even) {
         // causal mask: only blocks that reach past the wave's first query need it (a branch uniform per wave; out of line,
         // like the rescaling below: a taken branch costs a lone wave 40 cycles)
         if (__builtin_expect(kbase + 31 > wave_first, 0)) {
@@ -683,9 +682,12 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             __builtin_amdgcn_sched_barrier(0);
         });
         unroll<kAhead>([&](auto i) { carry.f[i.value] = fr[kSlots + i.value]; });
-        if (__builtin_expect(moved && kbase > 0, 0)) {
+        // The first block's products are of no block before it (what multiplied zero may be infinite): the accumulators
+        // start from zero behind them.  There `moved` is set, or no score of the wave is a number.
+        if (__builtin_expect(moved, 0)) {
             acc_settle();
-            unroll<kTiles>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
+            if (decltype(even)::value && kbase == 0) unroll<kTiles>([&](auto t) { AccTile<t.value>::zero(); });
+            else unroll<kTiles>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
         }
     };
 
@@ -728,7 +730,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     Carry carry;
     unroll<kAhead>([&](auto i) { carry.f[i.value].raw = frag_of(i, kb_lane + 32 * (kHeadDim * 2), vb_lane, 0); });
     // Tile kt: blocks 2 kt (keys already multiplied; scores of the tile's second half, values of the block before) and
-    // 2 kt + 1.  The first block multiplies zero probabilities with the first tile's values.
+    // 2 kt + 1.  The first block multiplies zero probabilities with the first tile's values, for accumulators that it then zeroes.
     int b3 = 0, b3p = 0;                                     // buffers of tile kt and of the values before it
     for (int kt = 0; kt < n_tiles; ++kt) {
         const int b3n = b3 == 2 ? 0 : b3 + 1, b3nn = b3n == 2 ? 0 : b3n + 1;
@@ -742,13 +744,13 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             else if (i < kDma * (NM + 1)) dma_k1(kt2, b3nn, i - kDma * NM);
         };
         auto dma1 = [&](int) {};
-        if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0);
+        if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0, std::true_type{});
         else {
             unroll<kDma * (NM + 1)>([&](auto i) { dma0(i.value); });
             if (hb == n_hb) pv_only(pb, vprev, 1);
         }
         if (hb + 1 < n_hb)
-            body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1);
+            body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1, std::false_type{});
         else if (hb + 1 == n_hb) pv_only(pa, vcur, 0);
         // (after the last tile nobody waits for the requests past the end: they fill buffers that are not read any more)
         if (kt + 1 < n_tiles) tile_barrier();

@@ -78,3 +78,32 @@ def test_prefill_moving_maximum_and_unused_slot(B, Tq):
     # one key dominates a row here: its probability, 1 before the last rescaling, is exact in fp16; the others carry 2^-11
     ok, worst = G.rows_close(got, ref, RTOL_PREFILL)
     assert ok, worst
+
+
+def _one_infinite_value(B, H, kk, Tq, q_start, pos):
+    """Output of a call whose value cache holds +inf in column 7 at position `pos` of every head, and the oracle's output with
+    0 in its place.  kk = 0: the dense entry point."""
+    g = np.random.default_rng(B + H + Tq + pos)
+    T = q_start + Tq
+    q, k, v = (W.normal(g, (B, H, n, 128), W.BF16) for n in (Tq, T, T))
+    h2c, rep = W.random_membership(g, B, H, kk) if kk else 2 * (np.tile(np.arange(H, dtype=np.int32), (B, 1)),)
+    v[:, :, pos, 7] = 0
+    ref = O.clustered_prefill(q, k, v, h2c, rep, q_start, SCALE)
+    vd = dev(v)
+    vd[:, :, pos, 7] = float("inf")
+    out = torch.full((B, H, Tq, 128), 7.0, dtype=torch.float32, device="cuda")
+    ws = torch.full((C.chai_prefill_workspace_bytes(B, H, kk or H, T),), 0xFF, dtype=torch.uint8, device="cuda")
+    if kk:
+        kc = torch.zeros((B, kk, T, 128), dtype=torch.bfloat16, device="cuda")
+        C.chai_compact_kcache(dev(k), dev(rep), kc, T)
+        C.chai_prefill_attention(dev(q), kc, vd, dev(h2c), dev(rep), q_start, SCALE, out, ws)
+    else:
+        C.chai_dense_prefill_attention(dev(q), dev(k), vd, q_start, SCALE, out, ws)
+    torch.cuda.synchronize()
+    return out.cpu().numpy(), ref
+
+
+@pytest.mark.parametrize("B,H,kk", [(1, 4, 2), (40, 16, 4), (2, 4, 0), (9, 32, 0)])      # narrow and wide tiles, dense
+def test_infinite_value_reaches_the_rows_that_see_it(B, H, kk):
+    got, _ = _one_infinite_value(B, H, kk, 129, 0, 5)
+    assert np.all(got[:, :, 5:, 7] == np.inf)

@@ -549,8 +549,10 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         f32x16 s[U];
     };
 
-    // products of block hb-1's probabilities with its values
-    auto pv_only = [&](const Prob &pp, const char *vb, int vhalf) {
+    // Products of the wave's last block, whose probabilities are pp: of all streams, or without the first one if that one's
+    // rows end before the block (its probabilities there are zero, but the values may be infinite).
+    const bool all_streams = U == 1 || (q_start + min(i0 + 31, Tq - 1)) / 32 >= n_hb - 1;
+    auto pv_streams = [&](auto from, const Prob &pp, const char *vb, int vhalf) {
         acc_written();
         unroll<8 * NM>([&](auto pc) {
             constexpr int p = pc.value;
@@ -558,9 +560,14 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             vf.raw = v_frag(vb, vhalf, p);
             unroll<U>([&](auto uc) {
                 constexpr int u = uc.value;
-                product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, vf.h, pp.f[u][(p >> 2) & 1].h);
+                if constexpr (u >= decltype(from)::value)
+                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, vf.h, pp.f[u][(p >> 2) & 1].h);
             });
         });
+    };
+    auto pv_last = [&](const Prob &pp, const char *vb, int vhalf) {
+        if (all_streams) pv_streams(std::integral_constant<int, 0>{}, pp, vb, vhalf);
+        else pv_streams(std::integral_constant<int, U - 1>{}, pp, vb, vhalf);
     };
 
     // slots of a block: 8 NM value fragments and 8 key fragments, every third (NM = 2) or second one a key fragment
@@ -747,17 +754,17 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0, std::true_type{});
         else {
             unroll<kDma * (NM + 1)>([&](auto i) { dma0(i.value); });
-            if (hb == n_hb) pv_only(pb, vprev, 1);
+            if (hb == n_hb) pv_last(pb, vprev, 1);
         }
         if (hb + 1 < n_hb)
             body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1, std::false_type{});
-        else if (hb + 1 == n_hb) pv_only(pa, vcur, 0);
+        else if (hb + 1 == n_hb) pv_last(pa, vcur, 0);
         // (after the last tile nobody waits for the requests past the end: they fill buffers that are not read any more)
         if (kt + 1 < n_tiles) tile_barrier();
         b3p = b3;
         b3 = b3n;
     }
-    if (n_hb == 2 * n_tiles) pv_only(pb, vb_lane + b3p * (kGroup * kVBufBytes), 1);
+    if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (kGroup * kVBufBytes), 1);
 
     if (n_hb > 0) {
         acc_settle();

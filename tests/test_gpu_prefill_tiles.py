@@ -107,3 +107,15 @@ def _one_infinite_value(B, H, kk, Tq, q_start, pos):
 def test_infinite_value_reaches_the_rows_that_see_it(B, H, kk):
     got, _ = _one_infinite_value(B, H, kk, 129, 0, 5)
     assert np.all(got[:, :, 5:, 7] == np.inf)
+
+
+@pytest.mark.parametrize("q_start,pos", [(0, 40), (20, 70), (0, 101)])
+@pytest.mark.parametrize("B,H,kk", [(1, 4, 2), (40, 16, 4), (9, 32, 0)])
+def test_infinite_value_stays_out_of_blocks_before_it(B, H, kk, q_start, pos):
+    """Rows whose block of 32 ends before the value's block of 32 keys begins do not meet it."""
+    got, ref = _one_infinite_value(B, H, kk, 140, q_start, pos)
+    last = 32 * ((pos // 32 * 32 - 1 - q_start + 1) // 32)        # rows of whole blocks that end before the value's block
+    assert last >= 32
+    ok, worst = G.rows_close(got[:, :, :last], ref[:, :, :last], RTOL_PREFILL)
+    assert ok, worst
+    assert np.all(got[:, :, max(pos - q_start, 0):, 7] == np.inf)

@@ -432,7 +432,7 @@ int chai_decode_attention_shared_v(const void *q, const void *k_compact, const v
     if (d != kHeadDim || B > kMaxGridYZ || H > kMaxGridYZ) return CHAI_ERR_UNSUPPORTED;
     if (!aligned16(q) || !aligned16(k_compact) || !aligned16(v_compact) || !aligned16(out)) return CHAI_ERR_ALIGN;
     // both caches hold k streams per batch row: the launch plan of k heads in k clusters
-    const DecodePlan plan = make_decode_plan(B, k, k, T, row_bytes_of(dtype));
+    const DecodePlan plan = make_decode_plan(B, k, k, T, row_bytes_of(dtype), true);
     if (B > 0 && (!workspace || (reinterpret_cast<uintptr_t>(workspace) & 255u) != 0 || workspace_bytes < plan.bytes))
         return CHAI_ERR_WORKSPACE;
     if (B == 0) return CHAI_OK;

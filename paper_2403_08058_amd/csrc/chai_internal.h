@@ -30,7 +30,8 @@ struct DecodePlan {
 // row_bytes: bytes of one cached row (rows that are a single cache line are never cut into column parts).  Neither the size of
 // the workspace nor what the score phase leaves in it (cs, n_cs, n_rec, off_scores, off_stats) differs between fp32 and bf16
 // rows: the two phase calls are planned one by one and each with its own type.
-DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes);
+// shared_rows: the H streams' rows are handed out to other heads by a launch of its own (MemberRows below).
+DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shared_rows = false);
 inline int row_bytes_of(int dtype) { return kHeadDim * (dtype == CHAI_F32 ? 4 : 2); }
 
 // Kernels that use more than 64 KB of dynamic LDS must be told so once on every device they run on.  `done` is the

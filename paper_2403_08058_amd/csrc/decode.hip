@@ -617,8 +617,13 @@ size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 }  // namespace
 
 constexpr long long kShortStream = 192 * 1024;     // bytes of values per workgroup up to which a head's tokens are not split
+// Streams that share their rows among heads are followed by a launch that hands the rows out, split or not; up to so many
+// streams short ones are then taken whole only up to so many tokens.  Whole / split: 4 streams at 1536 bf16 tokens 13.4 / 10.3
+// us, 16 at 768 11.5 / 10.5, 32 at 512 11.1 / 10.6 and at 256 10.0 / 10.3, 48 at 1536 18.0 / 17.1 and at 129 9.9 / 10.4, 8
+// of fp32 at 768 13.0 / 11.8 and at 256 10.1 / 11.5; 64 at 1280 bf16 tokens 17.3 / 17.5, 128 at 1024 19.0 / 20.8.
+constexpr int kSharedStreams = 48, kSharedTokens = 384;
 
-DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes)
+DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shared_rows)
 {
     DecodePlan pl;
     // Score chunk (measured on MI355X on the LLaMa-7B/33B, OPT-66B and 32k-context shapes): the largest of
@@ -642,8 +647,9 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes)
     const long long heads = (long long)B * H > 0 ? (long long)B * H : 1;
     auto value_chunk = [&](int bytes, int *parts) {
         const bool halves = bytes >= 256;                   // column halves are whole cache lines
-        const bool whole = heads < 384 && ((long long)T * bytes <= (halves ? 2 : 1) * kShortStream ||
-                                           (halves && heads >= 192 && T <= 1536));
+        const bool brief = (long long)T * bytes <= (halves ? 2 : 1) * kShortStream &&
+                           !(shared_rows && heads <= kSharedStreams && T > kSharedTokens);
+        const bool whole = heads < 384 && (brief || (halves && heads >= 192 && T <= 1536));
         *parts = whole && halves ? 2 : 1;
         long long want = heads >= 384 || whole ? 1 : (1024 + heads - 1) / heads;
         const long long most = (T + 127) / 128;

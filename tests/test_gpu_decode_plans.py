@@ -144,3 +144,25 @@ def test_kmeans_with_features_that_are_not_finite(H, F, k, bad, value):
         want = O.kmeans(feat, init, max_iter=max_iter)
         for a, b in zip(got, want):
             assert np.array_equal(a.cpu().numpy(), b)
+
+
+@pytest.mark.parametrize("dtype,B,H,kk,T", [
+    (W.BF16, 6, 12, 8, 384), (W.BF16, 6, 12, 8, 385), (W.BF16, 7, 9, 7, 385), (W.BF16, 1, 6, 4, 1537),     # 48, 49 streams
+    (W.F32, 6, 12, 8, 384), (W.F32, 1, 6, 4, 385), (W.F32, 7, 9, 7, 385), (W.BF16, 4, 72, 16, 1100), (W.F32, 1, 3, 1, 129)])
+def test_shared_values_at_plan_edges(dtype, B, H, kk, T):
+    """Few shared streams: whole up to 384 tokens, split beyond; more than 48 streams as every other call."""
+    print(f"[shared] dtype={dtype} B={B} H={H} k={kk} T={T}", flush=True)
+    g = np.random.default_rng(T + B)
+    h2c, rep = W.random_membership(g, B, H, kk)
+    q, k, v = W.normal(g, (B, H, 128), dtype), W.normal(g, (B, H, T, 128), dtype), W.normal(g, (B, H, T, 128), dtype)
+    kd, rd = dev(k), dev(rep)
+    kc = torch.zeros((B, kk, T, 128), dtype=kd.dtype, device="cuda")
+    vc = torch.zeros_like(kc)
+    C.chai_compact_kcache(kd, rd, kc, T)
+    C.chai_compact_kcache(dev(v), rd, vc, T)
+    ws = G.poisoned_workspace(B, H, kk, T, 128, dtype)
+    out = torch.full((B, H, 128), float("nan"), dtype=torch.float32, device="cuda")
+    C.chai_decode_attention_shared_v(dev(q), kc, vc, dev(h2c), rd, T, SCALE, out, ws)
+    torch.cuda.synchronize()
+    ok, worst = G.rows_close(out.cpu().numpy(), O.shared_v_decode(q, k, v, h2c, rep, T, SCALE), 1e-5 if dtype == W.F32 else 2e-5)
+    assert ok, worst

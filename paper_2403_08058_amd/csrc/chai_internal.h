@@ -23,8 +23,9 @@ struct DecodePlan {
     int n_rec;       // softmax-statistics records per (b, cluster): one per wave of every score workgroup
     int cp;          // tokens per workgroup of the value kernel
     int n_cp;        // value chunks per (b, head) = ceil(T / cp)
+    // (off_rows: staging rows of shared values; in other calls the records of 64-token score chunks)
     int ds;          // workgroups per (b, head, chunk) of the value kernel: 1, or 2 with half of the columns each
-    size_t off_scores, off_stats, off_partial, off_rows, bytes;   // off_rows: [B,H,128] fp32 staging rows
+    size_t off_scores, off_stats, off_partial, off_rows, bytes;   // off_rows: [B,H,128] fp32
 };
 
 // row_bytes: bytes of one cached row (rows that are a single cache line are never cut into column parts).  Neither the size of

@@ -659,13 +659,15 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
     pl.cp = value_chunk(row_bytes, &pl.ds);
     pl.n_cp = (T + pl.cp - 1) / pl.cp;
     // Up to 64 score workgroups of 256 tokens the launch is one wave's chain long: 64 tokens shorten it (8 clusters, both
-    // phases at 256 fp32 tokens 9.4 -> 8.8 us, at 512 bf16 tokens 9.6 -> 9.3; with 192 workgroups slower).  Their records lie
-    // where partial rows would (below), so no head may be split -- of NEITHER type: the two phase calls are planned one by
-    // one, may be given scores of one type and values of the other, and have to agree on number and place of the records.
-    // fp32 rows are split first; rows of 8-bit codes have no separate phases.
+    // phases at 256 fp32 tokens 9.4 -> 8.8 us, at 512 bf16 tokens 9.6 -> 9.3, at 1024 10.9 -> 10.6; with 192 workgroups
+    // slower).  They write more records than their region holds, so these go to rows that the call does not use otherwise:
+    // the staging rows (32 bytes per 64 tokens and cluster against 512 per head), or, where those are in use and no head
+    // is split, the partial rows.  The two phase calls are planned one by one and may be given scores of one type and values
+    // of the other: the rule and the place look at sizes alone, never at row_bytes.
     int parts;
-    const bool whole_any = (row_bytes < 256 ? pl.cp : value_chunk(kHeadDim * 4, &parts)) >= T;
-    if (whole_any && (long long)B * k * ((T + 255) / 256) <= 64) pl.cs = 64;
+    const bool few = (long long)B * k * ((T + 255) / 256) <= 64 && value_chunk(kHeadDim * 2, &parts) >= T;
+    const size_t few_bytes = (size_t)B * k * ((T + 63) / 64) * kScoreWaves * sizeof(float2), row_area = (size_t)B * H * kHeadDim * sizeof(float);
+    if (few && (shared_rows ? pl.n_cp == 1 : few_bytes <= row_area)) pl.cs = 64;
     pl.n_cs = (T + pl.cs - 1) / pl.cs;
     pl.n_rec = pl.n_cs * kScoreWaves;
 
@@ -676,11 +678,9 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
     pl.off_scores = off;  off = align_up(off + (size_t)B * k * T * sizeof(float), 256);
     pl.off_stats = off;   off = align_up(off + (size_t)B * k * max_n_rec * sizeof(float2), 256);
     pl.off_partial = off; off = align_up(off + (size_t)B * H * max_n_cp * kHeadDim * sizeof(float), 256);
-    pl.off_rows = off;    off = align_up(off + (size_t)B * H * kHeadDim * sizeof(float), 256);
+    pl.off_rows = off;    off = align_up(off + row_area, 256);
     pl.bytes = off;
-    // 64-token score chunks write more records than the region above holds; they go where the partial rows would be, which
-    // such a plan has none of (32 bytes per 64 tokens and cluster against 512 per 128 tokens and head)
-    if (pl.cs < 256) pl.off_stats = pl.off_partial;
+    if (pl.cs < 256) pl.off_stats = shared_rows ? pl.off_partial : pl.off_rows;
     return pl;
 }
 

@@ -292,7 +292,6 @@ __global__ __launch_bounds__(kJrWaves * 64) void project_rows_kernel(const char 
 constexpr int kJtWaves = 4, kJtTeams = 2, kJtTok = 64, kJtStages = 3;
 constexpr int kJtBlock = kJtWaves * kJtTeams * 64;
 constexpr int kJtNarrow = 256;               // tiles are 64 columns wide while that gives at most so many (one per CU)
-constexpr int kJtItems = 24576;              // tokens of all (row, slot) pairs up to which these tiles are the faster ones
 constexpr int kJtMaxHeads = 256;             // heads one workgroup can count
 constexpr int jt_stage_bytes(int nb) { return (kJtTok + 64 * nb) * kJStep * 2; }
 constexpr size_t kJtLdsBytes = (size_t)kJtTeams * kJtStages * jt_stage_bytes(2);
@@ -539,10 +538,18 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     // few tokens it holds, so calls with few tokens took 77-86 us (170-215 us at D = 9216) at any size:
     //   B*Tn <= 8           one row of MFMA columns per head: B 1, 8 of 32 heads: 77 -> 13 us; B 1, 16 of 72, D 9216:
     //                       171 -> 28 us (33 us with the 64-token tiles)
-    //   B*k*Tn <= kJtItems  64-token tiles, head-major: B 16, k 8, Tn 1 / 16 / 64 / 128: 80 / 82 / 82 / 85 -> 17 / 20 / 32 /
+    //   B*k*Tn <= most      64-token tiles, head-major: B 16, k 8, Tn 1 / 16 / 64 / 128: 80 / 82 / 82 / 85 -> 17 / 20 / 32 /
     //                       62 us; B 1, k 8, Tn 512 / 2043: 85 / 87 -> 21 / 60 us; B 4, k 16, D 9216, Tn 16 / 256:
     //                       175 / 215 -> 52 / 135 us; B 4, k 8, D 6656, Tn 512: 151 -> 95 us
     //   above               256-token tiles: B 16, k 8, Tn 256: 98 us (118 us with the small tiles)
+    // From 16384 pairs' tokens on the small tiles take a third round of the chip.  It pays where the large tiles need a second
+    // one, or are a long chain and do not fill theirs, or hold few tokens each; in us, large / small tiles:
+    //   B 16, k 8 (128 large tiles), Tn 144, 160 and 192: D 4096 85 / 80, 88 / 82 and 88 / 84, D 3072 66 / 65 and (192) 68 / 68,
+    //   D 2048 47.2 / 47.7, 47.8 / 48.0 and 49.1 / 50.6, D 1024 28 / 31 and (192) 30 / 33, D 512 19 / 24 and (192) 21 / 25
+    //   B 1, k 8, Tn 2304 and 3072: D 2048 49.9 / 48.3 and 50.8 / 51.3
+    //   B 16, k 10 (160), Tn 140, D 5120: 118 / 111
+    //   B 16, k 16 (256), Tn 72 / 80 / 96: D 4096 100 / 82 and (96) 104 / 108, D 9216 238 / 195, 238 / 196 and 238 / 246
+    //   B 16, k 32 (512), Tn 48: D 512 37 / 27, D 4096 202 / 90
     // Both small kernels list the pairs of a head in LDS (at most kJrMaxSlots of them).
     const long long items = (long long)B * k * Tn;
     const bool listed = (long long)B * k <= kJrMaxSlots;
@@ -550,7 +557,9 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
         return (int)launch_kernel(project_rows_kernel, dim3((unsigned int)H * kJrParts), dim3(kJrWaves * 64), 0, stream, ev,
                                   xc, wq, wk, rep, B, H, k, Tn, D, qo, ko, pos0, Tc_cap);
     // (the tile kernel addresses the activations and one head's weights with 32-bit byte offsets below 2 GiB)
-    if (listed && items <= kJtItems && H <= kJtMaxHeads && (long long)B * Tn * D * 2 < 0x7fffffffLL &&
+    const long long n_large = (long long)B * k * ((Tn + kJTok - 1) / kJTok);
+    const long long most = n_large > 256 ? 24576 : (D < 2048 ? 16384 : (D < 3072 || n_large > 200 ? 20480 : 24576));
+    if (listed && items <= most && H <= kJtMaxHeads && (long long)B * Tn * D * 2 < 0x7fffffffLL &&
         (long long)kHeadDim * D * 2 < 0x7fffffffLL) {
         static DeviceFlags tile_lds_allowed;
         const hipError_t attr = allow_dynamic_lds(reinterpret_cast<const void *>(&project_tile_kernel), kJtLdsBytes,

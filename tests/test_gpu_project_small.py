@@ -24,7 +24,7 @@ from test_gpu_project import check_rounded, run_case
     (1, 4, 3, 63, 64), (1, 4, 3, 64, 128), (1, 4, 3, 65, 192),         # around one tile; 1, 2, 3 stages for two teams
     (3, 8, 2, 43, 448),                                                # a tile that gathers tokens of several rows
     (2, 40, 32, 64, 128), (2, 40, 33, 64, 128),                        # 64 tiles (narrow columns), 66 tiles (wide)
-    (6, 16, 8, 512, 64), (6, 16, 8, 513, 64),                          # the last size with small tiles, the first without
+    (6, 16, 8, 512, 64), (6, 16, 8, 513, 64),                          # 24576 tokens and more: large tiles
     (2, 257, 3, 20, 64), (1, 256, 3, 20, 64),                          # more heads than a workgroup counts; the most
     (129, 8, 8, 1, 64), (128, 8, 8, 1, 64), (1025, 2, 1, 1, 64),       # more pairs than a workgroup lists; the most
 ])
@@ -53,3 +53,12 @@ def test_projection_of_few_tokens_repeated_representative(Tn):
             r = int(rep[b, j])
             check_rounded(qh[b, r], q_ref[b, j], np.einsum("te,ce->tc", x64[b], aq[r]), f"q b={b} j={j}")
             check_rounded(kh[b, j], k_ref[b, j], np.einsum("te,ce->tc", x64[b], ak[r]), f"k b={b} j={j}")
+
+
+@pytest.mark.parametrize("B,H,kk,Tn,D", [
+    (4, 8, 8, 512, 192), (4, 8, 8, 513, 192),                          # narrow products: small tiles up to 16384 tokens
+    (33, 8, 8, 63, 128),                                               # 264 tiles of 256 tokens: small ones beyond that
+])
+def test_projection_at_the_lines_of_the_third_round(B, H, kk, Tn, D):
+    print(f"[project] B={B} H={H} k={kk} tokens={Tn} width={D}", flush=True)
+    run_case(B, H, kk, Tn, D, 0, Tn, seed=B + Tn + D, holes=True)

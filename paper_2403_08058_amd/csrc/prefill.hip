@@ -208,7 +208,7 @@ constexpr size_t kLdsBytes = kBufs * (kKBufBytes + kGroup * kVBufBytes);
 // go out first; the last 32 to 63 pairs go out as single tiles, the largest first, which fills the last round.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kXcds = 8, kXcdCus = 32;
-constexpr int kSmallTiles = 450, kSmallDense = 256;      // see launch_prefill
+constexpr int kSmallTiles = 450;      // see launch_prefill
 struct PrefillWork {
     int b, gi;           // batch row, group (identity: head)
     int qt0, qt1, n_pass;   // query tiles
@@ -872,9 +872,20 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     // and where a block has no more rows than that.  The lines lie at a number of 256-row tiles of the most groups the maps
     // can have.  Whole calls with 256 / 128 rows: clustered, at 136 tiles 118 / 97 us, at 384 164 / 153 us and 71 / 66 us, at
     // 440 28 / 25 us, at 416 81 / 86 us and 110 / 103 us, at 576 129 / 148 us, at 1280 472 / 567 us, 65 rows at 960 tiles
-    // 81 / 73 us; dense, at 128 tiles 39 / 32 us, at 256 68 / 66 us, at 260 48 / 60 us, at 4096 783 / 914 us.
+    // 81 / 73 us.
+    // Dense: up to 128 wide tiles the narrow ones are one round too, above 256 the wide ones fill the chip better (at 4096
+    // 783 / 914 us).  Between, two narrow tiles share a CU one after the other, the longest with the shortest: the second
+    // round starts with the 256-th longest, 128 * 256 / heads keys below the longest.  With 7 us for a start and 20 against 30
+    // ns per key of a narrow and a wide tile, two of those take less than one wide tile where
+    // heads * (4 (q_start + Tq in whole tiles) - 3 keys + 700) <= 131072.  Wide / narrow: one query tile per head, 256 keys,
+    // 160 / 192 / 256 heads 26.8 / 27.0, 27.3 / 28.4, 30.8 / 34.1 us, 256 behind 1000 keys 84 / 98; two tiles, 512 keys,
+    // 72 / 96 / 128 heads 31.3 / 26.5, 32.2 / 30.5, 33.9 / 35.8; four, 64 heads 45.3 / 42.5, behind 1000 keys 71 / 80; eight,
+    // 32 heads 69 / 61, behind 1000 keys 101 / 98.  Blocks of up to 128 rows fill half a wide tile: 512 heads, 100 rows
+    // 40.0 / 39.4, 24 rows level.
     const long long tiles = (long long)((Tq + 255) / 256) * max_groups * B;
-    const bool small = identity ? tiles <= kSmallDense : (tiles <= kSmallTiles || Tq <= 128);
+    bool small = Tq <= 128 || tiles <= (identity ? 128 : kSmallTiles);
+    if (identity && tiles <= 256)
+        small = small || (long long)B * H * (4LL * (q_start + (Tq + 127) / 128 * 128) - 3LL * n_keys + 700) <= 131072;
     auto *kernel = small ? (identity ? prefill_kernel<1, 4, true> : prefill_kernel<1, 4, false>)
                          : (identity ? prefill_kernel<1, 8, true> : prefill_kernel<2, 4, false>);
     const int threads = identity && !small ? 512 : 256, tile_rows = small ? 128 : 256;

@@ -37,7 +37,8 @@ def test_prefill_tile_edges(B, H, kk, Tq, q_start):
     run_case(B, H, kk, Tq, q_start, q_start + Tq + 3, seed=B + 5 * H + 7 * kk + Tq + q_start)
 
 
-@pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5), (5, 52, 257, 0)])
+@pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5), (5, 52, 257, 0),
+                                            (1, 137, 256, 0), (1, 138, 256, 0), (9, 32, 128, 3)])
 def test_dense_prefill_tiles(B, H, Tq, q_start):
     """Dense entry point: 128-row tiles; 256-row tiles of eight waves."""
     g = np.random.default_rng(B)

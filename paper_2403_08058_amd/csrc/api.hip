@@ -120,7 +120,7 @@ int chai_assign_clusters(const float *feat, int B, int H, int F, int k, const in
     if (!feat || !init_heads || !head_to_cluster || !rep_heads || !n_clusters) return CHAI_ERR_NULL;
     if (B < 0 || H < 1 || F < 1 || k < 1 || k > H || max_iter < 1) return CHAI_ERR_SHAPE;
     if (H > 256 || F > 64 || (long long)k * F > 7168) return CHAI_ERR_UNSUPPORTED;
-    if (assign_clusters_lds_bytes(H, F, k) > 64 * 1024 - 64) return CHAI_ERR_UNSUPPORTED;
+    if (!assign_clusters_supported(H, F, k)) return CHAI_ERR_UNSUPPORTED;
     if (B == 0) return CHAI_OK;
     return hip_status(launch_assign_clusters(feat, B, H, F, k, init_heads, max_iter, head_to_cluster, rep_heads,
                                              n_clusters, iters, static_cast<hipStream_t>(stream)));

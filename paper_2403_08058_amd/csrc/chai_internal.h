@@ -111,7 +111,7 @@ int launch_score_features(const void *q5, const void *k5, int B, int H, int n_to
 
 int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const int32_t *init_heads, int max_iter,
                            int32_t *h2c, int32_t *rep, int32_t *ncl, int32_t *iters, hipStream_t stream);
-size_t assign_clusters_lds_bytes(int H, int F, int k);
+bool assign_clusters_supported(int H, int F, int k);
 
 // sse and rep_out (nearest-to-mean member of every cluster) are optional outputs of the same kernel
 int launch_cluster_error(const float *feat, const int32_t *h2c, int B, int H, int F, int k, double *sse,

@@ -425,23 +425,24 @@ int launch_score_features(const void *q5, const void *k5, int B, int H, int n_to
                               dtype == CHAI_BF16 ? 1 : 0, (long long)qs, (long long)ks, (double)scale, feat);
 }
 
-// The sizes the entry point accepts are those of this formula (64 KB); the kernel itself needs what kmeans_layout says.
-size_t assign_clusters_lds_bytes(int H, int F, int k)
+// Sizes that are accepted, next to H <= 256, F <= 64 and k*F <= 7168: a line that callers know, drawn on its own.  What the
+// kernel allocates is kmeans_layout's, at most 73 976 bytes on this side of the line (244 heads, 25 coordinates, 240 centres).
+bool assign_clusters_supported(int H, int F, int k)
 {
-    size_t sl = 512 / H;
-    if (sl > (size_t)k) sl = k;
-    if (sl < 1) sl = 1;
-    return sizeof(double) * ((size_t)k * F + H + H * sl) + sizeof(int) * (H * sl + 3 * (size_t)H + 7 * (size_t)k);
+    const long long s = 512 / H < 1 ? 1 : (512 / H > k ? k : 512 / H);
+    return 8LL * k * F + 20LL * H + 12LL * H * s + 28LL * k <= 65472;
 }
+
+constexpr size_t kKmeansLds = 96 * 1024;     // most LDS of a workgroup (its CU has 160 KB)
 
 int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const int32_t *init_heads, int max_iter,
                            int32_t *h2c, int32_t *rep, int32_t *ncl, int32_t *iters, hipStream_t stream)
 {
     const KmeansLayout L = kmeans_layout(H, F, k);
+    if (L.bytes > kKmeansLds) return (int)hipErrorInvalidConfiguration;
     if (L.bytes > 64 * 1024) {                              // the mask words of many centres over many heads
         static DeviceFlags lds_allowed;
-        // what the accepted sizes can need: 64 KB of the old formula, 6 KB of padding, 16 KB of masks
-        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), 96 * 1024, lds_allowed);
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), kKmeansLds, lds_allowed);
         if (e != hipSuccess) return (int)e;
     }
     // threads: the lanes of all heads, and enough for the update to be one round where that is not much more

@@ -119,24 +119,26 @@ __device__ __forceinline__ void plan_row(const int32_t *__restrict__ h2c, const 
 // Pre-pass, one launch.  V^T in blocks of 64 keys: vt[b][h][t/64][dd][16*((t%64)/16) + key_slot16(t%16)] =
 // fp16(V[b][h][t][dd]) for t < n_keys, 0 up to Tp (a multiple of 64).  A block is 16 KB of consecutive memory with whole
 // cache lines per value column, which is what the main kernels' direct loads to LDS ask for (rows of 64 bytes in blocks
-// of 32 keys made each of those loads touch twice as many lines).  grid (Tp/64 + 1, H, B), 256 threads; a 64 x 128 tile
-// goes through LDS.  The workgroups with blockIdx.x = 0 make the work list, one per batch row (h2c != NULL; a launch of
-// its own took 5 us for a few thousand instructions); dynamic LDS: the tile, or what
+// of 32 keys made each of those loads touch twice as many lines).  grid (n_lists + Tp/64 * H * B), 256 threads; a 64 x 128 tile
+// goes through LDS.  The first n_lists workgroups make the work list, one per batch row (0 without maps; a launch of its
+// own took 5 us for a few thousand instructions; as one workgroup more per head, all but B of them empty, 3 us on 520
+// heads of one block).  Dynamic LDS: the tile, or what
 // plan_row needs if that is more.
 // ---------------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v, int H, int T_cap, int n_keys, int Tp,
-                                                      _Float16 *__restrict__ vt, const int32_t *__restrict__ h2c,
+                                                      _Float16 *__restrict__ vt, int n_lists, const int32_t *__restrict__ h2c,
                                                       const int32_t *__restrict__ rep, int k, int max_groups,
                                                       int32_t *__restrict__ groups, int32_t *__restrict__ n_groups)
 {
     extern __shared__ __attribute__((aligned(16))) char pre_lds[];
     _Float16 (*tile)[kKTile + 2] = reinterpret_cast<_Float16 (*)[kKTile + 2]>(pre_lds);
-    const int tid = threadIdx.x, h = blockIdx.y, b = blockIdx.z;
-    if (blockIdx.x == 0) {
-        if (h == 0 && h2c != nullptr) plan_row(h2c, rep, H, k, max_groups, groups, n_groups, b, reinterpret_cast<int32_t *>(pre_lds));
+    const int tid = threadIdx.x;
+    if ((int)blockIdx.x < n_lists) {
+        plan_row(h2c, rep, H, k, max_groups, groups, n_groups, blockIdx.x, reinterpret_cast<int32_t *>(pre_lds));
         return;
     }
-    const int block = (int)blockIdx.x - 1, t0 = block * kKTile;
+    const unsigned item = blockIdx.x - n_lists, n_blocks = (unsigned)Tp / kKTile, row = item / n_blocks;
+    const int block = (int)(item - row * n_blocks), t0 = block * kKTile, h = (int)(row % (unsigned)H), b = (int)(row / (unsigned)H);
     const char *vhead = v + ((size_t)b * H + h) * (size_t)T_cap * (kHeadDim * 2);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -863,9 +865,12 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     _Float16 *vt = reinterpret_cast<_Float16 *>(ws);
 
     const size_t tile_lds = (size_t)kHeadDim * (kKTile + 2) * sizeof(_Float16), plan_lds = (size_t)(H + 2 * k) * sizeof(int32_t);
-    hipError_t e = launch_kernel(prepass_kernel, dim3(Tp / kKTile + 1, H, B), dim3(256),
+    const int n_lists = identity ? 0 : B;
+    const long long n_pre = n_lists + (long long)(Tp / kKTile) * H * B;
+    if (n_pre > 0xffffff) return (int)hipErrorInvalidConfiguration;       // 256 GB of values
+    hipError_t e = launch_kernel(prepass_kernel, dim3((unsigned int)n_pre), dim3(256),
                                  identity || plan_lds < tile_lds ? tile_lds : plan_lds, stream, KernelEvents(),
-                                 static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt, h2c, rep, k, max_groups, groups,
+                                 static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt, n_lists, h2c, rep, k, max_groups, groups,
                                  n_groups);
     if (e != hipSuccess) return (int)e;
     // Tiles of 256 or of 128 query rows: 128 where the wide tiles would leave CUs without work or end in a ragged last round,

@@ -195,6 +195,8 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // LDS: rings of three K and three V^T tiles (64 keys).  While tile t is computed, K(t+2) and V(t+1) are loaded with
 // direct loads, requested in the first half of the tile; K runs ahead of V because the scores of a block are issued one
 // block before its softmax, and V lags because its products come one block after.  ONE barrier per tile.
+// Dense attention over at most two tiles of keys has rings of two (BUFS), 64 KB: it is all start and end, and two workgroups
+// on a CU cover each other's (10 x 52 heads of 40 keys 25.4 -> 21.2 us, of 128 keys 36.8 -> 31.9 us).
 //
 // A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
 // through LDS (670-840 against 578 us per 8-cluster LLaMa-7B layer), three members in one wave (630 against 553 us).
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 constexpr int kBufs = 3;
 constexpr size_t kKBufBytes = (size_t)kKTile * kHeadDim * 2;        // 64 rows of 256 B (16 pieces), swizzled
 constexpr size_t kVBufBytes = (size_t)kHeadDim * kKTile * 2;        // one member: 128 rows of 128 B (8 pieces), swizzled
-constexpr size_t kLdsBytes = kBufs * (kKBufBytes + kGroup * kVBufBytes);
+constexpr size_t prefill_lds_bytes(bool ident, int bufs) { return bufs * (kKBufBytes + (ident ? 1 : kGroup) * kVBufBytes); }
 
 // ---------------------------------------------------------------------------------------------------------
 // Which query tiles of which (batch row, group) a workgroup takes.  The hardware deals consecutive workgroup ids
@@ -452,7 +454,8 @@ struct OpSchedule {
 };
 
 // One query tile (NW waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
-template <int NM, int U, int NW>
+// LDS: rings of BUFS tiles (2: at most two key tiles), a value tile with room for G members.
+template <int NM, int U, int NW, int G, int BUFS>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
                                           int qt, int rhead, float scale2, float *__restrict__ out)
@@ -505,7 +508,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     const unsigned int v_off = (unsigned int)(v_row * (kKTile * 2) + v_piece * 16);
     auto dma_v1 = [&](int kt, int buf, int g, int i) {
         load_to_lds(g == 0 ? v_rs0 : v_rs1, (unsigned int)kt * (unsigned int)kVBufBytes + v_off + i * 8 * NW * (kKTile * 2),
-                    v_lds + (buf * kGroup + g) * kVBufBytes + (w + NW * i) * 1024);
+                    v_lds + (buf * G + g) * kVBufBytes + (w + NW * i) * 1024);
     };
     auto dma_k = [&](int kt, int buf) {
 #pragma unroll
@@ -746,13 +749,15 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     // 2 kt + 1.  The first block multiplies zero probabilities with the first tile's values, for accumulators that it then zeroes.
     int b3 = 0, b3p = 0;                                     // buffers of tile kt and of the values before it
     for (int kt = 0; kt < n_tiles; ++kt) {
-        const int b3n = b3 == 2 ? 0 : b3 + 1, b3nn = b3n == 2 ? 0 : b3n + 1;
+        const int b3n = b3 == BUFS - 1 ? 0 : b3 + 1, b3nn = b3n == BUFS - 1 ? 0 : b3n + 1;
         const int kt2 = min(kt + 2, n_tiles - 1), kt1 = min(kt + 1, n_tiles - 1);      // past the end: requested, not read
         const int hb = 2 * kt;
-        const char *vprev = vb_lane + b3p * (kGroup * kVBufBytes), *vcur = vb_lane + b3 * (kGroup * kVBufBytes);
+        const char *vprev = vb_lane + b3p * (G * kVBufBytes), *vcur = vb_lane + b3 * (G * kVBufBytes);
         const char *k_odd = kb_lane + b3 * kKBufBytes + 32 * (kHeadDim * 2), *k_even = kb_lane + b3n * kKBufBytes;
         auto dma0 = [&](int i) {                             // the next tiles' kDma (NM + 1) requests, early in this one
-            if (i < kDma) dma_v1(kt1, b3n, 0, i);
+            if (BUFS == 2) {                                 // two tiles at most: the second one's values, its keys are there
+                if (i < kDma * NM && kt + 1 < n_tiles) dma_v1(kt1, b3n, i < kDma ? 0 : 1, i % kDma);
+            } else if (i < kDma) dma_v1(kt1, b3n, 0, i);
             else if (i < kDma * NM) dma_v1(kt1, b3n, 1, i - kDma);
             else if (i < kDma * (NM + 1)) dma_k1(kt2, b3nn, i - kDma * NM);
         };
@@ -770,7 +775,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         b3p = b3;
         b3 = b3n;
     }
-    if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (kGroup * kVBufBytes), 1);
+    if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (G * kVBufBytes), 1);
 
     if (n_hb > 0) {
         acc_settle();
@@ -801,7 +806,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #endif
 }
 
-template <int U, int NW, bool IDENT>
+template <int U, int NW, bool IDENT, int BUFS>
 __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
                                                                   const _Float16 *__restrict__ vt,
                                                                   const int32_t *__restrict__ groups,
@@ -832,11 +837,11 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__
         const int qt = __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1);
         if (pass != 0) __syncthreads();
         if (!IDENT && n_mem == 2)
-            prefill_tile<2, U, NW>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
-                         scale * kLog2e, out);
+            prefill_tile<2, U, NW, kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start,
+                                                 qt, rhead, scale * kLog2e, out);
         else
-            prefill_tile<1, U, NW>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt, rhead,
-                         scale * kLog2e, out);
+            prefill_tile<1, U, NW, IDENT ? 1 : kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
+                                                             q_start, qt, rhead, scale * kLog2e, out);
     }
 }
 
@@ -895,18 +900,23 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     bool small = Tq <= 128 || tiles <= (identity ? 128 : kSmallTiles);
     if (identity && tiles <= 256)
         small = small || (long long)B * H * (4LL * (q_start + (Tq + 127) / 128 * 128) - 3LL * n_keys + 700) <= 131072;
-    auto *kernel = small ? (identity ? prefill_kernel<1, 4, true> : prefill_kernel<1, 4, false>)
-                         : (identity ? prefill_kernel<1, 8, true> : prefill_kernel<2, 4, false>);
+    const bool brief = identity && n_keys <= 2 * kKTile;    // (one narrow query tile per head)
+    auto *kernel = small ? (identity ? (brief ? prefill_kernel<1, 4, true, 2> : prefill_kernel<1, 4, true, kBufs>)
+                                     : prefill_kernel<1, 4, false, kBufs>)
+                         : (identity ? prefill_kernel<1, 8, true, kBufs> : prefill_kernel<2, 4, false, kBufs>);
+    const size_t lds_bytes = prefill_lds_bytes(identity, brief ? 2 : kBufs);
     const int threads = identity && !small ? 512 : 256, tile_rows = small ? 128 : 256;
-    static DeviceFlags lds_allowed[4];
-    e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kLdsBytes, lds_allowed[(small ? 2 : 0) + (identity ? 1 : 0)]);
-    if (e != hipSuccess) return (int)e;
+    if (!brief) {                                           // 64 KB need no leave
+        static DeviceFlags lds_allowed[4];
+        e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[(small ? 2 : 0) + (identity ? 1 : 0)]);
+        if (e != hipSuccess) return (int)e;
+    }
     const int n_qt = (Tq + tile_rows - 1) / tile_rows;
     // the most workgroups an XCD can need (find_work): its pairs, the last of them as single tiles of padded groups
     const long long n_pairs = (n_qt + 1) / 2, most = (long long)max_groups * B * n_pairs / kXcds + 1;
     const long long n_wg = kXcds * (most + (most < 2 * kXcdCus ? most : 2 * kXcdCus) + 4 * n_pairs);
     if (n_wg > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(threads), kLdsBytes, stream, ev,
+    return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(threads), lds_bytes, stream, ev,
                               static_cast<const char *>(q), static_cast<const char *>(kc), vt, groups, n_groups, H, k, Tq,
                               q_start, Tc_cap, Tp, n_qt, max_groups, B, scale, out);
 }

@@ -38,9 +38,11 @@ def test_prefill_tile_edges(B, H, kk, Tq, q_start):
 
 
 @pytest.mark.parametrize("B,H,Tq,q_start", [(2, 8, 130, 10), (13, 16, 800, 5), (5, 52, 257, 0),
-                                            (1, 137, 256, 0), (1, 138, 256, 0), (9, 32, 128, 3)])
+                                            (1, 137, 256, 0), (1, 138, 256, 0), (9, 32, 128, 3),
+                                            (30, 20, 1, 0), (2, 8, 64, 0), (2, 8, 64, 1), (30, 20, 128, 0), (2, 8, 33, 95),
+                                            (2, 8, 1, 127), (2, 8, 1, 128)])
 def test_dense_prefill_tiles(B, H, Tq, q_start):
-    """Dense entry point: 128-row tiles; 256-row tiles of eight waves."""
+    """Dense entry point: 128-row tiles; 256-row tiles of eight waves; rings of two up to 128 keys (one tile, two, three)."""
     g = np.random.default_rng(B)
     T = q_start + Tq
     q, k, v = (W.normal(g, (B, H, n, 128), W.BF16) for n in (Tq, T, T))
@@ -104,9 +106,10 @@ def _one_infinite_value(B, H, kk, Tq, q_start, pos):
     return out.cpu().numpy(), ref
 
 
-@pytest.mark.parametrize("B,H,kk", [(1, 4, 2), (40, 16, 4), (2, 4, 0), (9, 32, 0)])      # narrow and wide tiles, dense
-def test_infinite_value_reaches_the_rows_that_see_it(B, H, kk):
-    got, _ = _one_infinite_value(B, H, kk, 129, 0, 5)
+@pytest.mark.parametrize("B,H,kk,Tq", [(1, 4, 2, 129), (40, 16, 4, 129), (2, 4, 0, 129), (9, 32, 0, 129), (2, 4, 0, 100)])
+def test_infinite_value_reaches_the_rows_that_see_it(B, H, kk, Tq):
+    """Narrow and wide tiles, dense narrow and wide ones and rings of two."""
+    got, _ = _one_infinite_value(B, H, kk, Tq, 0, 5)
     assert np.all(got[:, :, 5:, 7] == np.inf)
 
 

@@ -216,7 +216,7 @@ constexpr size_t prefill_lds_bytes(bool ident, int bufs) { return bufs * (kKBufB
 // go out first; the last 32 to 63 pairs go out as single tiles, the largest first, which fills the last round.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kXcdCus = 32;
-constexpr int kSmallTiles = 450;      // see launch_prefill
+constexpr int kSmallTiles = 450, kFewTiles = 1450;      // see launch_prefill
 struct PrefillWork {
     int b, gi;           // batch row, group (identity: head)
     int qt0, qt1, n_pass;   // query tiles
@@ -886,7 +886,13 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     // and where a block has no more rows than that.  The lines lie at a number of 256-row tiles of the most groups the maps
     // can have.  Whole calls with 256 / 128 rows: clustered, at 136 tiles 118 / 97 us, at 384 164 / 153 us and 71 / 66 us, at
     // 440 28 / 25 us, at 416 81 / 86 us and 110 / 103 us, at 576 129 / 148 us, at 1280 472 / 567 us, 65 rows at 960 tiles
-    // 81 / 73 us.
+    // 81 / 73 us.  Five narrow tiles are half a wide tile less and leave no wide one without its pair: 513 positions, 30 rows x 32
+    // heads in 8 clusters 240 / 225 us, 12 x 52 in 8 157 / 145, 16 x 52 in 4 204 / 181, 64 x 32 in 8 489 / 466, behind 200
+    // 606 / 582, 16 x 72 in 16 behind 1000 643 / 620.  So are three, where launch and block are short: 257 positions, 12 x 52
+    // and 30 x 32 (816 and 1440 tiles) 85 / 78 and 127 / 118, behind 128 101 / 93 and 154 / 142, behind 200 level, but 16 x 72
+    // in 16 (1664 tiles) 143 / 143 and with 300 positions 152 / 157, 64 x 32 (3072) 233 / 251.  Six against three wide ones
+    // only between 900 and 1450: 768 positions, 16 x 52 in 4 (1440) 282 / 268, 16 x 32 in 4 (960) 173 / 168, but 8 x 52 (720)
+    // 134 / 140, and 641 positions, 64 x 32 in 8 (4608) 576 / 594.  Seven: 769 positions 340 / 359.
     // Dense: up to 128 wide tiles the narrow ones are one round too, above 256 the wide ones fill the chip better (at 4096
     // 783 / 914 us).  Between, two narrow tiles share a CU one after the other, the longest with the shortest: the second
     // round starts with the 256-th longest, 128 * 256 / heads keys below the longest.  With 7 us for a start and 20 against 30
@@ -897,7 +903,11 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     // 32 heads 69 / 61, behind 1000 keys 101 / 98.  Blocks of up to 128 rows fill half a wide tile: 512 heads, 100 rows
     // 40.0 / 39.4, 24 rows level.
     const long long tiles = (long long)((Tq + 255) / 256) * max_groups * B;
+    const int n_narrow = (Tq + 127) / 128;
     bool small = Tq <= 128 || tiles <= (identity ? 128 : kSmallTiles);
+    if (!identity)
+        small = small || (n_narrow == 3 && q_start <= 128 && tiles <= kFewTiles) || n_narrow == 5 ||
+                (n_narrow == 6 && tiles >= 2 * kSmallTiles && tiles <= kFewTiles);
     if (identity && tiles <= 256)
         small = small || (long long)B * H * (4LL * (q_start + (Tq + 127) / 128 * 128) - 3LL * n_keys + 700) <= 131072;
     const bool brief = identity && n_keys <= 2 * kKTile;    // (one narrow query tile per head)

@@ -31,6 +31,8 @@ SCALE = float(np.float32(1 / math.sqrt(128)))
     (14, 32, 8, 257, 3), (14, 32, 8, 512, 0),              # 672: two tiles per group, pairs and singles
     (66, 4, 2, 769, 5),                                    # wide, four tiles, 66 rows
     (5, 24, 24, 1000, 30),                                 # wide, every head alone
+    (20, 16, 4, 300, 128), (20, 16, 4, 300, 129), (20, 16, 4, 513, 40),      # three narrow tiles, two wide ones, five narrow
+    (26, 16, 4, 700, 5),                                   # 936 wide tiles: six narrow ones
 ])
 def test_prefill_tile_edges(B, H, kk, Tq, q_start):
     print(f"[prefill] B={B} H={H} k={kk} Tq={Tq} q_start={q_start}", flush=True)

@@ -425,7 +425,9 @@ int chai_dense_decode_attention(const void *q, const void *k_cache, const void *
  * accumulate in fp32 from exact bf16 products; probabilities are rounded to
  * fp16 and values converted to fp16 for the second product (fp32
  * accumulation): the conversion is exact for 2^-14 <= |v| <= 65504, loses
- * low bits below that, and |v| must not exceed 65504.
+ * low bits below that, and |v| must not exceed 65504 (a larger value counts
+ * as infinite; an infinite value reaches the rows that see it and may leave
+ * NaN in up to 62 rows before them).
  *
  *   q         [B,H,Tq,d]        only representatives' rows are read
  *   k_compact [B,k,Tc_cap,d]    keys of positions 0 .. q_start+Tq-1 present
@@ -442,8 +444,8 @@ int chai_dense_decode_attention(const void *q, const void *k_cache, const void *
  *
  * chai_prefill_attention_timed: the same call with two hipEvent_t handles
  * passed as void* (timing enabled, either may be NULL) that the runtime
- * stamps with the begin and the end of the main kernel; the V^T pre-pass and
- * the work-list kernel that run before it are outside the pair.
+ * stamps with the begin and the end of the main kernel; the pre-pass that runs
+ * before it (V^T and the work list) is outside the pair.
  */
 size_t chai_prefill_workspace_bytes(int B, int H, int k, int n_keys);
 int chai_prefill_attention(const void *q, const void *k_compact, const void *v_cache,

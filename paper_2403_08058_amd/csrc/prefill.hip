@@ -185,9 +185,9 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // CU busy, at 1.8 to 1.9 GHz instead of 2.4: the chip lowers its clock on this data (the matrix pipe alone reaches 64 % of
 // its nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
 // tile adds 11 us for its start, the diagonal that the four waves finish one after the other, and the output rows.
-// Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls: 16 rows x 2043
-// positions, 32 heads in 8 clusters 632 -> 616 us, dense 820 -> 783 us; 4 rows x 4000, 4 clusters 520 -> 472 us (with the balanced numbering
-// below); 1 row x 2043 94 -> 61 us; 256 positions behind 1792 keys, 4 rows x 52 heads 131 -> 97 us.
+// Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls timed in turn: 16 rows
+// x 2043 positions, 32 heads in 8 clusters 663 -> 616 us, dense 809 -> 780 us; 4 rows x 4000, 4 clusters 520 -> 467 us (with
+// the balanced numbering below); 1 row x 2043 97 -> 63 us; 256 positions behind 1792 keys, 4 rows x 52 heads 128 -> 93 us.
 //
 // NW = 4 with U = 1 halves a workgroup's rows for launches that leave CUs without work (rule in launch_prefill): a wave's LDS
 // reads per MFMA double, but twice as many CUs work, on half as long a chain.

@@ -7,32 +7,34 @@
 //       q_out[b][r][i][:]            = bf16( x[b][i][:] . w_q[r*128 .. r*128+127][:]^T )
 //       k_compact[b][j][pos0 + i][:] = bf16( x[b][i][:] . w_k[r*128 .. r*128+127][:]^T )
 //
-// Three kernels, chosen in launch_project_qk by the number of tokens; this is the one for prompts.  One workgroup
-// (8 waves) computes a 256-token x 256-column tile: the 128 query columns and the 128 key columns of one
-// representative, which share the activation tile.  The product is formed transposed, C^T = W X^T, with
-// v_mfma_f32_32x32x16_bf16: both operands are then read along the contraction axis (weights are stored one row
-// per output feature), a lane owns one token and gets 4 consecutive output features per register quad, so rows
-// are written in 8-byte pieces.  Operand tiles of 64 contraction steps go global -> registers -> LDS (double
-// buffered, one barrier per step); fp32 accumulation, one rounding to bf16 at the end.
+// Three kernels, chosen in launch_project_qk by the number of tokens; the first below is the one for prompts.  In all of them
+// the product is formed transposed, C^T = W X^T: both operands are then read along the contraction axis (weights are stored
+// one row per output feature), a lane owns one token and gets 4 consecutive output features per register quad; fp32
+// accumulation, one rounding to bf16 at the end.
 #include "chai_internal.h"
 
 #include <hip/hip_ext.h>
+
+#include <type_traits>
+#include <utility>
 
 namespace chai {
 
 namespace {
 
-constexpr int kJBlock = 512;                 // threads (8 waves: 4 along the tokens x 2 along the columns)
+constexpr int kJBlock = 256;                 // threads (4 waves, one per SIMD: 2 along the tokens x 2 along the columns)
 constexpr int kJTok = 256;                   // tokens per workgroup tile
 constexpr int kJCol = 2 * kHeadDim;          // columns per workgroup tile: query + key columns of one head
-constexpr int kJStep = 64;                   // contraction elements per LDS tile
-constexpr int kJStride = kJStep + 8;         // halves per LDS row (144 B: rows land on different banks)
-constexpr size_t kJTileBytes = (size_t)(kJTok + kJCol) * kJStride * 2;     // activations + weights, one stage
-constexpr size_t kJLdsBytes = 2 * kJTileBytes;
-constexpr int kJPieces = (kJTok + kJCol) * kJStep * 2 / 16 / kJBlock;      // 16-byte pieces per thread per stage (8)
+constexpr int kJStep = 64;                   // contraction elements per stage; widths are multiples of it
+constexpr int kJStageBytes = (kJTok + kJCol) * kJStep * 2;                 // 64 KB: activations, then weights; rows of 128 B
+constexpr int kJLoads = kJStageBytes / 1024 / (kJBlock / 64);              // direct loads per wave and stage (16)
+constexpr int kJOutBytes = 32 * kHeadDim * 2;                              // output staging of one wave: 32 tokens
+constexpr size_t kJLdsBytes = 2 * (size_t)kJStageBytes + kJBlock / 64 * kJOutBytes;          // all 160 KB of a CU
+constexpr int kJCus = 256;                   // workgroups of the large tiles: one per CU
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -41,126 +43,218 @@ union Frag {
     bf16x8 bf;
 };
 
-// 1-D grid of n_mt * k * B workgroups, renumbered so that each XCD owns a contiguous range of (batch row, token
-// tile) pairs with all their cluster slots: the slots of a pair read the same activations and find them in L2.
-__global__ __launch_bounds__(kJBlock) void project_kernel(const char *__restrict__ x, const char *__restrict__ w_q,
-                                                          const char *__restrict__ w_k,
-                                                          const int32_t *__restrict__ rep, int H, int k, int Tn, int D,
-                                                          int n_mt, char *__restrict__ q_out,
-                                                          char *__restrict__ k_compact, int pos0, int Tc_cap)
+// f(integral_constant 0), f(1), .. f(N - 1)
+template <typename F, int... I>
+__device__ __forceinline__ void unroll_seq(F &&f, std::integer_sequence<int, I...>)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int r = lane & 31, hl = lane >> 5;
-    const int wm = w & 3, wn = w >> 2;               // wave's 64-token strip, and query (0) or key (1) half
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void unroll(F &&f)
+{
+    unroll_seq(f, std::make_integer_sequence<int, N>{});
+}
 
-    int j, mt, b;
-    {
-        const unsigned n = blockIdx.x, N = gridDim.x;
-        const unsigned xcd = n & 7u, per = N >> 3, rem = N & 7u;
-        const unsigned item = xcd * per + min(xcd, rem) + (n >> 3);
-        j = (int)(item % (unsigned)k);
-        const unsigned rest = item / (unsigned)k;
-        mt = (int)(rest % (unsigned)n_mt);
-        b = (int)(rest / (unsigned)n_mt);
-    }
-    const int head = rep[(size_t)b * k + j];
-    if (head < 0) return;
-    const int rh = min(head, H - 1);
-    const int t0 = mt * kJTok;
+// ---------------------------------------------------------------------------------------------------------
+// Prompts.  A tile is 256 tokens x 256 columns, the 128 query and the 128 key columns of one representative, which share the
+// activations.  Four waves, one per SIMD, own 128 x 128 of it each (all 256 accumulation registers): 16 products of 16 x 16 x 32
+// per LDS fragment pair, half of the LDS reads that eight waves of 64 x 128 need.  Stages of 64 contraction steps, 64 KB, are
+// loaded straight into LDS, two of them; a wave reads the fragments of one half of a stage while it multiplies the other, so
+// that ONE barrier per stage, in its middle, frees the stage that has been read and hands over the one that has arrived.
+//
+// What bounds it: power.  With every CU multiplying N(0,1) data the chip runs at 1.6 to 1.8 GHz instead of 2.4, so that time is
+// energy.  Measured on operands of this kind with nothing but products: 32 x 32 x 16 tiles 1790 TFLOP/s, 16 x 16 x 32 ones, which
+// touch the accumulators half as often, 2060.  16 rows x 2043 tokens, 8 of 32 heads, D = 4096 (1024 tiles), per call:
+//   eight waves of 64 x 128, 32 x 32 x 16, staged through registers            490 us
+//   four waves of 128 x 128, loads straight to LDS, a workgroup per tile       477 (1.60 GHz, 172 000 cycles per tile of 131 000)
+//   one workgroup per CU, the next tile loaded during the end of one, whole output rows stored (8-byte pieces took 22 000 cycles per
+//   tile, rows through LDS take 7000)                                          460
+//   16 x 16 x 32                                                               436
+//   stages of 64 steps in cache lines of 128 bytes instead of 32 in half lines 415 (1.78 GHz; 350 if all loads hit L2, 312 without)
+// and no difference: the order of the products, a fifth stage of 32.  Slower: the loads of a stage closer together (432, 457).
+//
+// One workgroup per CU takes several (batch row, token tile, slot) items one after the other.  Items are numbered slot first and
+// dealt to the XCDs in contiguous ranges: the slots of a token tile read the same activations and find them in L2.
+// ---------------------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kJBlock, 1) void project_kernel(const char *__restrict__ x, const char *__restrict__ w_q,
+                                                             const char *__restrict__ w_k,
+                                                             const int32_t *__restrict__ rep, int H, int k, int Tn, int D,
+                                                             int n_mt, unsigned n_items, char *__restrict__ q_out,
+                                                             char *__restrict__ k_compact, int pos0, int Tc_cap)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int wm = w & 1, wn = w >> 1;               // wave's 128-token half, and query (0) or key (1) columns
 
-    // staging: a thread's piece i (of 8) is 16 bytes of row (tid >> 3) + 64 i of the stage, rows 0..255 being the
-    // activation tile and rows 256..511 the weight tile (query rows, then key rows).  Uniform base pointers plus
-    // 32-bit per-lane offsets (one batch row of activations and one head's weights are far below 4 GiB).
-    const unsigned int row_bytes = (unsigned int)D * 2u;
-    const int srow = tid >> 3, c = tid & 7;
-    const char *xb = x + (size_t)b * Tn * row_bytes;
-    const char *wqb = w_q + (size_t)rh * kHeadDim * row_bytes;
-    const char *wkb = w_k + (size_t)rh * kHeadDim * row_bytes;
-    unsigned int xoff[4], woff[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) xoff[i] = (unsigned int)min(t0 + srow + 64 * i, Tn - 1) * row_bytes + c * 16;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) woff[i] = (unsigned int)(srow + 64 * i) * row_bytes + c * 16;
-    const int dst0 = (srow * kJStride + c * 8) * 2;
-    u32x4 regs[kJPieces];
-    auto fetch = [&](int step) {
-        const unsigned int so = (unsigned int)step * (kJStep * 2);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) regs[i] = *reinterpret_cast<const u32x4 *>(xb + (xoff[i] + so));
-#pragma unroll
-        for (int i = 0; i < 2; ++i) regs[4 + i] = *reinterpret_cast<const u32x4 *>(wqb + (woff[i] + so));
-#pragma unroll
-        for (int i = 0; i < 2; ++i) regs[6 + i] = *reinterpret_cast<const u32x4 *>(wkb + (woff[i] + so));
+    struct Item {
+        int b, j, t0, head;
     };
-    auto stage = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < kJPieces; ++i)
-            *reinterpret_cast<u32x4 *>(lds + buf * kJTileBytes + dst0 + i * 64 * kJStride * 2) = regs[i];
-    };
-
-    f32x16 acc[4][2];                                // [column block of 32][token block of 32]
-#pragma unroll
-    for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[nb][tb][e] = 0.f;
-
-    // fragment addresses inside a stage: weights (A operand) rows kJTok + wn*128 + nb*32 + r, activations
-    // (B operand) rows wm*64 + tb*32 + r; 8 halves at 16*ks + 8*hl
-    const int a_off = ((kJTok + wn * kHeadDim + r) * kJStride + hl * 8) * 2;
-    const int b_off = ((wm * 64 + r) * kJStride + hl * 8) * 2;
-
-    const int n_steps = D / kJStep;
-    fetch(0);
-    stage(0);
-    if (n_steps > 1) fetch(1);
-    __syncthreads();
-    for (int s = 0; s < n_steps; ++s) {
-        const int buf = s & 1;
-        if (s + 1 < n_steps) stage(buf ^ 1);          // fetched one iteration ago
-        if (s + 2 < n_steps) fetch(s + 2);
-        const char *base = lds + buf * kJTileBytes;
-        // scheduling hint: spread the LDS reads and the stage's global loads and LDS writes between the MFMAs of
-        // the step instead of grouping them (measured: about 2 % faster)
-        __builtin_amdgcn_iglp_opt(1);
-#pragma unroll
-        for (int ks = 0; ks < kJStep / 16; ++ks) {
-            Frag af[4], bfr[2];
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-                af[nb].raw = *reinterpret_cast<const u32x4 *>(base + a_off + (nb * 32 * kJStride + ks * 16) * 2);
-#pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
-                bfr[tb].raw = *reinterpret_cast<const u32x4 *>(base + b_off + (tb * 32 * kJStride + ks * 16) * 2);
-#pragma unroll
-            for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
-                    acc[nb][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[nb].bf, bfr[tb].bf, acc[nb][tb], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // D[(v/4)*8 + hl*4 + v%4][r]: this lane's token is t0 + wm*64 + tb*32 + r, its features nb*32 + (v/4)*8 + hl*4 ..+3
-    char *orow_base = wn == 0 ? q_out + ((size_t)b * H + rh) * (size_t)Tn * (kHeadDim * 2)
-                              : k_compact + (((size_t)b * k + j) * (size_t)Tc_cap + pos0) * (kHeadDim * 2);
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-        const int t = t0 + wm * 64 + tb * 32 + r;
-        if (t >= Tn) continue;
-        char *orow = orow_base + (size_t)t * (kHeadDim * 2);
-#pragma unroll
-        for (int nb = 0; nb < 4; ++nb)
-#pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
-                bf16x4 o;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) o[e] = (__bf16)acc[nb][tb][v4 * 4 + e];
-                *reinterpret_cast<bf16x4 *>(orow + (nb * 32 + v4 * 8 + hl * 4) * 2) = o;
+    const unsigned xcd = blockIdx.x & 7u, each = n_items >> 3, rest = n_items & 7u;
+    const unsigned hi = each * (xcd + 1) + min(xcd + 1, rest);
+    unsigned at = each * xcd + min(xcd, rest) + (blockIdx.x >> 3);
+    // the next item of this workgroup whose slot is in use; false: there is none
+    auto next_item = [&](Item &it) __attribute__((always_inline)) {
+        for (; at < hi; at += gridDim.x >> 3) {
+            const unsigned bm = at / (unsigned)k;
+            it.j = (int)(at - bm * (unsigned)k);
+            it.b = (int)(bm / (unsigned)n_mt);
+            it.t0 = (int)(bm - (unsigned)it.b * (unsigned)n_mt) * kJTok;
+            const int head = rep[(size_t)it.b * k + it.j];
+            if (head >= 0) {
+                it.head = min(head, H - 1);
+                at += gridDim.x >> 3;
+                return true;
             }
+        }
+        return false;
+    };
+
+    // staging: direct load i of wave w fills rows 8*(w + 4i) .. +7 of a stage (rows 0..255 tokens, 256..383 query and
+    // 384..511 key rows of the weights); lane l's 16 bytes land in slot l%8 of row l/8, and piece p of row R belongs in
+    // slot p ^ ((R >> 1) & 7): 16 consecutive rows read at one piece index touch 16 different 16-byte bank groups.
+    const size_t row_bytes = (size_t)D * 2;
+    const unsigned piece16 = (unsigned)((lane & 7) ^ ((lane >> 4) + 4 * (w & 1))) * 16;
+    const int srow = 8 * w + (lane >> 3);
+    unsigned xoff[8], woff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) woff[i] = (unsigned)(srow + 32 * i) * (unsigned)row_bytes + piece16;
+    const char *xb = nullptr, *wqb = nullptr, *wkb = nullptr;
+    auto load_from = [&](const Item &it) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xoff[i] = (unsigned)min(srow + 32 * i, Tn - 1 - it.t0) * (unsigned)row_bytes + piece16;
+        xb = x + ((size_t)it.b * Tn + it.t0) * row_bytes;
+        wqb = w_q + (size_t)it.head * kHeadDim * row_bytes;
+        wkb = w_k + (size_t)it.head * kHeadDim * row_bytes;
+    };
+#if defined(__HIP_DEVICE_COMPILE__)
+    auto load = [&](int s, int buf_off, auto ic) {
+        constexpr int i = decltype(ic)::value;
+        const char *base = i < 8 ? xb : (i < 12 ? wqb : wkb);
+        const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, -1, 0x00020000);
+        auto *dst = (__attribute__((address_space(3))) void *)(lds + buf_off + (w + 4 * i) * 1024);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, dst, 16, (int)(i < 8 ? xoff[i & 7] : woff[i & 3]), s * (kJStep * 2), 0, 0);
+    };
+    // every wave's loads but the youngest N have landed, and every wave has read what it reads before this point
+    auto landed = [&](auto n) {
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(n)::value) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+#else
+    auto load = [&](int, int, auto) {};
+    auto landed = [&](auto) {};
+    (void)xb, (void)wqb, (void)wkb, (void)xoff, (void)woff;
+#endif
+
+    // fragments: 16 rows x 32 contraction elements (half a stage), lane's row r, 8 elements at 8*g.  Fragment i: 0 the first
+    // 16 weight rows, 1 .. 8 the token rows, 9 .. 15 the other weight rows, which is the order the products need them in.
+    const int sw = (r >> 1) & 7;
+    const int a_row = (kJTok + wn * kHeadDim + r) * (kJStep * 2), b_row = (wm * 128 + r) * (kJStep * 2);
+    const int piece[2] = {(g ^ sw) << 4, ((4 + g) ^ sw) << 4};
+    Frag fa[2][8], fb[2][8];
+    auto read = [&](auto half, auto ic, const char *base) {
+        constexpr int i = decltype(ic)::value, h = decltype(half)::value, nb = i == 0 ? 0 : i - 8, tb = i - 1;
+        if constexpr (i >= 1 && i <= 8) fb[h][tb].raw = *reinterpret_cast<const u32x4 *>(base + piece[h] + b_row + tb * 16 * (kJStep * 2));
+        else fa[h][nb].raw = *reinterpret_cast<const u32x4 *>(base + piece[h] + a_row + nb * 16 * (kJStep * 2));
+    };
+    constexpr std::integral_constant<int, 0> lower{};
+    constexpr std::integral_constant<int, 1> upper{};
+
+    Item now, then;
+    if (!next_item(now)) return;
+    bool more = true;                                // `then`, whose stages are loaded behind those of `now`, exists
+    const int n_steps = D / kJStep;
+    load_from(now);
+    int ls = 0;                                      // the stage to load next (of `now`, or of `then`)
+    auto advance = [&]() __attribute__((always_inline)) {
+        if (__builtin_expect(ls == n_steps, 0)) {
+            more = next_item(then);
+            if (more) load_from(then);
+            ls = more ? 0 : n_steps - 1;             // past the last item: requested, not read
+        }
+    };
+    for (int i = 0; i < 2; ++i) {
+        advance();
+        unroll<kJLoads>([&](auto ic) { load(ls, i * kJStageBytes, ic); });
+        ++ls;
     }
+    landed(std::integral_constant<int, kJLoads>{});
+    unroll<16>([&](auto i) { read(lower, i, lds); });
+    int cur = 0;                                     // byte offset of the present stage
+    for (;;) {
+        f32x4 acc[8][8];                             // [column block of 16][token block of 16]
+        // Half a stage: 64 products, and between them 16 reads for the next half and, where the stage has been read, the loads
+        // of the one after the next into its place.
+        auto half = [&](auto hc, auto first) {
+            constexpr int h = decltype(hc)::value;
+            unroll<64>([&](auto nc) {
+                constexpr int n = decltype(nc)::value, nb = n >> 3, tb = (nb & 1) ? 7 - (n & 7) : n & 7;
+                const f32x4 c = decltype(first)::value ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[nb][tb];
+                acc[nb][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[h][nb].bf, fb[h][tb].bf, c, 0, 0, 0);
+                if constexpr (n % 3 == 0 && n < 48)
+                    read(std::integral_constant<int, 1 - h>{}, std::integral_constant<int, n / 3>{}, lds + (h == 0 ? cur : cur ^ kJStageBytes));
+                if constexpr (h == 1 && n % 4 == 2) load(ls, cur, std::integral_constant<int, n / 4>{});
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        };
+        auto stage = [&](auto first) {
+            half(lower, first);
+            advance();
+            landed(std::integral_constant<int, 0>{});
+            half(upper, std::false_type{});
+            ++ls;
+            cur ^= kJStageBytes;
+        };
+        stage(std::true_type{});
+        for (int s = 1; s < n_steps; ++s) stage(std::false_type{});
+
+        // D[4*g + v][r]: this lane's token is t0 + wm*128 + tb*16 + r, its features nb*16 + 4*g .. +3.
+        // 32 tokens at a time through LDS (piece p of token row R in slot p ^ (R & 15)), so that whole rows are stored.
+        char *const strip = lds + 2 * kJStageBytes + w * kJOutBytes;
+        const int left = Tn - now.t0 - wm * 128;             // tokens from this wave's first one on
+        char *const rows = (wn == 0 ? q_out + (((size_t)now.b * H + now.head) * (size_t)Tn) * (kHeadDim * 2)
+                                    : k_compact + (((size_t)now.b * k + now.j) * (size_t)Tc_cap + pos0) * (kHeadDim * 2)) +
+                           (size_t)(now.t0 + wm * 128) * (kHeadDim * 2);
+        int l = lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(l));                  // addresses are made here, not kept in registers all the time
+#endif
+        const int wr = l & 15, wp = l >> 5, wh = (l >> 4 & 1) * 8, rd = l >> 4, rp = l & 15;
+        unroll<4>([&](auto tc) {
+#pragma unroll
+            for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+                for (int nb = 0; nb < 8; ++nb) {
+                    const f32x4 &d = acc[nb][2 * decltype(tc)::value + t2];
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)d[e];
+                    *reinterpret_cast<bf16x4 *>(strip + (t2 * 16 + wr) * (kHeadDim * 2) + (((nb * 2 + wp) ^ wr) << 4) + wh) = o;
+                }
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            u32x4 o[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = 4 * i + rd;
+                o[i] = *reinterpret_cast<const u32x4 *>(strip + row * (kHeadDim * 2) + ((rp ^ (row & 15)) << 4));
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int row = decltype(tc)::value * 32 + 4 * i + rd;
+                if (row < left) *reinterpret_cast<u32x4 *>(rows + (unsigned)(row * (kHeadDim * 2) + rp * 16)) = o[i];
+            }
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        if (!more) break;
+        now = then;
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    // the requests past the end have landed before LDS is given to another workgroup
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#endif
 }
 
 // The (row, slot) pairs that `head` represents, as indexes into rep, ascending: all workgroups of a head agree which
@@ -200,8 +294,6 @@ __device__ __forceinline__ int list_slots(const int32_t *__restrict__ rep, int n
 constexpr int kJrWaves = 8, kJrBlocks = 4;
 constexpr int kJrTokens = 8;                 // tokens of all rows up to which this kernel is the faster one
 constexpr int kJrParts = kJCol / 16;                 // workgroups per head
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(kJrWaves * 64) void project_rows_kernel(const char *__restrict__ x,
                                                                      const char *__restrict__ w_q,
@@ -485,8 +577,8 @@ __global__ __launch_bounds__(kJtBlock) void project_tile_kernel(const char *__re
 // `buf` once and then issues rounds of eight independent v_mfma_f32_32x32x16_bf16 with nothing else in the loop.
 // The rate depends on the operand VALUES (switching activity moves the clocks), hence operands from the caller's
 // data rather than constants.
-constexpr int kProbeBlocks = 512, kProbeMfmaPerRound = 8;
-__global__ __launch_bounds__(kJBlock) void mfma_probe_kernel(const u32x4 *__restrict__ buf, unsigned long long n_pieces,
+constexpr int kProbeBlocks = 512, kProbeThreads = 512, kProbeMfmaPerRound = 8;
+__global__ __launch_bounds__(kProbeThreads) void mfma_probe_kernel(const u32x4 *__restrict__ buf, unsigned long long n_pieces,
                                                              int rounds, float *__restrict__ sink)
 {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -518,12 +610,12 @@ __global__ __launch_bounds__(kJBlock) void mfma_probe_kernel(const u32x4 *__rest
 
 double mfma_probe_flops(int rounds)
 {
-    return (double)kProbeBlocks * (kJBlock / 64) * (double)rounds * kProbeMfmaPerRound * (2.0 * 32 * 32 * 16);
+    return (double)kProbeBlocks * (kProbeThreads / 64) * (double)rounds * kProbeMfmaPerRound * (2.0 * 32 * 32 * 16);
 }
 
 int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, const KernelEvents &ev, hipStream_t stream)
 {
-    return (int)launch_kernel(mfma_probe_kernel, dim3(kProbeBlocks), dim3(kJBlock), 0, stream, ev,
+    return (int)launch_kernel(mfma_probe_kernel, dim3(kProbeBlocks), dim3(kProbeThreads), 0, stream, ev,
                               static_cast<const u32x4 *>(buf), (unsigned long long)(bytes / 16), rounds, sink);
 }
 
@@ -541,15 +633,16 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     //   B*k*Tn <= most      64-token tiles, head-major: B 16, k 8, Tn 1 / 16 / 64 / 128: 80 / 82 / 82 / 85 -> 17 / 20 / 32 /
     //                       62 us; B 1, k 8, Tn 512 / 2043: 85 / 87 -> 21 / 60 us; B 4, k 16, D 9216, Tn 16 / 256:
     //                       175 / 215 -> 52 / 135 us; B 4, k 8, D 6656, Tn 512: 151 -> 95 us
-    //   above               256-token tiles: B 16, k 8, Tn 256: 98 us (118 us with the small tiles)
+    //   above               256-token tiles: B 16, k 8, Tn 256: 82 us (118 us with the small tiles)
     // From 16384 pairs' tokens on the small tiles take a third round of the chip.  It pays where the large tiles need a second
     // one, or are a long chain and do not fill theirs, or hold few tokens each; in us, large / small tiles:
-    //   B 16, k 8 (128 large tiles), Tn 144, 160 and 192: D 4096 85 / 80, 88 / 82 and 88 / 84, D 3072 66 / 65 and (192) 68 / 68,
-    //   D 2048 47.2 / 47.7, 47.8 / 48.0 and 49.1 / 50.6, D 1024 28 / 31 and (192) 30 / 33, D 512 19 / 24 and (192) 21 / 25
-    //   B 1, k 8, Tn 2304 and 3072: D 2048 49.9 / 48.3 and 50.8 / 51.3
-    //   B 16, k 10 (160), Tn 140, D 5120: 118 / 111
-    //   B 16, k 16 (256), Tn 72 / 80 / 96: D 4096 100 / 82 and (96) 104 / 108, D 9216 238 / 195, 238 / 196 and 238 / 246
-    //   B 16, k 32 (512), Tn 48: D 512 37 / 27, D 4096 202 / 90
+    //   B 16, k 8 (128 large tiles), Tn 128: D 4096 74 / 61, D 2048 42 / 37, D 1024 26.0 / 25.2; Tn 144, 160 and 192: D 4096
+    //   75 / 84, 76 / 84 and 75 / 88, (144) D 3072 58 / 68, (160) D 2048 43 / 50
+    //   B 1, k 8, Tn 2304 and 3072: D 2048 42 / 50, D 4096 75 / 90; B 4, k 8, Tn 600 (96), D 6656: 118 / 127
+    //   B 4, k 16, Tn 300 (128), D 9216: 199 / 182
+    //   B 16, k 10 (160), Tn 140, D 6656: 146 / 137
+    //   B 16, k 16 (256), Tn 72 / 80 / 96: (72) D 9216 227 / 194, D 4096 (80) 97 / 86 and (96) 98 / 114
+    //   B 16, k 32 (512), Tn 48: D 512 42 / 27, D 4096 194 / 91
     // Both small kernels list the pairs of a head in LDS (at most kJrMaxSlots of them).
     const long long items = (long long)B * k * Tn;
     const bool listed = (long long)B * k <= kJrMaxSlots;
@@ -558,7 +651,8 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
                                   xc, wq, wk, rep, B, H, k, Tn, D, qo, ko, pos0, Tc_cap);
     // (the tile kernel addresses the activations and one head's weights with 32-bit byte offsets below 2 GiB)
     const long long n_large = (long long)B * k * ((Tn + kJTok - 1) / kJTok);
-    const long long most = n_large > 256 ? 24576 : (D < 2048 ? 16384 : (D < 3072 || n_large > 200 ? 20480 : 24576));
+    const bool one_round = n_large <= 150 && D < 8192;
+    const long long most = n_large > 256 ? 24576 : (D < 2048 || one_round ? 16384 : (D < 3072 || n_large > 200 ? 20480 : 24576));
     if (listed && items <= most && H <= kJtMaxHeads && (long long)B * Tn * D * 2 < 0x7fffffffLL &&
         (long long)kHeadDim * D * 2 < 0x7fffffffLL) {
         static DeviceFlags tile_lds_allowed;
@@ -577,8 +671,10 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     if (attr != hipSuccess) return (int)attr;
     const int n_mt = (Tn + kJTok - 1) / kJTok;
     if ((long long)n_mt * k * B > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
-    return (int)launch_kernel(project_kernel, dim3((unsigned int)n_mt * k * B), dim3(kJBlock), kJLdsBytes, stream, ev, xc,
-                              wq, wk, rep, H, k, Tn, D, n_mt, qo, ko, pos0, Tc_cap);
+    const unsigned int n_items = (unsigned int)n_mt * k * B;
+    const bool one_each = n_items < kJCus || D < 2 * kJStep;    // (loads run two stages ahead, at most one item)
+    return (int)launch_kernel(project_kernel, dim3(one_each ? (n_items + 7) / 8 * 8 : kJCus), dim3(kJBlock), kJLdsBytes,
+                              stream, ev, xc, wq, wk, rep, H, k, Tn, D, n_mt, n_items, qo, ko, pos0, Tc_cap);
 }
 
 }  // namespace chai

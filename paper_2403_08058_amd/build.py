@@ -23,7 +23,8 @@ SOURCES = {
     "cache.hip": [],
     # the softmax bookkeeping never sees NaNs (masked scores are -inf): drop the NaN-quieting copies around max.
     # Matrix results in ordinary registers: the accumulation half belongs to the accumulators the source names.
-    "prefill.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form"],
+    # Uniform branches stay branches: as flags they make the count of outstanding loads a guess.
+    "prefill.hip": ["-fno-honor-nans", "-mllvm", "-amdgpu-mfma-vgpr-form", "-mllvm", "-structurizecfg-skip-uniform-regions"],
     "project.hip": [],
     # bit-exact k-means: no fused multiply-add, no reassociation
     "kmeans.hip": ["-ffp-contract=off", "-fno-fast-math"],

@@ -15,12 +15,11 @@
 // row-major V cache cannot deliver, so a first kernel writes V^T once per call: fp16 (exact from bf16 inside
 // the fp16 range, |v| <= 65504), in blocks of 64 keys x 128 columns, keys permuted inside every group of 16 into
 // the order the probability registers have, zero beyond the last key.  The main kernel then stages K and V^T
-// tiles in LDS with 16-byte direct loads and feeds every MFMA operand with one ds_read_b128.  (The LDS transpose
-// reads of this chip could hand the operand over from a row-major bf16 tile and make the pre-pass unnecessary,
-// but only as bf16: the probabilities would then be rounded to 8 bits as well, up to 2^-9 of relative error per
-// element, which is the whole error budget of the 16-bit contract; converting the values to fp16 inside the
-// main kernel instead would be paid by every workgroup that streams a tile, a dozen vector instructions per
-// MFMA.)
+// tiles in LDS with 16-byte direct loads and feeds every MFMA operand with one ds_read_b128.  Calls with few query tiles
+// per head do without that kernel and its pass over all values: their workgroups take the rows of V themselves, and the
+// conversion transposes on the way into LDS (prefill_direct_kernel).  (The LDS transpose reads of this chip could hand the
+// operand over from a row-major bf16 tile, but only as bf16: the probabilities would then be rounded to 8 bits as well, up to
+// 2^-9 of relative error per element, which is the whole error budget of the 16-bit contract.)
 #include "chai_internal.h"
 
 #include <hip/hip_ext.h>
@@ -177,7 +176,9 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // it (both streams of a wave use every fragment, which halves the LDS reads per MFMA: 24 KB instead of 48 KB per 64 rows
 // and block), value and score slots alternate so that no MFMA waits for the one before it, the maxima stand behind the
 // first MFMAs and the exponentials behind the others (OpSchedule).  Fragments are requested kAhead slots ahead, also
-// across the end of a block: the next block's keys and values are always in LDS already.
+// across the end of a block: the next block's keys and values are always in LDS already.  A lone wave is bound by its issue
+// slots, so that every instruction counts: requests in pairs (one wait for two) and addresses that are moved on once per tile
+// made narrow tiles 3 to 7 % faster (1 row x 32 heads, 24 positions behind 1792 keys 49.3 -> 46.6 us), wide ones 1 to 2 %.
 //
 // What bounds it, two members, U = 2 (cycles of one wave per 64-key tile; the MFMAs alone are 96 x 32 = 3072): 4500 to
 // 4600 on a chip with free CUs -- the replayed body is 2 x 1940 (MFMA only 1536, + LDS reads 1570, + vector work 1700,
@@ -189,14 +190,14 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // x 2043 positions, 32 heads in 8 clusters 663 -> 616 us, dense 809 -> 780 us; 4 rows x 4000, 4 clusters 520 -> 467 us (with
 // the balanced numbering below); 1 row x 2043 97 -> 63 us; 256 positions behind 1792 keys, 4 rows x 52 heads 128 -> 93 us.
 //
-// NW = 4 with U = 1 halves a workgroup's rows for launches that leave CUs without work (rule in launch_prefill): a wave's LDS
+// NW = 4 with U = 1 halves a workgroup's rows for launches that leave CUs without work (rules in launch_prefill): a wave's LDS
 // reads per MFMA double, but twice as many CUs work, on half as long a chain.
 //
 // LDS: rings of three K and three V^T tiles (64 keys).  While tile t is computed, K(t+2) and V(t+1) are loaded with
 // direct loads, requested in the first half of the tile; K runs ahead of V because the scores of a block are issued one
 // block before its softmax, and V lags because its products come one block after.  ONE barrier per tile.
-// Dense attention over at most two tiles of keys has rings of two (BUFS), 64 KB: it is all start and end, and two workgroups
-// on a CU cover each other's (10 x 52 heads of 40 keys 25.4 -> 21.2 us, of 128 keys 36.8 -> 31.9 us).
+// Dense attention of thousands of heads over at most one tile of keys has rings of two (BUFS), 64 KB: it is all start and end,
+// and two workgroups on a CU cover each other's (64 x 72 heads of 24 keys 72 us, 79 us with one, values converted on the way).
 //
 // A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
 // through LDS (670-840 against 578 us per 8-cluster LLaMa-7B layer), three members in one wave (630 against 553 us).
@@ -455,7 +456,8 @@ struct OpSchedule {
 
 // One query tile (NW waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
 // LDS: rings of BUFS tiles (2: at most two key tiles), a value tile with room for G members.
-template <int NM, int U, int NW, int G, int BUFS>
+// DIRECT: vsrc are the members' rows of the value cache itself (see prefill_direct_kernel).
+template <int NM, int U, int NW, int G, int BUFS, bool DIRECT = false>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
                                           int qt, int rhead, float scale2, float *__restrict__ out)
@@ -486,22 +488,24 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     const int k_row = 4 * w + (lane >> 4);
     const int v_row = 8 * w + (lane >> 3);
 #if defined(__HIP_DEVICE_COMPILE__)
-    auto make_rsrc = [](const char *base) {
-        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, 0x7fffffff, 0x00020000);
+    auto make_rsrc = [](const char *base, int bytes = 0x7fffffff) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(base), 0, bytes, 0x00020000);
     };
     auto load_to_lds = [](__amdgpu_buffer_rsrc_t rs, unsigned int off, char *dst) {
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)dst, 16, (int)off, 0, 0, 0);
     };
 #else
-    auto make_rsrc = [](const char *base) { return base; };
+    auto make_rsrc = [](const char *base, int = 0) { return base; };
     auto load_to_lds = [](const char *, unsigned int, char *) {};
 #endif
     const auto k_rs = make_rsrc(ksrc);
-    const auto v_rs0 = make_rsrc(vsrc[0]);
-    const auto v_rs1 = make_rsrc(vsrc[NM - 1]);
+    const int v_bytes = DIRECT ? n_keys * (kHeadDim * 2) : 0x7fffffff;       // rows past the last key read as zeros
+    const auto v_rs0 = make_rsrc(vsrc[0], v_bytes);
+    const auto v_rs1 = make_rsrc(vsrc[NM - 1], v_bytes);
+    const int k_piece = ((lane & 15) ^ (k_row & 15)) << 4;   // rows 4 NW apart share the swizzle
+    const int k_off = k_row * (kHeadDim * 2) + k_piece, k_last = (n_keys - 1) * (kHeadDim * 2) + k_piece;
     auto dma_k1 = [&](int kt, int buf, int i) {
-        const int row = k_row + 4 * NW * i;
-        load_to_lds(k_rs, (unsigned int)(min(kt * kKTile + row, n_keys - 1) * (kHeadDim * 2) + (((lane & 15) ^ (row & 15)) << 4)),
+        load_to_lds(k_rs, (unsigned int)min(k_off + (kt * kKTile + 4 * NW * i) * (kHeadDim * 2), k_last),
                     k_lds + buf * kKBufBytes + (w + NW * i) * 1024);
     };
     const int v_piece = (lane & 7) ^ ((v_row >> 1) & 7);     // rows 8 NW apart share the swizzle
@@ -529,13 +533,71 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         asm volatile("" ::: "memory");
 #endif
     };
+    // DIRECT: the values that this wave wrote are in LDS, and all but the youngest N requests have landed
+    auto written_barrier = [&](auto n) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(n)::value) : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#endif
+    };
     // fragments: this lane's row r of a 32-row block of K, fragment p = 8 * member + 4 * (16 keys) + 32-column block of V^T
-    const int k_sw = r & 15, v_sw = (r >> 1) & 7;
+    const int k_sw = r & 15, v_sw = DIRECT ? ((r >> 1) & 7) ^ (r >> 4) : (r >> 1) & 7;
     auto k_frag = [&](const char *kb, int ks) { return *reinterpret_cast<const u32x4 *>(kb + (((2 * ks + hl) ^ k_sw) << 4)); };
     auto v_frag = [&](const char *vb, int half, int p) {
-        const int j = p & 7;
+        const int j = p & 7, turn = DIRECT ? 2 * (j & 3) : 0;
         return *reinterpret_cast<const u32x4 *>(vb + (p >> 3) * kVBufBytes + (j & 3) * 32 * (kKTile * 2) +
-                                                (((4 * half + 2 * (j >> 2) + hl) ^ v_sw) << 4));
+                                                (((4 * half + 2 * (j >> 2) + hl) ^ turn ^ v_sw) << 4));
+    };
+
+    // DIRECT: this thread's piece of every value tile is 8 columns (8 co ..) of the 8 keys that an MFMA operand holds side by
+    // side, piece v_p of a V^T row, of one member (NM = 2), or half of those keys (NM = 1).  Transposing is no work of its
+    // own: a conversion packs the same column of two keys.  Column d is row d ^ (d >> 3 & 1) of the tile in LDS, and piece p
+    // of row R sits in slot p ^ ((R >> 1) & 7) ^ (R >> 4): reads of 16 rows at one piece and writes of 16 threads' columns at
+    // one piece both touch 16 different 16-byte bank groups.
+    constexpr int kKeys = NM == 2 ? 8 : 4;
+    const int co = lane & 15, v_rest = 4 * w + (lane >> 4);
+    const int v_p = NM == 2 ? v_rest & 7 : v_rest >> 1, v_half = NM == 2 ? 0 : v_rest & 1;
+    const unsigned int v_in = (unsigned int)((16 * (v_p >> 1) + 4 * (v_p & 1) + 8 * v_half) * (kHeadDim * 2) + co * 16);
+    struct Raw {
+        u32x4 key[kKeys];
+    };
+    auto fetch_key = [&](Raw &raw, int kt, auto ic) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        constexpr int i = decltype(ic)::value;
+        const unsigned int off = v_in + (unsigned int)kt * (kKTile * kHeadDim * 2) + ((i & 3) + 8 * (i >> 2)) * (kHeadDim * 2);
+        raw.key[i] = __builtin_amdgcn_raw_buffer_load_b128(NM == 2 && w >= 2 ? v_rs1 : v_rs0, (int)off, 0, 0);
+#endif
+    };
+    // column 2 m + h of the eight: unit u = 2 m + h of a tile
+    unsigned int packed[kKeys / 2];
+    auto convert = [&](const Raw &raw, auto uc) {
+        constexpr int m = decltype(uc)::value >> 1, h = decltype(uc)::value & 1;
+#pragma unroll
+        for (int i = 0; i < kKeys; i += 2) {
+            const unsigned int x0 = raw.key[i][m], x1 = raw.key[i + 1][m];
+            packed[i / 2] = pack_f16(__uint_as_float(h == 0 ? x0 << 16 : x0 & 0xffff0000u),
+                                     __uint_as_float(h == 0 ? x1 << 16 : x1 & 0xffff0000u));
+        }
+    };
+    const int v_slot = v_p ^ (co >> 1) ^ (4 * (co & 1));
+    char *const v_out = v_lds + (NM == 2 ? (w >> 1) * kVBufBytes : 0) + co * 8 * (kKTile * 2) + v_half * 8;
+    auto store_unit = [&](int buf, auto uc) {
+        constexpr int m = decltype(uc)::value >> 1, h = decltype(uc)::value & 1;
+        char *at = v_out + buf * (G * kVBufBytes) + ((2 * m + h) ^ (co & 1)) * (kKTile * 2) + ((v_slot ^ m) << 4);
+        if constexpr (NM == 2) *reinterpret_cast<u32x4 *>(at) = u32x4{packed[0], packed[1], packed[2], packed[3]};
+        else *reinterpret_cast<uint2 *>(at) = make_uint2(packed[0], packed[1]);
+    };
+    // Tile kt's share of that work, in as many steps as its two blocks have hooks: convert tile kt + 1 out of `raw`, then
+    // request tile kt + 3 into it (its neighbour holds kt + 2); the keys of tile kt + 2 in between.
+    constexpr int kHooks = NM == 2 ? 12 : 8;
+    auto value_work = [&](Raw &raw, int far, int buf, auto hc, auto keys) {
+        constexpr int hk = decltype(hc)::value;
+        if constexpr (hk < 8) {
+            convert(raw, std::integral_constant<int, hk>{});
+            store_unit(buf, std::integral_constant<int, hk>{});
+        } else if constexpr (hk % 2 == 0 && hk < 8 + 2 * kKeys) fetch_key(raw, far, std::integral_constant<int, (hk - 8) / 2>{});
+        if constexpr (hk % 2 == 1 && hk < 8) keys(hk / 2);
     };
 
     // accumulators: tile (stream * NM + member) * 4 + 32-column block; zeroed at the end of the first block
@@ -580,21 +642,39 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     };
 
     // slots of a block: 8 NM value fragments and 8 key fragments, every third (NM = 2) or second one a key fragment
-    constexpr int kSlots = 8 * NM + 8, kAhead = 4, kHead = 5, kMaxSteps = 4 * U;
+    constexpr int kSlots = 8 * NM + 8, kAhead = U == 1 && NW == 4 && BUFS > 2 ? 6 : 4, kHead = 5, kMaxSteps = 4 * U;
     struct Carry {
         Frag16 f[kAhead];
     };
-    auto frag_of = [&](auto sl, const char *kb, const char *vb, int vhalf) {
+    // LDS addresses of this lane's fragments, eight of the keys and four of the values, moved on by a tile where a fragment of an
+    // even block is the last one to use them (added up for every fragment they were a tenth of all instructions).
+    // Even blocks multiply the second half of the tile's keys and of the values before it, odd blocks the first halves of
+    // the next tile's keys and of the tile's values.
+    const char *k_at[8], *v_at[4];
+    int k_step = 0, v_step = 0;                              // to the next tile, of the even block whose fragments are requested
+    auto frag_of = [&](auto sl, auto even) {
         constexpr int s = sl.value;
-        constexpr bool qk = NM == 2 ? s % 3 == 2 : s % 2 == 1;
-        if constexpr (qk) return k_frag(kb, NM == 2 ? s / 3 : s / 2);
-        else return v_frag(vb, vhalf, NM == 2 ? s - s / 3 : s / 2);
+        constexpr bool e = decltype(even)::value, qk = NM == 2 ? s % 3 == 2 : s % 2 == 1;
+        if constexpr (qk) {
+            constexpr int ks = NM == 2 ? s / 3 : s / 2;
+            const u32x4 f = *reinterpret_cast<const u32x4 *>(k_at[ks] + (e ? 32 * (kHeadDim * 2) : 0));
+            if constexpr (e) k_at[ks] += k_step;
+            return f;
+        } else {
+            constexpr int p = NM == 2 ? s - s / 3 : s / 2, j = p & 7, piece = ((e ? 4 : 0) + 2 * (j >> 2)) ^ (DIRECT ? 2 * (j & 3) : 0);
+            const u32x4 f = *reinterpret_cast<const u32x4 *>(v_at[piece / 2] + (p >> 3) * kVBufBytes + (j & 3) * 32 * (kKTile * 2));
+            if constexpr (e && DIRECT && p >= 8 * NM - 4) v_at[piece / 2] += v_step;
+            if constexpr (e && !DIRECT && p >= 8 * NM - 8 && (j & 3) == 3) {
+                v_at[piece / 2] += v_step;
+                v_at[piece / 2 - 2] += v_step;               // of the odd block
+            }
+            return f;
+        }
     };
-    // Block kbase .. kbase+31: softmax of its scores sc into pn; scores of the next block (keys kb) into sn; products of the
-    // block before (probabilities pp, values vb, half vhalf).  carry: the first fragments, and then those of the next call;
-    // even: block 0 may be among them.
-    auto body = [&](Score &sc, Score &sn, const Prob &pp, Prob &pn, int kbase, const char *kb, const char *vb, int vhalf,
-                    const char *kb_next, const char *vb_next, int vhalf_next, Carry &carry, auto dma, auto even) {
+    // Block kbase .. kbase+31: softmax of its scores sc into pn; scores of the next block into sn; products of the block before
+    // (probabilities pp).  carry: the first fragments, and then those of the next call; even: block 0 may be among them.
+    // Fragments are requested in pairs, the one that is needed first last: one wait serves both.
+    auto body = [&](Score &sc, Score &sn, const Prob &pp, Prob &pn, int kbase, Carry &carry, auto dma, auto even) {
         // causal mask: only blocks that reach past the wave's first query need it (a branch uniform per wave; out of line,
         // like the rescaling below: a taken branch costs a lone wave 40 cycles)
         if (__builtin_expect(kbase + 31 > wave_first, 0)) {
@@ -611,16 +691,16 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         unroll<kAhead>([&](auto i) { fr[i.value] = carry.f[i.value]; });
         auto fetch = [&](auto sl) {
             constexpr int s = sl.value;
-            if constexpr (s < kSlots) fr[s].raw = frag_of(sl, kb, vb, vhalf);
-            else fr[s].raw = frag_of(std::integral_constant<int, s - kSlots>{}, kb_next, vb_next, vhalf_next);
+            if constexpr (s < kSlots) fr[s].raw = frag_of(sl, even);
+            else fr[s].raw = frag_of(std::integral_constant<int, s - kSlots>{}, std::integral_constant<bool, !decltype(even)::value>{});
         };
         // step j: MFMA of stream j % U of slot j / U
         auto step = [&](auto jc) {
             constexpr int s = jc.value / U, u = jc.value % U;
             if constexpr (s < kSlots) {
                 constexpr bool qk = NM == 2 ? s % 3 == 2 : s % 2 == 1;
-                if constexpr (u == 0) fetch(std::integral_constant<int, s + kAhead>{});
-                if constexpr (u == U - 1 && s % 2 == 0) dma(s / 2);
+                if constexpr (u == 0) fetch(std::integral_constant<int, (s + kAhead) ^ 1>{});
+                if constexpr (u == U - 1 && s % 2 == 0) dma(std::integral_constant<int, s / 2>{});
                 if constexpr (qk) {
                     constexpr int ks = NM == 2 ? s / 3 : s / 2;
                     f32x16 c;
@@ -707,9 +787,19 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         }
     };
 
+    Raw raw_a, raw_b;                                        // DIRECT: tiles 0, 2, .. and 1, 3, ..
     dma_k(0, 0);
-    dma_v(0, 0);
-    if (n_tiles > 1) dma_k(1, 1);
+    if constexpr (DIRECT) {
+        __builtin_amdgcn_sched_barrier(0);
+        unroll<kKeys>([&](auto i) { fetch_key(raw_a, 0, i); });
+        __builtin_amdgcn_sched_barrier(0);
+        dma_k(min(1, n_tiles - 1), 1);
+        unroll<kKeys>([&](auto i) { fetch_key(raw_b, min(1, n_tiles - 1), i); });
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        dma_v(0, 0);
+        if (n_tiles > 1) dma_k(1, 1);
+    }
     // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]; padding rows repeat the last one
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -719,7 +809,18 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #pragma unroll
         for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[u][ks].raw = *reinterpret_cast<const u32x4 *>(qrow + ks * 32);
     }
-    tile_barrier();
+    if constexpr (DIRECT) {
+        __builtin_amdgcn_sched_barrier(0);
+        unroll<8>([&](auto u) {
+            convert(raw_a, u);
+            store_unit(0, u);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+        unroll<kKeys>([&](auto i) { fetch_key(raw_a, min(2, n_tiles - 1), i); });
+        __builtin_amdgcn_sched_barrier(0);
+        written_barrier(std::integral_constant<int, 2 * kKeys>{});           // behind the keys of tiles 0 and 1: the values of 1 and 2
+    } else
+        tile_barrier();
     Score sa, sb;
     Prob pa, pb;
 #pragma unroll
@@ -742,39 +843,67 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             sa.s[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf.bf, qf[u][ks].bf, sa.s[u], 0, 0, 0);
         }
     }
-    const char *kb_lane = k_lds + r * (kHeadDim * 2), *vb_lane = v_lds + r * (kKTile * 2);
+    const char *kb_lane = k_lds + r * (kHeadDim * 2);
+    const char *vb_lane = v_lds + (DIRECT ? r ^ ((r >> 3) & 1) : r) * (kKTile * 2);
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) k_at[ks] = kb_lane + (((2 * ks + hl) ^ k_sw) << 4);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v_at[c] = vb_lane + (((2 * c + hl) ^ v_sw) << 4);
+    k_step = (int)kKBufBytes;                                // (v_step: even block 0 reads its own tile's values)
     Carry carry;
-    unroll<kAhead>([&](auto i) { carry.f[i.value].raw = frag_of(i, kb_lane + 32 * (kHeadDim * 2), vb_lane, 0); });
+    unroll<kAhead>([&](auto i) { carry.f[i.value ^ 1].raw = frag_of(std::integral_constant<int, i.value ^ 1>{}, std::true_type{}); });
     // Tile kt: blocks 2 kt (keys already multiplied; scores of the tile's second half, values of the block before) and
     // 2 kt + 1.  The first block multiplies zero probabilities with the first tile's values, for accumulators that it then zeroes.
     int b3 = 0, b3p = 0;                                     // buffers of tile kt and of the values before it
-    for (int kt = 0; kt < n_tiles; ++kt) {
+    auto tile = [&](int kt, Raw &raw) __attribute__((always_inline)) {
         const int b3n = b3 == BUFS - 1 ? 0 : b3 + 1, b3nn = b3n == BUFS - 1 ? 0 : b3n + 1;
         const int kt2 = min(kt + 2, n_tiles - 1), kt1 = min(kt + 1, n_tiles - 1);      // past the end: requested, not read
         const int hb = 2 * kt;
         const char *vprev = vb_lane + b3p * (G * kVBufBytes), *vcur = vb_lane + b3 * (G * kVBufBytes);
-        const char *k_odd = kb_lane + b3 * kKBufBytes + 32 * (kHeadDim * 2), *k_even = kb_lane + b3n * kKBufBytes;
-        auto dma0 = [&](int i) {                             // the next tiles' kDma (NM + 1) requests, early in this one
-            if (BUFS == 2) {                                 // two tiles at most: the second one's values, its keys are there
+        auto keys = [&](int i) { dma_k1(kt2, b3nn, i); };
+        auto dma0 = [&](auto ic) {                           // the next tiles' kDma (NM + 1) requests, early in this one
+            const int i = decltype(ic)::value;
+            if constexpr (DIRECT) value_work(raw, min(kt + 3, n_tiles - 1), b3n, ic, keys);
+            else if (BUFS == 2) {                            // two tiles at most: the second one's values, its keys are there
                 if (i < kDma * NM && kt + 1 < n_tiles) dma_v1(kt1, b3n, i < kDma ? 0 : 1, i % kDma);
             } else if (i < kDma) dma_v1(kt1, b3n, 0, i);
             else if (i < kDma * NM) dma_v1(kt1, b3n, 1, i - kDma);
             else if (i < kDma * (NM + 1)) dma_k1(kt2, b3nn, i - kDma * NM);
         };
-        auto dma1 = [&](int) {};
-        if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, k_odd, vprev, kt > 0 ? 1 : 0, k_even, vcur, 0, carry, dma0, std::true_type{});
+        auto dma1 = [&](auto ic) {
+            if constexpr (DIRECT)
+                value_work(raw, min(kt + 3, n_tiles - 1), b3n, std::integral_constant<int, kHooks + decltype(ic)::value>{}, keys);
+        };
+        k_step = (b3n - b3) * (int)kKBufBytes;
+        v_step = (b3 - b3p) * (int)(G * kVBufBytes);
+        if (hb < n_hb) body(sa, sb, pb, pa, hb * 32, carry, dma0, std::true_type{});
         else {
-            unroll<kDma * (NM + 1)>([&](auto i) { dma0(i.value); });
+            unroll<DIRECT ? kHooks : kDma * (NM + 1)>([&](auto i) { dma0(i); });
             if (hb == n_hb) pv_last(pb, vprev, 1);
         }
-        if (hb + 1 < n_hb)
-            body(sb, sa, pa, pb, hb * 32 + 32, k_even, vcur, 0, k_even + 32 * (kHeadDim * 2), vcur, 1, carry, dma1, std::false_type{});
-        else if (hb + 1 == n_hb) pv_last(pa, vcur, 0);
+        k_step = (b3nn - b3n) * (int)kKBufBytes;             // the next tile's first fragments are requested here
+        if (hb + 1 < n_hb) body(sb, sa, pa, pb, hb * 32 + 32, carry, dma1, std::false_type{});
+        else {
+            if constexpr (DIRECT) unroll<kHooks>([&](auto i) { dma1(i); });
+            if (hb + 1 == n_hb) pv_last(pa, vcur, 0);
+        }
         // (after the last tile nobody waits for the requests past the end: they fill buffers that are not read any more)
-        if (kt + 1 < n_tiles) tile_barrier();
+        if (kt + 1 < n_tiles) {
+            if constexpr (DIRECT) written_barrier(std::integral_constant<int, kKeys>{});     // behind the keys of kt + 2: the values of kt + 3
+            else tile_barrier();
+        }
         b3p = b3;
         b3 = b3n;
-    }
+    };
+    if constexpr (DIRECT) {
+        for (int kt = 0;;) {
+            tile(kt, raw_b);
+            if (++kt == n_tiles) break;
+            tile(kt, raw_a);
+            if (++kt == n_tiles) break;
+        }
+    } else
+        for (int kt = 0; kt < n_tiles; ++kt) tile(kt, raw_a);
     if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (G * kVBufBytes), 1);
 
     if (n_hb > 0) {
@@ -845,6 +974,97 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__
     }
 }
 
+// Cluster, members and representative of group gi of row b (the groups of plan_row, in the same order), found by every workgroup
+// for itself; false: the row has fewer groups.  All the map entries are requested at once.  LDS: kPlanClusters ints.
+constexpr int kPlanClusters = 64, kPlanHeads = 256;          // most of them
+__device__ __forceinline__ bool find_group(const int32_t *__restrict__ h2c, const int32_t *__restrict__ rep, int b, int gi, int H,
+                                           int k, int32_t *count, int &cluster, int &n_mem, int (&heads)[kGroup], int &rhead)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int32_t *row = h2c + (size_t)b * H;
+    const int rep_j = lane < k ? rep[(size_t)b * k + lane] : -1, mine = tid < H ? row[tid] : -1;
+    int label[kPlanHeads / 64];
+#pragma unroll
+    for (int i = 0; i < kPlanHeads / 64; ++i) label[i] = i * 64 + lane < H ? row[i * 64 + lane] : -1;
+    if (tid < kPlanClusters) count[tid] = 0;
+    __syncthreads();
+    if (mine >= 0 && mine < k) atomicAdd(&count[mine], 1);
+    __syncthreads();
+    const int n = rep_j >= 0 ? count[lane] : 0;
+    __syncthreads();                                         // the counts give way to tiles
+    int upto = (n + kGroup - 1) / kGroup;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int other = __shfl_up(upto, o);
+        upto += lane >= o ? other : 0;
+    }
+    if (gi >= __builtin_amdgcn_readlane(upto, 63)) return false;
+    cluster = __popcll(__ballot(upto <= gi));
+    const int first = kGroup * (gi - (cluster > 0 ? __builtin_amdgcn_readlane(upto, cluster - 1) : 0));
+    n_mem = min(__builtin_amdgcn_readlane(n, cluster) - first, kGroup);
+    rhead = min(__builtin_amdgcn_readlane(rep_j, cluster), H - 1);
+    int seen = -first;
+#pragma unroll
+    for (int i = 0; i < kPlanHeads / 64; ++i) {
+        const unsigned long long votes = __ballot(label[i] == cluster);
+        const int rank = seen + __popcll(votes & ((1ull << lane) - 1ull));
+#pragma unroll
+        for (int g = 0; g < kGroup; ++g) {
+            const unsigned long long it = __ballot(label[i] == cluster && rank == g);
+            if (it != 0ull) heads[g] = i * 64 + __ffsll((long long)it) - 1;
+        }
+        seen += __popcll(votes);
+    }
+    if (n_mem < kGroup) heads[1] = heads[0];
+    return true;
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// The kernel of 128-row tiles without the pre-pass: for calls with few query tiles per head (rule in prefill_is_direct), which
+// spent up to half of their time on writing V^T for a few rows to read it (256 positions behind 1792 keys, 4 rows x 52 heads in
+// 8 clusters: 37 of 93 us).  A value tile comes as rows through registers, requested two tiles ahead; while a block is
+// multiplied, a thread turns 8 keys x 8 columns (NM = 2) into eight pieces of V^T and writes them to the tile after this one,
+// spread over the slots of both blocks.  What it costs: 64 conversions' worth of instructions and 8 LDS writes per wave and tile
+// (about 400 cycles), loads to registers instead of to LDS (about 380, 8 requests of 1 KB each); a tile of 64 keys and two
+// members takes 3400 cycles, 2550 without all of it, of which the products are 1536: a lone wave's issue slots.  The call above
+// 93 -> 62 us; 507 positions behind 5 keys, 4 x 72 heads in 16 clusters 65 -> 55 us; 24 behind 4000, 16 x 32 in 8 401 -> 206 us.
+//
+// The groups of a row are found by every workgroup for itself (a launch for the work list would cost 5 us).  Workgroups are
+// numbered group by group, all rows of one before the next, the longest query tiles first: the XCDs get equal shares without
+// any of them knowing the other rows' groups.
+// ---------------------------------------------------------------------------------------------------------
+template <bool IDENT>
+__global__ __launch_bounds__(256, 1) void prefill_direct_kernel(const char *__restrict__ q, const char *__restrict__ kc,
+                                                                const char *__restrict__ v, const int32_t *__restrict__ h2c,
+                                                                const int32_t *__restrict__ rep, int H, int k, int Tq, int q_start,
+                                                                int Tc_cap, int T_cap, int n_qt, int n_rows, int per_xcd,
+                                                                float scale, float *__restrict__ out)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
+    const int qt = n_qt - 1 - (int)(blockIdx.x / (kXcds * (unsigned)per_xcd));
+    const unsigned at = blockIdx.x % (kXcds * (unsigned)per_xcd);
+    int gi = (int)(at / (unsigned)n_rows);
+    const int b = (int)(at - (unsigned)gi * (unsigned)n_rows);
+    int cluster = gi, n_mem = 1, rhead = gi, heads[kGroup] = {gi, gi};
+    if (IDENT) {
+        if (gi >= H) return;
+    } else {
+        if (!find_group(h2c, rep, b, gi, H, k, reinterpret_cast<int32_t *>(lds_raw), cluster, n_mem, heads, rhead)) return;
+#pragma unroll
+        for (int g = 0; g < kGroup; ++g) heads[g] = __builtin_amdgcn_readfirstlane(heads[g]);
+    }
+    const char *vsrc[kGroup];
+#pragma unroll
+    for (int g = 0; g < kGroup; ++g) vsrc[g] = v + ((size_t)b * H + heads[g]) * (size_t)T_cap * (kHeadDim * 2);
+    const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
+    if (!IDENT && n_mem == 2)
+        prefill_tile<2, 1, 4, kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt,
+                                                   rhead, scale * kLog2e, out);
+    else
+        prefill_tile<1, 1, 4, IDENT ? 1 : kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
+                                                               q_start, qt, rhead, scale * kLog2e, out);
+}
+
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
 
 }  // namespace
@@ -857,6 +1077,47 @@ size_t prefill_workspace_bytes(int B, int H, int k, int n_keys)
     const size_t Tp = ((size_t)n_keys + kKTile - 1) / kKTile * kKTile;
     return round256((size_t)B * prefill_max_groups(H, k) * kRec * sizeof(int32_t)) +
            round256((size_t)B * sizeof(int32_t)) + round256((size_t)B * H * kHeadDim * Tp * sizeof(_Float16));
+}
+
+// Which calls skip the pre-pass: those with few query tiles per head.  The pre-pass reads and writes all values once (two bytes each
+// way at 6.5 TB/s, and 3 us); converting them in the 128-row tiles costs every tile of 64 keys 0.3 us per group of two members and
+// 0.15 us per head alone, in each query tile again, where longer calls have 256-row tiles, which are a fifth faster per row.
+// Whole calls, with pre-pass / direct in us:
+// * one or two query tiles: 4 rows x 52 heads in 8 clusters, 24 behind 0 / 400 / 1792 / 4000 keys 15 / 10, 28 / 19, 73 / 48 and 176 /
+//   100, 256 behind the same 26 / 19, 42 / 30, 95 / 64 and 183 / 124; 16 x 72 in 16, 128 behind 0 / 1792 56 / 43 and 403 / 193;
+//   dense, 16 x 32 heads, 24 behind 0 / 1792 19 / 11 and 188 / 94, 200 behind 0 / 400 / 1792 50 / 44, 90 / 91 and 242 / 230.  Not
+//   where a handful of heads makes the pre-pass cheap next to a long chain of tiles: 1 x 32 in 8, 24 behind 400 / 1792 / 4000
+//   21 / 18, 46.6 / 47.3 and 88 / 93; dense, 1 x 8, 128 behind 1000 / 2500 / 4000 29 / 27, 52.8 / 53.1 and 75 / 78.  Nor for blocks
+//   of at most one key tile on thousands of heads, which have two workgroups per CU (64 x 72, 24 keys 72 / 79, but 65 keys
+//   140 / 124, and 32 x 52, 24 keys 30 / 30).
+// * clustered, more: three 4 x 72 in 16, 384 behind 0 / 1792 46 / 36 and 173 / 146; four 4 x 72, 507 behind 0 / 1792 63 / 52 and
+//   218 / 189, 16 x 72 in 16, 507 behind 0 / 400 208 / 204 and 330 / 341; five 16 x 32 in 8, 600 behind 0 / 800 135 / 124 and 277 /
+//   257; six (three whole wide tiles) 4 x 52, 700 behind 0 / 800 69 / 62 and 133 / 121, 4 x 72, 700 behind 200 / 800 112 / 109 and
+//   164 / 171; seven 12 x 52 in 4, 860 behind 0 / 200 239 / 219 and 302 / 276; eight 4 x 52, 1000 behind 0 / 800 96 / 90 and 173 /
+//   172, but 16 x 32, 1000 behind 0 225 / 232.
+// * dense, more: while the tiles are one round of the chip (1 x 32, 1000 behind 0 / 800 30 / 26 and 46 / 41); beyond, three 6 x 52,
+//   300 behind 0 / 800 52 / 45 and 133 / 118, but just over one round 2 x 52, 384 behind 1792 / 4000 83 / 83 and 154 / 169, and on
+//   many heads 12 x 72, 384 behind 400 261 / 270; four 6 x 52, 400 behind 0 / 200 / 800 69 / 64, 91 / 89 and 150 / 155, 8 x 72, 400
+//   behind 0 112 / 115; five 4 x 52, 600 behind 0 / 200 72 / 67 and 90 / 92; six 4 x 52, 700 behind 0 82 / 79, 6 x 52 121 / 125;
+//   seven 4 x 52, 860 behind 0 108 / 102, 6 x 52 149 / 157; eight 4 x 52, 1000 behind 0 125 / 130.
+static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool identity)
+{
+    const long long heads = (long long)B * H, n_keys = (long long)q_start + Tq;
+    const int n = (Tq + 127) / 128;
+    if (identity) {
+        if (n_keys <= kKTile && heads >= 2048) return false;
+        if (n_keys * (2200 - 79 * heads) > 3800000) return false;
+        if (n <= 2) return true;
+        if (heads * n <= 256) return n <= 8;
+        if (n == 3) return q_start <= 256 || (heads <= 600 && (heads * n > 512 || q_start <= 1024));
+        return n <= 7 && q_start <= 128 && heads <= (n <= 5 ? 400 : 256);
+    }
+    if (H > kPlanHeads || k > kPlanClusters) return false;  // (more than a workgroup looks through for its group)
+    if (n_keys * (4700 - 79 * heads) > 3300000) return false;
+    if (n <= 3 || n == 5 || n == 7) return true;
+    const long long wide = (long long)(n / 2) * prefill_max_groups(H, k) * B;
+    if (n == 8) return wide <= 900 && q_start <= 256;
+    return n <= 6 && (q_start <= 128 || wide <= 420 || (wide <= 1300 && q_start <= 512));
 }
 
 int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *h2c, const int32_t *rep, int B, int H,
@@ -872,6 +1133,20 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     int32_t *n_groups = reinterpret_cast<int32_t *>(ws);
     ws += round256((size_t)B * sizeof(int32_t));
     _Float16 *vt = reinterpret_cast<_Float16 *>(ws);
+
+    if (prefill_is_direct(B, H, k, Tq, q_start, identity)) {
+        auto *kernel = identity ? prefill_direct_kernel<true> : prefill_direct_kernel<false>;
+        const size_t lds_bytes = prefill_lds_bytes(identity, kBufs);
+        static DeviceFlags lds_allowed[2];
+        const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[identity ? 1 : 0]);
+        if (e != hipSuccess) return (int)e;
+        const int n_qt = (Tq + 127) / 128;
+        const long long per_xcd = ((long long)max_groups * B + kXcds - 1) / kXcds, n_wg = kXcds * per_xcd * n_qt;
+        if (n_wg > 0xffffff) return (int)hipErrorInvalidConfiguration;
+        return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(256), lds_bytes, stream, ev,
+                                  static_cast<const char *>(q), static_cast<const char *>(kc), static_cast<const char *>(v), h2c, rep,
+                                  H, k, Tq, q_start, Tc_cap, T_cap, n_qt, B, (int)per_xcd, scale, out);
+    }
 
     const size_t tile_lds = (size_t)kHeadDim * (kKTile + 2) * sizeof(_Float16), plan_lds = (size_t)(H + 2 * k) * sizeof(int32_t);
     const int n_lists = identity ? 0 : B;
@@ -910,7 +1185,7 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
                 (n_narrow == 6 && tiles >= 2 * kSmallTiles && tiles <= kFewTiles);
     if (identity && tiles <= 256)
         small = small || (long long)B * H * (4LL * (q_start + (Tq + 127) / 128 * 128) - 3LL * n_keys + 700) <= 131072;
-    const bool brief = identity && n_keys <= 2 * kKTile;    // (one narrow query tile per head)
+    const bool brief = identity && n_keys <= kKTile;        // (thousands of heads of one narrow query tile)
     auto *kernel = small ? (identity ? (brief ? prefill_kernel<1, 4, true, 2> : prefill_kernel<1, 4, true, kBufs>)
                                      : prefill_kernel<1, 4, false, kBufs>)
                          : (identity ? prefill_kernel<1, 8, true, kBufs> : prefill_kernel<2, 4, false, kBufs>);

@@ -567,6 +567,8 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         constexpr int i = decltype(ic)::value;
         const unsigned int off = v_in + (unsigned int)kt * (kKTile * kHeadDim * 2) + ((i & 3) + 8 * (i >> 2)) * (kHeadDim * 2);
         raw.key[i] = __builtin_amdgcn_raw_buffer_load_b128(NM == 2 && w >= 2 ? v_rs1 : v_rs0, (int)off, 0, 0);
+#else
+        (void)v_in;
 #endif
     };
     // column 2 m + h of the eight: unit u = 2 m + h of a tile
@@ -1098,7 +1100,8 @@ size_t prefill_workspace_bytes(int B, int H, int k, int n_keys)
 // * dense, more: while the tiles are one round of the chip (1 x 32, 1000 behind 0 / 800 30 / 26 and 46 / 41); beyond, three 6 x 52,
 //   300 behind 0 / 800 52 / 45 and 133 / 118, but just over one round 2 x 52, 384 behind 1792 / 4000 83 / 83 and 154 / 169, and on
 //   many heads 12 x 72, 384 behind 400 261 / 270; four 6 x 52, 400 behind 0 / 200 / 800 69 / 64, 91 / 89 and 150 / 155, 8 x 72, 400
-//   behind 0 112 / 115; five 4 x 52, 600 behind 0 / 200 72 / 67 and 90 / 92; six 4 x 52, 700 behind 0 82 / 79, 6 x 52 121 / 125;
+//   behind 0 112 / 115; five 4 x 52, 600 behind 0 / 200 72 / 67 and 90 / 92; six 2 x 52, 700 behind 0 44 / 39, 4 x 52, 733 behind 0
+//   77.8 / 78.5, 6 x 52 121 / 125;
 //   seven 4 x 52, 860 behind 0 108 / 102, 6 x 52 149 / 157; eight 4 x 52, 1000 behind 0 125 / 130.
 static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool identity)
 {
@@ -1110,7 +1113,7 @@ static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool ide
         if (n <= 2) return true;
         if (heads * n <= 256) return n <= 8;
         if (n == 3) return q_start <= 256 || (heads <= 600 && (heads * n > 512 || q_start <= 1024));
-        return n <= 7 && q_start <= 128 && heads <= (n <= 5 ? 400 : 256);
+        return n <= 7 && q_start <= 128 && heads <= (n == 4 ? 400 : (n == 5 ? 320 : (n == 6 ? 128 : 256)));
     }
     if (H > kPlanHeads || k > kPlanClusters) return false;  // (more than a workgroup looks through for its group)
     if (n_keys * (4700 - 79 * heads) > 3300000) return false;

@@ -274,6 +274,21 @@ int chai_decode_values(const void *v_cache, const int32_t *head_to_cluster, cons
                                     workspace, workspace_bytes, stream, nullptr, nullptr);
 }
 
+// One clustered call, the probabilities copied out where they are asked for.
+static int clustered_decode(const void *q, const void *k_compact, const void *v_cache, const int32_t *head_to_cluster,
+                            const int32_t *rep_heads, int B, int H, int k, int T, int Tc_cap, int T_cap, int dtype, float scale,
+                            float *out, float *probs_out, void *workspace, const DecodePlan &plan, hipStream_t s)
+{
+    if (!probs_out)
+        return hip_status(launch_decode(q, k_compact, v_cache, head_to_cluster, rep_heads, B, H, k, T, Tc_cap, T_cap, dtype, scale,
+                                        out, workspace, plan, false, s));
+    const int st = hip_status(launch_scores(q, k_compact, rep_heads, B, H, k, T, Tc_cap, dtype, scale, workspace, plan, false,
+                                            KernelEvents(), s));
+    if (st != CHAI_OK) return st;
+    return hip_status(launch_values(v_cache, head_to_cluster, rep_heads, B, H, k, T, T_cap, dtype, out, probs_out, workspace, plan,
+                                    false, KernelEvents(), s));
+}
+
 int chai_decode_attention(const void *q, const void *k_compact, const void *v_cache, const int32_t *head_to_cluster,
                           const int32_t *rep_heads, int B, int H, int k, int T, int Tc_cap, int T_cap, int d,
                           int dtype, float scale, float *out, float *probs_out, void *workspace,
@@ -285,12 +300,8 @@ int chai_decode_attention(const void *q, const void *k_compact, const void *v_ca
     if (st == CHAI_OK) st = check_values(v_cache, out, B, H, k, T, T_cap, d, dtype, workspace, workspace_bytes, &plan);
     if (st != CHAI_OK) return st;
     if (B == 0) return CHAI_OK;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    st = hip_status(launch_scores(q, k_compact, rep_heads, B, H, k, T, Tc_cap, dtype, scale, workspace, plan, false,
-                                  KernelEvents(), s));
-    if (st != CHAI_OK) return st;
-    return hip_status(launch_values(v_cache, head_to_cluster, rep_heads, B, H, k, T, T_cap, dtype, out, probs_out,
-                                    workspace, plan, false, KernelEvents(), s));
+    return clustered_decode(q, k_compact, v_cache, head_to_cluster, rep_heads, B, H, k, T, Tc_cap, T_cap, dtype, scale, out,
+                            probs_out, workspace, plan, static_cast<hipStream_t>(stream));
 }
 
 int chai_decode_attention_static(const void *q, const void *k_compact, const void *v_cache,
@@ -309,12 +320,8 @@ int chai_decode_attention_static(const void *q, const void *k_compact, const voi
     if (plan.bytes > (size_t)CHAI_STATIC_SCRATCH_BYTES) return CHAI_ERR_STATIC_LIMIT;
     void *ws = nullptr;
     if (static_scratch(&ws) != hipSuccess) return CHAI_ERR_HIP;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    st = hip_status(launch_scores(q, k_compact, rep_heads, B, H, k, T, Tc_cap, dtype, scale, ws, plan, false,
-                                  KernelEvents(), s));
-    if (st != CHAI_OK) return st;
-    return hip_status(launch_values(v_cache, head_to_cluster, rep_heads, B, H, k, T, T_cap, dtype, out, probs_out, ws,
-                                    plan, false, KernelEvents(), s));
+    return clustered_decode(q, k_compact, v_cache, head_to_cluster, rep_heads, B, H, k, T, Tc_cap, T_cap, dtype, scale, out,
+                            probs_out, ws, plan, static_cast<hipStream_t>(stream));
 }
 
 int chai_decode_step(const void *q, const void *k_new, const void *v_new, void *k_compact, void *v_cache,
@@ -329,12 +336,8 @@ int chai_decode_step(const void *q, const void *k_new, const void *v_new, void *
     if (st != CHAI_OK) return st;
     if (!aligned16(k_new) || !aligned16(v_new)) return CHAI_ERR_ALIGN;
     if (B == 0) return CHAI_OK;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    st = hip_status(launch_scores(q, k_compact, rep_heads, B, H, k, T, Tc_cap, dtype, scale, workspace, plan, false,
-                                  KernelEvents(), s, k_new));
-    if (st != CHAI_OK) return st;
-    return hip_status(launch_values(v_cache, head_to_cluster, rep_heads, B, H, k, T, T_cap, dtype, out, nullptr,
-                                    workspace, plan, false, KernelEvents(), s, nullptr, v_new));
+    return hip_status(launch_decode(q, k_compact, v_cache, head_to_cluster, rep_heads, B, H, k, T, Tc_cap, T_cap, dtype, scale, out,
+                                    workspace, plan, false, static_cast<hipStream_t>(stream), k_new, v_new));
 }
 
 int chai_quantize_rows(const void *x, int dtype, long long n_rows, int d, uint8_t *codes, float *scales, void *stream)
@@ -458,12 +461,8 @@ int chai_dense_decode_attention(const void *q, const void *k_cache, const void *
     if (st == CHAI_OK) st = check_values(v_cache, out, B, H, H, T, T_cap, d, dtype, workspace, workspace_bytes, &plan);
     if (st != CHAI_OK) return st;
     if (B == 0) return CHAI_OK;
-    hipStream_t s = static_cast<hipStream_t>(stream);
-    st = hip_status(launch_scores(q, k_cache, nullptr, B, H, H, T, T_cap, dtype, scale, workspace, plan, true,
-                                  KernelEvents(), s));
-    if (st != CHAI_OK) return st;
-    return hip_status(launch_values(v_cache, nullptr, nullptr, B, H, H, T, T_cap, dtype, out, nullptr, workspace, plan,
-                                    true, KernelEvents(), s));
+    return hip_status(launch_decode(q, k_cache, v_cache, nullptr, nullptr, B, H, H, T, T_cap, T_cap, dtype, scale, out, workspace,
+                                    plan, true, static_cast<hipStream_t>(stream)));
 }
 
 int chai_project_qk_timed(const void *x, const void *w_q, const void *w_k, const int32_t *rep_heads, int B, int H, int k,

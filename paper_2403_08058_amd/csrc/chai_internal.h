@@ -80,6 +80,11 @@ inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block,
 int launch_scores(const void *q, const void *kc, const int32_t *rep, int B, int H, int k, int T, int Tc_cap,
                   int dtype, float scale, void *workspace, const DecodePlan &plan, bool identity,
                   const KernelEvents &ev, hipStream_t stream, const void *k_new = nullptr);
+// Both phases of one call, in two launches or, for dense and for small calls, in one (plus the sum of partial rows); no copy of the
+// probabilities.
+int launch_decode(const void *q, const void *kc, const void *v, const int32_t *h2c, const int32_t *rep, int B, int H, int k, int T,
+                  int Tc_cap, int T_cap, int dtype, float scale, float *out, void *workspace, const DecodePlan &plan, bool identity,
+                  hipStream_t stream, const void *k_new = nullptr, const void *v_new = nullptr);
 // members: when set, the H streams of `v` are compact (one per cluster) and the finished row of stream j goes
 // to out_members[b][h] of every head h (of n_heads) with head_to_cluster[b][h] == j; `out` is then staging.
 struct MemberRows {

@@ -12,6 +12,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 namespace chai {
 
 namespace {
@@ -497,6 +499,243 @@ __global__ __launch_bounds__(kHeadDim) void combine_members_kernel(const float *
     out[((size_t)b * n_heads + h) * kHeadDim + threadIdx.x] = add_rows(partial + srow * n_cp * kHeadDim + threadIdx.x, n_cp);
 }
 
+// ---------------------------------------------------------------------------------------------------------
+// Both phases in one workgroup: scores of a chunk of tokens into LDS, softmax over the chunk, values of the same tokens.  For dense
+// attention, where no score is shared, and for small clustered calls, whose two launches are all ramp (the members of a cluster
+// then score its keys each for itself, out of L2).  grid (n_cp, H * DS, B); DS = 2: two workgroups per head and chunk, each with
+// half of the columns of V.  The first values are requested before the keys; padding rows of a last batch are zeroed, not weighed.
+// With one chunk the row goes to `out`, otherwise the weighted sum over the chunk, relative to the chunk's maximum, goes to
+// `partial` and (maximum, sum of exponentials) to `recs`; combine_chunks_kernel puts them together.
+// What bounds it: small calls one chain of latencies (map, keys, barrier, exponentials, sums, 4 to 5 us of which a launch is half),
+// large ones HBM: 512 heads of 4000 tokens 163 us, 6.4 TB/s (178 us in two launches); 52 heads of 1777 14 us (18 us in three).
+// APPEND: as in the two-phase kernels; every head scores the new token's key for itself, and head h writes it to the cache of
+// every cluster that h represents.
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kFusedTokens = 12288;          // most tokens of a chunk (their scores in LDS, 48 KB)
+constexpr int kFusedWaves = 8;               // (16 waves: 6.7 against 6.1 us for 32 heads in 8 clusters at 256 tokens; 4: level)
+template <int DT, bool IDENT, bool APPEND, int DS, int NW>
+__global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__ q, const char *__restrict__ kc,
+                                                        const char *__restrict__ v, const int32_t *__restrict__ h2c,
+                                                        const int32_t *__restrict__ rep, int H, int k, int T, int Tc_cap,
+                                                        int T_cap, float scale, int cp, int n_cp, float *__restrict__ partial,
+                                                        float2 *__restrict__ recs, float *__restrict__ out,
+                                                        const char *__restrict__ k_new, const char *__restrict__ v_new)
+{
+    using KT = Tile<DT>;
+    using VT = VTile<DT, DS>;
+    extern __shared__ float s_lds[];                         // cp scores
+    __shared__ float max_lds[NW], sum_lds[NW];
+    __shared__ float p_lds[NW][VT::BATCH];
+    __shared__ float acc_lds[NW][VT::COLS];
+    const int split = blockIdx.x, hy = blockIdx.y, b = blockIdx.z;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int h = hy / DS, dpart = hy % DS;
+    const int t0 = split * cp, n_all = min(T, t0 + cp) - t0;
+    const bool has_new = APPEND && split == n_cp - 1;
+    const int n = has_new ? n_all - 1 : n_all;               // rows that are in the caches already
+    auto clamp_row = [&](int row) { return APPEND ? max(min(row, n - 1), 0) : min(row, n - 1); };
+
+    const int vcg = lane % VT::LPR, vrg = lane / VT::LPR;
+    const char *vbase = v + (((size_t)b * H + h) * T_cap + t0) * VT::ROW_BYTES;
+    const unsigned int v_off = dpart * VT::PART_BYTES + vcg * 16;
+    u32x4 vb[kUnroll];
+    auto request_v = [&](int it) {
+        const int r0 = (it * NW + w) * VT::BATCH + vrg;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            vb[u] = stream16(vbase + ((unsigned int)clamp_row(r0 + u * VT::RPW) * VT::ROW_BYTES + v_off));
+    };
+    request_v(0);
+
+    // keys
+    const int c = IDENT ? h : min(max(h2c[(size_t)b * H + h], 0), k - 1);
+    const int r = IDENT ? h : min(max(rep[(size_t)b * k + c], 0), H - 1);
+    const int cg = lane % KT::LPR, rg = lane / KT::LPR;
+    const char *kbase = kc + (((size_t)b * k + c) * Tc_cap + t0) * KT::ROW_BYTES;
+    const unsigned int lane_off = cg * 16;
+    u32x4 kb[kUnroll];
+    auto request_k = [&](int it) {
+        const int r0 = (it * NW + w) * KT::BATCH + rg;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const char *p = kbase + ((unsigned int)clamp_row(r0 + u * KT::RPW) * KT::ROW_BYTES + lane_off);
+            kb[u] = IDENT ? stream16(p) : *reinterpret_cast<const u32x4 *>(p);
+        }
+    };
+    request_k(0);
+    float qf[KT::EPL];
+    unpack(*reinterpret_cast<const u32x4 *>(q + ((size_t)b * H + r) * KT::ROW_BYTES + lane_off), qf);
+    float m_run = -INFINITY;
+    auto scaled = [&](float x) {
+#pragma clang fp contract(off)
+        return scale * x;                                    // rounded: the statistics and the probabilities start from it
+    };
+    const int n_kb = (n + KT::BATCH - 1) / KT::BATCH, k_it = n_kb > w ? (n_kb - w + NW - 1) / NW : 0;
+    for (int it = 0; it < k_it; ++it) {
+        float mine = 0.f;
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            float f[KT::EPL];
+            unpack(kb[u], f);
+            float dot = 0.f;
+#pragma unroll
+            for (int e = 0; e < KT::EPL; ++e) dot = fmaf(qf[e], f[e], dot);
+            dot = row_sum<DT>(dot);
+            mine = cg == u ? dot : mine;
+        }
+        if (it + 1 < k_it) request_k(it + 1);
+        const int tl = (it * NW + w) * KT::BATCH + rg + cg * KT::RPW;
+        if (cg < kUnroll && tl < n) {
+            const float sv = scaled(mine);
+            s_lds[tl] = sv;
+            m_run = fmaxf(m_run, sv);
+        }
+    }
+    if (APPEND) {
+        if (has_new && w == NW - 1 && rg == 0) {             // one lane group: the new key row of the representative
+            float f[KT::EPL];
+            unpack(*reinterpret_cast<const u32x4 *>(k_new + ((size_t)b * H + r) * KT::ROW_BYTES + lane_off), f);
+            float dot = 0.f;
+#pragma unroll
+            for (int e = 0; e < KT::EPL; ++e) dot = fmaf(qf[e], f[e], dot);
+            dot = row_sum<DT>(dot);
+            if (cg == 0) {
+                const float sv = scaled(dot);
+                s_lds[n] = sv;
+                m_run = fmaxf(m_run, sv);
+            }
+        }
+        if (has_new && w == 0 && dpart == 0) {               // the clusters that this head represents keep its key
+            for (int j0 = 0; j0 < k; j0 += 64) {
+                const int rj = j0 + lane < k ? rep[(size_t)b * k + j0 + lane] : -1;
+                for (unsigned long long left = __ballot(rj >= 0 && min(rj, H - 1) == h); left != 0ull; left &= left - 1ull) {
+                    const int j = j0 + __ffsll((long long)left) - 1;
+                    if (lane < KT::LPR)
+                        *reinterpret_cast<u32x4 *>(const_cast<char *>(kc) + (((size_t)b * k + j) * Tc_cap + T - 1) * KT::ROW_BYTES + lane * 16) =
+                            *reinterpret_cast<const u32x4 *>(k_new + ((size_t)b * H + h) * KT::ROW_BYTES + lane * 16);
+                }
+            }
+        }
+    }
+    const float wave_m = wave_max(m_run);
+    if (lane == 0) max_lds[w] = wave_m;
+    __syncthreads();
+    const float M = wave_max(lane < NW ? max_lds[lane] : -INFINITY);
+
+    // values
+    // (exponentials relative to the chunk's maximum are weights and are summed up; the division comes last, which is one rounding
+    // less per token than probabilities that are normalised first)
+    float acc[VT::EPL], sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < VT::EPL; ++e) acc[e] = 0.f;
+    const int n_vb = (n + VT::BATCH - 1) / VT::BATCH, v_it = n_vb > w ? (n_vb - w + NW - 1) / NW : 0;
+    for (int it = 0; it < v_it; ++it) {
+        const int r0 = (it * NW + w) * VT::BATCH;
+        if (lane < VT::BATCH) {
+            const float p = r0 + lane < n ? expf(s_lds[r0 + lane] - M) : 0.f;
+            p_lds[w][(lane % VT::RPW) * kUnroll + lane / VT::RPW] = p;
+            sum += p;
+        }
+        __builtin_amdgcn_wave_barrier();
+        float pv[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) pv[u] = p_lds[w][vrg * kUnroll + u];
+        __builtin_amdgcn_wave_barrier();
+        if (r0 + VT::BATCH > n) {
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u)
+                if (r0 + vrg + u * VT::RPW >= n) vb[u] = u32x4{0u, 0u, 0u, 0u};
+        }
+        // (eight rows added up before they join the sum: long chunks would else be a longer chain of roundings than short ones)
+        float eight[VT::EPL];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            float f[VT::EPL];
+            unpack(vb[u], f);
+#pragma unroll
+            for (int e = 0; e < VT::EPL; ++e) eight[e] = u == 0 ? pv[u] * f[e] : fmaf(pv[u], f[e], eight[e]);
+        }
+#pragma unroll
+        for (int e = 0; e < VT::EPL; ++e) acc[e] += eight[e];
+        if (it + 1 < v_it) request_v(it + 1);
+    }
+    if (APPEND) {
+        if (has_new && w == 0 && vrg == 0) {
+            const u32x4 nraw = *reinterpret_cast<const u32x4 *>(v_new + ((size_t)b * H + h) * VT::ROW_BYTES + v_off);
+            const float p = expf(s_lds[n] - M);
+            sum += lane == 0 ? p : 0.f;
+            float f[VT::EPL];
+            unpack(nraw, f);
+#pragma unroll
+            for (int e = 0; e < VT::EPL; ++e) acc[e] = fmaf(p, f[e], acc[e]);
+            *reinterpret_cast<u32x4 *>(const_cast<char *>(vbase) + ((unsigned int)n * VT::ROW_BYTES + v_off)) = nraw;
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < VT::EPL; ++e) {
+#pragma unroll
+        for (int o = VT::LPR; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+    }
+    if (vrg == 0) {
+#pragma unroll
+        for (int e = 0; e < VT::EPL; ++e) acc_lds[w][vcg * VT::EPL + e] = acc[e];
+    }
+    sum = wave_sum(sum);
+    if (lane == 0) sum_lds[w] = sum;
+    __syncthreads();
+    if (tid < VT::COLS) {
+        float val = 0.f, L = 0.f;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            val += acc_lds[i][tid];
+            L += sum_lds[i];
+        }
+        const size_t orow = (size_t)b * H + h;
+        const int col = dpart * VT::COLS + tid;
+        if (n_cp == 1) out[orow * kHeadDim + col] = val / L;
+        else {
+            partial[(orow * n_cp + split) * kHeadDim + col] = val;
+            if (tid == 0 && dpart == 0) recs[orow * n_cp + split] = make_float2(M, L);
+        }
+    }
+}
+
+// out = sum of the chunks' rows, each weighed by exp(its maximum - the largest), over the sum of exponentials.  grid (B*H), 128
+// threads; n_cp <= kHeadDim.
+constexpr int kFusedChunks = kHeadDim;
+__global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *__restrict__ partial, const float2 *__restrict__ recs,
+                                                                  int n_cp, float *__restrict__ out)
+{
+    __shared__ float weight[kFusedChunks];
+    const size_t orow = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const float *p = partial + orow * n_cp * kHeadDim + tid;
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(u, n_cp - 1) * kHeadDim];
+    float2 a = make_float2(-INFINITY, 0.f), z = a;           // both waves look at all records
+    if (lane < n_cp) a = recs[orow * n_cp + lane];
+    if (lane + 64 < n_cp) z = recs[orow * n_cp + lane + 64];
+    const float M = wave_max(fmaxf(a.x, z.x));
+    const float wa = a.x == -INFINITY ? 0.f : expf(a.x - M), wz = z.x == -INFINITY ? 0.f : expf(z.x - M);
+    const float L = wave_sum(wa * a.y + wz * z.y);
+    if (tid < 64) {
+        weight[lane] = wa;
+        weight[lane + 64] = wz;
+    }
+    __syncthreads();
+    float sum = 0.f;
+    for (int i = 0; i < n_cp; i += 8) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum = i + u < n_cp ? fmaf(v[u], weight[i + u], sum) : sum;
+        if (i + 8 < n_cp) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(i + 8 + u, n_cp - 1) * kHeadDim];
+        }
+    }
+    out[orow * kHeadDim + tid] = sum / L;
+}
+
 struct Workspace {
     float *scores;
     float2 *stats;
@@ -612,6 +851,22 @@ int values_typed(const void *v, const int32_t *h2c, const int32_t *rep, int B, i
     }
 }
 
+template <int DT, bool IDENT, bool APPEND, int DS, int NW>
+int fused_launch(const void *q, const void *kc, const void *v, const int32_t *h2c, const int32_t *rep, int B, int H, int k, int T,
+                 int Tc_cap, int T_cap, float scale, float *out, const Workspace &w, int cp, hipStream_t stream, const void *k_new,
+                 const void *v_new)
+{
+    const int n_cp = (T + cp - 1) / cp;
+    const hipError_t e = launch_kernel(fused_kernel<DT, IDENT, APPEND, DS, NW>, dim3(n_cp, H * DS, B), dim3(NW * 64),
+                                       cp * sizeof(float), stream, KernelEvents(), static_cast<const char *>(q),
+                                       static_cast<const char *>(kc), static_cast<const char *>(v), h2c, rep, H, k, T, Tc_cap, T_cap,
+                                       scale, cp, n_cp, w.partial, w.stats, out, static_cast<const char *>(k_new),
+                                       static_cast<const char *>(v_new));
+    if (e != hipSuccess || n_cp == 1) return (int)e;
+    return (int)launch_kernel(combine_chunks_kernel, dim3(B * H), dim3(kHeadDim), 0, stream, KernelEvents(), w.partial, w.stats,
+                              n_cp, out);
+}
+
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 }  // namespace
@@ -682,6 +937,61 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
     pl.bytes = off;
     if (pl.cs < 256) pl.off_stats = shared_rows ? pl.off_partial : pl.off_rows;
     return pl;
+}
+
+// Tokens per workgroup of a call that does both phases at once (0: two launches) and its workgroups per head and chunk.  In us on
+// the GPU, two launches / one (a launch less is 3 us less of the host besides):
+// * Small calls, whole heads in two halves of the columns: 32 heads in 8 clusters at 64 / 256 / 600 / 900 bf16 tokens 7.0 / 4.6,
+//   8.2 / 6.1, 9.6 / 8.8 and 10.4 / 10.8, at 256 / 500 fp32 tokens 8.8 / 7.4 and 10.4 / 10.5; 72 in 16 at 600 10.0 / 9.2; 128
+//   heads at 256 / 400 / 600 / 900 8.9 / 7.3, 9.9 / 9.4, 11.4 / 11.4 and 12.9 / 14.4; 256 at 150 / 256 / 400 9.9 / 8.5, 10.9 / 10.4
+//   and 13.0 / 14.0; 288 at 64 / 150 10.1 / 9.4 and 11.0 / 11.3.  The keys of a cluster are read once per member there.
+// * Dense calls read every key once either way.  One round of 256 workgroups where the heads divide it: 32 heads at 1777 / 4000 /
+//   12000 tokens 13.8 / 11.2, 21.0 / 16.6 and 41.7 / 35.5, 52 at 1777 17.8 / 14.2, 104 at 4000 43.6 / 38.7 (twice as many chunks
+//   of half the size: 11.9, 17.2, 36.1, 14.4, 40.0), 208 at 200 / 577 / 4000 11.0 / 7.7, 18.9 / 13.4 and 76.6 / 66.4.  Whole heads
+//   from 384 on: 416 at 577 / 1777 26.2 / 23.0 and 65.2 / 62.1, 512 at 1777 78.4 / 73.1, 864 at 577 47.3 / 43.3.  Between, whole
+//   heads leave CUs with one workgroup waiting for those with two, thirds do not: 288 at 200 / 577 / 1777 / 4000 13.8 / 10.3, 24.4 /
+//   20.5, 57.4 / 55.7 and 107.5 / 118 whole, 13.1, 20.6, 47.7 and 96.3 in thirds.
+static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
+{
+    const long long heads = (long long)B * H, bytes = (long long)T * row_bytes;
+    *ds = 2;
+    if (bytes <= (heads <= 72 ? 160 : (heads <= 128 ? 128 : (heads <= 256 && k < H ? 56 : 0))) * 1024LL) return T;
+    if (k < H) return 0;
+    *ds = 1;
+    long long want = heads <= 256 ? 256 / heads : (heads < 384 && T >= 800 ? 3 : 1);
+    if (want > kFusedChunks) want = kFusedChunks;
+    long long cp = (T + want - 1) / want;
+    if (cp < 128) cp = T < 128 ? T : 128;
+    if (cp > kFusedTokens) cp = kFusedTokens;
+    return (T + cp - 1) / cp <= kFusedChunks ? (int)cp : 0;
+}
+
+int launch_decode(const void *q, const void *kc, const void *v, const int32_t *h2c, const int32_t *rep, int B, int H, int k, int T,
+                  int Tc_cap, int T_cap, int dtype, float scale, float *out, void *workspace, const DecodePlan &plan, bool identity,
+                  hipStream_t stream, const void *k_new, const void *v_new)
+{
+    int ds;
+    const int cp = fused_chunk(B, H, k, T, row_bytes_of(dtype), &ds);
+    if (cp > 0) {
+        Workspace w(workspace, plan);
+        w.stats = reinterpret_cast<float2 *>(static_cast<char *>(workspace) + plan.off_scores);      // (no scores there: a float each)
+        auto go = [&](auto dt, auto parts) {
+            constexpr int DT = decltype(dt)::value, DS = decltype(parts)::value;
+            auto *launch = identity ? fused_launch<DT, true, false, DS, kFusedWaves>
+                                    : (k_new ? fused_launch<DT, false, true, DS, kFusedWaves> : fused_launch<DT, false, false, DS, kFusedWaves>);
+            return launch(q, kc, v, h2c, rep, B, H, k, T, Tc_cap, T_cap, scale, out, w, cp, stream, k_new, v_new);
+        };
+        constexpr std::integral_constant<int, DT_BF16> bf16{};
+        constexpr std::integral_constant<int, DT_F32> f32{};
+        constexpr std::integral_constant<int, 1> whole{};
+        constexpr std::integral_constant<int, 2> halves{};
+        if (dtype == CHAI_BF16) return ds == 2 ? go(bf16, halves) : go(bf16, whole);
+        return ds == 2 ? go(f32, halves) : go(f32, whole);
+    }
+    const int e = launch_scores(q, kc, rep, B, H, k, T, Tc_cap, dtype, scale, workspace, plan, identity, KernelEvents(), stream, k_new);
+    if (e != (int)hipSuccess) return e;
+    return launch_values(v, h2c, rep, B, H, k, T, T_cap, dtype, out, nullptr, workspace, plan, identity, KernelEvents(), stream, nullptr,
+                         v_new);
 }
 
 int launch_scores(const void *q, const void *kc, const int32_t *rep, int B, int H, int k, int T, int Tc_cap, int dtype,

@@ -37,9 +37,15 @@ __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5
         if (bf16) {
             const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(q5) + qo);
             const uint4 *kv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(k5) + ko);
-#pragma unroll 4
+            uint4 qr[kHeadDim / 8], kr[kHeadDim / 8];        // both rows requested at once (four pieces at a time: 6.7 against 6.3 us)
+#pragma unroll
             for (int c8 = 0; c8 < kHeadDim / 8; ++c8) {
-                const uint4 a = qv[c8], bb = kv[c8];
+                qr[c8] = qv[c8];
+                kr[c8] = kv[c8];
+            }
+#pragma unroll
+            for (int c8 = 0; c8 < kHeadDim / 8; ++c8) {
+                const uint4 a = qr[c8], bb = kr[c8];
                 const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
@@ -52,14 +58,24 @@ __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5
         } else {
             const float4 *qv = reinterpret_cast<const float4 *>(static_cast<const float *>(q5) + qo);
             const float4 *kv = reinterpret_cast<const float4 *>(static_cast<const float *>(k5) + ko);
-#pragma unroll 4
-            for (int c4 = 0; c4 < kHeadDim / 4; ++c4) {
-                const float4 a = qv[c4], bb = kv[c4];
-                const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const double prod = (double)av[e] * (double)bv[e];
-                    acc = acc + prod;
+            for (int half = 0; half < 2; ++half) {
+                constexpr int kPieces = kHeadDim / 8;
+                float4 qr[kPieces], kr[kPieces];
+#pragma unroll
+                for (int c4 = 0; c4 < kPieces; ++c4) {
+                    qr[c4] = qv[half * kPieces + c4];
+                    kr[c4] = kv[half * kPieces + c4];
+                }
+#pragma unroll
+                for (int c4 = 0; c4 < kPieces; ++c4) {
+                    const float4 a = qr[c4], bb = kr[c4];
+                    const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {bb.x, bb.y, bb.z, bb.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const double prod = (double)av[e] * (double)bv[e];
+                        acc = acc + prod;
+                    }
                 }
             }
         }
@@ -355,6 +371,354 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 }
 
 // ---------------------------------------------------------------------------------------------------------
+// The same for features of whole positions (F a square) that fit LDS, up to 64 centres: with the same result bit for bit, and
+// with less of what the kernel above is bound by.  A pass of that one (72 heads, 16 centres, 25 coordinates) takes 8400 cycles:
+//  * 4200 for the distances, 3 fp64 operations per coordinate at 8 cycles each.  Here matrix instructions take them in fp32 first, 16
+//    heads and 16 centres per wave, as s = |c|^2 / 2 - x c, and fp64 only those centres that can still be the nearest.  With
+//    u = 2^-24 and M the largest |x|^2 (a centre is a mean of heads, or one: |c|^2 <= M, |x| |c| <= M) the F products of x c, each
+//    rounded at most twice and of a centre rounded to fp32, are off by less than (2F + 2) u M, |c|^2 / 2 by (F + 2) u M, so that a
+//    centre whose s exceeds the least by more than 2 (3F + 4) u M has the larger distance, in fp64 as well (whose own error is 2^-28
+//    of this).  Twice that is allowed for, and 1e-30 for what underflows.  One centre left: it is the nearest.  Where a value is not
+//    finite all centres are taken in fp64.
+//  * 2900 for walking the members' bits, word by word.  Here every head ranks itself among its cluster's and the sum goes along a
+//    list of members, four per word.
+//  * 1200 for barriers and the look for empty centres.
+// The numbering at the end ranks the centres by readlane in one wave; fp64 distances to the own centre, which the repair of empty
+// centres asks for, are taken there.  A pass takes 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
+// start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 16 problems of 72 heads, 16 centres and 25
+// coordinates; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
+// launching (up to 40 heads) takes what it did.  Where most passes need the 64-bit distances of all centres (problems of a few tight
+// clusters) it is level with the general kernel: 71.9 and 71.6 us for 8 of 256 heads, 16 centres, 25 coordinates.
+// Dynamic LDS (FastLayout): centres [k][FP] fp64, features [H][FP] fp32, centres [16 n][C32] fp32, masks, lists of members, ...
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kFastCentres = 64;
+typedef float km_f32x4 __attribute__((ext_vector_type(4)));
+template <int F>
+struct FastLayout {
+    // coordinates per lane group of a matrix operand: F and the place of |c|^2, the last of the fourth group
+    static constexpr int FP = (F + 3) / 4 * 4, G = (F / 4 + 1 + 3) / 4 * 4, C32 = 4 * G + 4;
+    static_assert(4 * G > F, "room for |c|^2");
+    int W, LS, tiles;                                        // mask words per centre, bytes of a list, tiles of 16 centres
+    size_t x, c32, mask, list, assign, dmin, count, label, flag, bytes;
+    __host__ __device__ FastLayout(int H, int k)
+    {
+        W = (H + 31) / 32;
+        LS = (H + 3) / 4 * 4;
+        tiles = (k + 15) / 16;
+        size_t at = sizeof(double) * (size_t)k * FP;
+        x = at;      at += sizeof(float) * (size_t)H * FP;
+        c32 = at;    at += sizeof(float) * (size_t)tiles * 16 * C32;
+        dmin = at;   at += sizeof(double) * (size_t)((H + 1) / 2 * 2);
+        list = at;   at += (size_t)k * LS;
+        mask = at;   at += sizeof(unsigned) * 2 * (size_t)k * W;
+        assign = at; at += sizeof(int) * (size_t)H;
+        count = at;  at += sizeof(int) * (size_t)k;
+        label = at;  at += sizeof(int) * (size_t)k;
+        flag = at;   at += sizeof(int) * 4;
+        bytes = at;
+    }
+};
+
+// op over the four lanes l, l ^ 16, l ^ 32, l ^ 48; all of them get it
+template <typename T, typename Op>
+__device__ __forceinline__ T over_groups(T x, Op op)
+{
+    static_assert(sizeof(T) == 4, "one register");
+    auto bits = [](T v) { unsigned u; __builtin_memcpy(&u, &v, 4); return u; };
+    auto value = [](unsigned u) { T v; __builtin_memcpy(&v, &u, 4); return v; };
+    const auto a = __builtin_amdgcn_permlane32_swap(bits(x), bits(x), false, false);
+    x = op(value(a[0]), value(a[1]));
+    const auto b = __builtin_amdgcn_permlane16_swap(bits(x), bits(x), false, false);
+    return op(value(b[0]), value(b[1]));
+}
+
+template <int F>
+__global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__restrict__ feat, int H, int k,
+                                                                 const int32_t *__restrict__ init_heads, int max_iter,
+                                                                 int32_t *__restrict__ h2c, int32_t *__restrict__ rep,
+                                                                 int32_t *__restrict__ ncl, int32_t *__restrict__ iters)
+{
+    extern __shared__ __attribute__((aligned(16))) char km_lds[];
+    constexpr int FP = FastLayout<F>::FP, G = FastLayout<F>::G, C32 = FastLayout<F>::C32;
+    const FastLayout<F> L(H, k);
+    const int W = L.W;
+    double *centre = reinterpret_cast<double *>(km_lds);
+    float *x_lds = reinterpret_cast<float *>(km_lds + L.x), *c32 = reinterpret_cast<float *>(km_lds + L.c32);
+    double *dmin = reinterpret_cast<double *>(km_lds + L.dmin);
+    unsigned char *list = reinterpret_cast<unsigned char *>(km_lds + L.list);
+    unsigned *masks = reinterpret_cast<unsigned *>(km_lds + L.mask);
+    int *assign = reinterpret_cast<int *>(km_lds + L.assign), *count = reinterpret_cast<int *>(km_lds + L.count);
+    int *label = reinterpret_cast<int *>(km_lds + L.label), *flag = reinterpret_cast<int *>(km_lds + L.flag);
+
+    const int b = blockIdx.x, tid = threadIdx.x, n_thr = blockDim.x, lane = tid & 63;
+    const float *Xg = feat + (size_t)b * H * F;
+    for (int j = tid; j < k; j += n_thr) label[j] = min(max(init_heads[(size_t)b * k + j], 0), H - 1);
+    for (int i0 = tid; i0 < H * FP; i0 += 8 * n_thr) {      // (eight requests in flight: one by one the load takes 2 us)
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = min(i0 + u * n_thr, H * FP - 1), h = i / FP, f = i - h * FP;
+            v[u] = Xg[h * F + min(f, F - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int i = i0 + u * n_thr;
+            if (i < H * FP) x_lds[i] = i % FP < F ? v[u] : 0.f;
+        }
+    }
+    for (int i = tid; i < 2 * k * W; i += n_thr) masks[i] = 0u;
+    for (int i = tid; i < k * L.LS / 4; i += n_thr) reinterpret_cast<unsigned *>(list)[i] = 0u;
+    for (int i = tid; i < L.tiles * 16 * C32; i += n_thr) c32[i] = 0.f;
+    if (tid < 4) flag[tid] = 0;
+    __syncthreads();
+
+    // wave -> 16 heads, a lane's own the one of its number in the group of 16; group g holds coordinates G g .. of it
+    const int my_h = tid / 64 * 16 + (lane & 15), g = lane >> 4;
+    const bool searching = tid / 64 * 16 < H, owner = my_h < H;      // (searching: this wave has heads)
+    float xr[G];
+    float x2 = 0.f;
+#pragma unroll
+    for (int t = 0; t < G; ++t) {
+        const int f = G * g + t;
+        xr[t] = f < FP ? x_lds[min(my_h, H - 1) * FP + min(f, FP - 1)] : 0.f;
+        x2 = __builtin_fmaf(xr[t], xr[t], x2);
+    }
+    x2 = over_groups(x2, [](float p, float q) { return p + q; });
+    if (g == 3) xr[G - 1] = -1.f;                            // times |c|^2 / 2
+    // the largest |x|^2 of all heads, as the bits of a float (a NaN is larger than all others)
+    if (g == 0 && owner) atomicMax(&flag[2], __float_as_int(x2) & 0x7fffffff);
+    for (int i = tid; i < k * FP; i += n_thr) {
+        const int j = i / FP, f = i - j * FP;
+        const float v = x_lds[label[j] * FP + f];
+        centre[i] = (double)v;
+        c32[j * C32 + f] = v;
+    }
+    int prev = -1;                                          // the head's centre in the pass before
+    __syncthreads();
+    constexpr float kU = 5.9604645e-8f;
+    const float slack = 4.f * (3 * F + 4) * kU * 1.01f * __int_as_float(flag[2]) + 1e-30f;
+
+    // fp64 distance of this thread's head to centre j, as the general kernel takes it
+    auto exact = [&](int j) {
+        const float4 *xp = reinterpret_cast<const float4 *>(x_lds + my_h * FP);
+        const double2 *cp = reinterpret_cast<const double2 *>(centre + j * FP);
+        double a = 0.0;
+#pragma unroll 4
+        for (int t = 0; t < FP / 4; ++t) {                  // (past F both are 0)
+            const float4 x = xp[t];
+            const double2 c0 = cp[2 * t], c1 = cp[2 * t + 1];
+            const double e0 = (double)x.x - c0.x, e1 = (double)x.y - c0.y, e2 = (double)x.z - c1.x, e3 = (double)x.w - c1.y;
+            const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2, s3 = e3 * e3;
+            a = a + s0;
+            a = a + s1;
+            a = a + s2;
+            a = a + s3;
+        }
+        return rank_distance(a, j);
+    };
+    int it = 0;
+    for (;;) {
+        unsigned *mask = masks + (it & 1) * (k * W);
+        int *moved_flag = flag + (it & 1);
+        ++it;
+        for (int j = tid; j < k; j += n_thr) count[j] = 0;
+        const int before = prev;
+        if (searching) {
+            // lane: centres 16 i + 4 g + 0 .. 3 of its head
+            float s[kFastCentres / 16][4], least = INFINITY;
+            bool sound = true;
+#pragma unroll
+            for (int i = 0; i < kFastCentres / 16; ++i) {
+                if (i < L.tiles) {
+                    float c[G], c2 = 0.f;
+#pragma unroll
+                    for (int t = 0; t < G; t += 4) {
+                        const float4 v = *reinterpret_cast<const float4 *>(c32 + (i * 16 + (lane & 15)) * C32 + G * g + t);
+                        c[t] = v.x; c[t + 1] = v.y; c[t + 2] = v.z; c[t + 3] = v.w;
+                    }
+#pragma unroll
+                    for (int t = 0; t < G; ++t) c2 = __builtin_fmaf(c[t], c[t], c2);
+                    c2 = over_groups(c2, [](float p, float q) { return p + q; });
+                    if (g == 3) c[G - 1] = 0.5f * c2;
+                    km_f32x4 acc = {0.f, 0.f, 0.f, 0.f};     // x c - |c|^2 / 2
+#pragma unroll
+                    for (int t = 0; t < G; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t], xr[t], acc, 0, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const bool there = i * 16 + 4 * g + e < k;
+                        sound = sound && (!there || fabsf(acc[e]) < INFINITY);       // false for NaN
+                        s[i][e] = there ? -acc[e] : INFINITY;
+                        least = fminf(least, s[i][e]);
+                    }
+                }
+            }
+            least = over_groups(least, [](float p, float q) { return fminf(p, q); });
+            const float limit = least + slack;
+            int near = sound && limit < INFINITY ? 0 : 1 << 16, best = kFastCentres;
+#pragma unroll
+            for (int i = kFastCentres / 16 - 1; i >= 0; --i) {
+                if (i < L.tiles) {
+#pragma unroll
+                    for (int e = 3; e >= 0; --e) {
+                        near += s[i][e] <= limit;
+                        best = s[i][e] <= limit ? i * 16 + 4 * g + e : best;
+                    }
+                }
+            }
+            near = over_groups(near, [](int p, int q) { return p + q; });
+            best = over_groups(best, [](int p, int q) { return min(p, q); });
+            if (__any(owner && near != 1)) {
+                double bd = HUGE_VAL;
+                int by = kFastCentres;                       // loses against any
+                if (owner && near != 1) {
+#pragma unroll 1
+                    for (int j = 4 * g; j < k; j += (j & 3) == 3 ? 13 : 1) {
+                        float sj = INFINITY;
+#pragma unroll
+                        for (int i = 0; i < kFastCentres / 16; ++i)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) sj = i < L.tiles && j == i * 16 + 4 * g + e ? s[i][e] : sj;
+                        if (near < 1 << 16 && !(sj <= limit)) continue;
+                        const double dj = exact(j);
+                        if (by == kFastCentres || dj < bd) {
+                            bd = dj;
+                            by = j;
+                        }
+                    }
+                }
+#pragma unroll
+                for (int o = 16; o < 64; o <<= 1) {
+                    const double od = __shfl_xor(bd, o);
+                    const int oj = __shfl_xor(by, o);
+                    const bool other = od < bd || (od == bd && oj < by);     // never NaN: all lanes of a head decide alike
+                    bd = other ? od : bd;
+                    by = other ? oj : by;
+                }
+                if (near != 1) best = by;
+            }
+            if (owner && g == 0) {
+                assign[my_h] = best;
+                atomicOr(&mask[best * W + (my_h >> 5)], 1u << (my_h & 31));
+                if (best != prev) *moved_flag = 1;
+            }
+            prev = best;
+        }
+        __syncthreads();
+
+        // members of a centre, and of those the ones below head h
+        auto members = [&](int j, int h, int &below) {
+            int n = 0;
+            below = 0;
+            for (int i0 = 0; i0 < W; i0 += 4) {
+                unsigned word[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) word[u] = mask[j * W + min(i0 + u, W - 1)];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u;
+                    const unsigned m = i < W ? word[u] : 0u, low = i < (h >> 5) ? ~0u : (i == (h >> 5) ? (1u << (h & 31)) - 1u : 0u);
+                    n += __popc(m);
+                    below += __popc(m & low);
+                }
+            }
+            return n;
+        };
+        // empty centres: as in the general kernel
+        int rank, ignored;
+        int n_mine = members(max(min(prev, k - 1), 0), my_h, rank);     // (lanes without a head: any centre)
+        const bool empty = lane < k && members(lane, 0, ignored) == 0;
+        int changed = *moved_flag;
+        if (__any(empty)) {                                 // the same in every wave
+            if (owner && g == 0) dmin[my_h] = exact(prev);
+            for (int j = tid; j < k; j += n_thr) label[j] = members(j, 0, ignored);
+            __syncthreads();
+            if (tid == 0) {
+                for (int j = 0; j < k; ++j) {
+                    if (label[j] != 0) continue;
+                    int pick = -1;
+                    double far = 0.0;
+                    for (int h = 0; h < H; ++h)
+                        if (label[assign[h]] >= 2 && dmin[h] > far) { far = dmin[h]; pick = h; }
+                    if (pick < 0) continue;
+                    const int from = assign[pick];
+                    label[from]--;
+                    mask[from * W + (pick >> 5)] &= ~(1u << (pick & 31));
+                    assign[pick] = j;
+                    label[j] = 1;
+                    mask[j * W + (pick >> 5)] |= 1u << (pick & 31);
+                    dmin[pick] = 0.0;
+                }
+            }
+            __syncthreads();
+            const int now = owner ? assign[my_h] : 0;
+            changed = __syncthreads_or(owner && now != before);
+            prev = now;
+            n_mine = members(prev, my_h, rank);
+        }
+        if (!changed || it >= max_iter) break;
+        // every head takes its place in the list of its cluster
+        if (owner && g == 0) {
+            list[prev * L.LS + rank] = (unsigned char)my_h;
+            count[prev] = n_mine;
+        }
+        __syncthreads();
+        // update: one thread per (centre, coordinate), members added in head order
+        for (int i = tid; i < k * F; i += n_thr) {
+            const int j = i / F, f = i - j * F, n = count[j];
+            const unsigned *row = reinterpret_cast<const unsigned *>(list + j * L.LS);
+            const int last = L.LS / 4 - 1;
+            double acc = 0.0;
+            for (int m = 0; m < n; m += 8) {                 // eight members requested at a time (whatever the list holds is a head)
+                const unsigned w0 = row[m / 4], w1 = row[min(m / 4 + 1, last)];
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = x_lds[(((u < 4 ? w0 : w1) >> (8 * (u & 3))) & 0xffu) * FP + f];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) acc = acc + (double)(m + u < n ? v[u] : -0.0f);      // (-0 changes no sum)
+            }
+            if (n != 0) {
+                const double mean = acc / (double)n;
+                centre[j * FP + f] = mean;
+                c32[j * C32 + f] = (float)mean;
+            }
+        }
+        unsigned *next = masks + (it & 1) * (k * W);
+        for (int i = tid; i < k * W; i += n_thr) next[i] = 0u;
+        if (tid == 0) flag[it & 1] = 0;
+        __syncthreads();
+    }
+
+    // canonical labels: clusters numbered by their lowest member, which represents them
+    if (tid < 64) {
+        const unsigned *mask = masks + ((it - 1) & 1) * (k * W);
+        int low = H;
+        for (int i0 = 0; i0 < W; i0 += 4) {
+            unsigned word[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) word[u] = mask[min(lane, k - 1) * W + min(i0 + u, W - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (i0 + u < W && word[u] != 0u) low = min(low, (i0 + u) * 32 + __ffs(word[u]) - 1);
+        }
+        if (lane >= k) low = H;
+        int rank = 0;
+        for (int i = 0; i < k; ++i) rank += __builtin_amdgcn_readlane(low, i) < low;
+        const int used = __popcll(__ballot(low < H));
+        if (lane < k) {
+            label[lane] = rank;
+            if (low < H) rep[(size_t)b * k + rank] = low;
+            if (lane >= used) rep[(size_t)b * k + lane] = -1;
+        }
+        if (lane == 0) {
+            ncl[b] = used;
+            if (iters) iters[b] = it;
+        }
+    }
+    __syncthreads();
+    for (int h = tid; h < H; h += n_thr) h2c[(size_t)b * H + h] = label[assign[h]];
+}
+
+// ---------------------------------------------------------------------------------------------------------
 // Clustering error of a given partition (Section 3.2): grid (B), 256 threads.  Means per (cluster, coordinate)
 // by one thread each (members in head order), distance of every head to its cluster's mean by one thread each,
 // then thread 0 adds the distances cluster by cluster, heads ascending: the order of the sequential statement.
@@ -435,11 +799,33 @@ bool assign_clusters_supported(int H, int F, int k)
 
 constexpr size_t kKmeansLds = 96 * 1024;     // most LDS of a workgroup (its CU has 160 KB)
 
+template <int F>
+static bool launch_fast(const float *feat, int B, int H, int k, const int32_t *init_heads, int max_iter, int32_t *h2c, int32_t *rep,
+                        int32_t *ncl, int32_t *iters, hipStream_t stream, int &status)
+{
+    const FastLayout<F> L(H, k);
+    if (L.bytes > 64 * 1024 || k > kFastCentres || H > 256) return false;
+    // threads: the waves of all heads, and enough for the update to be one round where that is not much more
+    int n_thr = (H + 15) / 16 * 64;
+    const int update = (k * F + 63) / 64 * 64;
+    if (n_thr < update) n_thr = update < 512 ? update : (n_thr < 512 ? 512 : n_thr);
+    status = (int)launch_kernel(kmeans_fast_kernel<F>, dim3(B), dim3(n_thr), L.bytes, stream, KernelEvents(), feat, H, k, init_heads,
+                                max_iter, h2c, rep, ncl, iters);
+    return true;
+}
+
 int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const int32_t *init_heads, int max_iter,
                            int32_t *h2c, int32_t *rep, int32_t *ncl, int32_t *iters, hipStream_t stream)
 {
     const KmeansLayout L = kmeans_layout(H, F, k);
     if (L.bytes > kKmeansLds) return (int)hipErrorInvalidConfiguration;
+    // features of 3 to 8 positions: never slower there (the comment at the kernel); others would each need a kernel of their own,
+    // and no prompt gives them
+    int status = 0;
+    auto fast = [&](auto *launch) { return launch(feat, B, H, k, init_heads, max_iter, h2c, rep, ncl, iters, stream, status); };
+    if ((F == 9 && fast(launch_fast<9>)) || (F == 16 && fast(launch_fast<16>)) || (F == 25 && fast(launch_fast<25>)) ||
+        (F == 36 && fast(launch_fast<36>)) || (F == 49 && fast(launch_fast<49>)) || (F == 64 && fast(launch_fast<64>)))
+        return status;
     if (L.bytes > 64 * 1024) {                              // the mask words of many centres over many heads
         static DeviceFlags lds_allowed;
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), kKmeansLds, lds_allowed);

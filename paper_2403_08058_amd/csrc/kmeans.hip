@@ -385,7 +385,7 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 //  * 1200 for barriers and the look for empty centres.
 // The numbering at the end ranks the centres by readlane in one wave; fp64 distances to the own centre, which the repair of empty
 // centres asks for, are taken there.  A pass takes 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
-// start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 16 problems of 72 heads, 16 centres and 25
+// start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 4 problems of 72 heads, 16 centres and 25
 // coordinates; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
 // launching (up to 40 heads) takes what it did.  Where most passes need the 64-bit distances of all centres (problems of a few tight
 // clusters) it is level with the general kernel: 71.9 and 71.6 us for 8 of 256 heads, 16 centres, 25 coordinates.

@@ -512,6 +512,7 @@ __global__ __launch_bounds__(kHeadDim) void combine_members_kernel(const float *
 // every cluster that h represents.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kFusedTokens = 12288;          // most tokens of a chunk (their scores in LDS, 48 KB)
+constexpr float kFusedDown = 0x1p-14f;       // times kFusedTokens weights of at most 1: less than 1
 constexpr int kFusedWaves = 8;               // (16 waves: 6.7 against 6.1 us for 32 heads in 8 clusters at 256 tokens; 4: level)
 template <int DT, bool IDENT, bool APPEND, int DS, int NW>
 __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__ q, const char *__restrict__ kc,
@@ -621,10 +622,11 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
     if (lane == 0) max_lds[w] = wave_m;
     __syncthreads();
     const float M = wave_max(lane < NW ? max_lds[lane] : -INFINITY);
+    const float ref = M == -INFINITY ? 0.f : M;              // scores that are all -inf weigh 0, another chunk's may not be
 
     // values
     // (exponentials relative to the chunk's maximum are weights and are summed up; the division comes last, which is one rounding
-    // less per token than probabilities that are normalised first)
+    // less per token than probabilities that are normalised first; kFusedDown, a power of two, keeps the sum below the largest value)
     float acc[VT::EPL], sum = 0.f;
 #pragma unroll
     for (int e = 0; e < VT::EPL; ++e) acc[e] = 0.f;
@@ -632,7 +634,7 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
     for (int it = 0; it < v_it; ++it) {
         const int r0 = (it * NW + w) * VT::BATCH;
         if (lane < VT::BATCH) {
-            const float p = r0 + lane < n ? expf(s_lds[r0 + lane] - M) : 0.f;
+            const float p = r0 + lane < n ? expf(s_lds[r0 + lane] - ref) * kFusedDown : 0.f;
             p_lds[w][(lane % VT::RPW) * kUnroll + lane / VT::RPW] = p;
             sum += p;
         }
@@ -662,7 +664,7 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
     if (APPEND) {
         if (has_new && w == 0 && vrg == 0) {
             const u32x4 nraw = *reinterpret_cast<const u32x4 *>(v_new + ((size_t)b * H + h) * VT::ROW_BYTES + v_off);
-            const float p = expf(s_lds[n] - M);
+            const float p = expf(s_lds[n] - ref) * kFusedDown;
             sum += lane == 0 ? p : 0.f;
             float f[VT::EPL];
             unpack(nraw, f);
@@ -703,6 +705,7 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
 // out = sum of the chunks' rows, each weighed by exp(its maximum - the largest), over the sum of exponentials.  grid (B*H), 128
 // threads; n_cp <= kHeadDim.
 constexpr int kFusedChunks = kHeadDim;
+constexpr float kChunksDown = 0x1p-7f;       // times kFusedChunks weights of at most 1: 1
 __global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *__restrict__ partial, const float2 *__restrict__ recs,
                                                                   int n_cp, float *__restrict__ out)
 {
@@ -717,7 +720,7 @@ __global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *_
     if (lane < n_cp) a = recs[orow * n_cp + lane];
     if (lane + 64 < n_cp) z = recs[orow * n_cp + lane + 64];
     const float M = wave_max(fmaxf(a.x, z.x));
-    const float wa = a.x == -INFINITY ? 0.f : expf(a.x - M), wz = z.x == -INFINITY ? 0.f : expf(z.x - M);
+    const float wa = a.x == -INFINITY ? 0.f : expf(a.x - M) * kChunksDown, wz = z.x == -INFINITY ? 0.f : expf(z.x - M) * kChunksDown;
     const float L = wave_sum(wa * a.y + wz * z.y);
     if (tid < 64) {
         weight[lane] = wa;

@@ -134,3 +134,22 @@ def test_large_scores_and_an_infinite_value(H, T):
     C.chai_dense_decode_attention(q, k, v, T, SCALE, out, ws)
     torch.cuda.synchronize()
     assert bool((out[:, :, 7] == float("inf")).all()) and bool(torch.isfinite(out[:, :, :7]).all()) and bool(torch.isfinite(out[:, :, 8:]).all())
+
+
+@pytest.mark.parametrize("dtype,H,T", [("bf16", 4, 100), ("f32", 4, 2000), ("bf16", 4, 12289), ("bf16", 300, 900)])
+def test_values_near_the_largest_and_chunks_without_weight(dtype, H, T):
+    """Sums of values that a float just holds stay finite, and keys that give -inf leave their tokens without weight, whole
+    chunks of them too."""
+    q, k, v = _tensors(1, H, H, T, T, dtype, T)
+    q[..., 0] = 1.0
+    k[:, :, : T // 2, 0] = -float("inf")
+    v[..., 5] = -2e38
+    ident = np.arange(H, dtype=np.int32)[None]
+    out = torch.full((1, H, 128), float("nan"), device="cuda")
+    C.chai_dense_decode_attention(q, k, v, T, SCALE, out, G.poisoned_workspace(1, H, H, T, 128, CODE[dtype]))
+    torch.cuda.synchronize()
+    ref = _reference(q, k, v, ident, ident, T)
+    # column 5 by itself: next to it the others would be nothing
+    _check(out[..., 5:6], ref[..., 5:6], dtype)
+    others = [c for c in range(128) if c != 5]
+    _check(out[..., others], ref[..., others], dtype)

@@ -964,6 +964,8 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
 //   from 384 on: 416 at 577 / 1777 26.2 / 23.0 and 65.2 / 62.1, 512 at 1777 78.4 / 73.1, 864 at 577 47.3 / 43.3.  Between, whole
 //   heads leave CUs with one workgroup waiting for those with two, thirds do not: 288 at 200 / 577 / 1777 / 4000 13.8 / 10.3, 24.4 /
 //   20.5, 57.4 / 55.7 and 107.5 / 118 whole, 13.1, 20.6, 47.7 and 96.3 in thirds.
+//   Chunks that LDS cannot hold are doubled in number (two launches / chunks of the most tokens / equal ones): 128 at 32768 342 /
+//   354 / 309, 256 at 13000 285 / 323 / 253, 384 at 13000 435 / 479 / 377, 104 at 25000 230 / 289 / 201.
 static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
 {
     const long long heads = (long long)B * H, bytes = (long long)T * row_bytes;
@@ -975,7 +977,7 @@ static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
     if (want > kFusedChunks) want = kFusedChunks;
     long long cp = (T + want - 1) / want;
     if (cp < 128) cp = T < 128 ? T : 128;
-    if (cp > kFusedTokens) cp = kFusedTokens;
+    for (; cp > kFusedTokens; cp = (T + want - 1) / want) want *= 2;         // equal chunks, whole rounds of them
     return (T + cp - 1) / cp <= kFusedChunks ? (int)cp : 0;
 }
 

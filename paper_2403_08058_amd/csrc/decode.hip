@@ -965,7 +965,9 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
 //   heads leave CUs with one workgroup waiting for those with two, thirds do not: 288 at 200 / 577 / 1777 / 4000 13.8 / 10.3, 24.4 /
 //   20.5, 57.4 / 55.7 and 107.5 / 118 whole, 13.1, 20.6, 47.7 and 96.3 in thirds.
 //   Chunks that LDS cannot hold are doubled in number (two launches / chunks of the most tokens / equal ones): 128 at 32768 342 /
-//   354 / 309, 256 at 13000 285 / 323 / 253, 384 at 13000 435 / 479 / 377, 104 at 25000 230 / 289 / 201.
+//   354 / 309, 256 at 13000 285 / 323 / 253, 384 at 13000 435 / 479 / 377, 104 at 25000 230 / 289 / 201.  Two per head leave CUs idle
+//   with 129 to 255 heads, sixths do not (two launches / halves / sixths): 130 at 16000 187 / 227 / 176, 144 196 / 230 / 183, 160
+//   220 / 237 / 192.
 static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
 {
     const long long heads = (long long)B * H, bytes = (long long)T * row_bytes;
@@ -974,6 +976,7 @@ static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
     if (k < H) return 0;
     *ds = 1;
     long long want = heads <= 256 ? 256 / heads : (heads < 384 && T >= 800 ? 3 : 1);
+    if (heads > 128 && heads < 256 && T > kFusedTokens) want = 6;
     if (want > kFusedChunks) want = kFusedChunks;
     long long cp = (T + want - 1) / want;
     if (cp < 128) cp = T < 128 ? T : 128;

@@ -97,6 +97,7 @@ def test_small_clustered_calls(dtype, B, H, kk, T):
     ("bf16", 2, 64, 513), ("bf16", 1, 129, 1), ("bf16", 3, 43, 300), ("bf16", 8, 32, 130), ("f32", 1, 256, 900),
     ("bf16", 1, 257, 799), ("bf16", 1, 257, 800), ("bf16", 1, 383, 801), ("bf16", 6, 64, 801), ("f32", 10, 50, 333),
     ("bf16", 1, 130, 12288), ("bf16", 1, 130, 12289),                  # the most tokens of a chunk
+    ("bf16", 1, 128, 24577), ("bf16", 1, 256, 12289),                  # chunks doubled in number
     ("bf16", 1, 1, 1600000),                                           # more than the chunks hold: two launches
 ])
 def test_dense_calls(dtype, B, H, T):

@@ -504,8 +504,8 @@ __global__ __launch_bounds__(kHeadDim) void combine_members_kernel(const float *
 // attention, where no score is shared, and for small clustered calls, whose two launches are all ramp (the members of a cluster
 // then score its keys each for itself, out of L2).  grid (n_cp, H * DS, B); DS = 2: two workgroups per head and chunk, each with
 // half of the columns of V.  The first values are requested before the keys; padding rows of a last batch are zeroed, not weighed.
-// With one chunk the row goes to `out`, otherwise the weighted sum over the chunk, relative to the chunk's maximum, goes to
-// `partial` and (maximum, sum of exponentials) to `recs`; combine_chunks_kernel puts them together.
+// With one chunk the row goes to `out`, otherwise the chunk's weighted mean goes to `partial` and (maximum, sum of exponentials
+// relative to it) to `recs`; combine_chunks_kernel puts them together.
 // What bounds it: small calls one chain of latencies (map, keys, barrier, exponentials, sums, 4 to 5 us of which a launch is half),
 // large ones HBM: 512 heads of 4000 tokens 163 us, 6.4 TB/s (178 us in two launches); 52 heads of 1777 14 us (18 us in three).
 // APPEND: as in the two-phase kernels; every head scores the new token's key for itself, and head h writes it to the cache of
@@ -513,9 +513,10 @@ __global__ __launch_bounds__(kHeadDim) void combine_members_kernel(const float *
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kFusedTokens = 12288;          // most tokens of a chunk (their scores in LDS, 48 KB)
 constexpr float kFusedDown = 0x1p-14f;       // times kFusedTokens weights of at most 1: less than 1
+constexpr float kFusedLarge = 0x1p120f;      // sums of a wave up to this add up to a finite one
 constexpr int kFusedWaves = 8;               // (16 waves: 6.7 against 6.1 us for 32 heads in 8 clusters at 256 tokens; 4: level)
 template <int DT, bool IDENT, bool APPEND, int DS, int NW>
-__global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__ q, const char *__restrict__ kc,
+__global__ __launch_bounds__(NW * 64, 4) void fused_kernel(const char *__restrict__ q, const char *__restrict__ kc,
                                                         const char *__restrict__ v, const int32_t *__restrict__ h2c,
                                                         const int32_t *__restrict__ rep, int H, int k, int T, int Tc_cap,
                                                         int T_cap, float scale, int cp, int n_cp, float *__restrict__ partial,
@@ -528,8 +529,9 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
     __shared__ float max_lds[NW], sum_lds[NW];
     __shared__ float p_lds[NW][VT::BATCH];
     __shared__ float acc_lds[NW][VT::COLS];
+    __shared__ int large_lds[NW];
     const int split = blockIdx.x, hy = blockIdx.y, b = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int h = hy / DS, dpart = hy % DS;
     const int t0 = split * cp, n_all = min(T, t0 + cp) - t0;
     const bool has_new = APPEND && split == n_cp - 1;
@@ -626,66 +628,84 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
 
     // values
     // (exponentials relative to the chunk's maximum are weights and are summed up; the division comes last, which is one rounding
-    // less per token than probabilities that are normalised first; kFusedDown, a power of two, keeps the sum below the largest value)
-    float acc[VT::EPL], sum = 0.f;
-#pragma unroll
-    for (int e = 0; e < VT::EPL; ++e) acc[e] = 0.f;
+    // less per token than probabilities that are normalised first.  Sums of many values near the largest float can exceed it where
+    // the quotient does not: these are taken again with smaller weights.  Smaller ones from the start would lose the low bits of
+    // products with values near the smallest float.)
     const int n_vb = (n + VT::BATCH - 1) / VT::BATCH, v_it = n_vb > w ? (n_vb - w + NW - 1) / NW : 0;
-    for (int it = 0; it < v_it; ++it) {
-        const int r0 = (it * NW + w) * VT::BATCH;
-        if (lane < VT::BATCH) {
-            const float p = r0 + lane < n ? expf(s_lds[r0 + lane] - ref) * kFusedDown : 0.f;
-            p_lds[w][(lane % VT::RPW) * kUnroll + lane / VT::RPW] = p;
-            sum += p;
+    float down = 1.f;
+    for (;;) {
+        float acc[VT::EPL], sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < VT::EPL; ++e) acc[e] = 0.f;
+        for (int it = 0; it < v_it; ++it) {
+            const int r0 = (it * NW + w) * VT::BATCH;
+            if (lane < VT::BATCH) {
+                const float p = r0 + lane < n ? expf(s_lds[r0 + lane] - ref) * down : 0.f;
+                p_lds[w][(lane % VT::RPW) * kUnroll + lane / VT::RPW] = p;
+                sum += p;
+            }
+            __builtin_amdgcn_wave_barrier();
+            float pv[kUnroll];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) pv[u] = p_lds[w][vrg * kUnroll + u];
+            __builtin_amdgcn_wave_barrier();
+            if (r0 + VT::BATCH > n) {
+#pragma unroll
+                for (int u = 0; u < kUnroll; ++u)
+                    if (r0 + vrg + u * VT::RPW >= n) vb[u] = u32x4{0u, 0u, 0u, 0u};
+            }
+            // (eight rows added up before they join the sum, in two chains: long chunks would else be a longer chain of roundings
+            // than short ones, and eight in one chain were up to 3 % further off for 32 heads at 256 tokens than the two launches)
+            float four[2][VT::EPL];
+#pragma unroll
+            for (int u = 0; u < kUnroll; ++u) {
+                float f[VT::EPL];
+                unpack(vb[u], f);
+#pragma unroll
+                for (int e = 0; e < VT::EPL; ++e) four[u & 1][e] = u < 2 ? pv[u] * f[e] : fmaf(pv[u], f[e], four[u & 1][e]);
+            }
+#pragma unroll
+            for (int e = 0; e < VT::EPL; ++e) acc[e] += four[0][e] + four[1][e];
+            if (it + 1 < v_it) request_v(it + 1);
         }
-        __builtin_amdgcn_wave_barrier();
-        float pv[kUnroll];
+        if (APPEND) {
+            if (has_new && w == 0 && vrg == 0) {
+                const u32x4 nraw = *reinterpret_cast<const u32x4 *>(v_new + ((size_t)b * H + h) * VT::ROW_BYTES + v_off);
+                const float p = expf(s_lds[n] - ref) * down;
+                sum += lane == 0 ? p : 0.f;
+                float f[VT::EPL];
+                unpack(nraw, f);
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) pv[u] = p_lds[w][vrg * kUnroll + u];
-        __builtin_amdgcn_wave_barrier();
-        if (r0 + VT::BATCH > n) {
-#pragma unroll
-            for (int u = 0; u < kUnroll; ++u)
-                if (r0 + vrg + u * VT::RPW >= n) vb[u] = u32x4{0u, 0u, 0u, 0u};
+                for (int e = 0; e < VT::EPL; ++e) acc[e] = fmaf(p, f[e], acc[e]);
+                *reinterpret_cast<u32x4 *>(const_cast<char *>(vbase) + ((unsigned int)n * VT::ROW_BYTES + v_off)) = nraw;
+            }
         }
-        // (eight rows added up before they join the sum, in two chains: long chunks would else be a longer chain of roundings than
-        // short ones, and eight in one chain were up to 3 % further off for 32 heads at 256 tokens than the two launches)
-        float four[2][VT::EPL];
+        bool large = false;                                  // (or not finite)
 #pragma unroll
-        for (int u = 0; u < kUnroll; ++u) {
-            float f[VT::EPL];
-            unpack(vb[u], f);
+        for (int e = 0; e < VT::EPL; ++e) {
 #pragma unroll
-            for (int e = 0; e < VT::EPL; ++e) four[u & 1][e] = u < 2 ? pv[u] * f[e] : fmaf(pv[u], f[e], four[u & 1][e]);
+            for (int o = VT::LPR; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+            large = large || !(fabsf(acc[e]) <= kFusedLarge);
         }
+        if (vrg == 0) {
 #pragma unroll
-        for (int e = 0; e < VT::EPL; ++e) acc[e] += four[0][e] + four[1][e];
-        if (it + 1 < v_it) request_v(it + 1);
-    }
-    if (APPEND) {
-        if (has_new && w == 0 && vrg == 0) {
-            const u32x4 nraw = *reinterpret_cast<const u32x4 *>(v_new + ((size_t)b * H + h) * VT::ROW_BYTES + v_off);
-            const float p = expf(s_lds[n] - ref) * kFusedDown;
-            sum += lane == 0 ? p : 0.f;
-            float f[VT::EPL];
-            unpack(nraw, f);
-#pragma unroll
-            for (int e = 0; e < VT::EPL; ++e) acc[e] = fmaf(p, f[e], acc[e]);
-            *reinterpret_cast<u32x4 *>(const_cast<char *>(vbase) + ((unsigned int)n * VT::ROW_BYTES + v_off)) = nraw;
+            for (int e = 0; e < VT::EPL; ++e) acc_lds[w][vcg * VT::EPL + e] = acc[e];
         }
-    }
+        sum = wave_sum(sum);
+        const bool wave_large = __any(large);
+        if (lane == 0) {
+            sum_lds[w] = sum;
+            large_lds[w] = wave_large;
+        }
+        __syncthreads();
+        int any_large = 0;
 #pragma unroll
-    for (int e = 0; e < VT::EPL; ++e) {
-#pragma unroll
-        for (int o = VT::LPR; o < 64; o <<= 1) acc[e] += __shfl_xor(acc[e], o);
+        for (int i = 0; i < NW; ++i) any_large |= large_lds[i];
+        if (__builtin_amdgcn_readfirstlane(any_large) == 0 || down != 1.f) break;            // the same in every wave
+        down = kFusedDown;
+        __syncthreads();                                     // the sums have been looked at
+        request_v(0);
     }
-    if (vrg == 0) {
-#pragma unroll
-        for (int e = 0; e < VT::EPL; ++e) acc_lds[w][vcg * VT::EPL + e] = acc[e];
-    }
-    sum = wave_sum(sum);
-    if (lane == 0) sum_lds[w] = sum;
-    __syncthreads();
     if (tid < VT::COLS) {
         float vals[NW], sums[NW];
 #pragma unroll
@@ -706,16 +726,15 @@ __global__ __launch_bounds__(NW * 64) void fused_kernel(const char *__restrict__
         const int col = dpart * VT::COLS + tid;
         if (n_cp == 1) out[orow * kHeadDim + col] = val / L;
         else {
-            partial[(orow * n_cp + split) * kHeadDim + col] = val;
-            if (tid == 0 && dpart == 0) recs[orow * n_cp + split] = make_float2(M, L);
+            partial[(orow * n_cp + split) * kHeadDim + col] = L == 0.f ? val : val / L;
+            if (tid == 0 && dpart == 0) recs[orow * n_cp + split] = make_float2(M, L / down);
         }
     }
 }
 
-// out = sum of the chunks' rows, each weighed by exp(its maximum - the largest), over the sum of exponentials.  grid (B*H), 128
+// out = mean of the chunks' rows, each weighed by its sum of exponentials times exp(its maximum - the largest).  grid (B*H), 128
 // threads; n_cp <= kHeadDim.
 constexpr int kFusedChunks = kHeadDim;
-constexpr float kChunksDown = 0x1p-7f;       // times kFusedChunks weights of at most 1: 1
 __global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *__restrict__ partial, const float2 *__restrict__ recs,
                                                                   int n_cp, float *__restrict__ out)
 {
@@ -730,11 +749,12 @@ __global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *_
     if (lane < n_cp) a = recs[orow * n_cp + lane];
     if (lane + 64 < n_cp) z = recs[orow * n_cp + lane + 64];
     const float M = wave_max(fmaxf(a.x, z.x));
-    const float wa = a.x == -INFINITY ? 0.f : expf(a.x - M) * kChunksDown, wz = z.x == -INFINITY ? 0.f : expf(z.x - M) * kChunksDown;
-    const float L = wave_sum(wa * a.y + wz * z.y);
+    // (a chunk whose scores are all -inf has the sum 0, one with NaN among them NaN)
+    const float wa = a.x == -INFINITY ? a.y : expf(a.x - M) * a.y, wz = z.x == -INFINITY ? z.y : expf(z.x - M) * z.y;
+    const float L = wave_sum(wa + wz);
     if (tid < 64) {
-        weight[lane] = wa;
-        weight[lane + 64] = wz;
+        weight[lane] = wa / L;
+        weight[lane + 64] = wz / L;
     }
     __syncthreads();
     float sum = 0.f;
@@ -746,7 +766,7 @@ __global__ __launch_bounds__(kHeadDim) void combine_chunks_kernel(const float *_
             for (int u = 0; u < 8; ++u) v[u] = p[(size_t)min(i + 8 + u, n_cp - 1) * kHeadDim];
         }
     }
-    out[orow * kHeadDim + tid] = sum / L;
+    out[orow * kHeadDim + tid] = sum;
 }
 
 struct Workspace {

@@ -154,3 +154,18 @@ def test_values_near_the_largest_and_chunks_without_weight(dtype, H, T):
     _check(out[..., 5:6], ref[..., 5:6], dtype)
     others = [c for c in range(128) if c != 5]
     _check(out[..., others], ref[..., others], dtype)
+
+
+@pytest.mark.parametrize("dtype,H,T", [("f32", 4, 256), ("bf16", 4, 300), ("f32", 4, 2000), ("bf16", 300, 900)])
+def test_values_near_the_smallest(dtype, H, T):
+    """Values of 2^-120, whose products with probabilities are denormal: a product of a weight and a value is off by 2^-150 at
+    most, the T of them by T 2^-150, next to a result of at least 2^-120 T^-1/2."""
+    q, k, v = _tensors(1, H, H, T, T, dtype, T)
+    v = (v.double() * 2.0 ** -120).to(v.dtype)
+    ident = np.arange(H, dtype=np.int32)[None]
+    out = torch.full((1, H, 128), float("nan"), device="cuda")
+    C.chai_dense_decode_attention(q, k, v, T, SCALE, out, G.poisoned_workspace(1, H, H, T, 128, CODE[dtype]))
+    torch.cuda.synchronize()
+    ref = _reference(q, k, v, ident, ident, T)
+    err = (out.double() - ref).abs().amax(-1) / ref.abs().amax(-1)
+    assert float(err.max()) < (1e-5 if dtype == "f32" else 2e-5) + T ** 1.5 * 2.0 ** -30, float(err.max())

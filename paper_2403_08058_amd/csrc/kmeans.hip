@@ -798,13 +798,14 @@ bool assign_clusters_supported(int H, int F, int k)
 }
 
 constexpr size_t kKmeansLds = 96 * 1024;     // most LDS of a workgroup (its CU has 160 KB)
+constexpr size_t kPlainLds = 63 * 1024;      // most dynamic LDS without leave: 64 KB with what the kernels have besides (256 bytes)
 
 template <int F>
 static bool launch_fast(const float *feat, int B, int H, int k, const int32_t *init_heads, int max_iter, int32_t *h2c, int32_t *rep,
                         int32_t *ncl, int32_t *iters, hipStream_t stream, int &status)
 {
     const FastLayout<F> L(H, k);
-    if (L.bytes > 64 * 1024 || k > kFastCentres || H > 256) return false;
+    if (L.bytes > kPlainLds || k > kFastCentres || H > 256) return false;
     // threads: the waves of all heads, and enough for the update to be one round where that is not much more
     int n_thr = (H + 15) / 16 * 64;
     const int update = (k * F + 63) / 64 * 64;
@@ -826,7 +827,7 @@ int launch_assign_clusters(const float *feat, int B, int H, int F, int k, const 
     if ((F == 9 && fast(launch_fast<9>)) || (F == 16 && fast(launch_fast<16>)) || (F == 25 && fast(launch_fast<25>)) ||
         (F == 36 && fast(launch_fast<36>)) || (F == 49 && fast(launch_fast<49>)) || (F == 64 && fast(launch_fast<64>)))
         return status;
-    if (L.bytes > 64 * 1024) {                              // the mask words of many centres over many heads
+    if (L.bytes > kPlainLds) {                              // the mask words of many centres over many heads
         static DeviceFlags lds_allowed;
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(&kmeans_kernel), kKmeansLds, lds_allowed);
         if (e != hipSuccess) return (int)e;

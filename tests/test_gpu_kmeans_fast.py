@@ -41,6 +41,16 @@ def test_edges_of_tiles(F, H, k):
     _same(feat, _starts(g, 3, H, k))
 
 
+# 64 512 bytes of LDS, the most that the quick kernel takes, in the first and the fourth; just above it, and up to 65 484, in the
+# others of 25 and 36 coordinates; the general kernel without leave for more (64 512), with it, and at 65 536
+@pytest.mark.parametrize("H,k,F", [(196, 64, 25), (212, 58, 25), (231, 52, 25), (225, 33, 36), (139, 64, 36), (254, 226, 16),
+                                   (96, 88, 55), (218, 203, 20)])
+def test_sizes_at_the_limit_of_lds(H, k, F):
+    print(f"[kmeans] F={F} H={H} k={k}", flush=True)
+    g = np.random.default_rng(H + k)
+    _same(g.random((2, H, F)).astype(np.float32), _starts(g, 2, H, k), passes=(1, 50))
+
+
 @pytest.mark.parametrize("H,k", [(32, 8), (72, 16), (100, 40)])
 @pytest.mark.parametrize("scale", [1e-42, 1e-30, 1e-22, 1e-12, 1.0, 1e12, 1e18, 3e19, 1e38])
 def test_features_of_every_magnitude(H, k, scale):

@@ -52,3 +52,30 @@ def test_projection_of_several_tiles_per_workgroup(B, H, kk, Tn, D, unused):
             assert np.all(kh[b, j, :pos0] == nine) and np.all(kh[b, j, pos0 + Tn:] == nine), "rows outside the block touched"
             for got, w, what in ((qh[b, r], wq[r], "q"), (kh[b, j, pos0:pos0 + Tn], wk[r], "k")):
                 check_rounded(got, (xs[b] @ w.t()).numpy(), (xs[b].abs() @ w.abs().t()).numpy(), f"{what} b={b} j={j}")
+
+
+def test_unused_slots_cost_next_to_nothing():
+    """8 slots in use of 8 and of 32 (as many as an XCD has workgroups, so that a workgroup that went by slot numbers would meet
+    one slot only): the same rows, in much the same time."""
+    B, H, Tn, D = 16, 32, 2043, 1024
+    rep8 = torch.stack([torch.randperm(H, generator=torch.Generator().manual_seed(b))[:8] for b in range(B)]).int()
+    x, w_q, w_k = (torch.randn(s, generator=torch.Generator("cuda").manual_seed(i), device="cuda").to(torch.bfloat16)
+                   for i, s in enumerate([(B, Tn, D), (H * 128, D), (H * 128, D)]))
+    took, got = {}, {}
+    for kk in (8, 32):
+        rep = torch.full((B, kk), -1, dtype=torch.int32)
+        rep[:, :8] = rep8
+        rep = rep.cuda()
+        q_out = torch.zeros((B, H, Tn, 128), dtype=torch.bfloat16, device="cuda")
+        kc = torch.zeros((B, kk, Tn, 128), dtype=torch.bfloat16, device="cuda")
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            C.chai_project_qk(x, w_q, w_k, rep, q_out, kc, 0)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        took[kk], got[kk] = sorted(times)[2], (q_out, kc)
+    assert torch.equal(got[8][0], got[32][0]) and torch.equal(got[8][1], got[32][1][:, :8]) and not bool(got[32][1][:, 8:].any())
+    assert took[32] < 1.8 * took[8], took                    # 3.3 times with workgroups that stand idle

@@ -1033,18 +1033,21 @@ __device__ __forceinline__ bool find_group(const int32_t *__restrict__ h2c, cons
 //
 // The groups of a row are found by every workgroup for itself (a launch for the work list would cost 5 us).  Workgroups are
 // numbered group by group, all rows of one before the next, the longest query tiles first: the XCDs get equal shares without
-// any of them knowing the other rows' groups.
+// any of them knowing the other rows' groups.  (by_group: all query tiles of a group before the next group.  The groups that the
+// rows do not have are all at the end then, and the others' tiles fill the CUs of all XCDs alike: 1 row x 64 heads in 2 clusters, 862
+// positions behind 3018 keys, 33 groups of seven tiles, 144 -> 104 us, 112 with the pre-pass.)
 // ---------------------------------------------------------------------------------------------------------
 template <bool IDENT>
 __global__ __launch_bounds__(256, 1) void prefill_direct_kernel(const char *__restrict__ q, const char *__restrict__ kc,
                                                                 const char *__restrict__ v, const int32_t *__restrict__ h2c,
                                                                 const int32_t *__restrict__ rep, int H, int k, int Tq, int q_start,
-                                                                int Tc_cap, int T_cap, int n_qt, int n_rows, int per_xcd,
+                                                                int Tc_cap, int T_cap, int n_qt, int n_rows, int per_xcd, int by_group,
                                                                 float scale, float *__restrict__ out)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
-    const int qt = n_qt - 1 - (int)(blockIdx.x / (kXcds * (unsigned)per_xcd));
-    const unsigned at = blockIdx.x % (kXcds * (unsigned)per_xcd);
+    const unsigned inner = by_group ? (unsigned)n_qt : kXcds * (unsigned)per_xcd, quot = blockIdx.x / inner, rest = blockIdx.x - quot * inner;
+    const int qt = n_qt - 1 - (int)(by_group ? rest : quot);
+    const unsigned at = by_group ? quot : rest;
     int gi = (int)(at / (unsigned)n_rows);
     const int b = (int)(at - (unsigned)gi * (unsigned)n_rows);
     int cluster = gi, n_mem = 1, rhead = gi, heads[kGroup] = {gi, gi};
@@ -1081,6 +1084,9 @@ size_t prefill_workspace_bytes(int B, int H, int k, int n_keys)
            round256((size_t)B * sizeof(int32_t)) + round256((size_t)B * H * kHeadDim * Tp * sizeof(_Float16));
 }
 
+// The most groups of a row that there can be: a cluster has half a group more than half its heads at most.
+static int direct_groups(int H, int k, bool identity) { return identity || (H + k) / kGroup > H ? H : (H + k) / kGroup; }
+
 // Which calls skip the pre-pass: those with few query tiles per head.  The pre-pass reads and writes all values once (two bytes each
 // way at 6.5 TB/s, and 3 us); converting them in the 128-row tiles costs every tile of 64 keys 0.3 us per group of two members and
 // 0.15 us per head alone, in each query tile again, where longer calls have 256-row tiles, which are a fifth faster per row.
@@ -1095,14 +1101,17 @@ size_t prefill_workspace_bytes(int B, int H, int k, int n_keys)
 // * clustered, more: three 4 x 72 in 16, 384 behind 0 / 1792 46 / 36 and 173 / 146; four 4 x 72, 507 behind 0 / 1792 63 / 52 and
 //   218 / 189, 16 x 72 in 16, 507 behind 0 / 400 208 / 204 and 330 / 341; five 16 x 32 in 8, 600 behind 0 / 800 135 / 124 and 277 /
 //   257; six (three whole wide tiles) 4 x 52, 700 behind 0 / 800 69 / 62 and 133 / 121, 4 x 72, 700 behind 200 / 800 112 / 109 and
-//   164 / 171; seven 12 x 52 in 4, 860 behind 0 / 200 239 / 219 and 302 / 276; eight 4 x 52, 1000 behind 0 / 800 96 / 90 and 173 /
-//   172, but 16 x 32, 1000 behind 0 225 / 232.
+//   164 / 171.  Each key tile behind costs seven query tiles seven conversions: 12 x 52 in 4, 860 behind 0 / 200 239 / 219 and 302 /
+//   276, but 3 x 72 in 8, 842 behind 1223 184 / 195, 9 x 52 in 8, 885 behind 555 270 / 296, 4 x 32 in 8, 872 behind 2090 164 / 189;
+//   eight 4 x 52, 1000 behind 0 96 / 90, but 6 x 52 in 4, 926 behind 0 119 / 125.  The lines from five tiles on lie where the two were
+//   level over a thousand calls of 8 to 128 heads in 2 to 32 clusters, 1 to 24 rows and 0 to 6000 keys behind, for each number of tiles;
+//   on either side of them one is up to 5 % ahead, and 12 % with seven or eight tiles.
 // * dense, more: while the tiles are one round of the chip (1 x 32, 1000 behind 0 / 800 30 / 26 and 46 / 41); beyond, three 6 x 52,
 //   300 behind 0 / 800 52 / 45 and 133 / 118, but just over one round 2 x 52, 384 behind 1792 / 4000 83 / 83 and 154 / 169, and on
 //   many heads 12 x 72, 384 behind 400 261 / 270; four 6 x 52, 400 behind 0 / 200 / 800 69 / 64, 91 / 89 and 150 / 155, 8 x 72, 400
 //   behind 0 112 / 115; five 4 x 52, 600 behind 0 / 200 72 / 67 and 90 / 92; six 2 x 52, 700 behind 0 44 / 39, 4 x 52, 733 behind 0
-//   77.8 / 78.5, 6 x 52 121 / 125;
-//   seven 4 x 52, 860 behind 0 108 / 102, 6 x 52 149 / 157; eight 4 x 52, 1000 behind 0 125 / 130.
+//   77.8 / 78.5, 6 x 52 121 / 125; seven 2 x 52, 869 behind 0 51 / 46, 2 x 96 85 / 89, 6 x 52 149 / 157; eight 4 x 52, 1000 behind 0
+//   125 / 130.
 static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool identity)
 {
     const long long heads = (long long)B * H, n_keys = (long long)q_start + Tq;
@@ -1113,14 +1122,17 @@ static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool ide
         if (n <= 2) return true;
         if (heads * n <= 256) return n <= 8;
         if (n == 3) return q_start <= 256 || (heads <= 600 && (heads * n > 512 || q_start <= 1024));
-        return n <= 7 && q_start <= 128 && heads <= (n == 4 ? 400 : (n == 5 ? 320 : (n == 6 ? 128 : 256)));
+        return n <= 7 && q_start <= 128 && heads <= (n == 4 ? 400 : (n == 5 ? 320 : (n == 6 ? 128 : 180)));
     }
     if (H > kPlanHeads || k > kPlanClusters) return false;  // (more than a workgroup looks through for its group)
     if (n_keys * (4700 - 79 * heads) > 3300000) return false;
-    if (n <= 3 || n == 5 || n == 7) return true;
-    const long long wide = (long long)(n / 2) * prefill_max_groups(H, k) * B;
-    if (n == 8) return wide <= 900 && q_start <= 256;
-    return n <= 6 && (q_start <= 128 || wide <= 420 || (wide <= 1300 && q_start <= 512));
+    if (n <= 3) return true;
+    const long long most = (long long)direct_groups(H, k, false) * B, wide = (long long)(n / 2) * prefill_max_groups(H, k) * B;
+    if (n == 4) return q_start <= 128 || wide <= 420 || (wide <= 1300 && q_start <= 512);
+    if (n == 5) return q_start <= 512 || most <= 420;
+    if (n == 6) return (q_start <= 128 && most <= 800) || most <= 110 || (most <= 180 && q_start <= 512);
+    if (n == 7) return most * (q_start + 400) <= 195000;
+    return n == 8 && most * (q_start + 100) <= 20000;
 }
 
 int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *h2c, const int32_t *rep, int B, int H,
@@ -1144,11 +1156,20 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[identity ? 1 : 0]);
         if (e != hipSuccess) return (int)e;
         const int n_qt = (Tq + 127) / 128;
-        const long long per_xcd = ((long long)max_groups * B + kXcds - 1) / kXcds, n_wg = kXcds * per_xcd * n_qt;
+        const long long groups = (long long)direct_groups(H, k, identity) * B, tiles = groups * n_qt;
+        long long per_xcd = ((long long)max_groups * B + kXcds - 1) / kXcds;
+        // One round of the chip, or nearly: no room for groups that cannot be, and where whole groups per XCD would still make two
+        // rounds on some, group by group.  Not where a second round can be of short chains only, which the longest are better not.
+        // (Beyond, the numbering with room was as fast on average, and up to 10 % either way.)
+        if (per_xcd * n_qt > kXcdCus && tiles <= (kXcds + 1) * kXcdCus) per_xcd = (groups + kXcds - 1) / kXcds;
+        const bool by_group = per_xcd * n_qt > kXcdCus && kXcdCus % n_qt != 0 &&
+                              (identity ? tiles <= kXcds * kXcdCus
+                                        : (q_start >= 256 ? tiles <= (kXcds + 1) * kXcdCus : (tiles <= kXcds * kXcdCus && n_qt < 7)));
+        const long long n_wg = kXcds * per_xcd * n_qt;
         if (n_wg > 0xffffff) return (int)hipErrorInvalidConfiguration;
         return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(256), lds_bytes, stream, ev,
                                   static_cast<const char *>(q), static_cast<const char *>(kc), static_cast<const char *>(v), h2c, rep,
-                                  H, k, Tq, q_start, Tc_cap, T_cap, n_qt, B, (int)per_xcd, scale, out);
+                                  H, k, Tq, q_start, Tc_cap, T_cap, n_qt, B, (int)per_xcd, by_group, scale, out);
     }
 
     const size_t tile_lds = (size_t)kHeadDim * (kKTile + 2) * sizeof(_Float16), plan_lds = (size_t)(H + 2 * k) * sizeof(int32_t);

@@ -455,7 +455,7 @@ struct OpSchedule {
 };
 
 // One query tile (NW waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
-// LDS: rings of BUFS tiles (2: at most two key tiles), a value tile with room for G members.
+// LDS: rings of BUFS tiles (2: one key tile only), a value tile with room for G members.
 // DIRECT: vsrc are the members' rows of the value cache itself (see prefill_direct_kernel).
 template <int NM, int U, int NW, int G, int BUFS, bool DIRECT = false>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
@@ -800,7 +800,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         __builtin_amdgcn_sched_barrier(0);
     } else {
         dma_v(0, 0);
-        if (n_tiles > 1) dma_k(1, 1);
+        if (BUFS > 2 && n_tiles > 1) dma_k(1, 1);
     }
     // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]; padding rows repeat the last one
 #pragma unroll
@@ -866,9 +866,8 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         auto dma0 = [&](auto ic) {                           // the next tiles' kDma (NM + 1) requests, early in this one
             const int i = decltype(ic)::value;
             if constexpr (DIRECT) value_work(raw, min(kt + 3, n_tiles - 1), b3n, ic, keys);
-            else if (BUFS == 2) {                            // two tiles at most: the second one's values, its keys are there
-                if (i < kDma * NM && kt + 1 < n_tiles) dma_v1(kt1, b3n, i < kDma ? 0 : 1, i % kDma);
-            } else if (i < kDma) dma_v1(kt1, b3n, 0, i);
+            else if (BUFS == 2) return;                      // one tile: nothing comes after it
+            else if (i < kDma) dma_v1(kt1, b3n, 0, i);
             else if (i < kDma * NM) dma_v1(kt1, b3n, 1, i - kDma);
             else if (i < kDma * (NM + 1)) dma_k1(kt2, b3nn, i - kDma * NM);
         };
@@ -1085,7 +1084,11 @@ size_t prefill_workspace_bytes(int B, int H, int k, int n_keys)
 }
 
 // The most groups of a row that there can be: a cluster has half a group more than half its heads at most.
-static int direct_groups(int H, int k, bool identity) { return identity || (H + k) / kGroup > H ? H : (H + k) / kGroup; }
+static int direct_groups(int H, int k, bool identity)
+{
+    static_assert(kGroup == 2, "half a group");
+    return identity || (H + k) / 2 > H ? H : (H + k) / 2;
+}
 
 // Which calls skip the pre-pass: those with few query tiles per head.  The pre-pass reads and writes all values once (two bytes each
 // way at 6.5 TB/s, and 3 us); converting them in the 128-row tiles costs every tile of 64 keys 0.3 us per group of two members and
@@ -1191,7 +1194,8 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     // and 30 x 32 (816 and 1440 tiles) 85 / 78 and 127 / 118, behind 128 101 / 93 and 154 / 142, behind 200 level, but 16 x 72
     // in 16 (1664 tiles) 143 / 143 and with 300 positions 152 / 157, 64 x 32 (3072) 233 / 251.  Six against three wide ones
     // only between 900 and 1450: 768 positions, 16 x 52 in 4 (1440) 282 / 268, 16 x 32 in 4 (960) 173 / 168, but 8 x 52 (720)
-    // 134 / 140, and 641 positions, 64 x 32 in 8 (4608) 576 / 594.  Seven: 769 positions 340 / 359.
+    // 134 / 140, and 641 positions, 64 x 32 in 8 (4608) 576 / 594.  Seven: 769 positions 340 / 359.  (Of three and five tiles what is
+    // left here is past the lines of prefill_is_direct, or of more heads or clusters than it takes: 1 x 260 in 4, 300 positions.)
     // Dense: up to 128 wide tiles the narrow ones are one round too, above 256 the wide ones fill the chip better (at 4096
     // 783 / 914 us).  Between, two narrow tiles share a CU one after the other, the longest with the shortest: the second
     // round starts with the 256-th longest, 128 * 256 / heads keys below the longest.  With 7 us for a start and 20 against 30

@@ -121,6 +121,13 @@ def run_clustered_layer(cfg: W.Config, x: W.LayerInputs, check_probs=True):
     ok, worst = rows_close(out.cpu().numpy(), out_o, RTOL[cfg.dtype])
     assert ok, f"clustered decode output off: worst err/allowed = {worst:.3g}"
     assert guards_intact(out_whole, (B, H, d), float("nan"))
+    # without the copy of the probabilities small calls, and those of as many clusters as heads, go to a kernel of their own
+    plain_whole, plain = guarded((B, H, d), torch.float32, float("nan"))
+    C.chai_decode_attention(q_dev, kc, v_dev, h2c_d, rep_d, T, cfg.scale, plain, poisoned_workspace(B, H, k, T, d, cfg.dtype))
+    torch.cuda.synchronize()
+    ok, worst_plain = rows_close(plain.cpu().numpy(), out_o, RTOL[cfg.dtype])
+    assert ok, f"clustered decode output without probabilities off: worst err/allowed = {worst_plain:.3g}"
+    assert guards_intact(plain_whole, (B, H, d), float("nan"))
     if check_probs:
         p = probs.cpu().numpy().astype(np.float64)
         used = rep_h >= 0

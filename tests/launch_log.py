@@ -40,7 +40,7 @@ void launches_clear() { seen.clear(); }
 
 _CHILD = """
 import ctypes, json, os
-S = ctypes.CDLL(os.environ["LD_PRELOAD"])
+S = ctypes.CDLL(os.environ["CHAI_STAND_IN"], mode=ctypes.RTLD_GLOBAL)        # found before the runtime, which comes with the library
 S.launches_count.restype = ctypes.c_size_t
 S.launches_name.restype = ctypes.c_char_p
 S.launches_name.argtypes = [ctypes.c_size_t]
@@ -64,7 +64,7 @@ def run(tmp_path, code):
     with open(src, "w") as f:
         f.write(_STAND_IN)
     subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", src, "-o", lib], check=True)
-    env = dict(os.environ, LD_PRELOAD=lib, CHAI_LIBRARY=build.LIB)
+    env = dict(os.environ, CHAI_STAND_IN=lib, CHAI_LIBRARY=build.LIB)
     done = subprocess.run([sys.executable, "-c", _CHILD + textwrap.dedent(code) + "\nprint(json.dumps(result))"], env=env,
                           capture_output=True, text=True)
     assert done.returncode == 0, done.stderr

@@ -43,9 +43,12 @@ def check_layer(cfg, layer, T, q, kfull, v, h2c_d, rep_d, kc, seed):
     ws = C.alloc_workspace(B, H, H, T, d, cfg.dtype)         # as bench.py sizes it
     ws.fill_(0xFF)
     C.chai_decode_attention(q, kc, v, h2c_d, rep_d, T, cfg.scale, out, ws, probs_out=probs)
+    # the call that leaves the probabilities out: a kernel of its own where every head is a cluster
+    plain = torch.empty_like(out)
+    C.chai_decode_attention(q, kc, v, h2c_d, rep_d, T, cfg.scale, plain, ws)
     torch.cuda.synchronize()
     h2c, rep = h2c_d.cpu().numpy(), rep_d.cpu().numpy()
-    assert bool(torch.isfinite(out).all())
+    assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(plain).all())
     used = torch.as_tensor(rep >= 0, device="cuda")
     psum = probs.sum(-1)
     assert float((psum[used] - 1).abs().max()) < 2e-5 and bool((probs[used] >= 0).all())
@@ -62,6 +65,8 @@ def check_layer(cfg, layer, T, q, kfull, v, h2c_d, rep_d, kc, seed):
         ref, p_ref = oracle_one_head(q_rep, k_rep, W.torch_to_host_bits(v[b, h]), T, cfg.scale)
         ok, ratio = G.rows_close(out[b, h].cpu().numpy()[None], ref[None], G.RTOL[cfg.dtype])
         assert ok, f"{cfg.name} layer {layer} (b={b}, h={h}): err/allowed {ratio:.3g}"
+        ok, ratio_plain = G.rows_close(plain[b, h].cpu().numpy()[None], ref[None], G.RTOL[cfg.dtype])
+        assert ok, f"{cfg.name} layer {layer} (b={b}, h={h}) without probabilities: err/allowed {ratio_plain:.3g}"
         assert np.abs(probs[b, c].cpu().numpy() - p_ref).max() <= G.PROB_ATOL
         worst = max(worst, ratio)
     return worst

@@ -45,6 +45,7 @@ def test_key_requests_are_older_than_the_waits_allow(kernels):
             n = int(re.search(r"vmcnt\((\d+)\)", lines[i]).group(1))
             seen, j = 0, i - 1
             while seen < n:
+                assert j >= 0, f"{name}: only {seen} requests before '{lines[i]}'"
                 ln = lines[j]
                 if ln.startswith(("buffer_load", "global_load")):
                     assert not ln.endswith("lds"), f"{name}: '{ln}' within the last {n} requests before '{lines[i]}'"

@@ -72,6 +72,8 @@ __device__ __forceinline__ void unroll(F &&f)
 //   16 x 16 x 32                                                               436
 //   stages of 64 steps in cache lines of 128 bytes instead of 32 in half lines 415 (1.78 GHz; 350 if all loads hit L2, 312 without)
 // and no difference: the order of the products, a fifth stage of 32.  Slower: the loads of a stage closer together (432, 457).
+// All 256 ordinary registers are taken as well, and 39 more are kept in scratch (80 bytes per lane), where a tile ends and the next
+// one's addresses are made; within a tile nothing is.
 //
 // One workgroup per CU takes several (batch row, token tile, slot) items one after the other.  Items are numbered slot first and
 // dealt to the XCDs in contiguous ranges: the slots of a token tile read the same activations and find them in L2.
@@ -130,15 +132,19 @@ __global__ __launch_bounds__(kJBlock, 1) void project_kernel(const char *__restr
     // 384..511 key rows of the weights); lane l's 16 bytes land in slot l%8 of row l/8, and piece p of row R belongs in
     // slot p ^ ((R >> 1) & 7): 16 consecutive rows read at one piece index touch 16 different 16-byte bank groups.
     const size_t row_bytes = (size_t)D * 2;
-    const unsigned piece16 = (unsigned)((lane & 7) ^ ((lane >> 4) + 4 * (w & 1))) * 16;
-    const int srow = 8 * w + (lane >> 3);
+    auto piece16 = [&](int l) { return (unsigned)((l & 7) ^ ((l >> 4) + 4 * (w & 1))) * 16; };
+    auto srow = [&](int l) { return 8 * w + (l >> 3); };
     unsigned xoff[8], woff[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) woff[i] = (unsigned)(srow + 32 * i) * (unsigned)row_bytes + piece16;
+    for (int i = 0; i < 4; ++i) woff[i] = (unsigned)(srow(lane) + 32 * i) * (unsigned)row_bytes + piece16(lane);
     const char *xb = nullptr, *wqb = nullptr, *wkb = nullptr;
     auto load_from = [&](const Item &it) __attribute__((always_inline)) {
+        int l = lane;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(l));                  // made here, too
+#endif
 #pragma unroll
-        for (int i = 0; i < 8; ++i) xoff[i] = (unsigned)min(srow + 32 * i, Tn - 1 - it.t0) * (unsigned)row_bytes + piece16;
+        for (int i = 0; i < 8; ++i) xoff[i] = (unsigned)min(srow(l) + 32 * i, Tn - 1 - it.t0) * (unsigned)row_bytes + piece16(l);
         xb = x + ((size_t)it.b * Tn + it.t0) * row_bytes;
         wqb = w_q + (size_t)it.head * kHeadDim * row_bytes;
         wkb = w_k + (size_t)it.head * kHeadDim * row_bytes;

@@ -193,8 +193,9 @@ def read_ceiling(layers, C, torch):
 
 
 def mfma_ceiling(data, C, torch):
-    """Rate of the matrix pipe alone (the library's probe kernel) on operands taken from the workload's own data,
-    in TFLOP/s: what the bf16 MFMAs reach on this device with these values when nothing else is in the way."""
+    """Rate of 32 x 32 x 16 bf16 products alone (the library's probe kernel) on operands taken from the workload's own
+    data, in TFLOP/s: what they reach on this device with these values when nothing else is in the way.  Products of
+    another shape may reach more."""
     hev = HipEvents()
     sink = torch.zeros((1,), dtype=torch.float32, device="cuda")
     recs = []
@@ -357,7 +358,7 @@ def prefill_main(args, cfg, torch, C, W):
                 "kernel_ms_by_clusters": {str(k): sum(v) / len(v) for k, v in sorted(kern.items())}}
         ceil_tf = mfma_ceiling(layers[-1].q, C, torch)
         roof["mfma_ceiling"] = {"TFLOPs": ceil_tf, "frac_of_peak": ceil_tf / 2500.0, "kernel_frac_of_ceiling": ach / ceil_tf,
-                                "how": "matrix pipe alone on the workload's query data (chai_mfma_rate_probe)"}
+                                "how": "32 x 32 x 16 products alone on the workload's query data (chai_mfma_rate_probe)"}
     else:
         ach = flops / (ms * 1e-3) / 1e12
         roof = {"bound": "mfma", "kernel": "whole call (V^T pre-pass, work list, prefill_kernel)", "achieved": ach,
@@ -570,7 +571,7 @@ def project_main(args, cfg, torch, C, W):
     ceil_tf = mfma_ceiling(layers[-1].kfull, C, torch)
     result["roofline"]["mfma_ceiling"] = {"TFLOPs": ceil_tf, "frac_of_peak": ceil_tf / 2500.0,
                                           "kernel_frac_of_ceiling": ach / ceil_tf,
-                                          "how": "matrix pipe alone on the workload's weight data (chai_mfma_rate_probe)"}
+                                          "how": "32 x 32 x 16 products alone on the workload's weight data (chai_mfma_rate_probe); the kernel's are 16 x 16 x 32"}
     if dense_ms is not None:
         result["dense_projection"] = {"ms_per_step": dense_ms, "TFLOPs": dense_flops / (dense_ms * 1e-3) / 1e12,
                                       "speedup_pruned_over_dense": dense_ms / ms,

@@ -213,7 +213,11 @@ size_t chai_decode_workspace_bytes(int B, int H, int k, int T, int d, int dtype)
  *       out[b][h][:] = sum_t p_c[t] * v_cache[b][h][t][:]
  * Long contexts are processed in token chunks whose partial softmax
  * statistics and partial outputs are merged exactly; the result is the
- * one-pass definition above up to fp32 rounding order.
+ * one-pass definition above up to fp32 rounding order.  Small calls, and
+ * those with as many clusters as heads, take both phases at once in another
+ * order of the same sums, unless probs_out is given: `out` agrees to
+ * rounding with and without it, not bit for bit.  With k = H every head's
+ * keys are read, whatever slots are in use: pass the number of clusters.
  *
  *   q               [B,H,d]           only representatives' rows are read
  *   k_compact       [B,k,Tc_cap,d]
@@ -262,7 +266,7 @@ int chai_decode_attention_static(const void *q, const void *k_compact, const voi
 
 /*
  * The two phases of chai_decode_attention as separate calls (same arguments,
- * same workspace, same results): chai_decode_scores computes the scaled
+ * same workspace, results equal to rounding): chai_decode_scores computes the scaled
  * scores of every cluster and their per-chunk softmax statistics into the
  * workspace (scores of Section 2, one per cluster as in Section 3.4);
  * chai_decode_values turns them into probabilities and applies them to every
@@ -271,7 +275,8 @@ int chai_decode_attention_static(const void *q, const void *k_compact, const voi
  * the types of the two calls may differ (dtype: of q and k_compact in the
  * first, of v_cache in the second).
  * Meant for callers that time or overlap the phases; chai_decode_attention
- * is exactly the two in sequence.
+ * with probs_out is exactly the two in sequence, and so it is without probs_out
+ * where it does not take both phases in one launch.
  */
 int chai_decode_scores(const void *q, const void *k_compact, const int32_t *rep_heads, int B, int H, int k,
                        int T, int Tc_cap, int d, int dtype, float scale, void *workspace,
@@ -397,8 +402,11 @@ int chai_decode_attention_q8_timed(const void *q, const uint8_t *k8, const float
 /*
  * Dense multi-head decode attention, the definition of Section 2
  * (A_h = softmax(q_h K_h^T / sqrt(d)), y = A_0 V_0 (+) A_1 V_1 ...): the
- * baseline clustered attention is compared against.  Runs the same kernels
- * with every head its own cluster and K read in place.
+ * baseline clustered attention is compared against, every head its own
+ * cluster and K read in place.  One kernel takes both phases (of contexts of
+ * up to 0.8 to 1.5 million tokens, by the number of heads), the one that small
+ * clustered calls and those with k = H go to; the results are those of
+ * chai_decode_attention with k = H, identity maps and no probs_out, bit for bit.
  *
  *   q [B,H,d]; k_cache, v_cache [B,H,T_cap,d]; out [B,H,d] fp32
  *   workspace: chai_decode_workspace_bytes(B,H,H,T,d,dtype) bytes.

@@ -2,7 +2,7 @@
  * chai_probe.h -- measurement aids of libchai.so.  NOT part of the method's boundary (that is chai.h): two kernels
  * that do no useful work and exist so that the benchmark can quote the library's kernels against what the device
  * at hand reaches with nothing in the way -- a bare streaming read (the practical ceiling of the HBM-bound decode
- * kernels) and the matrix pipe alone (the practical ceiling of the prefill and projection kernels).  Conventions
+ * kernels) and matrix products alone (of the shape that the prefill kernels use).  Conventions
  * (device pointers, streams, status codes) as in chai.h.
  */
 #ifndef CHAI_PROBE_H
@@ -32,7 +32,7 @@ int chai_stream_read_probe(const void *buf, size_t bytes, float *sink, void *str
                            void *stop_event);
 
 /*
- * Measurement aid, not a step of the method: the matrix pipe alone.  Every
+ * Measurement aid, not a step of the method: matrix products alone.  Every
  * wave of a chip-filling launch (two waves per SIMD) takes six bf16 operand
  * fragments from `buf` (device memory, at least 16 bytes, 16-byte aligned;
  * read modulo its length) and issues `rounds` rounds of eight independent
@@ -41,7 +41,10 @@ int chai_stream_read_probe(const void *buf, size_t bytes, float *sink, void *str
  * data of the workload at hand.  *flops (HOST pointer, may be NULL) receives
  * the floating-point operations of one launch; sink and the events as for
  * chai_stream_read_probe.  The benchmark quotes the prefill and projection
- * kernels against this rate next to the nominal peak.
+ * kernels against this rate next to the nominal peak.  It is the rate of these
+ * products and no bound on others: 16 x 16 x 32 ones, which the projection
+ * kernel for prompts uses, touch the accumulators half as often, need less
+ * energy and reach a sixth more on the same data.
  */
 int chai_mfma_rate_probe(const void *buf, size_t bytes, int rounds, float *sink, double *flops, void *stream,
                          void *start_event, void *stop_event);

@@ -267,7 +267,7 @@ def chai_project_qk(x, w_q, w_k, rep_heads, q_out, k_compact, pos0: int, stream=
 
 
 def chai_mfma_rate_probe(buf, rounds: int, sink, stream=None, start_event=None, stop_event=None) -> float:
-    """The matrix pipe alone on operands taken from `buf` (measurement aid); returns the flops of the launch."""
+    """32 x 32 x 16 products alone on operands taken from `buf` (measurement aid); returns the flops of the launch."""
     flops = ctypes.c_double(0.0)
     _check("chai_mfma_rate_probe",
            _lib.chai_mfma_rate_probe(_ptr(buf), buf.numel() * buf.element_size(), rounds, _ptr(sink), ctypes.byref(flops),
@@ -386,7 +386,7 @@ def chai_decode_step(q, k_new, v_new, k_compact, v_cache, head_to_cluster, rep_h
 
 def chai_decode_scores_timed(q, k_compact, rep_heads, T: int, scale: float, workspace, stream=None, start_event=None,
                              stop_event=None):
-    """First phase of chai_decode_attention: scores and chunk statistics of every cluster into the workspace.
+    """First phase of chai_decode_attention with probabilities: scores and chunk statistics of every cluster into the workspace.
     start_event / stop_event: raw hipEvent_t handles (ints) stamped with the kernel's begin and end, or None."""
     B, H, d = q.shape
     k, Tc_cap = k_compact.shape[1], k_compact.shape[2]
@@ -399,7 +399,7 @@ def chai_decode_scores_timed(q, k_compact, rep_heads, T: int, scale: float, work
 
 def chai_decode_values_timed(v_cache, head_to_cluster, rep_heads, T: int, out, workspace, probs_out=None, stream=None,
                              start_event=None, stop_event=None):
-    """Second phase of chai_decode_attention: probabilities from the workspace applied to every head's values."""
+    """Second phase of chai_decode_attention with probabilities: those in the workspace applied to every head's values."""
     B, H, T_cap, d = v_cache.shape
     k = rep_heads.shape[1]
     _check("chai_decode_values_timed",

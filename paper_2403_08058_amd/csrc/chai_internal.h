@@ -135,7 +135,7 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
                       int D, void *q_out, void *k_compact, int pos0, int Tc_cap, const KernelEvents &ev,
                       hipStream_t stream);
 
-// the matrix pipe alone: `rounds` rounds of 8 MFMAs per wave on operands taken from buf; flops of one launch
+// 32 x 32 x 16 products alone: `rounds` rounds of 8 of them per wave on operands taken from buf; flops of one launch
 int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, const KernelEvents &ev, hipStream_t stream);
 double mfma_probe_flops(int rounds);
 

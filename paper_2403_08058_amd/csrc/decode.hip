@@ -988,6 +988,12 @@ DecodePlan make_decode_plan(int B, int H, int k, int T, int row_bytes, bool shar
 //   354 / 309, 256 at 13000 285 / 323 / 253, 384 at 13000 435 / 479 / 377, 104 at 25000 230 / 289 / 201.  Two per head leave CUs idle
 //   with 129 to 255 heads, sixths do not (two launches / halves / sixths): 130 at 16000 187 / 227 / 176, 144 196 / 230 / 183, 160
 //   220 / 237 / 192.
+//   At some lengths the starts of the chunks meet on the same memory channels: 240 heads of 9274 tokens 187 / 221, 72 of 27858 175 /
+//   178 to 206, 96 of 18568 164 / 169 to 192, 144 of 4638 64 / 69 to 72 (0.4 % of calls drawn at random more than 2 % slower than in
+//   two launches).  Other chunk counts, or another start in each head, only move these lengths.
+// * Clustered calls with k = H are taken like dense ones, so that as many clusters as heads give the bits of dense attention.  With
+//   few slots in use, every head of a cluster then scores the same keys: 16 x 32 heads at 2048 tokens, 8 used, 64 / 70; 4 x 72 at
+//   2048, 16 used, 40 / 46.5; 15 x 72 at 272 21 / 33.6.  The caller who passes the number of clusters as k has them in two launches.
 static int fused_chunk(int B, int H, int k, int T, int row_bytes, int *ds)
 {
     const long long heads = (long long)B * H, bytes = (long long)T * row_bytes;

@@ -183,8 +183,8 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // What bounds it, two members, U = 2 (cycles of one wave per 64-key tile; the MFMAs alone are 96 x 32 = 3072): 4500 to
 // 4600 on a chip with free CUs -- the replayed body is 2 x 1940 (MFMA only 1536, + LDS reads 1570, + vector work 1700,
 // all of it 1940: issue slots), the 12 direct loads to LDS about 25 each, the barrier 40 to 150 -- and about 5000 with every
-// CU busy, at 1.8 to 1.9 GHz instead of 2.4: the chip lowers its clock on this data (the matrix pipe alone reaches 64 % of
-// its nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
+// CU busy, at 1.8 to 1.9 GHz instead of 2.4: the chip lowers its clock on this data (these products alone reach 64 % of
+// the nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
 // tile adds 11 us for its start, the diagonal that the four waves finish one after the other, and the output rows.
 // Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls timed in turn: 16 rows
 // x 2043 positions, 32 heads in 8 clusters 663 -> 616 us, dense 809 -> 780 us; 4 rows x 4000, 4 clusters 520 -> 467 us (with

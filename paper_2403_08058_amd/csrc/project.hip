@@ -595,7 +595,8 @@ __global__ __launch_bounds__(kJtBlock) void project_tile_kernel(const char *__re
         project_tile<2>(x, w_q, w_k, H, k, Tn, D, q_out, k_compact, pos0, Tc_cap, lds, slots, head, n_items, c0, item % 2 * 128);
 }
 
-// Measurement aid: the matrix pipe alone.  Every wave (two per SIMD on every CU) loads six operand fragments from
+// Measurement aid: 32 x 32 x 16 products alone, the prefill kernels' shape (16 x 16 x 32 ones, project_kernel's, reach a sixth
+// more on the same data: 2060 TFLOP/s where these reach 1790).  Every wave (two per SIMD on every CU) loads six operand fragments from
 // `buf` once and then issues rounds of eight independent v_mfma_f32_32x32x16_bf16 with nothing else in the loop.
 // The rate depends on the operand VALUES (switching activity moves the clocks), hence operands from the caller's
 // data rather than constants.

@@ -303,24 +303,27 @@ template <int T>
 struct AccTile;
 #if defined(__HIP_DEVICE_COMPILE__)
 #define CHAI_ACC_ZERO(r) asm volatile("v_accvgpr_write_b32 " r ", 0" ::: r)
-#define CHAI_ACC_SCALE(r)                                                                                              \
-    asm volatile("v_accvgpr_read_b32 %0, " r "\n\tv_mul_f32 %0, %1, %0\n\tv_accvgpr_write_b32 " r ", %0"               \
-                 : "=&v"(t)                                                                                            \
-                 : "v"(alpha)                                                                                          \
-                 : r)
+#define CHAI_ACC_SCALE(i, r)                                                                                           \
+    {                                                                                                                  \
+        float t;                                                                                                       \
+        asm volatile("v_accvgpr_read_b32 %0, " r "\n\tv_mul_f32 %0, %1, %0\n\tv_accvgpr_write_b32 " r ", %0"           \
+                     : "=&v"(t)                                                                                        \
+                     : "v"(by[i])                                                                                      \
+                     : r);                                                                                             \
+    }
 #define CHAI_ACC_READ(i, r) asm volatile("v_accvgpr_read_b32 %0, " r : "=v"(x[i]))
 #define CHAI_ACC_MFMA(range, ...)                                                                                      \
-    asm volatile("v_mfma_f32_32x32x16_f16 " range ", %0, %1, " range ::"v"(a), "v"(b) : __VA_ARGS__)
+    asm volatile("v_mfma_f32_32x32x16_f16 " range ", %0, %1, " range ::"v"(p), "v"(v) : __VA_ARGS__)
 #else
 #define CHAI_ACC_ZERO(r) (void)0
-#define CHAI_ACC_SCALE(r) (void)0
+#define CHAI_ACC_SCALE(i, r) (void)by
 #define CHAI_ACC_READ(i, r) x[i] = 0.f
 #define CHAI_ACC_MFMA(range, ...) (void)0
 #endif
 #define CHAI_ACC_TILE(T, range, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15)                   \
     template <>                                                                                                        \
     struct AccTile<T> {                                                                                                \
-        static __device__ __forceinline__ void mfma(const f16x8 &a, const f16x8 &b)                                    \
+        static __device__ __forceinline__ void mfma(const f16x8 &p, const f16x8 &v)                                    \
         {                                                                                                              \
             CHAI_ACC_MFMA(range, r0, r1, r2, r3, r4, r5, r6, r7, r8, r9, r10, r11, r12, r13, r14, r15);                 \
         }                                                                                                              \
@@ -331,21 +334,37 @@ struct AccTile;
             CHAI_ACC_ZERO(r8); CHAI_ACC_ZERO(r9); CHAI_ACC_ZERO(r10); CHAI_ACC_ZERO(r11);                               \
             CHAI_ACC_ZERO(r12); CHAI_ACC_ZERO(r13); CHAI_ACC_ZERO(r14); CHAI_ACC_ZERO(r15);                             \
         }                                                                                                              \
-        static __device__ __forceinline__ void scale(float alpha)                                                      \
+        static __device__ __forceinline__ void scale(const float (&by)[4], std::integral_constant<int, 0>)              \
         {                                                                                                              \
-            float t = alpha;                                                                                           \
-            (void)t;                                                                                                   \
-            CHAI_ACC_SCALE(r0); CHAI_ACC_SCALE(r1); CHAI_ACC_SCALE(r2); CHAI_ACC_SCALE(r3);                             \
-            CHAI_ACC_SCALE(r4); CHAI_ACC_SCALE(r5); CHAI_ACC_SCALE(r6); CHAI_ACC_SCALE(r7);                             \
-            CHAI_ACC_SCALE(r8); CHAI_ACC_SCALE(r9); CHAI_ACC_SCALE(r10); CHAI_ACC_SCALE(r11);                           \
-            CHAI_ACC_SCALE(r12); CHAI_ACC_SCALE(r13); CHAI_ACC_SCALE(r14); CHAI_ACC_SCALE(r15);                         \
+            CHAI_ACC_SCALE(0, r0); CHAI_ACC_SCALE(1, r1); CHAI_ACC_SCALE(2, r2); CHAI_ACC_SCALE(3, r3);                 \
         }                                                                                                              \
-        static __device__ __forceinline__ void read(float (&x)[16])                                                    \
+        static __device__ __forceinline__ void scale(const float (&by)[4], std::integral_constant<int, 1>)              \
+        {                                                                                                              \
+            CHAI_ACC_SCALE(0, r4); CHAI_ACC_SCALE(1, r5); CHAI_ACC_SCALE(2, r6); CHAI_ACC_SCALE(3, r7);                 \
+        }                                                                                                              \
+        static __device__ __forceinline__ void scale(const float (&by)[4], std::integral_constant<int, 2>)              \
+        {                                                                                                              \
+            CHAI_ACC_SCALE(0, r8); CHAI_ACC_SCALE(1, r9); CHAI_ACC_SCALE(2, r10); CHAI_ACC_SCALE(3, r11);               \
+        }                                                                                                              \
+        static __device__ __forceinline__ void scale(const float (&by)[4], std::integral_constant<int, 3>)              \
+        {                                                                                                              \
+            CHAI_ACC_SCALE(0, r12); CHAI_ACC_SCALE(1, r13); CHAI_ACC_SCALE(2, r14); CHAI_ACC_SCALE(3, r15);             \
+        }                                                                                                              \
+        static __device__ __forceinline__ void read(float (&x)[4], std::integral_constant<int, 0>)                      \
         {                                                                                                              \
             CHAI_ACC_READ(0, r0); CHAI_ACC_READ(1, r1); CHAI_ACC_READ(2, r2); CHAI_ACC_READ(3, r3);                     \
-            CHAI_ACC_READ(4, r4); CHAI_ACC_READ(5, r5); CHAI_ACC_READ(6, r6); CHAI_ACC_READ(7, r7);                     \
-            CHAI_ACC_READ(8, r8); CHAI_ACC_READ(9, r9); CHAI_ACC_READ(10, r10); CHAI_ACC_READ(11, r11);                 \
-            CHAI_ACC_READ(12, r12); CHAI_ACC_READ(13, r13); CHAI_ACC_READ(14, r14); CHAI_ACC_READ(15, r15);             \
+        }                                                                                                              \
+        static __device__ __forceinline__ void read(float (&x)[4], std::integral_constant<int, 1>)                      \
+        {                                                                                                              \
+            CHAI_ACC_READ(0, r4); CHAI_ACC_READ(1, r5); CHAI_ACC_READ(2, r6); CHAI_ACC_READ(3, r7);                     \
+        }                                                                                                              \
+        static __device__ __forceinline__ void read(float (&x)[4], std::integral_constant<int, 2>)                      \
+        {                                                                                                              \
+            CHAI_ACC_READ(0, r8); CHAI_ACC_READ(1, r9); CHAI_ACC_READ(2, r10); CHAI_ACC_READ(3, r11);                   \
+        }                                                                                                              \
+        static __device__ __forceinline__ void read(float (&x)[4], std::integral_constant<int, 3>)                      \
+        {                                                                                                              \
+            CHAI_ACC_READ(0, r12); CHAI_ACC_READ(1, r13); CHAI_ACC_READ(2, r14); CHAI_ACC_READ(3, r15);                 \
         }                                                                                                              \
     };
 CHAI_ACC_TILE(0, "a[0:15]", "a0", "a1", "a2", "a3", "a4", "a5", "a6", "a7", "a8", "a9", "a10", "a11", "a12", "a13", "a14", "a15")
@@ -462,7 +481,11 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
                                           int qt, int rhead, float scale2, float *__restrict__ out)
 {
-    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int lane = tid & 63;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(lane));                           // (what follows from it is worked out again for every query tile)
+#endif
     const int r = lane & 31, hl = lane >> 5;
     const int n_keys = q_start + Tq;
     const int i0 = (qt * NW + w) * (32 * U);                // first query row of this wave
@@ -523,6 +546,11 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         for (int g = 0; g < NM; ++g)
 #pragma unroll
             for (int i = 0; i < kDma; ++i) dma_v1(kt, buf, g, i);
+    };
+    auto store_row = [&](char *base, int n_rows, int off, int soff, float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), make_rsrc(base, n_rows * (kHeadDim * 4)), off, soff, 0);
+#endif
     };
     // every wave waits for its own requests (the compiler does not track loads that land in LDS), then a bare s_barrier:
     // __syncthreads() would add fences that the loads to LDS do not need
@@ -604,9 +632,23 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 
     // accumulators: tile (stream * NM + member) * 4 + 32-column block; zeroed at the end of the first block
     constexpr int kTiles = 4 * U * NM;
-    auto product = [&](auto t, const f16x8 &a, const f16x8 &b) {
-        AccTile<t.value>::mfma(a, b);
+    auto product = [&](auto t, const f16x8 &p, const f16x8 &v) {
+        AccTile<t.value>::mfma(p, v);
         if constexpr (NW == 8) acc_hold();
+    };
+    // Registers 4 q .. 4 q + 3 of an accumulator tile are rows 8 q + 4 hl .. + 3: of a value per row, which the row's two lanes
+    // hold, what these registers need.  (The lane is counted here: no register is kept for it through the loop.)
+    auto half_of_lane = []() {
+        int at = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(at));
+#endif
+        return at >> 5;
+    };
+    auto of_rows = [](float x, int half, auto quad, float (&y)[4]) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            y[e] = __int_as_float(__builtin_amdgcn_ds_bpermute(16 * half + 4 * (8 * decltype(quad)::value + e), __float_as_int(x)));
     };
     float m_run[U], l_run[U];
 #pragma unroll
@@ -634,7 +676,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             unroll<U>([&](auto uc) {
                 constexpr int u = uc.value;
                 if constexpr (u >= decltype(from)::value)
-                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, vf.h, pp.f[u][(p >> 2) & 1].h);
+                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, pp.f[u][(p >> 2) & 1].h, vf.h);
             });
         });
     };
@@ -715,7 +757,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                     if constexpr (NW == 8) acc_hold();
                 } else {
                     constexpr int p = NM == 2 ? s - s / 3 : s / 2;
-                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, fr[s].h, pp.f[u][(p >> 2) & 1].h);
+                    product(std::integral_constant<int, (u * NM + (p >> 3)) * 4 + (p & 3)>{}, pp.f[u][(p >> 2) & 1].h, fr[s].h);
                 }
             }
         };
@@ -785,7 +827,17 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         if (__builtin_expect(moved, 0)) {
             acc_settle();
             if (decltype(even)::value && kbase == 0) unroll<kTiles>([&](auto t) { AccTile<t.value>::zero(); });
-            else unroll<kTiles>([&](auto t) { AccTile<t.value>::scale(alpha[t.value / (4 * NM)]); });
+            else {
+                const int half = half_of_lane();
+                unroll<4 * U>([&](auto c) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    constexpr int u = c.value / 4;
+                    const std::integral_constant<int, c.value % 4> quad;
+                    float by[4];
+                    of_rows(alpha[u], half, quad, by);
+                    unroll<4 * NM>([&](auto t) { AccTile<u * 4 * NM + t.value>::scale(by, quad); });
+                });
+            }
         }
     };
 
@@ -907,33 +959,42 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         for (int kt = 0; kt < n_tiles; ++kt) tile(kt, raw_a);
     if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (G * kVBufBytes), 1);
 
-    if (n_hb > 0) {
-        acc_settle();
-        float inv[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float lo, hi;
-            both_halves(l_run[u], lo, hi);
-            inv[u] = 1.0f / (lo + hi);
-        }
-        unroll<kTiles>([&](auto tc) {
-            constexpr int t = tc.value, u = t / (4 * NM), g = t / 4 % NM, blk = t % 4;
-            const int my_i = i0 + u * 32 + r;
-            float x[16];
-            AccTile<t>::read(x);
-            if (my_i < Tq) {
-                float *orow = out + ((brow * H + heads[g]) * Tq + my_i) * kHeadDim + blk * 32 + hl * 4;
-#pragma unroll
-                for (int v4 = 0; v4 < 4; ++v4)
-                    *reinterpret_cast<float4 *>(orow + v4 * 8) = make_float4(x[v4 * 4] * inv[u], x[v4 * 4 + 1] * inv[u],
-                                                                            x[v4 * 4 + 2] * inv[u], x[v4 * 4 + 3] * inv[u]);
-            }
-        });
-    }
 #if defined(__HIP_DEVICE_COMPILE__)
     // the requests past the end have landed before LDS is given to another tile or workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
+    if (n_hb > 0) {
+        acc_settle();
+        float inv_sum[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float lo, hi;
+            both_halves(l_run[u], lo, hi);
+            inv_sum[u] = 1.0f / (lo + hi);
+        }
+        // Rows past the block's last lie beyond the end of the buffer that is written to.
+        const int n_rows = min(Tq - i0, 32 * U);
+        int at = hl * 4 * (kHeadDim * 4) + r * 4;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(at));                         // (not worked out, with all that is added to it, before the loop)
+#endif
+        char *row0[NM];
+#pragma unroll
+        for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((brow * H + heads[g]) * Tq + i0) * kHeadDim);
+        unroll<4 * U>([&](auto c) {
+            constexpr int u = c.value / 4, rows = 32 * u + 8 * (c.value % 4);
+            const std::integral_constant<int, c.value % 4> quad;
+            float inv[4];
+            of_rows(inv_sum[u], hl, quad, inv);
+            unroll<4 * NM>([&](auto t) {
+                float x[4];
+                AccTile<u * 4 * NM + t.value>::read(x, quad);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    store_row(row0[t.value / 4], n_rows, at + e * (kHeadDim * 4) + t.value % 4 * 128, rows * (kHeadDim * 4), x[e] * inv[e]);
+            });
+        });
+    }
 }
 
 template <int U, int NW, bool IDENT, int BUFS>

@@ -148,3 +148,13 @@ def test_bench_refuses_more_than_one_gpu():
     res = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                          timeout=120)
     assert res.returncode == 2 and "ONE GPU" in res.stderr and res.stdout.strip() == ""
+
+
+def test_package_names_are_looked_up_once():
+    """A name of the binding is an ordinary attribute of the package after its first use, and the same object."""
+    import paper_2403_08058_amd as C
+    for name in ("chai_version", "chai_decode_attention", "ChaiError", "CHAI_BF16"):
+        assert getattr(C, name) is getattr(C.binding, name)
+        assert vars(C)[name] is getattr(C.binding, name)
+    with pytest.raises(AttributeError):
+        C.no_such_entry_point

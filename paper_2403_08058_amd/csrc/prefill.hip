@@ -10,8 +10,12 @@
 //   D[32][32]: lane holds D[(v/4)*8 + hl*4 + v%4][r] for v = 0..15
 // Scores are computed transposed, S^T = K_tile Q^T (bf16 inputs): a lane then owns ONE query column and half of
 // the keys of the tile, so row maxima and sums are in-lane plus one exchange with lane l^32, and the tile of
-// probabilities is already in the B-operand layout of O^T += V^T P^T.  That second product runs in fp16 (P in
-// [0,256] keeps 11 bits instead of bf16's 8).  Its A operand needs 8 keys of one value column per lane, which a
+// probabilities is already in the A-operand layout of O += P V: a lane then has one column of 16 rows in an
+// accumulator tile, and what is per row (the factors of a rescaling, one over the row sum) comes from the lanes
+// that own the rows.  (As O^T += V^T P^T, the same registers in the other order, a lane had its own row's factors, but
+// every 16-byte store of an output row touched 64 cache lines, and the output rows of a query tile cost as much as four
+// tiles of keys.)  That second product runs in fp16 (P in [0,256] keeps 11 bits instead of bf16's 8).  Its B operand
+// needs 8 keys of one value column per lane, which a
 // row-major V cache cannot deliver, so a first kernel writes V^T once per call: fp16 (exact from bf16 inside
 // the fp16 range, |v| <= 65504), in blocks of 64 keys x 128 columns, keys permuted inside every group of 16 into
 // the order the probability registers have, zero beyond the last key.  The main kernel then stages K and V^T
@@ -63,6 +67,10 @@ __device__ __forceinline__ void both_halves(float x, float &lo, float &hi)
 // Position of key jj (0..15) inside its group of 16 in V^T: lane half hl of MFMA step s multiplies its
 // probability registers e = 0..7, which hold keys 16s + (e/4)*8 + hl*4 + e%4, with 8 consecutive halves.
 __device__ __forceinline__ int key_slot16(int r16) { return 8 * ((r16 & 7) >> 2) + 4 * (r16 >> 3) + (r16 & 3); }
+
+// Row of V^T that holds value column d: the columns 4 r + 0 .. 3 are row r of its four blocks of 32, so that a lane of the second
+// product has four neighbouring columns of an output row in its four accumulator tiles, and a store writes whole rows.
+__host__ __device__ constexpr int value_row(int d) { return (d & 3) * 32 + (d >> 2); }
 
 // ---------------------------------------------------------------------------------------------------------
 // Work list: the heads of every cluster, in ascending order, cut into groups of at most kGroup members.
@@ -116,8 +124,8 @@ __device__ __forceinline__ void plan_row(const int32_t *__restrict__ h2c, const 
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// Pre-pass, one launch.  V^T in blocks of 64 keys: vt[b][h][t/64][dd][16*((t%64)/16) + key_slot16(t%16)] =
-// fp16(V[b][h][t][dd]) for t < n_keys, 0 up to Tp (a multiple of 64).  A block is 16 KB of consecutive memory with whole
+// Pre-pass, one launch.  V^T in blocks of 64 keys: vt[b][h][t/64][value_row(d)][16*((t%64)/16) + key_slot16(t%16)] =
+// fp16(V[b][h][t][d]) for t < n_keys, 0 up to Tp (a multiple of 64).  A block is 16 KB of consecutive memory with whole
 // cache lines per value column, which is what the main kernels' direct loads to LDS ask for (rows of 64 bytes in blocks
 // of 32 keys made each of those loads touch twice as many lines).  grid (n_lists + Tp/64 * H * B), 256 threads; a 64 x 128 tile
 // goes through LDS.  The first n_lists workgroups make the work list, one per batch row (0 without maps; a launch of its
@@ -152,7 +160,7 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
             x.raw = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(vhead + (size_t)(t0 + jj) * (kHeadDim * 2) + c8 * 16));
         const int slot = 16 * (jj >> 4) + key_slot16(jj & 15);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) tile[c8 * 8 + e][slot] = (_Float16)(float)x.bf[e];
+        for (int e = 0; e < 8; ++e) tile[value_row(c8 * 8 + e)][slot] = (_Float16)(float)x.bf[e];
     }
     __syncthreads();
     _Float16 *dst = vt + (((size_t)b * H + h) * (Tp / kKTile) + block) * (size_t)(kHeadDim * kKTile);
@@ -185,7 +193,11 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // all of it 1940: issue slots), the 12 direct loads to LDS about 25 each, the barrier 40 to 150 -- and about 5000 with every
 // CU busy, at 1.8 to 1.9 GHz instead of 2.4: the chip lowers its clock on this data (these products alone reach 64 % of
 // the nominal rate on N(0,1) operands), so that fewer cycles there buy less time than on small launches.  Each query
-// tile adds 11 us for its start, the diagonal that the four waves finish one after the other, and the output rows.
+// tile adds its start (4600 cycles alone, 7000 on a full chip), the diagonal that the four waves finish one after the other, and
+// the output rows (64 stores of two whole rows per wave; 8500 cycles as 256 of two cache lines each, some 16 000 as 16 bytes of 64
+// lines).  The rows of a workgroup's first query tile are written while the second one's first tiles are on their way.
+// Both together, and queries fetched as whole lines (dma_q): 16 rows x 2043 positions, 32 heads in 8 clusters 598 -> 569 us, 4 x 507,
+// 72 in 16 51.9 -> 47.0, dense 8 x 2043, 32 heads 391 -> 372.
 // Against the kernel before (eight waves, one stream of 32 rows each, two waves per SIMD), whole calls timed in turn: 16 rows
 // x 2043 positions, 32 heads in 8 clusters 663 -> 616 us, dense 809 -> 780 us; 4 rows x 4000, 4 clusters 520 -> 467 us (with
 // the balanced numbering below); 1 row x 2043 97 -> 63 us; 256 positions behind 1792 keys, 4 rows x 52 heads 128 -> 93 us.
@@ -196,7 +208,7 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // LDS: rings of three K and three V^T tiles (64 keys).  While tile t is computed, K(t+2) and V(t+1) are loaded with
 // direct loads, requested in the first half of the tile; K runs ahead of V because the scores of a block are issued one
 // block before its softmax, and V lags because its products come one block after.  ONE barrier per tile.
-// Dense attention of thousands of heads over at most one tile of keys has rings of two (BUFS), 64 KB: it is all start and end,
+// Dense attention of thousands of heads over at most one tile of keys has rings of two (BUFS), 80 KB: it is all start and end,
 // and two workgroups on a CU cover each other's (64 x 72 heads of 24 keys 72 us, 79 us with one, values converted on the way).
 //
 // A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
@@ -205,7 +217,13 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 constexpr int kBufs = 3;
 constexpr size_t kKBufBytes = (size_t)kKTile * kHeadDim * 2;        // 64 rows of 256 B (16 pieces), swizzled
 constexpr size_t kVBufBytes = (size_t)kHeadDim * kKTile * 2;        // one member: 128 rows of 128 B (8 pieces), swizzled
-constexpr size_t prefill_lds_bytes(bool ident, int bufs) { return bufs * (kKBufBytes + (ident ? 1 : kGroup) * kVBufBytes); }
+// rows: query rows of a workgroup, which stand behind the first value tile at the start
+constexpr size_t prefill_lds_bytes(bool ident, int bufs, int rows)
+{
+    const size_t v_tile = (ident ? 1 : kGroup) * kVBufBytes, rings = bufs * (kKBufBytes + v_tile);
+    const size_t start = bufs * kKBufBytes + v_tile + (size_t)rows * (kHeadDim * 2);
+    return rings > start ? rings : start;
+}
 
 // ---------------------------------------------------------------------------------------------------------
 // Which query tiles of which (batch row, group) a workgroup takes.  The hardware deals consecutive workgroup ids
@@ -473,13 +491,22 @@ struct OpSchedule {
     }
 };
 
-// One query tile (NW waves x 32 U rows) of one group of NM members.  heads, vsrc: the members' heads and V^T; brow: batch row.
+// What is left to do for a query tile whose accumulators are complete
+template <int U>
+struct Finished {
+    int i0;                                                  // first query row of the wave
+    float inv[U];                                            // one over this lane's row sum
+};
+
+// Query tile number `pass` (of n_pass; NW waves x 32 U rows) of one group of NM members, and before it, once the tile's first
+// requests are on their way, the output rows of the tile before (done; those alone if pass is n_pass).  heads, vsrc: the members' heads and V^T; brow: batch row.
 // LDS: rings of BUFS tiles (2: one key tile only), a value tile with room for G members.
 // DIRECT: vsrc are the members' rows of the value cache itself (see prefill_direct_kernel).
 template <int NM, int U, int NW, int G, int BUFS, bool DIRECT = false>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
-                                          int qt, int rhead, float scale2, float *__restrict__ out)
+                                          int qt, int pass, int n_pass, int rhead, float scale2, float *__restrict__ out,
+                                          Finished<U> &done)
 {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63;
@@ -541,15 +568,29 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #pragma unroll
         for (int i = 0; i < kDma; ++i) dma_k1(kt, buf, i);
     };
+    // The wave's query rows, as whole cache lines: as fragments from memory every line is asked for by four instructions, and the
+    // rows of a workgroup are more than the first cache holds.  They stand where the value tiles after the first will.
+    char *const q_lds = v_lds + G * kVBufBytes + w * (32 * U * kHeadDim * 2);
+    auto dma_q = [&]() {
+        const auto q_rs = make_rsrc(q + (brow * H + rhead) * (size_t)Tq * (kHeadDim * 2));
+#pragma unroll
+        for (int i = 0; i < 8 * U; ++i) {
+            const int row = 4 * i + (lane >> 4);
+            load_to_lds(q_rs, (unsigned int)(min(i0 + row, Tq - 1) * (kHeadDim * 2) + (((lane & 15) ^ (row & 15)) << 4)), q_lds + i * 1024);
+        }
+    };
     auto dma_v = [&](int kt, int buf) {
 #pragma unroll
         for (int g = 0; g < NM; ++g)
 #pragma unroll
             for (int i = 0; i < kDma; ++i) dma_v1(kt, buf, g, i);
     };
-    auto store_row = [&](char *base, int n_rows, int off, int soff, float x) {
+    // (No scalar offset: with one the compiler takes it that the data registers may be written again in the very next
+    // instruction, and a 16-byte store then wrote what had come after it.)
+    auto store_row = [&](char *base, int n_rows, int off, const float (&x)[4]) {
 #if defined(__HIP_DEVICE_COMPILE__)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), make_rsrc(base, n_rows * (kHeadDim * 4)), off, soff, 0);
+        const u32x4 bits = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+        __builtin_amdgcn_raw_buffer_store_b128(bits, make_rsrc(base, n_rows * (kHeadDim * 4)), off, 0, 0);
 #endif
     };
     // every wave waits for its own requests (the compiler does not track loads that land in LDS), then a bare s_barrier:
@@ -561,7 +602,12 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         asm volatile("" ::: "memory");
 #endif
     };
-    // DIRECT: the values that this wave wrote are in LDS, and all but the youngest N requests have landed
+    auto landed = [&](auto n) {
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(decltype(n)::value) : "memory");
+#endif
+    };
+    // what this wave wrote to LDS is there, what it read has arrived, and all but the youngest N requests have landed
     auto written_barrier = [&](auto n) {
 #if defined(__HIP_DEVICE_COMPILE__)
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(decltype(n)::value) : "memory");
@@ -570,19 +616,19 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #endif
     };
     // fragments: this lane's row r of a 32-row block of K, fragment p = 8 * member + 4 * (16 keys) + 32-column block of V^T
-    const int k_sw = r & 15, v_sw = DIRECT ? ((r >> 1) & 7) ^ (r >> 4) : (r >> 1) & 7;
+    const int k_sw = r & 15, v_sw = (r >> 1) & 7;
     auto k_frag = [&](const char *kb, int ks) { return *reinterpret_cast<const u32x4 *>(kb + (((2 * ks + hl) ^ k_sw) << 4)); };
     auto v_frag = [&](const char *vb, int half, int p) {
-        const int j = p & 7, turn = DIRECT ? 2 * (j & 3) : 0;
+        const int j = p & 7;
         return *reinterpret_cast<const u32x4 *>(vb + (p >> 3) * kVBufBytes + (j & 3) * 32 * (kKTile * 2) +
-                                                (((4 * half + 2 * (j >> 2) + hl) ^ turn ^ v_sw) << 4));
+                                                (((4 * half + 2 * (j >> 2) + hl) ^ v_sw) << 4));
     };
 
     // DIRECT: this thread's piece of every value tile is 8 columns (8 co ..) of the 8 keys that an MFMA operand holds side by
     // side, piece v_p of a V^T row, of one member (NM = 2), or half of those keys (NM = 1).  Transposing is no work of its
-    // own: a conversion packs the same column of two keys.  Column d is row d ^ (d >> 3 & 1) of the tile in LDS, and piece p
-    // of row R sits in slot p ^ ((R >> 1) & 7) ^ (R >> 4): reads of 16 rows at one piece and writes of 16 threads' columns at
-    // one piece both touch 16 different 16-byte bank groups.
+    // own: a conversion packs the same column of two keys.  Row R of V^T is row R ^ (R >> 4 & 1) of the tile in LDS, and piece p
+    // of row R sits in slot p ^ ((R >> 1) & 7): reads of 16 rows at one piece and writes of 16 threads' columns at one piece (every
+    // other row of 32) both touch 16 different 16-byte bank groups.
     constexpr int kKeys = NM == 2 ? 8 : 4;
     const int co = lane & 15, v_rest = 4 * w + (lane >> 4);
     const int v_p = NM == 2 ? v_rest & 7 : v_rest >> 1, v_half = NM == 2 ? 0 : v_rest & 1;
@@ -610,11 +656,12 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                                      __uint_as_float(h == 0 ? x1 << 16 : x1 & 0xffff0000u));
         }
     };
-    const int v_slot = v_p ^ (co >> 1) ^ (4 * (co & 1));
-    char *const v_out = v_lds + (NM == 2 ? (w >> 1) * kVBufBytes : 0) + co * 8 * (kKTile * 2) + v_half * 8;
+    char *const v_out = v_lds + (NM == 2 ? (w >> 1) * kVBufBytes : 0) + co * 2 * (kKTile * 2) + ((v_p ^ (co & 7)) << 4) + v_half * 8;
+    const int v_flip[2] = {(co >> 3) * (kKTile * 2), (1 - (co >> 3)) * (kKTile * 2)};
     auto store_unit = [&](int buf, auto uc) {
-        constexpr int m = decltype(uc)::value >> 1, h = decltype(uc)::value & 1;
-        char *at = v_out + buf * (G * kVBufBytes) + ((2 * m + h) ^ (co & 1)) * (kKTile * 2) + ((v_slot ^ m) << 4);
+        constexpr int u = decltype(uc)::value;
+        static_assert(value_row(8 * 3 + u) == 2 * 3 + (u & 3) * 32 + (u >> 2), "rows of this thread's columns");
+        char *at = v_out + buf * (G * kVBufBytes) + (u & 3) * 32 * (kKTile * 2) + v_flip[u >> 2];
         if constexpr (NM == 2) *reinterpret_cast<u32x4 *>(at) = u32x4{packed[0], packed[1], packed[2], packed[3]};
         else *reinterpret_cast<uint2 *>(at) = make_uint2(packed[0], packed[1]);
     };
@@ -656,6 +703,36 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         m_run[u] = -INFINITY;
         l_run[u] = 0.f;
     }
+
+    // the output rows of the pass before, while this one's first tiles are on their way
+    auto write_rows = [&]() {
+        if (done.i0 >= Tq) return;                           // a padding wave
+        acc_settle();
+        // Rows past the block's last lie beyond the end of the buffer that is written to.
+        const int n_rows = min(Tq - done.i0, 32 * U);
+        int at = hl * 4 * (kHeadDim * 4) + r * 16;
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("" : "+v"(at));                         // (not worked out, with all that is added to it, before the loop)
+#endif
+        char *row0[NM];
+#pragma unroll
+        for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((brow * H + heads[g]) * Tq + done.i0) * kHeadDim);
+        unroll<4 * U>([&](auto c) {
+            constexpr int u = c.value / 4, rows = 32 * u + 8 * (c.value % 4);
+            const std::integral_constant<int, c.value % 4> quad;
+            float inv[4];
+            of_rows(done.inv[u], hl, quad, inv);
+            unroll<NM>([&](auto g) {
+                float x[4][4];                               // [32-column block][row]
+                unroll<4>([&](auto blk) { AccTile<(u * NM + g.value) * 4 + blk.value>::read(x[blk.value], quad); });
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float y[4] = {x[0][e] * inv[e], x[1][e] * inv[e], x[2][e] * inv[e], x[3][e] * inv[e]};
+                    store_row(row0[g.value], n_rows, at + rows * (kHeadDim * 4) + e * (kHeadDim * 4), y);
+                }
+            });
+        });
+    };
 
     struct Prob {
         Frag16 f[U][2];                                      // [stream][16 keys]
@@ -705,10 +782,9 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             if constexpr (e) k_at[ks] += k_step;
             return f;
         } else {
-            constexpr int p = NM == 2 ? s - s / 3 : s / 2, j = p & 7, piece = ((e ? 4 : 0) + 2 * (j >> 2)) ^ (DIRECT ? 2 * (j & 3) : 0);
+            constexpr int p = NM == 2 ? s - s / 3 : s / 2, j = p & 7, piece = (e ? 4 : 0) + 2 * (j >> 2);
             const u32x4 f = *reinterpret_cast<const u32x4 *>(v_at[piece / 2] + (p >> 3) * kVBufBytes + (j & 3) * 32 * (kKTile * 2));
-            if constexpr (e && DIRECT && p >= 8 * NM - 4) v_at[piece / 2] += v_step;
-            if constexpr (e && !DIRECT && p >= 8 * NM - 8 && (j & 3) == 3) {
+            if constexpr (e && p >= 8 * NM - 8 && (j & 3) == 3) {
                 v_at[piece / 2] += v_step;
                 v_at[piece / 2 - 2] += v_step;               // of the odd block
             }
@@ -842,27 +918,32 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     };
 
     Raw raw_a, raw_b;                                        // DIRECT: tiles 0, 2, .. and 1, 3, ..
-    dma_k(0, 0);
-    if constexpr (DIRECT) {
-        __builtin_amdgcn_sched_barrier(0);
-        unroll<kKeys>([&](auto i) { fetch_key(raw_a, 0, i); });
-        __builtin_amdgcn_sched_barrier(0);
-        dma_k(min(1, n_tiles - 1), 1);
-        unroll<kKeys>([&](auto i) { fetch_key(raw_b, min(1, n_tiles - 1), i); });
-        __builtin_amdgcn_sched_barrier(0);
-    } else {
-        dma_v(0, 0);
-        if (BUFS > 2 && n_tiles > 1) dma_k(1, 1);
+    if (pass < n_pass) {
+        dma_k(0, 0);
+        dma_q();
+        if constexpr (DIRECT) {
+            __builtin_amdgcn_sched_barrier(0);
+            unroll<kKeys>([&](auto i) { fetch_key(raw_a, 0, i); });
+            __builtin_amdgcn_sched_barrier(0);
+            dma_k(min(1, n_tiles - 1), 1);
+            unroll<kKeys>([&](auto i) { fetch_key(raw_b, min(1, n_tiles - 1), i); });
+            __builtin_amdgcn_sched_barrier(0);
+        } else {
+            dma_v(0, 0);
+            if (BUFS > 2 && n_tiles > 1) dma_k(1, 1);
+        }
     }
-    // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]; padding rows repeat the last one
+    if (pass > 0) write_rows();
+    if (pass == n_pass) return;
+    // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int i = min(i0 + u * 32 + r, Tq - 1);
-        q_abs[u] = q_start + i;
-        const char *qrow = q + ((brow * H + rhead) * Tq + i) * (kHeadDim * 2) + hl * 16;
+    for (int u = 0; u < U; ++u) q_abs[u] = q_start + min(i0 + u * 32 + r, Tq - 1);
+    auto read_q = [&]() {
 #pragma unroll
-        for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[u][ks].raw = *reinterpret_cast<const u32x4 *>(qrow + ks * 32);
-    }
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[u][ks].raw = k_frag(q_lds + (u * 32 + r) * (kHeadDim * 2), ks);
+    };                                                       // (before the barrier: behind it the other waves' values come here)
     if constexpr (DIRECT) {
         __builtin_amdgcn_sched_barrier(0);
         unroll<8>([&](auto u) {
@@ -872,9 +953,14 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         __builtin_amdgcn_sched_barrier(0);
         unroll<kKeys>([&](auto i) { fetch_key(raw_a, min(2, n_tiles - 1), i); });
         __builtin_amdgcn_sched_barrier(0);
-        written_barrier(std::integral_constant<int, 2 * kKeys>{});           // behind the keys of tiles 0 and 1: the values of 1 and 2
-    } else
-        tile_barrier();
+        landed(std::integral_constant<int, 2 * kKeys>{});                    // behind the keys of tiles 0 and 1: the values of 1 and 2
+        read_q();
+        written_barrier(std::integral_constant<int, 2 * kKeys>{});
+    } else {
+        landed(std::integral_constant<int, 0>{});
+        read_q();
+        written_barrier(std::integral_constant<int, 0>{});
+    }
     Score sa, sb;
     Prob pa, pb;
 #pragma unroll
@@ -898,7 +984,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         }
     }
     const char *kb_lane = k_lds + r * (kHeadDim * 2);
-    const char *vb_lane = v_lds + (DIRECT ? r ^ ((r >> 3) & 1) : r) * (kKTile * 2);
+    const char *vb_lane = v_lds + (DIRECT ? r ^ (r >> 4) : r) * (kKTile * 2);
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) k_at[ks] = kb_lane + (((2 * ks + hl) ^ k_sw) << 4);
 #pragma unroll
@@ -959,42 +1045,21 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         for (int kt = 0; kt < n_tiles; ++kt) tile(kt, raw_a);
     if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (G * kVBufBytes), 1);
 
+    done.i0 = i0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        float lo, hi;
+        both_halves(l_run[u], lo, hi);
+        done.inv[u] = 1.0f / (lo + hi);
+    }
 #if defined(__HIP_DEVICE_COMPILE__)
     // the requests past the end have landed before LDS is given to another tile or workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#endif
-    if (n_hb > 0) {
-        acc_settle();
-        float inv_sum[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float lo, hi;
-            both_halves(l_run[u], lo, hi);
-            inv_sum[u] = 1.0f / (lo + hi);
-        }
-        // Rows past the block's last lie beyond the end of the buffer that is written to.
-        const int n_rows = min(Tq - i0, 32 * U);
-        int at = hl * 4 * (kHeadDim * 4) + r * 4;
-#if defined(__HIP_DEVICE_COMPILE__)
-        asm volatile("" : "+v"(at));                         // (not worked out, with all that is added to it, before the loop)
-#endif
-        char *row0[NM];
-#pragma unroll
-        for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((brow * H + heads[g]) * Tq + i0) * kHeadDim);
-        unroll<4 * U>([&](auto c) {
-            constexpr int u = c.value / 4, rows = 32 * u + 8 * (c.value % 4);
-            const std::integral_constant<int, c.value % 4> quad;
-            float inv[4];
-            of_rows(inv_sum[u], hl, quad, inv);
-            unroll<4 * NM>([&](auto t) {
-                float x[4];
-                AccTile<u * 4 * NM + t.value>::read(x, quad);
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    store_row(row0[t.value / 4], n_rows, at + e * (kHeadDim * 4) + t.value % 4 * 128, rows * (kHeadDim * 4), x[e] * inv[e]);
-            });
-        });
+    if (pass + 1 < n_pass) {
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
     }
+#endif
 }
 
 template <int U, int NW, bool IDENT, int BUFS>
@@ -1024,16 +1089,19 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__
     for (int g = 0; g < kGroup; ++g)
         vsrc[g] = reinterpret_cast<const char *>(vt + ((size_t)b * H + heads[g]) * (size_t)kHeadDim * Tp);
     const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
-    for (int pass = 0; pass < work.n_pass; ++pass) {
-        const int qt = __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1);
-        if (pass != 0) __syncthreads();
-        if (!IDENT && n_mem == 2)
+    const int n_pass = __builtin_amdgcn_readfirstlane(work.n_pass);
+    Finished<U> done;
+    done.i0 = Tq;
+    if (!IDENT && n_mem == 2)
+        for (int pass = 0; pass <= n_pass; ++pass)
             prefill_tile<2, U, NW, kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start,
-                                                 qt, rhead, scale * kLog2e, out);
-        else
-            prefill_tile<1, U, NW, IDENT ? 1 : kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
-                                                             q_start, qt, rhead, scale * kLog2e, out);
-    }
+                                                 __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1), pass, n_pass, rhead,
+                                                 scale * kLog2e, out, done);
+    else
+        for (int pass = 0; pass <= n_pass; ++pass)
+            prefill_tile<1, U, NW, IDENT ? 1 : kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start,
+                                                             __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1), pass,
+                                                             n_pass, rhead, scale * kLog2e, out, done);
 }
 
 // Cluster, members and representative of group gi of row b (the groups of plan_row, in the same order), found by every workgroup
@@ -1122,12 +1190,15 @@ __global__ __launch_bounds__(256, 1) void prefill_direct_kernel(const char *__re
 #pragma unroll
     for (int g = 0; g < kGroup; ++g) vsrc[g] = v + ((size_t)b * H + heads[g]) * (size_t)T_cap * (kHeadDim * 2);
     const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
+    Finished<1> done;
     if (!IDENT && n_mem == 2)
-        prefill_tile<2, 1, 4, kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt,
-                                                   rhead, scale * kLog2e, out);
+        for (int pass = 0; pass <= 1; ++pass)
+            prefill_tile<2, 1, 4, kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt,
+                                                       pass, 1, rhead, scale * kLog2e, out, done);
     else
-        prefill_tile<1, 1, 4, IDENT ? 1 : kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
-                                                               q_start, qt, rhead, scale * kLog2e, out);
+        for (int pass = 0; pass <= 1; ++pass)
+            prefill_tile<1, 1, 4, IDENT ? 1 : kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
+                                                                   q_start, qt, pass, 1, rhead, scale * kLog2e, out, done);
 }
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
@@ -1215,7 +1286,7 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
 
     if (prefill_is_direct(B, H, k, Tq, q_start, identity)) {
         auto *kernel = identity ? prefill_direct_kernel<true> : prefill_direct_kernel<false>;
-        const size_t lds_bytes = prefill_lds_bytes(identity, kBufs);
+        const size_t lds_bytes = prefill_lds_bytes(identity, kBufs, 128);
         static DeviceFlags lds_allowed[2];
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[identity ? 1 : 0]);
         if (e != hipSuccess) return (int)e;
@@ -1278,13 +1349,11 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     auto *kernel = small ? (identity ? (brief ? prefill_kernel<1, 4, true, 2> : prefill_kernel<1, 4, true, kBufs>)
                                      : prefill_kernel<1, 4, false, kBufs>)
                          : (identity ? prefill_kernel<1, 8, true, kBufs> : prefill_kernel<2, 4, false, kBufs>);
-    const size_t lds_bytes = prefill_lds_bytes(identity, brief ? 2 : kBufs);
     const int threads = identity && !small ? 512 : 256, tile_rows = small ? 128 : 256;
-    if (!brief) {                                           // 64 KB need no leave
-        static DeviceFlags lds_allowed[4];
-        e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[(small ? 2 : 0) + (identity ? 1 : 0)]);
-        if (e != hipSuccess) return (int)e;
-    }
+    const size_t lds_bytes = prefill_lds_bytes(identity, brief ? 2 : kBufs, tile_rows);
+    static DeviceFlags lds_allowed[5];
+    e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[brief ? 4 : (small ? 2 : 0) + (identity ? 1 : 0)]);
+    if (e != hipSuccess) return (int)e;
     const int n_qt = (Tq + tile_rows - 1) / tile_rows;
     // the most workgroups an XCD can need (find_work): its pairs, the last of them as single tiles of padded groups
     const long long n_pairs = (n_qt + 1) / 2, most = (long long)max_groups * B * n_pairs / kXcds + 1;

@@ -280,8 +280,8 @@ __global__ __launch_bounds__(kJBlock, 1) void project_kernel(const char *__restr
 }
 
 // The (row, slot) pairs that `head` represents, as indexes into rep, ascending: all workgroups of a head agree which
-// tokens belong to which chunk.  Returns their number; B*k <= kJrMaxSlots.  Every thread of the workgroup calls it.
-constexpr int kJrMaxSlots = 1024;
+// tokens belong to which chunk.  Returns their number; B*k <= kJtMaxSlots.  Every thread of the workgroup calls it.
+constexpr int kJtMaxSlots = 1024;
 template <int WAVES>
 __device__ __forceinline__ int list_slots(const int32_t *__restrict__ rep, int n, int head, int H, int *slots, int *wave_slots)
 {
@@ -306,83 +306,245 @@ __device__ __forceinline__ int list_slots(const int32_t *__restrict__ rep, int n
 }
 
 // ---------------------------------------------------------------------------------------------------------
-// One token, or a few of one request: the call is bound by reading the representatives' weights once.  One workgroup
-// per (head, 16 output features), the 16 rows of a 16 x 16 x 32 MFMA tile: it looks up which (row, slot) pairs the head
-// represents -- none: done -- and gathers their tokens as the tile's columns.  The contraction is dealt to the 8 waves
-// in blocks of 64 elements (the workgroup walks 1 KB of every weight row per round), operands go from memory straight
-// into the MFMA registers -- a weight element is used by one workgroup only, LDS would be a detour --, kJrBlocks
-// blocks ahead, and the waves' fp32 sums are added in wave order.  grid (H * 16).
+// A few tokens per head (the new tokens of a batch, a short block of one request): the call is bound by reading the
+// representatives' weights once.  The 256 query and key columns of every head in use are cut into equal parts of 8 to 64 columns,
+// as many as fill the CUs evenly (a unit of 8 weight rows is one direct load to LDS: eight lines of 128 bytes), so that 8 heads in
+// use keep the chip as busy as 32.  Which heads those are, which part of which one it takes and where its tokens stand every wave
+// finds out for itself: there is no barrier before the sums.  The contraction is dealt to the 8 waves in blocks of 64 elements;
+// a wave streams its blocks of weights and of up to 32 tokens through a ring of its own in LDS and multiplies what has landed.  The
+// waves' fp32 sums are added in wave order.
+//
+// What bounds it: launch, map look-up and ramp (5 to 6 us together: 8 heads of width 1024 take 6 us), then HBM.  Against the kernels
+// before (at most 8 tokens: 16 weight rows per workgroup, fragments straight from memory, each of whose loads touched 16 half
+// lines; more: 64 x 64 or 64 x 128 tiles of two teams of waves with a barrier per stage, which leave half of the CUs without work
+// where 32 heads are in use), weights not in any cache: 16 rows x 1 token, 8 of 32 heads, D = 4096 20.1 -> 14.1 us (16.2 -> 11.3
+// with weights that the memory-side cache holds); 1 x 1 12.0 -> 7.3; 1 x 32 18.6 -> 10.1; 16 x 4 24.4 -> 20.9; 2 x 1, 16 of 72, D = 9216
+// 30.7 -> 23.0; 4 x 1 41.8 -> 30.4; 16 x 1, 8 of 52, D = 6656 29.0 -> 20.9.  Found on the way: fragments of the weights straight from
+// memory, whole parts of 32 columns 17.2 us for the first of these; parts of 32 columns whatever is in use 13.2 there, but 14.0
+// for 3 x 1, 8 of 52 (12.4) and 37.8 for 4 x 1, 16 of 72 (30.4).
 // ---------------------------------------------------------------------------------------------------------
-constexpr int kJrWaves = 8, kJrBlocks = 4;
-constexpr int kJrTokens = 8;                 // tokens of all rows up to which this kernel is the faster one
-constexpr int kJrParts = kJCol / 16;                 // workgroups per head
+constexpr int kJsWaves = 8, kJsUnits = kJCol / 8, kJsFewUnits = 4, kJsMaxUnits = 8;      // units of a head, and most of a workgroup
+constexpr int kJsWaveBytes = 20 * 1024;      // ring of a wave: two blocks at least
+constexpr int kJsPass = 32;                   // tokens that are multiplied at a time
+constexpr size_t kJsLdsBytes = (size_t)kJsWaves * kJsWaveBytes;
 
-__global__ __launch_bounds__(kJrWaves * 64) void project_rows_kernel(const char *__restrict__ x,
-                                                                     const char *__restrict__ w_q,
-                                                                     const char *__restrict__ w_k,
-                                                                     const int32_t *__restrict__ rep, int B, int H, int k,
-                                                                     int Tn, int D, char *__restrict__ q_out,
-                                                                     char *__restrict__ k_compact, int pos0, int Tc_cap)
+// or over the wave, in every lane
+__device__ __forceinline__ unsigned wave_or(unsigned x)
 {
-    __shared__ int slots[kJrMaxSlots];
-    __shared__ int wave_slots[kJrWaves];
-    __shared__ f32x4 red[kJrWaves][64];
+    unsigned z = x;
+    z |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)z, 0x111, 0xf, 0xf, true);       // row_shr 1, 2, 4, 8
+    z |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)z, 0x112, 0xf, 0xf, true);
+    z |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)z, 0x114, 0xf, 0xf, true);
+    z |= (unsigned)__builtin_amdgcn_update_dpp(0, (int)z, 0x118, 0xf, 0xf, true);       // lane 15 of a row has the row's
+    return (unsigned)(__builtin_amdgcn_readlane((int)z, 15) | __builtin_amdgcn_readlane((int)z, 31) |
+                      __builtin_amdgcn_readlane((int)z, 47) | __builtin_amdgcn_readlane((int)z, 63));
+}
+
+template <int MOST>
+__global__ __launch_bounds__(kJsWaves * 64) void project_stream_kernel(const char *__restrict__ x, const char *__restrict__ w_q,
+                                                                       const char *__restrict__ w_k,
+                                                                       const int32_t *__restrict__ rep, int B, int H, int k,
+                                                                       int Tn, int D, char *__restrict__ q_out,
+                                                                       char *__restrict__ k_compact, int pos0, int Tc_cap)
+{
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int head = blockIdx.x / kJrParts, f0 = blockIdx.x % kJrParts * 16;     // features 0..127 query, 128..255 key
+    const int n_pairs = B * k, n_windows = (H + 63) / 64;
 
-    const int n_items = list_slots<kJrWaves>(rep, B * k, head, H, slots, wave_slots) * Tn;   // tokens of this head
-    const size_t row_bytes = (size_t)D * 2;
-    const int col = lane & 15, g = lane >> 4;        // operand row (weights) or token (activations), 8-element group
-    const char *wsrc = (f0 < kHeadDim ? w_q : w_k) + ((size_t)head * kHeadDim + (f0 & (kHeadDim - 1)) + col) * row_bytes + g * 16;
-    const int n_blk = D / 64;
+    // The first map entries are requested before anything else.
+    constexpr int kAhead = MOST;
+    int first[kAhead];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) first[u] = u * 64 + lane < n_pairs ? rep[u * 64 + lane] : -1;
+    auto each_pair = [&](auto f) __attribute__((always_inline)) {    // f(pair, its head or less than 0), 64 pairs at a time
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (u * 64 < n_pairs) f(u * 64 + lane, min(first[u], H - 1));
+        for (int i0 = kAhead * 64; i0 < n_pairs; i0 += 64) f(i0 + lane, i0 + lane < n_pairs ? min(rep[i0 + lane], H - 1) : -1);
+    };
+    auto window = [&](int i) __attribute__((always_inline)) {        // which of the heads 64 i .. 64 i + 63 are in use
+        unsigned lo = 0u, hi = 0u;
+        each_pair([&](int, int r) {
+            const unsigned bit = (r >> 6) == i ? 1u << (r & 31) : 0u;
+            lo |= (r & 32) ? 0u : bit;
+            hi |= (r & 32) ? bit : 0u;
+        });
+        return (unsigned long long)wave_or(hi) << 32 | wave_or(lo);
+    };
+    unsigned use_lo = 0u, use_hi = 0u;               // lane i: window i
+    int used = 0;
+    for (int i = 0; i < n_windows; ++i) {
+        const unsigned long long heads = window(i);
+        used += __popcll(heads);
+        use_lo = lane == i ? (unsigned)heads : use_lo;
+        use_hi = lane == i ? (unsigned)(heads >> 32) : use_hi;
+    }
+    // Units of a workgroup: as many as make (rounds of the chip) * (units + what a workgroup costs besides) least.  More than 16
+    // tokens at a time leave room in the rings for six.
+    int units = 1;
+    unsigned long long least = ~0ull;
+    int parts = kJsUnits;
+    const int most = B * Tn <= 16 ? MOST : min(MOST, kJsMaxUnits - 2);
+    unroll<MOST>([&](auto i) {
+        constexpr int u = i.value + 1, p = (kJsUnits + u - 1) / u;
+        const unsigned long long cost = (unsigned long long)((used * p + kJCus - 1) / kJCus) * (unsigned)(u * D + 4096);
+        if (u <= most && used * p <= (int)gridDim.x && cost < least) {
+            least = cost;
+            units = u;
+            parts = p;
+        }
+    });
+    const int rank = (int)blockIdx.x / parts, part = (int)blockIdx.x - rank * parts;
+    if (rank >= used) return;                        // (all waves alike)
+    int head = 0;
+    for (int i = 0, before = 0; i < n_windows; ++i) {
+        unsigned long long heads = i >= 64 ? window(i)
+                                           : (unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)use_hi, i) << 32 |
+                                                 (unsigned)__builtin_amdgcn_readlane((int)use_lo, i);
+        if (before + __popcll(heads) > rank) {
+            for (; before < rank; ++before) heads &= heads - 1ull;
+            head = i * 64 + __ffsll((long long)heads) - 1;
+            break;
+        }
+        before += __popcll(heads);
+    }
+    head = __builtin_amdgcn_readfirstlane(head);
+    // Pairs of this head, ascending: numbers p0 .. p0 + kJsPass - 1 of them to lanes 0 .. of `listed`; returns how many there are
+    int listed = 0;
+    auto list_pairs = [&](int p0) __attribute__((always_inline)) {
+        int n = -p0;
+        each_pair([&](int pair, int r) {
+            const unsigned long long votes = __ballot(r == head);
+            const int at = n + __popcll(votes & ((1ull << lane) - 1ull));
+            const int sent = __builtin_amdgcn_ds_permute(r == head && at >= 0 && at < kJsPass ? at * 4 : 63 * 4, pair);
+            const int more = n + __popcll(votes);
+            if (lane >= n && lane < more) listed = sent;
+            n = more;
+        });
+        return __builtin_amdgcn_readfirstlane(n) + p0;
+    };
+    const int n_items = list_pairs(0) * Tn;          // tokens of this head
 
-    for (int c0 = 0; c0 < n_items; c0 += 16) {
-        const int item = c0 + col, it = min(item, n_items - 1);      // columns past the end repeat the last token, unused
-        const int sl = slots[it / Tn], tok = it % Tn;
-        const char *xsrc = x + ((size_t)(sl / k) * Tn + tok) * row_bytes + g * 16;
-        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int col = lane & 15, g = lane >> 4, r8 = lane >> 3;
+    const unsigned int row_bytes = (unsigned int)D * 2u;
+    const int f0 = part * units * 8, n_units = min(units, kJsUnits - part * units);      // features 0..127 query, 128..255 key
+    const int n_mine = (D / 64 - w + kJsWaves - 1) / kJsWaves;                   // blocks of this wave: w, w + 8, ..
+    char *const ring = lds + w * kJsWaveBytes;
+    // piece p of row r of eight lands in slot p ^ (r >> 1), with 4 on top in every other group of eight rows: 16 rows read at one
+    // piece touch 16 different 16-byte bank groups
+    const int piece[2] = {((lane & 7) ^ (r8 >> 1)) * 16, ((lane & 7) ^ (4 + (r8 >> 1))) * 16};
+    unsigned int woff[MOST];
+#pragma unroll
+    for (int i = 0; i < MOST; ++i) {
+        const int f = min(f0 + 8 * i, kJCol - 8);    // (a unit is of queries or of keys)
+        woff[i] = (unsigned int)((f & (kHeadDim - 1)) + r8) * row_bytes + piece[i & 1];
+    }
+#if defined(__HIP_DEVICE_COMPILE__)
+    const size_t head_at = (size_t)head * kHeadDim * row_bytes;
+    const auto q_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_q + head_at), 0, -1, 0x00020000);
+    const auto k_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(w_k + head_at), 0, -1, 0x00020000);
+    const auto x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x), 0, -1, 0x00020000);
+#endif
 
-        // blocks w, w + 8, ... of 64 elements; a wave's surplus requests re-read the last block and are not used
-        struct Block {
-            Frag a[2], b[2];
+    // 8 XT tokens c0 .. with U units
+    auto run = [&](int c0, auto u_, auto xt_) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_)::value, XT = decltype(xt_)::value, NB = (U + 1) / 2, TT = (XT + 1) / 2;
+        constexpr int kLoads = U + XT, kBytes = kLoads * 1024, R = kJsWaveBytes / kBytes < 8 ? kJsWaveBytes / kBytes : 8;
+        static_assert(R >= 2 && kJsWaves * NB * TT * 1024 <= kJsWaves * kJsWaveBytes, "a block ahead; the sums fit");
+        unsigned int xoff[XT];
+#pragma unroll
+        for (int i = 0; i < XT; ++i) {
+            const int it = min(c0 + 8 * i + r8, n_items - 1);        // tokens past the end repeat the last one, unused
+            xoff[i] = (unsigned int)((__shfl(listed, it / Tn - c0 / Tn) / k) * Tn + it % Tn) * row_bytes + piece[i & 1];
+        }
+        auto fetch = [&](int s, int at) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            const unsigned int off = (unsigned int)(w + s * kJsWaves) * 128u;
+            auto load = [&](__amdgpu_buffer_rsrc_t rs, unsigned int from, int i) {
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (__attribute__((address_space(3))) void *)(ring + at * kBytes + i * 1024), 16,
+                                                         (int)from, 0, 0, 0);
+            };
+#pragma unroll
+            for (int i = 0; i < U; ++i) load(f0 + 8 * i < kHeadDim ? q_rs : k_rs, woff[i] + off, i);
+#pragma unroll
+            for (int i = 0; i < XT; ++i) load(x_rs, xoff[i] + off, U + i);
+#endif
         };
-        auto request = [&](Block &bl, int blk) {
-            const size_t at = (size_t)min(blk, n_blk - 1) * 128;
+        // all requests but those of the `younger` last blocks have landed
+        auto landed = [&](int younger) {
+#if defined(__HIP_DEVICE_COMPILE__)
+            if (younger >= R - 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((R - 1) * kLoads) : "memory");
+            else
+                unroll<R - 1>([&](auto m) {
+                    if (younger == m.value) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(m.value * kLoads) : "memory");
+                });
+#endif
+        };
+        f32x4 acc[NB][TT];
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < R - 1; ++s)
+            if (s < n_mine) fetch(s, s);
+        int at = 0;
+        for (int s = 0; s < n_mine; ++s) {
+            if (s + R - 1 < n_mine) fetch(s + R - 1, at == 0 ? R - 1 : at - 1);
+            landed(n_mine - 1 - s);
+            const char *base = ring + at * kBytes;
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                bl.a[i].raw = *reinterpret_cast<const u32x4 *>(wsrc + at + i * 64);
-                bl.b[i].raw = *reinterpret_cast<const u32x4 *>(xsrc + at + i * 64);
+                const int slot = ((4 * i + g) ^ ((col >> 1) & 7)) << 4;
+                Frag a[NB], b[TT];                   // (rows past an odd number of units are of no column or token)
+#pragma unroll
+                for (int n = 0; n < NB; ++n) a[n].raw = *reinterpret_cast<const u32x4 *>(base + (n * 16 + col) * 128 + slot);
+#pragma unroll
+                for (int t = 0; t < TT; ++t) b[t].raw = *reinterpret_cast<const u32x4 *>(base + (U * 8 + t * 16 + (XT == 1 ? col & 7 : col)) * 128 + (XT == 1 ? ((4 * i + g) ^ ((col & 7) >> 1)) << 4 : slot));
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+#pragma unroll
+                    for (int t = 0; t < TT; ++t) acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[n].bf, b[t].bf, acc[n][t], 0, 0, 0);
             }
-        };
-        Block bl[kJrBlocks];
-#pragma unroll
-        for (int u = 0; u < kJrBlocks; ++u) request(bl[u], w + u * kJrWaves);
-        for (int b0 = w; b0 < n_blk; b0 += kJrBlocks * kJrWaves) {
-#pragma unroll
-            for (int u = 0; u < kJrBlocks; ++u) {
-                if (b0 + u * kJrWaves < n_blk) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[u].a[i].bf, bl[u].b[i].bf, acc, 0, 0, 0);
-                }
-                request(bl[u], b0 + (u + kJrBlocks) * kJrWaves);
-            }
-        }
-        red[w][lane] = acc;
-        __syncthreads();
-        // lane l holds features f0 + 4*(l/16) .. +3 of token l%16
-        if (w == 0 && item < n_items) {
-            f32x4 sum = red[0][lane];
-#pragma unroll
-            for (int i = 1; i < kJrWaves; ++i) sum += red[i][lane];
-            char *orow = f0 < kHeadDim ? q_out + ((((size_t)(sl / k) * H + head) * Tn) + tok) * (kHeadDim * 2)
-                                       : k_compact + ((size_t)sl * Tc_cap + pos0 + tok) * (kHeadDim * 2);
-            bf16x4 o;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (__bf16)sum[e];
-            *reinterpret_cast<bf16x4 *>(orow + ((f0 & (kHeadDim - 1)) + g * 4) * 2) = o;
+            at = at == R - 1 ? 0 : at + 1;
         }
         __syncthreads();
+        f32x4 *const red = reinterpret_cast<f32x4 *>(lds);   // [wave][n][t][lane]
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int t = 0; t < TT; ++t) red[((w * NB + n) * TT + t) * 64 + lane] = acc[n][t];
+        __syncthreads();
+        // lane l holds features f0 + 16 n + 4*(l/16) .. +3 of token l%16
+        if (w < NB * TT) {
+            const int n = w / TT, t = w % TT, item = c0 + t * 16 + col, f = f0 + n * 16 + g * 4;
+            const int sl = __shfl(listed, min(item, n_items - 1) / Tn - c0 / Tn);
+            if (item < min(n_items, c0 + 8 * XT) && n * 16 + g * 4 < U * 8) {
+                f32x4 sum = red[(n * TT + t) * 64 + lane];
+#pragma unroll
+                for (int i = 1; i < kJsWaves; ++i) sum += red[((i * NB + n) * TT + t) * 64 + lane];
+                const int tok = item % Tn;
+                char *orow = f < kHeadDim ? q_out + ((((size_t)(sl / k) * H + head) * Tn) + tok) * (kHeadDim * 2)
+                                          : k_compact + ((size_t)sl * Tc_cap + pos0 + tok) * (kHeadDim * 2);
+                bf16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = (__bf16)sum[e];
+                *reinterpret_cast<bf16x4 *>(orow + (f & (kHeadDim - 1)) * 2) = o;
+            }
+        }
+        __syncthreads();
+    };
+    auto pass = [&](int c0, auto u_) __attribute__((always_inline)) {
+        const int left = n_items - c0;
+        if (left <= 8) run(c0, u_, std::integral_constant<int, 1>{});
+        else if (left <= 16) run(c0, u_, std::integral_constant<int, 2>{});
+        else if constexpr (decltype(u_)::value <= kJsMaxUnits - 2) run(c0, u_, std::integral_constant<int, 4>{});
+    };
+    for (int c0 = 0; c0 < n_items; c0 += kJsPass) {
+        if (c0 != 0) list_pairs(c0 / Tn);
+        unroll<MOST>([&](auto i) __attribute__((always_inline)) {
+            if (n_units == i.value + 1) pass(c0, std::integral_constant<int, i.value + 1>{});
+        });
     }
 }
 
@@ -548,7 +710,7 @@ __global__ __launch_bounds__(kJtBlock) void project_tile_kernel(const char *__re
                                                                 char *__restrict__ k_compact, int pos0, int Tc_cap)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
-    __shared__ int slots[kJrMaxSlots];
+    __shared__ int slots[kJtMaxSlots];
     __shared__ int wave_sum[kJtWaves * kJtTeams];
     __shared__ int count[kJtMaxHeads];
     __shared__ int mine[2];
@@ -642,6 +804,20 @@ int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, co
                               static_cast<const u32x4 *>(buf), (unsigned long long)(bytes / 16), rounds, sink);
 }
 
+// Which calls project_stream_kernel takes: up to 32 tokens over all rows, so that a head's tokens are multiplied in one pass.  More of
+// them where the heads in use are few, B * Tn up to 64 (two passes; 64-token tiles / this kernel in us: 1 x 64, 8 of 32, D 4096
+// 20.8 / 14.5; 16 x 4, 8 of 32 24.4 / 20.9; 16 x 4, 8 of 52, D 6656 37.3 / 32.8; 1 x 64, 16 of 72, D 9216 49.2 / 37.0; but 6 x 10, 16 of
+// 72 51.9 / 55.0; 4 x 16, 40 of 40, D 5120 35.8 / 42.7).  Not where many rows use most of 40 to 70 heads, enough 64-column tiles for
+// every CU and few tokens short of full ones (16 x 1, 16 of 72 45.5 / 46.7; 16 x 2 47.8 / 50.8; 12 x 2 45.2 / 48.3; 16 x 1, 16 of 52
+// 33.1 / 34.0; but 9 x 1, 16 of 72 42.3 / 42.0, 8 x 4 44.9 / 42.7, 16 x 1, 10 of 72 39.3 / 30.8 and 8 x 1, 72 of 72 87.8 / 67.1).
+static bool project_streams(int B, int H, int k, int Tn)
+{
+    const long long tokens = (long long)B * Tn, pairs = (long long)B * k, heads = H < pairs ? H : pairs;
+    if (tokens > 64) return false;
+    if (tokens > 32 && (pairs * Tn > 1024 || (k > 8 && pairs > 64))) return false;
+    return !(heads > 32 && k > 12 && B >= 6 && tokens >= 12);
+}
+
 int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int32_t *rep, int B, int H, int k, int Tn,
                       int D, void *q_out, void *k_compact, int pos0, int Tc_cap, const KernelEvents &ev,
                       hipStream_t stream)
@@ -651,11 +827,10 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     // Which kernel: by the number of tokens over all (row, slot) pairs, in time per call (before: 256-token tiles for
     // every size; D = 4096 unless noted).  A 256-token tile of one (row, slot) pair is a chain of D/64 stages however
     // few tokens it holds, so calls with few tokens took 77-86 us (170-215 us at D = 9216) at any size:
-    //   B*Tn <= 8           one row of MFMA columns per head: B 1, 8 of 32 heads: 77 -> 13 us; B 1, 16 of 72, D 9216:
-    //                       171 -> 28 us (33 us with the 64-token tiles)
-    //   B*k*Tn <= most      64-token tiles, head-major: B 16, k 8, Tn 1 / 16 / 64 / 128: 80 / 82 / 82 / 85 -> 17 / 20 / 32 /
-    //                       62 us; B 1, k 8, Tn 512 / 2043: 85 / 87 -> 21 / 60 us; B 4, k 16, D 9216, Tn 16 / 256:
-    //                       175 / 215 -> 52 / 135 us; B 4, k 8, D 6656, Tn 512: 151 -> 95 us
+    //   few tokens per head project_stream_kernel, see there and project_streams
+    //   B*k*Tn <= most      64-token tiles, head-major: B 16, k 8, Tn 16 / 64 / 128: 82 / 82 / 85 -> 20 / 32 / 62 us; B 1, k 8, Tn
+    //                       512 / 2043: 85 / 87 -> 21 / 60 us; B 4, k 16, D 9216, Tn 256: 215 -> 135 us; B 4, k 8, D 6656, Tn 512:
+    //                       151 -> 95 us
     //   above               256-token tiles: B 16, k 8, Tn 256: 82 us (118 us with the small tiles)
     // From 16384 pairs' tokens on the small tiles take a third round of the chip.  It pays where the large tiles need a second
     // one, or are a long chain and do not fill theirs, or hold few tokens each; in us, large / small tiles:
@@ -666,12 +841,22 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     //   B 16, k 10 (160), Tn 140, D 6656: 146 / 137
     //   B 16, k 16 (256), Tn 72 / 80 / 96: (72) D 9216 227 / 194, D 4096 (80) 97 / 86 and (96) 98 / 114
     //   B 16, k 32 (512), Tn 48: D 512 42 / 27, D 4096 194 / 91
-    // Both small kernels list the pairs of a head in LDS (at most kJrMaxSlots of them).
+    // The small tiles list the pairs of a head in LDS (at most kJtMaxSlots of them); 16 x 1 tokens of 72 of 72 heads, which are more,
+    // took 1058 us as 256-token tiles.
     const long long items = (long long)B * k * Tn;
-    const bool listed = (long long)B * k <= kJrMaxSlots;
-    if (listed && (long long)B * Tn <= kJrTokens && H <= 0x7fffffff / kJrParts)
-        return (int)launch_kernel(project_rows_kernel, dim3((unsigned int)H * kJrParts), dim3(kJrWaves * 64), 0, stream, ev,
-                                  xc, wq, wk, rep, B, H, k, Tn, D, qo, ko, pos0, Tc_cap);
+    const bool listed = (long long)B * k <= kJtMaxSlots;
+    if (project_streams(B, H, k, Tn) || (!listed && (long long)B * Tn <= 64)) {
+        // one round of the chip, or two, or what the most units of a workgroup ask for
+        const int heads = H < B * k ? H : B * k, most = heads * ((kJsUnits + kJsMaxUnits - 3) / (kJsMaxUnits - 2));
+        const bool few = heads <= kJCus / (kJsUnits / kJsFewUnits);
+        const int n_wg = few ? kJCus : (most > 2 * kJCus ? most : 2 * kJCus);
+        auto *kernel = few ? project_stream_kernel<kJsFewUnits> : project_stream_kernel<kJsMaxUnits>;
+        static DeviceFlags lds_allowed[2];
+        const hipError_t attr = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kJsLdsBytes, lds_allowed[few ? 1 : 0]);
+        if (attr != hipSuccess) return (int)attr;
+        return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(kJsWaves * 64), kJsLdsBytes, stream, ev, xc, wq, wk, rep, B, H, k, Tn,
+                                  D, qo, ko, pos0, Tc_cap);
+    }
     // (the tile kernel addresses the activations and one head's weights with 32-bit byte offsets below 2 GiB)
     const long long n_large = (long long)B * k * ((Tn + kJTok - 1) / kJTok);
     const bool one_round = n_large <= 150 && D < 8192;

@@ -14,73 +14,87 @@ namespace chai {
 namespace {
 
 // ---------------------------------------------------------------------------------------------------------
-// Features: grid (H, B), one wave per head.  Lane p < n_tok*(n_tok+1)/2 owns one causal (i, j) pair and runs
-// its 128-term dot product in element order in fp64, and then its element of the row's softmax.
+// Features: grid (H, B), one wave per head.  The 128-term fp64 dot product of a causal (i, j) pair is one chain of sums in element
+// order; SL neighbouring lanes share a pair: each converts and multiplies its 128 / SL elements at the same time as the others,
+// and then they continue the chain one after the other.  (One lane per pair did all of a pair's conversions and products
+// itself: 6.3 us for 4 x 72 heads, the kernel alone, now 4.2; the membership step of 4 x 72 heads 27.3 -> 24.5 with
+// the shorter sums of k-means.)  A pair's last lane then has its score; lane p takes pair p's element of the softmax.
 // ---------------------------------------------------------------------------------------------------------
+__device__ __forceinline__ double from_lane_before(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), 0x111, 0xf, 0xf, false);      // row_shr 1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), 0x111, 0xf, 0xf, false);
+    return __hiloint2double(hi, lo);
+}
+
+template <int SL>
 __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5, const void *__restrict__ k5,
                                                      int H, int n_tok, int bf16, long long qs, long long ks,
                                                      double scale, float *__restrict__ feat)
 {
+    constexpr int kElems = kHeadDim / SL;
     __shared__ double s[8][8], ex[8][8];
     const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
     const size_t head = (size_t)b * H + h;
 
-    // lane -> (i, j) with j <= i, row by row
-    int i = 0, j = lane;
-    while (i < n_tok && j > i) { j -= i + 1; ++i; }
-    if (i < n_tok) {
-        const size_t qo = head * (size_t)qs + (size_t)i * kHeadDim;
-        const size_t ko = head * (size_t)ks + (size_t)j * kHeadDim;
-        // 16-byte loads (rows start on 16-byte boundaries: the strides are multiples of 8 elements); the products
-        // are still added one by one in element order
-        double acc = 0.0;
-        if (bf16) {
-            const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(q5) + qo);
-            const uint4 *kv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(k5) + ko);
-            uint4 qr[kHeadDim / 8], kr[kHeadDim / 8];        // both rows requested at once (four pieces at a time: 6.7 against 6.3 us)
+    // pair -> (i, j) with j <= i, row by row
+    auto pair_of = [&](int p, int &i, int &j) {
+        i = 0;
+        j = p;
+        while (i < n_tok && j > i) { j -= i + 1; ++i; }
+    };
+    int i, j;
+    pair_of(lane / SL, i, j);
+    const int slice = lane % SL, si = min(i, n_tok - 1), sj = min(j, n_tok - 1);      // (lanes without a pair repeat another's loads)
+    const size_t qo = head * (size_t)qs + (size_t)si * kHeadDim + slice * kElems;
+    const size_t ko = head * (size_t)ks + (size_t)sj * kHeadDim + slice * kElems;
+    double prod[kElems];
+    // 16-byte loads (rows start on 16-byte boundaries: the strides are multiples of 8 elements), all of a lane's requested at once
+    if (bf16) {
+        const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(q5) + qo);
+        const uint4 *kv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(k5) + ko);
+        uint4 qr[kElems / 8], kr[kElems / 8];
 #pragma unroll
-            for (int c8 = 0; c8 < kHeadDim / 8; ++c8) {
-                qr[c8] = qv[c8];
-                kr[c8] = kv[c8];
-            }
+        for (int c8 = 0; c8 < kElems / 8; ++c8) {
+            qr[c8] = qv[c8];
+            kr[c8] = kv[c8];
+        }
 #pragma unroll
-            for (int c8 = 0; c8 < kHeadDim / 8; ++c8) {
-                const uint4 a = qr[c8], bb = kr[c8];
-                const unsigned int aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {bb.x, bb.y, bb.z, bb.w};
+        for (int c8 = 0; c8 < kElems / 8; ++c8) {
+            const unsigned int aw[4] = {qr[c8].x, qr[c8].y, qr[c8].z, qr[c8].w}, bw[4] = {kr[c8].x, kr[c8].y, kr[c8].z, kr[c8].w};
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const unsigned int abits = (e & 1) ? (aw[e >> 1] & 0xffff0000u) : (aw[e >> 1] << 16);
-                    const unsigned int bbits = (e & 1) ? (bw[e >> 1] & 0xffff0000u) : (bw[e >> 1] << 16);
-                    const double prod = (double)__uint_as_float(abits) * (double)__uint_as_float(bbits);
-                    acc = acc + prod;
-                }
-            }
-        } else {
-            const float4 *qv = reinterpret_cast<const float4 *>(static_cast<const float *>(q5) + qo);
-            const float4 *kv = reinterpret_cast<const float4 *>(static_cast<const float *>(k5) + ko);
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                constexpr int kPieces = kHeadDim / 8;
-                float4 qr[kPieces], kr[kPieces];
-#pragma unroll
-                for (int c4 = 0; c4 < kPieces; ++c4) {
-                    qr[c4] = qv[half * kPieces + c4];
-                    kr[c4] = kv[half * kPieces + c4];
-                }
-#pragma unroll
-                for (int c4 = 0; c4 < kPieces; ++c4) {
-                    const float4 a = qr[c4], bb = kr[c4];
-                    const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {bb.x, bb.y, bb.z, bb.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const double prod = (double)av[e] * (double)bv[e];
-                        acc = acc + prod;
-                    }
-                }
+            for (int e = 0; e < 8; ++e) {
+                const unsigned int abits = (e & 1) ? (aw[e >> 1] & 0xffff0000u) : (aw[e >> 1] << 16);
+                const unsigned int bbits = (e & 1) ? (bw[e >> 1] & 0xffff0000u) : (bw[e >> 1] << 16);
+                prod[c8 * 8 + e] = (double)__uint_as_float(abits) * (double)__uint_as_float(bbits);
             }
         }
-        s[i][j] = scale * acc;
+    } else {
+        const float4 *qv = reinterpret_cast<const float4 *>(static_cast<const float *>(q5) + qo);
+        const float4 *kv = reinterpret_cast<const float4 *>(static_cast<const float *>(k5) + ko);
+        float4 qr[kElems / 4], kr[kElems / 4];
+#pragma unroll
+        for (int c4 = 0; c4 < kElems / 4; ++c4) {
+            qr[c4] = qv[c4];
+            kr[c4] = kv[c4];
+        }
+#pragma unroll
+        for (int c4 = 0; c4 < kElems / 4; ++c4) {
+            const float av[4] = {qr[c4].x, qr[c4].y, qr[c4].z, qr[c4].w}, bv[4] = {kr[c4].x, kr[c4].y, kr[c4].z, kr[c4].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) prod[c4 * 4 + e] = (double)av[e] * (double)bv[e];
+        }
     }
+    // stage st: the pair's lane number st goes on from where the lane before it has come to (what the others add up is not used)
+    double acc = 0.0;
+#pragma unroll
+    for (int st = 0; st < SL; ++st) {
+        if (st > 0) acc = from_lane_before(acc);
+#pragma unroll
+        for (int e = 0; e < kElems; ++e) acc = acc + prod[e];
+    }
+    if (i < n_tok && slice == SL - 1) s[i][j] = scale * acc;
+    pair_of(lane, i, j);
     __syncthreads();
     // every pair's lane takes its own exponential and its own division (one lane per row took up to eight of each in a
     // row); the row sum is added in column order by all of them
@@ -376,9 +390,10 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 //  * 4200 for the distances, 3 fp64 operations per coordinate at 8 cycles each.  Here matrix instructions take them in fp32 first, 16
 //    heads and 16 centres per wave, as s = |c|^2 / 2 - x c, and fp64 only those centres that can still be the nearest.  With
 //    u = 2^-24 and M the largest |x|^2 (a centre is a mean of heads, or one: |c|^2 <= M, |x| |c| <= M) the F products of x c, each
-//    rounded at most twice and of a centre rounded to fp32, are off by less than (2F + 2) u M, |c|^2 / 2 by (F + 2) u M, so that a
-//    centre whose s exceeds the least by more than 2 (3F + 4) u M has the larger distance, in fp64 as well (whose own error is 2^-28
-//    of this).  Twice that is allowed for, and 1e-30 for what underflows.  One centre left: it is the nearest.  Where a value is not
+//    rounded at most twice and of a centre rounded to fp32, are off by less than (2F + 2) u M, |c|^2 / 2 by (F + 2) u M, the sum of
+//    the two chains that they are added up in by u M, so that a
+//    centre whose s exceeds the least by more than 2 (3F + 5) u M has the larger distance, in fp64 as well (whose own error is 2^-28
+//    of this).  Twice 2 (3F + 4) u M, which is more from F = 9 on, is allowed for, and 1e-30 for what underflows.  One centre left: it is the nearest.  Where a value is not
 //    finite all centres are taken in fp64.
 //  * 2900 for walking the members' bits, word by word.  Here every head ranks itself among its cluster's and the sum goes along a
 //    list of members, four per word.
@@ -386,7 +401,7 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 // The numbering at the end ranks the centres by readlane in one wave; fp64 distances to the own centre, which the repair of empty
 // centres asks for, are taken there.  A pass takes 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
 // start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 4 problems of 72 heads, 16 centres and 25
-// coordinates; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
+// coordinates, 18.7 with up to sixteen members of a sum requested at a time; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
 // launching (up to 40 heads) takes what it did.  Where most passes need the 64-bit distances of all centres (problems of a few tight
 // clusters) it is level with the general kernel: 71.9 and 71.6 us for 8 of 256 heads, 16 centres, 25 coordinates.
 // Dynamic LDS (FastLayout): centres [k][FP] fp64, features [H][FP] fp32, centres [16 n][C32] fp32, masks, lists of members, ...
@@ -540,9 +555,13 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
                     for (int t = 0; t < G; ++t) c2 = __builtin_fmaf(c[t], c[t], c2);
                     c2 = over_groups(c2, [](float p, float q) { return p + q; });
                     if (g == 3) c[G - 1] = 0.5f * c2;
-                    km_f32x4 acc = {0.f, 0.f, 0.f, 0.f};     // x c - |c|^2 / 2
+                    km_f32x4 acc = {0.f, 0.f, 0.f, 0.f}, odd = acc;      // x c - |c|^2 / 2, in two chains (|c|^2 last)
 #pragma unroll
-                    for (int t = 0; t < G; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t], xr[t], acc, 0, 0, 0);
+                    for (int t = 0; t < G; t += 2) {
+                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t], xr[t], acc, 0, 0, 0);
+                        odd = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t + 1], xr[t + 1], odd, 0, 0, 0);
+                    }
+                    acc = acc + odd;
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const bool there = i * 16 + 4 * g + e < k;
@@ -624,9 +643,29 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
             return n;
         };
         // empty centres: as in the general kernel
-        int rank, ignored;
-        int n_mine = members(max(min(prev, k - 1), 0), my_h, rank);     // (lanes without a head: any centre)
-        const bool empty = lane < k && members(lane, 0, ignored) == 0;
+        int rank, ignored, n_mine;
+        bool empty;
+        const int mine = max(min(prev, k - 1), 0);           // (lanes without a head: any centre)
+        if (W <= 4) {                                        // all words of both centres requested at once
+            unsigned own[4], seen[4], any = 0u;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                own[u] = mask[mine * W + min(u, W - 1)];
+                seen[u] = mask[min(lane, k - 1) * W + min(u, W - 1)];
+            }
+            n_mine = rank = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const unsigned m = u < W ? own[u] : 0u, low = u < (my_h >> 5) ? ~0u : (u == (my_h >> 5) ? (1u << (my_h & 31)) - 1u : 0u);
+                n_mine += __popc(m);
+                rank += __popc(m & low);
+                any |= seen[u];
+            }
+            empty = any == 0u;                               // (past the last centre: the last one's)
+        } else {
+            n_mine = members(mine, my_h, rank);
+            empty = lane < k && members(lane, 0, ignored) == 0;
+        }
         int changed = *moved_flag;
         if (__any(empty)) {                                 // the same in every wave
             if (owner && g == 0) dmin[my_h] = exact(prev);
@@ -668,13 +707,25 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
             const unsigned *row = reinterpret_cast<const unsigned *>(list + j * L.LS);
             const int last = L.LS / 4 - 1;
             double acc = 0.0;
-            for (int m = 0; m < n; m += 8) {                 // eight members requested at a time (whatever the list holds is a head)
-                const unsigned w0 = row[m / 4], w1 = row[min(m / 4 + 1, last)];
-                float v[8];
+            constexpr int kMost = F <= 25 ? 16 : 8;          // members requested at a time (more would not leave the registers for 1024
+            for (int m = 0; m < n; m += kMost) {             // threads; whatever the list holds is a head)
+                unsigned word[4];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) v[u] = x_lds[(((u < 4 ? w0 : w1) >> (8 * (u & 3))) & 0xffu) * FP + f];
+                for (int u = 0; u < kMost / 4; ++u) word[u] = row[min(m / 4 + u, last)];
+                float v[16];
+                auto request = [&](int u0) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) acc = acc + (double)(m + u < n ? v[u] : -0.0f);      // (-0 changes no sum)
+                    for (int u = u0; u < u0 + 8; ++u) v[u] = x_lds[((word[u >> 2] >> (8 * (u & 3))) & 0xffu) * FP + f];
+                };
+                auto add = [&](int u0) {
+#pragma unroll
+                    for (int u = u0; u < u0 + 8; ++u) acc = acc + (double)(m + u < n ? v[u] : -0.0f);      // (-0 changes no sum)
+                };
+                const bool more = kMost > 8 && __any(m + 8 < n);
+                request(0);
+                if (more) request(8);
+                add(0);
+                if (more) add(8);
             }
             if (n != 0) {
                 const double mean = acc / (double)n;
@@ -785,7 +836,9 @@ __global__ __launch_bounds__(kBlock) void cluster_error_kernel(const float *__re
 int launch_score_features(const void *q5, const void *k5, int B, int H, int n_tok, int dtype, int64_t qs, int64_t ks,
                           float scale, float *feat, hipStream_t stream)
 {
-    return (int)launch_kernel(feature_kernel, dim3(H, B), dim3(64), 0, stream, KernelEvents(), q5, k5, H, n_tok,
+    // pairs: 15 of five positions, 28 of seven, 36 of eight
+    auto *kernel = n_tok <= 5 ? feature_kernel<4> : (n_tok <= 7 ? feature_kernel<2> : feature_kernel<1>);
+    return (int)launch_kernel(kernel, dim3(H, B), dim3(64), 0, stream, KernelEvents(), q5, k5, H, n_tok,
                               dtype == CHAI_BF16 ? 1 : 0, (long long)qs, (long long)ks, (double)scale, feat);
 }
 

@@ -136,9 +136,11 @@ __device__ __forceinline__ void plan_row(const int32_t *__restrict__ h2c, const 
 __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v, int H, int T_cap, int n_keys, int Tp,
                                                       _Float16 *__restrict__ vt, int n_lists, const int32_t *__restrict__ h2c,
                                                       const int32_t *__restrict__ rep, int k, int max_groups,
-                                                      int32_t *__restrict__ groups, int32_t *__restrict__ n_groups)
+                                                      int32_t *__restrict__ groups, int32_t *__restrict__ n_groups,
+                                                      int32_t *__restrict__ tickets, int ticket_stride)
 {
     extern __shared__ __attribute__((aligned(16))) char pre_lds[];
+    if (blockIdx.x == 0 && threadIdx.x < kXcds) tickets[(threadIdx.x >> 2) * ticket_stride + (threadIdx.x & 3)] = 0;
     _Float16 (*tile)[kKTile + 2] = reinterpret_cast<_Float16 (*)[kKTile + 2]>(pre_lds);
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < n_lists) {
@@ -218,96 +220,118 @@ constexpr int kBufs = 3;
 constexpr size_t kKBufBytes = (size_t)kKTile * kHeadDim * 2;        // 64 rows of 256 B (16 pieces), swizzled
 constexpr size_t kVBufBytes = (size_t)kHeadDim * kKTile * 2;        // one member: 128 rows of 128 B (8 pieces), swizzled
 // rows: query rows of a workgroup, which stand behind the first value tile at the start
-constexpr size_t prefill_lds_bytes(bool ident, int bufs, int rows)
+__host__ __device__ constexpr size_t prefill_rings(bool ident, int bufs, int rows)
 {
     const size_t v_tile = (ident ? 1 : kGroup) * kVBufBytes, rings = bufs * (kKBufBytes + v_tile);
     const size_t start = bufs * kKBufBytes + v_tile + (size_t)rows * (kHeadDim * 2);
     return rings > start ? rings : start;
 }
+constexpr size_t prefill_lds_bytes(bool ident, int bufs, int rows) { return prefill_rings(ident, bufs, rows) + (bufs == 2 ? 0 : 16); }
 
 // ---------------------------------------------------------------------------------------------------------
 // Which query tiles of which (batch row, group) a workgroup takes.  The hardware deals consecutive workgroup ids
-// round-robin to the 8 XCDs, each with an L2 of its own, and hands the next id of an XCD to the first of its 32 CUs
-// that is free (one workgroup fits a CU).  The unit is a PAIR of query tiles of one group, the p-th largest and the
-// p-th smallest: under the causal mask tile q walks q+1 key tiles' worth of work, so all pairs cost the same.  The
-// pairs that EXIST (the groups of all rows, counted here from the plan) are dealt to the XCDs in equal contiguous
-// ranges, so that the pairs of one group share its keys and values in one L2.  Within an XCD whole rounds of 32 pairs
-// go out first; the last 32 to 63 pairs go out as single tiles, the largest first, which fills the last round.
+// round-robin to the 8 XCDs, each with an L2 of its own; every XCD has a queue of tiles, from which its 32 workgroups, one per CU, draw
+// one after the other (or which has a workgroup for every tile: launch_prefill).  The unit of the deal is a PAIR of query tiles of
+// one group, the p-th largest and the p-th smallest: under the causal mask tile q walks q+1 key tiles' worth of work, so all
+// pairs cost the same.  The pairs that EXIST (the groups of all rows, counted here from the plan) are dealt to the XCDs in equal
+// contiguous ranges, so that the pairs of one group share its keys and values in one L2.  A queue has whole rounds of 32
+// pairs first; the last 32 to 63 pairs stand in it as single tiles, the largest first, which fills the last round.
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kXcdCus = 32;
 constexpr int kSmallTiles = 450, kFewTiles = 1450;      // see launch_prefill
-struct PrefillWork {
-    int b, gi;           // batch row, group (identity: head)
-    int qt0, qt1, n_pass;   // query tiles
+struct WorkQueue {
+    unsigned n_pairs, lo, hi, mid, first, n_first, n_items;      // pairs lo .. mid-1, then mid .. hi-1, of n_first groups from `first`
+    int upto;                                                // groups of the first rows up to this lane's
 };
 template <bool IDENT>
-__device__ __forceinline__ bool find_work(const int32_t *__restrict__ n_groups, int n_rows, int H, int n_qt, PrefillWork &work)
+__device__ __forceinline__ WorkQueue make_queue(const int32_t *__restrict__ n_groups, int n_rows, int H, int n_qt)
 {
     const int lane = threadIdx.x & 63;
-    const unsigned n_pairs = (unsigned)(n_qt + 1) / 2;
-    unsigned total = 0;                                     // groups; total * n_pairs < 2^31 (launch_prefill)
-    int first_rows = 0;                                     // group count of this lane's row among the first 64
+    WorkQueue w;
+    w.n_pairs = (unsigned)(n_qt + 1) / 2;
+    unsigned total = 0;                                     // groups; total * n_pairs < 2^30 (launch_prefill)
+    w.upto = 0;
     if (IDENT) total = (unsigned)n_rows * (unsigned)H;
     else {
         for (int r0 = 0; r0 < n_rows; r0 += 64) {
-            int c = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
-            if (r0 == 0) first_rows = c;
+            int upto = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o);
-            total += (unsigned)__builtin_amdgcn_readfirstlane(c);
+            for (int o = 1; o < 64; o <<= 1) {
+                const int other = __shfl_up(upto, o);
+                upto += lane >= o ? other : 0;
+            }
+            total += (unsigned)__builtin_amdgcn_readlane(upto, 63);
+            if (r0 == 0) w.upto = upto;
         }
     }
-    const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, pairs = total * n_pairs;
+    const unsigned xcd = blockIdx.x % kXcds, pairs = total * w.n_pairs;
     const unsigned each = pairs / kXcds, rest = pairs % kXcds;               // the first `rest` XCDs take one more
-    const unsigned lo = each * xcd + min(xcd, rest), hi = lo + each + (xcd < rest ? 1u : 0u);
-    const unsigned rounds = (hi - lo) / kXcdCus;
-    const unsigned mid = lo + (rounds > 1 ? (rounds - 1) * kXcdCus : 0u);    // pairs lo .. mid-1, then single tiles
-    unsigned group;
-    if (local < mid - lo) {
-        const unsigned at = lo + local;
-        group = at / n_pairs;
-        const int pi = (int)(at - group * n_pairs);
-        work.qt0 = n_qt - 1 - pi;
-        work.qt1 = pi;
-        work.n_pass = work.qt0 > pi ? 2 : 1;                                 // the middle tile of an odd count is alone
-    } else {
-        if (mid >= hi) return false;
-        const unsigned first = mid / n_pairs, n_first = (hi - 1) / n_pairs - first + 1, m = n_first * n_pairs;
-        unsigned j = local - (mid - lo);
-        if (j >= 2 * m) return false;
-        const bool large = j < m;
-        if (!large) j -= m;
-        const unsigned row = j / n_first;
-        const int pi = (int)(large ? row : n_pairs - 1 - row);
-        group = first + j - row * n_first;
-        const unsigned at = group * n_pairs + (unsigned)pi;
-        if (at < mid || at >= hi || (!large && n_qt - 1 - pi == pi)) return false;
-        work.qt0 = large ? n_qt - 1 - pi : pi;
-        work.qt1 = 0;
-        work.n_pass = 1;
-    }
-    if (IDENT) {
-        work.b = (int)(group / (unsigned)H);
-        work.gi = (int)(group % (unsigned)H);
+    w.lo = each * xcd + min(xcd, rest);
+    w.hi = w.lo + each + (xcd < rest ? 1u : 0u);
+    const unsigned rounds = (w.hi - w.lo) / kXcdCus;
+    w.mid = w.lo + (rounds > 1 ? (rounds - 1) * kXcdCus : 0u);
+    w.first = w.mid / w.n_pairs;
+    w.n_first = w.mid < w.hi ? (w.hi - 1) / w.n_pairs - w.first + 1 : 0u;
+    w.n_items = n_qt == 1 ? w.hi - w.lo : 2 * (w.mid - w.lo) + 2 * w.n_first * w.n_pairs;
+    return w;
+}
+// Item i: group and query tile; false where there is none of that number.
+__device__ __forceinline__ bool queue_item(const WorkQueue &w, int n_qt, unsigned i, unsigned &group, int &qt)
+{
+    if (n_qt == 1) {
+        group = w.lo + i;
+        qt = 0;
         return true;
     }
+    if (i < 2 * (w.mid - w.lo)) {
+        const unsigned at = w.lo + i / 2;
+        group = at / w.n_pairs;
+        const int pi = (int)(at - group * w.n_pairs);
+        qt = (i & 1) ? pi : n_qt - 1 - pi;
+        return !(i & 1) || n_qt - 1 - pi != pi;              // the middle tile of an odd count is alone
+    }
+    unsigned j = i - 2 * (w.mid - w.lo);
+    const unsigned m = w.n_first * w.n_pairs;
+    const bool large = j < m;
+    if (!large) j -= m;
+    const unsigned row = j / w.n_first;
+    const int pi = (int)(large ? row : w.n_pairs - 1 - row);
+    group = w.first + j - row * w.n_first;
+    qt = large ? n_qt - 1 - pi : pi;
+    const unsigned at = group * w.n_pairs + (unsigned)pi;
+    return at >= w.mid && at < w.hi && (large || n_qt - 1 - pi != pi);
+}
+// Row and number in the row of a group.
+template <bool IDENT>
+__device__ __forceinline__ void find_row(const WorkQueue &w, const int32_t *__restrict__ n_groups, int n_rows, int H, unsigned group, int &b,
+                                         int &gi)
+{
+    const int lane = threadIdx.x & 63;
+    if (IDENT) {
+        b = (int)(group / (unsigned)H);
+        gi = (int)(group % (unsigned)H);
+        return;
+    }
+    b = gi = 0;
     for (int r0 = 0; r0 < n_rows; r0 += 64) {
-        int upto = r0 == 0 ? first_rows : (r0 + lane < n_rows ? n_groups[r0 + lane] : 0);
+        int upto = w.upto;
+        if (r0 != 0) {
+            upto = r0 + lane < n_rows ? n_groups[r0 + lane] : 0;
 #pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const int other = __shfl_up(upto, o);
-            upto += lane >= o ? other : 0;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int other = __shfl_up(upto, o);
+                upto += lane >= o ? other : 0;
+            }
         }
         const unsigned all = (unsigned)__builtin_amdgcn_readlane(upto, 63);
         if (group < all) {
             const int row = __popcll(__ballot((unsigned)upto <= group));
-            work.b = r0 + row;
-            work.gi = (int)group - (row > 0 ? __builtin_amdgcn_readlane(upto, row - 1) : 0);
-            return true;
+            b = r0 + row;
+            gi = (int)group - (row > 0 ? __builtin_amdgcn_readlane(upto, row - 1) : 0);
+            return;
         }
         group -= all;
     }
-    return false;
 }
 
 // Accumulator tile T of the kernel below: registers a[16 T .. 16 T + 15] of the accumulation half, BY NAME.  The compiler
@@ -494,19 +518,24 @@ struct OpSchedule {
 // What is left to do for a query tile whose accumulators are complete
 template <int U>
 struct Finished {
+    int n_mem;                                               // of how many members (0: none)
     int i0;                                                  // first query row of the wave
+    size_t b;                                                // batch row, members
+    int heads[kGroup];
     float inv[U];                                            // one over this lane's row sum
 };
 
-// Query tile number `pass` (of n_pass; NW waves x 32 U rows) of one group of NM members, and before it, once the tile's first
-// requests are on their way, the output rows of the tile before (done; those alone if pass is n_pass).  heads, vsrc: the members' heads and V^T; brow: batch row.
+// One query tile (NW waves x 32 U rows; has_tile) of one group of NM members, and before it, once the tile's first requests are on
+// their way, the output rows of the tile before, if that one was of NM members too (done).  heads, vsrc: the members' heads and
+// V^T; brow: batch row.
 // LDS: rings of BUFS tiles (2: one key tile only), a value tile with room for G members.
 // DIRECT: vsrc are the members' rows of the value cache itself (see prefill_direct_kernel).
-template <int NM, int U, int NW, int G, int BUFS, bool DIRECT = false>
+// draw: called once, two tiles of keys before the end
+template <int NM, int U, int NW, int G, int BUFS, bool DIRECT, typename Draw>
 __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const char *ksrc, const char *const (&vsrc)[kGroup],
                                           const char *q, const int (&heads)[kGroup], size_t brow, int H, int Tq, int q_start,
-                                          int qt, int pass, int n_pass, int rhead, float scale2, float *__restrict__ out,
-                                          Finished<U> &done)
+                                          int qt, bool has_tile, int rhead, float scale2, float *__restrict__ out,
+                                          Finished<U> &done, Draw draw)
 {
     const int tid = threadIdx.x, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     int lane = tid & 63;
@@ -716,7 +745,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #endif
         char *row0[NM];
 #pragma unroll
-        for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((brow * H + heads[g]) * Tq + done.i0) * kHeadDim);
+        for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((DIRECT ? brow * H + heads[g] : done.b * H + done.heads[g]) * Tq + done.i0) * kHeadDim);
         unroll<4 * U>([&](auto c) {
             constexpr int u = c.value / 4, rows = 32 * u + 8 * (c.value % 4);
             const std::integral_constant<int, c.value % 4> quad;
@@ -918,7 +947,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     };
 
     Raw raw_a, raw_b;                                        // DIRECT: tiles 0, 2, .. and 1, 3, ..
-    if (pass < n_pass) {
+    if (has_tile) {
         dma_k(0, 0);
         dma_q();
         if constexpr (DIRECT) {
@@ -933,8 +962,11 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             if (BUFS > 2 && n_tiles > 1) dma_k(1, 1);
         }
     }
-    if (pass > 0) write_rows();
-    if (pass == n_pass) return;
+    if (DIRECT ? !has_tile : done.n_mem == NM) write_rows();
+    if (!has_tile) {
+        done.n_mem = 0;
+        return;
+    }
     // query fragments (B operand of S^T = K Q^T): Q[row][16*ks + 8*hl .. +7]
 #pragma unroll
     for (int u = 0; u < U; ++u) q_abs[u] = q_start + min(i0 + u * 32 + r, Tq - 1);
@@ -1042,10 +1074,17 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             if (++kt == n_tiles) break;
         }
     } else
-        for (int kt = 0; kt < n_tiles; ++kt) tile(kt, raw_a);
+        for (int kt = 0; kt < n_tiles; ++kt) {
+            if (__builtin_expect(kt == max(n_tiles - 2, 0), 0)) draw();
+            tile(kt, raw_a);
+        }
     if (n_hb == 2 * n_tiles) pv_last(pb, vb_lane + b3p * (G * kVBufBytes), 1);
 
+    done.n_mem = NM;
     done.i0 = i0;
+    done.b = brow;
+#pragma unroll
+    for (int g = 0; g < NM; ++g) done.heads[g] = heads[g];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
         float lo, hi;
@@ -1055,13 +1094,19 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
 #if defined(__HIP_DEVICE_COMPILE__)
     // the requests past the end have landed before LDS is given to another tile or workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (pass + 1 < n_pass) {
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    }
 #endif
 }
 
+// One query tile of one group
+struct Job {
+    const char *ksrc, *vsrc[kGroup];                         // keys, the members' V^T
+    int heads[kGroup], b, rhead, qt, n_mem;
+};
+
+// One workgroup per CU (two with rings of two) takes query tiles from its XCD's queue until that is empty.  tickets: how many tiles
+// of the queue have been taken, per XCD, without the first one of every workgroup; zero at the start.
+// The next tile is drawn during the last but one tile of keys of the one before, whose output rows are written when the next one's
+// first requests are out.
 template <int U, int NW, bool IDENT, int BUFS>
 __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__restrict__ q, const char *__restrict__ kc,
                                                                   const _Float16 *__restrict__ vt,
@@ -1069,39 +1114,104 @@ __global__ __launch_bounds__(NW * 64, NW / 4) void prefill_kernel(const char *__
                                                                   const int32_t *__restrict__ n_groups, int H, int k,
                                                                   int Tq, int q_start, int Tc_cap, int Tp, int n_qt,
                                                                   int n_slots, int n_rows, float scale,
-                                                                  float *__restrict__ out)
+                                                                  float *__restrict__ out, int32_t *__restrict__ tickets,
+                                                                  int ticket_stride)
 {
     extern __shared__ __attribute__((aligned(1024))) char lds_raw[];
-    PrefillWork work;
-    if (!find_work<IDENT>(n_groups, n_rows, H, n_qt, work)) return;
-    const int gi = __builtin_amdgcn_readfirstlane(work.gi), b = __builtin_amdgcn_readfirstlane(work.b);
-    int cluster = gi, n_mem = 1, rhead = gi, heads[kGroup] = {gi, gi};
-    if (!IDENT) {
-        const int32_t *gr = groups + ((size_t)b * n_slots + gi) * kRec;
-        cluster = min(gr[0] & ((1 << kRecCount) - 1), k - 1);
-        n_mem = min(max(gr[0] >> kRecCount, 1), kGroup);
+    constexpr int G = IDENT ? 1 : kGroup;
+    char *const k_lds = lds_raw, *const v_lds = lds_raw + BUFS * kKBufBytes;
+    // the next item for all waves: behind the rings, or in the second key tile, which rings of two do not use
+    unsigned *const drawn = reinterpret_cast<unsigned *>(lds_raw + (BUFS == 2 ? kKBufBytes : prefill_rings(IDENT, BUFS, NW * 32 * U)));
+    const WorkQueue queue = make_queue<IDENT>(n_groups, n_rows, H, n_qt);
+    const unsigned xcd = blockIdx.x % kXcds, n_wg = gridDim.x / kXcds;
+    int32_t *const ticket = tickets + (xcd >> 2) * ticket_stride + (xcd & 3);
+    const bool draws = threadIdx.x == 0;
+    // the item after i of this workgroup's kind that exists, by the draws of thread 0
+    auto settle = [&](unsigned i) {
+        unsigned group;
+        int qt;
+        while (i < queue.n_items && !queue_item(queue, n_qt, i, group, qt)) i = n_wg + (unsigned)atomicAdd(ticket, 1);
+        return i;
+    };
+    auto look_up = [&](unsigned i, Job &job) {
+        unsigned group;
+        int b, gi, cluster, rhead, heads[kGroup];
+        queue_item(queue, n_qt, i, group, job.qt);
+        find_row<IDENT>(queue, n_groups, n_rows, H, group, b, gi);
+        b = __builtin_amdgcn_readfirstlane(b);
+        gi = __builtin_amdgcn_readfirstlane(gi);
+        job.qt = __builtin_amdgcn_readfirstlane(job.qt);
+        if (IDENT) {
+            cluster = rhead = heads[0] = heads[1] = gi;
+            job.n_mem = 1;
+        } else {
+            const int32_t *gr = groups + ((size_t)b * n_slots + gi) * kRec;
+            cluster = min(gr[0] & ((1 << kRecCount) - 1), k - 1);
+            job.n_mem = min(max(gr[0] >> kRecCount, 1), kGroup);
 #pragma unroll
-        for (int g = 0; g < kGroup; ++g) heads[g] = min(max(gr[1 + min(g, n_mem - 1)], 0), H - 1);
-        rhead = min(max(gr[1 + kGroup], 0), H - 1);
+            for (int g = 0; g < kGroup; ++g) heads[g] = min(max(gr[1 + min(g, job.n_mem - 1)], 0), H - 1);
+            rhead = min(max(gr[1 + kGroup], 0), H - 1);
+        }
+        job.ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
+        job.rhead = rhead;
+        job.b = b;
+#pragma unroll
+        for (int g = 0; g < kGroup; ++g) {
+            job.vsrc[g] = reinterpret_cast<const char *>(vt + ((size_t)b * H + heads[g]) * (size_t)kHeadDim * Tp);
+            job.heads[g] = heads[g];
+        }
+    };
+    auto barrier = [&]() {
+#if defined(__HIP_DEVICE_COMPILE__)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#endif
+    };
+
+    unsigned item = blockIdx.x / kXcds, group;
+    int qt;
+    const bool each = queue.n_items <= n_wg;                 // every item has a workgroup of its own: nothing is drawn
+    if (item >= queue.n_items) return;
+    if (!queue_item(queue, n_qt, item, group, qt)) {
+        if (each) return;
+        if (draws) *drawn = settle(item);
+        barrier();
+        item = (unsigned)__builtin_amdgcn_readfirstlane((int)*drawn);
+        if (item >= queue.n_items) return;
     }
-    const char *vsrc[kGroup];
-#pragma unroll
-    for (int g = 0; g < kGroup; ++g)
-        vsrc[g] = reinterpret_cast<const char *>(vt + ((size_t)b * H + heads[g]) * (size_t)kHeadDim * Tp);
-    const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
-    const int n_pass = __builtin_amdgcn_readfirstlane(work.n_pass);
+    Job job;
+    look_up(item, job);
     Finished<U> done;
-    done.i0 = Tq;
-    if (!IDENT && n_mem == 2)
-        for (int pass = 0; pass <= n_pass; ++pass)
-            prefill_tile<2, U, NW, kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start,
-                                                 __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1), pass, n_pass, rhead,
-                                                 scale * kLog2e, out, done);
-    else
-        for (int pass = 0; pass <= n_pass; ++pass)
-            prefill_tile<1, U, NW, IDENT ? 1 : kGroup, BUFS>(lds_raw, lds_raw + BUFS * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start,
-                                                             __builtin_amdgcn_readfirstlane(pass == 0 ? work.qt0 : work.qt1), pass,
-                                                             n_pass, rhead, scale * kLog2e, out, done);
+    done.n_mem = 0;
+    int later = 0;
+    auto draw = [&]() {
+        if (BUFS > 2 && !each && draws) later = atomicAdd(ticket, 1);
+    };
+    for (bool more = true;;) {
+        // rows of another number of members than the next tile's are written by themselves
+        const bool tile = more && (done.n_mem == 0 || done.n_mem == job.n_mem);
+        const int n_mem = tile ? job.n_mem : done.n_mem;
+        if (!IDENT && n_mem == 2)
+            prefill_tile<2, U, NW, G, BUFS, false>(k_lds, v_lds, job.ksrc, job.vsrc, q, job.heads, job.b, H, Tq, q_start, job.qt, tile,
+                                                   job.rhead, scale * kLog2e, out, done, draw);
+        else
+            prefill_tile<1, U, NW, G, BUFS, false>(k_lds, v_lds, job.ksrc, job.vsrc, q, job.heads, job.b, H, Tq, q_start, job.qt, tile,
+                                                   job.rhead, scale * kLog2e, out, done, draw);
+        if (!tile) {
+            if (!more) break;
+            continue;
+        }
+        if (BUFS == 2 || each) {
+            more = false;
+            continue;
+        }
+        if (draws) *drawn = settle(n_wg + (unsigned)later);
+        barrier();                                           // nobody reads this tile's keys and values any more
+        item = (unsigned)__builtin_amdgcn_readfirstlane((int)*drawn);
+        more = item < queue.n_items;
+        if (more) look_up(item, job);
+    }
 }
 
 // Cluster, members and representative of group gi of row b (the groups of plan_row, in the same order), found by every workgroup
@@ -1191,14 +1301,16 @@ __global__ __launch_bounds__(256, 1) void prefill_direct_kernel(const char *__re
     for (int g = 0; g < kGroup; ++g) vsrc[g] = v + ((size_t)b * H + heads[g]) * (size_t)T_cap * (kHeadDim * 2);
     const char *ksrc = kc + ((size_t)b * k + cluster) * (size_t)Tc_cap * (kHeadDim * 2);
     Finished<1> done;
+    done.n_mem = 0;
+    auto none = []() {};
     if (!IDENT && n_mem == 2)
-        for (int pass = 0; pass <= 1; ++pass)
+        for (int pass = 0; pass < 2; ++pass)
             prefill_tile<2, 1, 4, kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq, q_start, qt,
-                                                       pass, 1, rhead, scale * kLog2e, out, done);
+                                                       pass < 1, rhead, scale * kLog2e, out, done, none);
     else
-        for (int pass = 0; pass <= 1; ++pass)
+        for (int pass = 0; pass < 2; ++pass)
             prefill_tile<1, 1, 4, IDENT ? 1 : kGroup, kBufs, true>(lds_raw, lds_raw + kBufs * kKBufBytes, ksrc, vsrc, q, heads, b, H, Tq,
-                                                                   q_start, qt, pass, 1, rhead, scale * kLog2e, out, done);
+                                                                   q_start, qt, pass < 1, rhead, scale * kLog2e, out, done, none);
 }
 
 size_t round256(size_t x) { return (x + 255) / 256 * 256; }
@@ -1286,7 +1398,7 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
 
     if (prefill_is_direct(B, H, k, Tq, q_start, identity)) {
         auto *kernel = identity ? prefill_direct_kernel<true> : prefill_direct_kernel<false>;
-        const size_t lds_bytes = prefill_lds_bytes(identity, kBufs, 128);
+        const size_t lds_bytes = prefill_rings(identity, kBufs, 128);
         static DeviceFlags lds_allowed[2];
         const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[identity ? 1 : 0]);
         if (e != hipSuccess) return (int)e;
@@ -1308,13 +1420,18 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     }
 
     const size_t tile_lds = (size_t)kHeadDim * (kKTile + 2) * sizeof(_Float16), plan_lds = (size_t)(H + 2 * k) * sizeof(int32_t);
+    // Eight tickets in ints of the workspace that nothing else uses: the work list of a dense call; the last records of the first two
+    // rows' lists (a row has at most (H + k) / 2 groups, one less than its list has room for); behind the count of a single row.
+    int32_t *const tickets = identity ? groups : (B == 1 ? n_groups + 4 : groups + (size_t)(max_groups - 1) * kRec);
+    const int ticket_stride = identity || B == 1 ? 4 : max_groups * kRec;
+    static_assert(kRec >= 4 && kXcds == 8, "four tickets to a record");
     const int n_lists = identity ? 0 : B;
     const long long n_pre = n_lists + (long long)(Tp / kKTile) * H * B;
     if (n_pre > 0xffffff) return (int)hipErrorInvalidConfiguration;       // 256 GB of values
     hipError_t e = launch_kernel(prepass_kernel, dim3((unsigned int)n_pre), dim3(256),
                                  identity || plan_lds < tile_lds ? tile_lds : plan_lds, stream, KernelEvents(),
                                  static_cast<const char *>(v), H, T_cap, n_keys, Tp, vt, n_lists, h2c, rep, k, max_groups, groups,
-                                 n_groups);
+                                 n_groups, tickets, ticket_stride);
     if (e != hipSuccess) return (int)e;
     // Tiles of 256 or of 128 query rows: 128 where the wide tiles would leave CUs without work or end in a ragged last round,
     // and where a block has no more rows than that.  The lines lie at a number of 256-row tiles of the most groups the maps
@@ -1355,13 +1472,22 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     e = allow_dynamic_lds(reinterpret_cast<const void *>(kernel), lds_bytes, lds_allowed[brief ? 4 : (small ? 2 : 0) + (identity ? 1 : 0)]);
     if (e != hipSuccess) return (int)e;
     const int n_qt = (Tq + tile_rows - 1) / tile_rows;
-    // the most workgroups an XCD can need (find_work): its pairs, the last of them as single tiles of padded groups
-    const long long n_pairs = (n_qt + 1) / 2, most = (long long)max_groups * B * n_pairs / kXcds + 1;
-    const long long n_wg = kXcds * (most + (most < 2 * kXcdCus ? most : 2 * kXcdCus) + 4 * n_pairs);
+    // items are numbered in 32 bits (make_queue)
+    if ((long long)max_groups * B * (n_qt + 1) > 0x1fffffff) return (int)hipErrorInvalidConfiguration;
+    // One workgroup per CU, which draws tile after tile, from two rounds on; fewer tiles, and dense ones of at most two tiles of keys,
+    // have a workgroup each (as many as an XCD's queue can have items: its tiles, and room for two groups' where the last pairs are
+    // dealt as single tiles).  Drawing / a workgroup per tile or pair of tiles: 16 x 2043 positions, 32 heads in 8 clusters 556 / 569
+    // us, 12 x 900 behind 200, 52 in 8 270 / 279, 2 x 2043, 72 in 16 166 / 169, dense 64 x 300 behind 300, 32 heads 403 / 444, 16 x 400
+    // behind 200, 72 heads 247 / 261; but 1 x 2043, 32 in 8 (300 tiles) 53.9 / 51.9, dense 64 x 65, 72 heads
+    // 117.6 / 115.7; level within 1 % for short prompts of many rows (64 x 300, 32 in 8 198.1 / 196.8; 64 x 600 428 / 426).
+    const long long tiles_most = (long long)max_groups * B * n_qt, n_pairs = (n_qt + 1) / 2;
+    const long long per_xcd = ((long long)max_groups * B * n_pairs + kXcds - 1) / kXcds;
+    const bool drawn = tiles_most >= 2 * kXcds * kXcdCus && !(identity && n_keys <= 2 * kKTile);
+    const long long n_wg = drawn ? kXcds * kXcdCus : kXcds * (n_qt == 1 ? per_xcd : 2 * per_xcd + 4 * n_pairs);
     if (n_wg > 0x7fffffffLL) return (int)hipErrorInvalidConfiguration;
     return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(threads), lds_bytes, stream, ev,
                               static_cast<const char *>(q), static_cast<const char *>(kc), vt, groups, n_groups, H, k, Tq,
-                              q_start, Tc_cap, Tp, n_qt, max_groups, B, scale, out);
+                              q_start, Tc_cap, Tp, n_qt, max_groups, B, scale, out, tickets, ticket_stride);
 }
 
 }  // namespace chai

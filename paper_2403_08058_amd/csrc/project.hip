@@ -325,7 +325,9 @@ __device__ __forceinline__ int list_slots(const int32_t *__restrict__ rep, int n
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kJsWaves = 8, kJsUnits = kJCol / 8, kJsFewUnits = 4, kJsMaxUnits = 8;      // units of a head, and most of a workgroup
 constexpr int kJsWaveBytes = 20 * 1024;      // ring of a wave: two blocks at least
-constexpr int kJsPass = 32;                   // tokens that are multiplied at a time
+constexpr int kJsPass = 32;                  // the most tokens that are multiplied at a time
+// ... with so many units: more than 16 leave room in the rings for six
+constexpr int js_pass(int units) { return units <= kJsMaxUnits - 2 ? kJsPass : 16; }
 constexpr size_t kJsLdsBytes = (size_t)kJsWaves * kJsWaveBytes;
 
 // or over the wave, in every lane
@@ -379,12 +381,12 @@ __global__ __launch_bounds__(kJsWaves * 64) void project_stream_kernel(const cha
         use_lo = lane == i ? (unsigned)heads : use_lo;
         use_hi = lane == i ? (unsigned)(heads >> 32) : use_hi;
     }
-    // Units of a workgroup: as many as make (rounds of the chip) * (units + what a workgroup costs besides) least.  More than 16
-    // tokens at a time leave room in the rings for six.
+    // Units of a workgroup: as many as make (rounds of the chip) * (units + what a workgroup costs besides) least; none that would
+    // take two passes for the tokens of a head that stands once in every row.  (One that stands in several slots of a row has more.)
     int units = 1;
     unsigned long long least = ~0ull;
     int parts = kJsUnits;
-    const int most = B * Tn <= 16 ? MOST : min(MOST, kJsMaxUnits - 2);
+    const int most = B * Tn <= js_pass(MOST) ? MOST : min(MOST, kJsMaxUnits - 2);
     unroll<MOST>([&](auto i) {
         constexpr int u = i.value + 1, p = (kJsUnits + u - 1) / u;
         const unsigned long long cost = (unsigned long long)((used * p + kJCus - 1) / kJCus) * (unsigned)(u * D + 4096);
@@ -446,7 +448,7 @@ __global__ __launch_bounds__(kJsWaves * 64) void project_stream_kernel(const cha
     const auto x_rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<char *>(x), 0, -1, 0x00020000);
 #endif
 
-    // 8 XT tokens c0 .. with U units
+    // up to 8 XT tokens c0 .. with U units
     auto run = [&](int c0, auto u_, auto xt_) __attribute__((always_inline)) {
         constexpr int U = decltype(u_)::value, XT = decltype(xt_)::value, NB = (U + 1) / 2, TT = (XT + 1) / 2;
         constexpr int kLoads = U + XT, kBytes = kLoads * 1024, R = kJsWaveBytes / kBytes < 8 ? kJsWaveBytes / kBytes : 8;
@@ -537,10 +539,12 @@ __global__ __launch_bounds__(kJsWaves * 64) void project_stream_kernel(const cha
     auto pass = [&](int c0, auto u_) __attribute__((always_inline)) {
         const int left = n_items - c0;
         if (left <= 8) run(c0, u_, std::integral_constant<int, 1>{});
+        else if constexpr (js_pass(decltype(u_)::value) == 16) run(c0, u_, std::integral_constant<int, 2>{});
         else if (left <= 16) run(c0, u_, std::integral_constant<int, 2>{});
-        else if constexpr (decltype(u_)::value <= kJsMaxUnits - 2) run(c0, u_, std::integral_constant<int, 4>{});
+        else run(c0, u_, std::integral_constant<int, kJsPass / 8>{});
     };
-    for (int c0 = 0; c0 < n_items; c0 += kJsPass) {
+    const int step = js_pass(n_units);
+    for (int c0 = 0; c0 < n_items; c0 += step) {
         if (c0 != 0) list_pairs(c0 / Tn);
         unroll<MOST>([&](auto i) __attribute__((always_inline)) {
             if (n_units == i.value + 1) pass(c0, std::integral_constant<int, i.value + 1>{});

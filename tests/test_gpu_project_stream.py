@@ -1,5 +1,6 @@
 """GPU parity of the projection kernel that streams the weights for a few tokens per head, at the edges of its parts, passes and
 look-ups, against the CPU oracle with test_gpu_project's bar (a bf16 neighbour of the exact value)."""
+import numpy as np
 import pytest
 import torch
 
@@ -8,7 +9,12 @@ pytestmark = pytest.mark.gpu
 if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
-from test_gpu_project import run_case
+import paper_2403_08058_amd as C
+import workloads as W
+from oracle import chai_oracle as O
+
+from gpu_util import dev
+from test_gpu_project import check_rounded, run_case
 
 
 @pytest.mark.parametrize("B,H,kk,Tn,D", [
@@ -28,3 +34,54 @@ from test_gpu_project import run_case
 def test_projection_by_streamed_weights(B, H, kk, Tn, D):
     print(f"[project] B={B} H={H} k={kk} tokens={Tn} width={D}", flush=True)
     run_case(B, H, kk, Tn, D, 3, Tn + 7, seed=B * 5 + H * 3 + Tn + D, holes=B > 1 or kk > 4)
+
+
+def _repeats(B, H, kk, used, head, copies, past_the_end):
+    """Maps with `used` heads in use, `head` in the first copies[b] slots of row b, and a last slot of row 0 that names no head."""
+    others = [h for h in range(H) if h != head][:used - 1]
+    rep = np.full((B, kk), -1, np.int32)
+    at = 0
+    for b in range(B):
+        rep[b, :copies[b]] = head
+        for j in range(copies[b], kk - (1 if past_the_end and b == 0 else 0)):
+            if at < len(others):
+                rep[b, j] = others[at]
+                at += 1
+    assert at == len(others)
+    if past_the_end:
+        rep[0, kk - 1] = H + 3
+    return rep
+
+
+@pytest.mark.parametrize("B,H,kk,Tn,D,used,head,copies,past_the_end", [
+    (1, 72, 64, 8, 192, 63, 5, [2], False),                # eight units: 16 tokens of one head are one pass,
+    (1, 72, 64, 9, 1088, 63, 5, [2], False),               # 18 two; 3 blocks for the first wave
+    (1, 72, 64, 16, 128, 62, 71, [3], False),              # three whole passes, which begin with a slot each
+    (1, 80, 80, 1, 576, 64, 0, [17], False),               # 17 slots of one token
+    (1, 64, 48, 7, 128, 46, 9, [3], False),                # seven units, passes that begin inside a slot's tokens
+    (2, 72, 30, 8, 192, 47, 60, [2, 1], False),            # a repeat in one of two rows: 24 tokens
+    (2, 72, 30, 8, 192, 52, 60, [2, 2], False),
+    (4, 72, 16, 4, 320, 60, 71, [1, 1, 1, 1], True),       # an entry past the last head, whose tokens the last head gets
+    (2, 40, 20, 8, 128, 32, 3, [3, 3], False),             # at most six units: 48 tokens, 32 at a time
+])
+def test_streamed_projection_of_a_repeated_representative(B, H, kk, Tn, D, used, head, copies, past_the_end):
+    """A head that stands in several slots has more tokens than the batch has: every slot's keys and the head's queries are written,
+    whatever number of units a workgroup takes."""
+    print(f"[project] B={B} H={H} k={kk} tokens={Tn} width={D} used={used} copies={copies}", flush=True)
+    g = np.random.default_rng(used + Tn)
+    x, w_q, w_k = W.normal(g, (B, Tn, D), W.BF16), W.normal(g, (H * 128, D), W.BF16), W.normal(g, (H * 128, D), W.BF16)
+    rep = _repeats(B, H, kk, used, head, copies, past_the_end)
+    q_out = torch.zeros((B, H, Tn, 128), dtype=torch.bfloat16, device="cuda")
+    kc = torch.zeros((B, kk, Tn, 128), dtype=torch.bfloat16, device="cuda")
+    C.chai_project_qk(dev(x), dev(w_q), dev(w_k), dev(rep), q_out, kc, 0)
+    torch.cuda.synchronize()
+    q_ref, k_ref = O.project_qk(x, w_q, w_k, np.minimum(rep, H - 1), 128)
+    x64 = np.abs(W.as_f64(x))
+    aq, ak = np.abs(W.as_f64(w_q)).reshape(H, 128, D), np.abs(W.as_f64(w_k)).reshape(H, 128, D)
+    qh, kh = W.torch_to_host_bits(q_out), W.torch_to_host_bits(kc)
+    for b in range(B):
+        for j in range(kk):
+            r = int(rep[b, j])
+            if 0 <= r < H:
+                check_rounded(qh[b, r], q_ref[b, j], np.einsum("te,ce->tc", x64[b], aq[r]), f"q b={b} j={j}")
+                check_rounded(kh[b, j], k_ref[b, j], np.einsum("te,ce->tc", x64[b], ak[r]), f"k b={b} j={j}")

@@ -15,6 +15,9 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
+#include <cmath>
+#include <iterator>
 #include <type_traits>
 #include <utility>
 
@@ -303,6 +306,89 @@ __device__ __forceinline__ int list_slots(const int32_t *__restrict__ rep, int n
         __syncthreads();
     }
     return n_slots;
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// At most eight tokens, where the streamed weights (below) do not pay: narrow products, and more heads than they have rounds
+// for.  The call is bound by reading the representatives' weights once, or by its launch.  One workgroup
+// per (head, 16 output features), the 16 rows of a 16 x 16 x 32 MFMA tile: it looks up which (row, slot) pairs the head
+// represents -- none: done -- and gathers their tokens as the tile's columns.  The contraction is dealt to the 8 waves
+// in blocks of 64 elements (the workgroup walks 1 KB of every weight row per round), operands go from memory straight
+// into the MFMA registers -- a weight element is used by one workgroup only, LDS would be a detour --, kJrBlocks
+// blocks ahead, and the waves' fp32 sums are added in wave order.  grid (H * 16).  1 row x 1 token, 1000 of 1000 heads, D = 512 295 us (streamed 660), 256
+// of 256, D = 64 19.5 us (34.3).
+// ---------------------------------------------------------------------------------------------------------
+constexpr int kJrWaves = 8, kJrBlocks = 4;
+constexpr int kJrTokens = 8;                 // tokens of all rows up to which this kernel is faster than 64-token tiles
+constexpr int kJrParts = kJCol / 16;                 // workgroups per head
+
+__global__ __launch_bounds__(kJrWaves * 64) void project_rows_kernel(const char *__restrict__ x,
+                                                                     const char *__restrict__ w_q,
+                                                                     const char *__restrict__ w_k,
+                                                                     const int32_t *__restrict__ rep, int B, int H, int k,
+                                                                     int Tn, int D, char *__restrict__ q_out,
+                                                                     char *__restrict__ k_compact, int pos0, int Tc_cap)
+{
+    __shared__ int slots[kJtMaxSlots];
+    __shared__ int wave_slots[kJrWaves];
+    __shared__ f32x4 red[kJrWaves][64];
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int head = blockIdx.x / kJrParts, f0 = blockIdx.x % kJrParts * 16;     // features 0..127 query, 128..255 key
+
+    const int n_items = list_slots<kJrWaves>(rep, B * k, head, H, slots, wave_slots) * Tn;   // tokens of this head
+    const size_t row_bytes = (size_t)D * 2;
+    const int col = lane & 15, g = lane >> 4;        // operand row (weights) or token (activations), 8-element group
+    const char *wsrc = (f0 < kHeadDim ? w_q : w_k) + ((size_t)head * kHeadDim + (f0 & (kHeadDim - 1)) + col) * row_bytes + g * 16;
+    const int n_blk = D / 64;
+
+    for (int c0 = 0; c0 < n_items; c0 += 16) {
+        const int item = c0 + col, it = min(item, n_items - 1);      // columns past the end repeat the last token, unused
+        const int sl = slots[it / Tn], tok = it % Tn;
+        const char *xsrc = x + ((size_t)(sl / k) * Tn + tok) * row_bytes + g * 16;
+        f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+
+        // blocks w, w + 8, ... of 64 elements; a wave's surplus requests re-read the last block and are not used
+        struct Block {
+            Frag a[2], b[2];
+        };
+        auto request = [&](Block &bl, int blk) {
+            const size_t at = (size_t)min(blk, n_blk - 1) * 128;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                bl.a[i].raw = *reinterpret_cast<const u32x4 *>(wsrc + at + i * 64);
+                bl.b[i].raw = *reinterpret_cast<const u32x4 *>(xsrc + at + i * 64);
+            }
+        };
+        Block bl[kJrBlocks];
+#pragma unroll
+        for (int u = 0; u < kJrBlocks; ++u) request(bl[u], w + u * kJrWaves);
+        for (int b0 = w; b0 < n_blk; b0 += kJrBlocks * kJrWaves) {
+#pragma unroll
+            for (int u = 0; u < kJrBlocks; ++u) {
+                if (b0 + u * kJrWaves < n_blk) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bl[u].a[i].bf, bl[u].b[i].bf, acc, 0, 0, 0);
+                }
+                request(bl[u], b0 + (u + kJrBlocks) * kJrWaves);
+            }
+        }
+        red[w][lane] = acc;
+        __syncthreads();
+        // lane l holds features f0 + 4*(l/16) .. +3 of token l%16
+        if (w == 0 && item < n_items) {
+            f32x4 sum = red[0][lane];
+#pragma unroll
+            for (int i = 1; i < kJrWaves; ++i) sum += red[i][lane];
+            char *orow = f0 < kHeadDim ? q_out + ((((size_t)(sl / k) * H + head) * Tn) + tok) * (kHeadDim * 2)
+                                       : k_compact + ((size_t)sl * Tc_cap + pos0 + tok) * (kHeadDim * 2);
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)sum[e];
+            *reinterpret_cast<bf16x4 *>(orow + ((f0 & (kHeadDim - 1)) + g * 4) * 2) = o;
+        }
+        __syncthreads();
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -808,18 +894,46 @@ int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, co
                               static_cast<const u32x4 *>(buf), (unsigned long long)(bytes / 16), rounds, sink);
 }
 
-// Which calls project_stream_kernel takes: up to 32 tokens over all rows, so that a head's tokens are multiplied in one pass.  More of
-// them where the heads in use are few, B * Tn up to 64 (two passes; 64-token tiles / this kernel in us: 1 x 64, 8 of 32, D 4096
-// 20.8 / 14.5; 16 x 4, 8 of 32 24.4 / 20.9; 16 x 4, 8 of 52, D 6656 37.3 / 32.8; 1 x 64, 16 of 72, D 9216 49.2 / 37.0; but 6 x 10, 16 of
-// 72 51.9 / 55.0; 4 x 16, 40 of 40, D 5120 35.8 / 42.7).  Not where many rows use most of 40 to 70 heads, enough 64-column tiles for
-// every CU and few tokens short of full ones (16 x 1, 16 of 72 45.5 / 46.7; 16 x 2 47.8 / 50.8; 12 x 2 45.2 / 48.3; 16 x 1, 16 of 52
-// 33.1 / 34.0; but 9 x 1, 16 of 72 42.3 / 42.0, 8 x 4 44.9 / 42.7, 16 x 1, 10 of 72 39.3 / 30.8 and 8 x 1, 72 of 72 87.8 / 67.1).
-static bool project_streams(int B, int H, int k, int Tn)
+// Which calls project_stream_kernel takes.  Its workgroups need a CU each, so that what they save by streaming is lost again where
+// they are several rounds, and more tokens of a head than 16 cost it passes or units.  What decides is therefore how many heads are
+// in use (if the rows' maps are independent: H (1 - (1 - k/H)^B), the maps themselves are on the device), how many tokens such a head
+// has, and the width, against the kernel that the call takes otherwise: project_rows_kernel up to 8 tokens over all rows,
+// 64-token tiles above.  The lines lie where the two were level over 14 000 calls drawn at random (1 to 64 tokens, 1 to 600 heads,
+// widths 64 to 9216, weights in no cache); right of them the other kernel is ahead in 1 call of 30, by 5 % or more in 1 of 80.
+// Other kernel / this one in us, D = 4096 unless noted:
+// * up to 8 tokens: 1 x 1, 8 of 32 heads 12.0 / 7.3; 8 x 1, 72 of 72, D 9216 87.8 / 67.1; 4 x 1, 16 of 72, D 9216 41.8 / 30.4; 1 x 1, 128 of
+//   128, D 512 38.5 / 18.2; but 256 of 256, D 64 19.5 / 34.3, and 64 of 64, D 8192 52.4 / 63.5 (below).
+// * 9 to 32: 16 x 1, 8 of 32 20.1 / 14.1; 1 x 32, 8 of 32 18.6 / 10.1; 16 x 1, 10 of 72, D 9216 39.3 / 30.8; but 2 x 16, 72 of 72, D 1024
+//   12.5 / 18.5, 1 x 32, 64 of 72, D 9216 55.1 / 65.0, 32 x 1, 12 of 256, D 1024 8.9 / 25.7, 16 x 1, 16 of 72, D 9216 45.5 / 46.7.
+// * 33 to 64: 1 x 64, 8 of 32 20.8 / 14.5; 16 x 4, 8 of 32 24.0 / 21.4; 1 x 64, 16 of 72, D 9216 49.2 / 37.0; but 6 x 10, 16 of 72, D 9216 51.9 / 55.0, 2 x 32, 8 of 40, D
+//   512 6.9 / 7.7.
+// * where the call would be 256-token tiles (more pairs than are listed in LDS, or more heads than are counted there): 16 x 1, 72 of 72,
+//   D 9216 1032 / 79; 64 x 1, 40 of 40, D 1024 285 / 46; but 2 x 1, 600 of 600, D 512 87 / 357, and every wave looks through all
+//   pairs for every 64 heads: 1 x 1, 2000 of 2000, D 512 161 / 4990.
+static bool project_streams(int B, int H, int k, int Tn, int D)
 {
     const long long tokens = (long long)B * Tn, pairs = (long long)B * k, heads = H < pairs ? H : pairs;
     if (tokens > 64) return false;
-    if (tokens > 32 && (pairs * Tn > 1024 || (k > 8 && pairs > 64))) return false;
-    return !(heads > 32 && k > 12 && B >= 6 && tokens >= 12);
+    if (pairs > kJtMaxSlots || (H > kJtMaxHeads && tokens > kJrTokens))
+        return heads <= 128 || (heads <= 320 && D >= (heads <= 200 ? 1024 : 8 * heads));
+    if (H > kJtMaxHeads && heads <= 128) return true;        // (the other kernel starts 16 workgroups for every head there is)
+    const double used = H * (1.0 - pow(1.0 - (double)k / H, B)), each = (double)(pairs * Tn) / used;
+    if (tokens <= kJrTokens) {
+        // Eight units leave the rings two blocks.  With rows that all begin on the same memory channels that is not enough.
+        if (((used > 51.5 && used < 64.5) || (used > 102.5 && used < 128.5)) && D % 4096 == 0 && tokens <= D / 2048) return false;
+        return used < 256.5 && D >= (H <= 16 ? 2560 : (used < 8.5 ? 1024 : (used < 42.5 || used > 128.5 ? 512 : 256)));
+    }
+    // at most so many heads in use, so many tokens of each, and at least this width
+    struct Line {
+        double used, each;
+        int width;
+    };
+    static const Line to32[] = {{16, 32, 1024}, {32, 16, 1536}, {32, 32, 2560}, {42, 4, 2048}, {42, 32, 2560},
+                                {51, 4, 2048},  {64, 2, 2048},  {64, 4, 2560},  {51, 8, 4096}, {85, 3, 4096}};
+    static const Line to64[] = {{8, 64, 2048}, {16, 32, 2560}, {16, 64, 5120}, {32, 17, 2560},
+                                {42, 8, 2560}, {64, 4, 2560},  {51, 8, 5120},  {85, 4, 4096}};
+    auto within = [&](const Line &l) { return used < l.used + 0.01 && each < l.each + 0.01 && D >= l.width; };
+    return tokens <= 32 ? std::any_of(std::begin(to32), std::end(to32), within) : std::any_of(std::begin(to64), std::end(to64), within);
 }
 
 int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int32_t *rep, int B, int H, int k, int Tn,
@@ -831,7 +945,7 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     // Which kernel: by the number of tokens over all (row, slot) pairs, in time per call (before: 256-token tiles for
     // every size; D = 4096 unless noted).  A 256-token tile of one (row, slot) pair is a chain of D/64 stages however
     // few tokens it holds, so calls with few tokens took 77-86 us (170-215 us at D = 9216) at any size:
-    //   few tokens per head project_stream_kernel, see there and project_streams
+    //   few tokens          project_stream_kernel, see there and project_streams; up to 8 project_rows_kernel where that one does not pay
     //   B*k*Tn <= most      64-token tiles, head-major: B 16, k 8, Tn 16 / 64 / 128: 82 / 82 / 85 -> 20 / 32 / 62 us; B 1, k 8, Tn
     //                       512 / 2043: 85 / 87 -> 21 / 60 us; B 4, k 16, D 9216, Tn 256: 215 -> 135 us; B 4, k 8, D 6656, Tn 512:
     //                       151 -> 95 us
@@ -845,11 +959,10 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
     //   B 16, k 10 (160), Tn 140, D 6656: 146 / 137
     //   B 16, k 16 (256), Tn 72 / 80 / 96: (72) D 9216 227 / 194, D 4096 (80) 97 / 86 and (96) 98 / 114
     //   B 16, k 32 (512), Tn 48: D 512 42 / 27, D 4096 194 / 91
-    // The small tiles list the pairs of a head in LDS (at most kJtMaxSlots of them); 16 x 1 tokens of 72 of 72 heads, which are more,
-    // took 1058 us as 256-token tiles.
+    // The small tiles and project_rows_kernel list the pairs of a head in LDS (at most kJtMaxSlots of them).
     const long long items = (long long)B * k * Tn;
     const bool listed = (long long)B * k <= kJtMaxSlots;
-    if (project_streams(B, H, k, Tn) || (!listed && (long long)B * Tn <= 64)) {
+    if (project_streams(B, H, k, Tn, D)) {
         // one round of the chip, or two, or what the most units of a workgroup ask for
         const int heads = H < B * k ? H : B * k, most = heads * ((kJsUnits + kJsMaxUnits - 3) / (kJsMaxUnits - 2));
         const bool few = heads <= kJCus / (kJsUnits / kJsFewUnits);
@@ -861,6 +974,9 @@ int launch_project_qk(const void *x, const void *w_q, const void *w_k, const int
         return (int)launch_kernel(kernel, dim3((unsigned int)n_wg), dim3(kJsWaves * 64), kJsLdsBytes, stream, ev, xc, wq, wk, rep, B, H, k, Tn,
                                   D, qo, ko, pos0, Tc_cap);
     }
+    if (listed && (long long)B * Tn <= kJrTokens && H <= 0x7fffffff / kJrParts)
+        return (int)launch_kernel(project_rows_kernel, dim3((unsigned int)H * kJrParts), dim3(kJrWaves * 64), 0, stream, ev,
+                                  xc, wq, wk, rep, B, H, k, Tn, D, qo, ko, pos0, Tc_cap);
     // (the tile kernel addresses the activations and one head's weights with 32-bit byte offsets below 2 GiB)
     const long long n_large = (long long)B * k * ((Tn + kJTok - 1) / kJTok);
     const bool one_round = n_large <= 150 && D < 8192;

@@ -1,5 +1,6 @@
 """GPU parity of the projection kernel that streams the weights for a few tokens per head, at the edges of its parts, passes and
-look-ups, against the CPU oracle with test_gpu_project's bar (a bf16 neighbour of the exact value)."""
+look-ups, and of the calls on either side of the lines to the other kernels, against the CPU oracle with test_gpu_project's bar (a bf16
+neighbour of the exact value)."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,7 @@ from test_gpu_project import check_rounded, run_case
     (5, 8, 8, 7, 128), (3, 6, 6, 21, 64),                              # passes that begin inside a row's tokens
     (16, 40, 12, 2, 128), (16, 40, 13, 1, 128),                        # either side of the line to the 64-token tiles
     (1, 40, 8, 64, 64), (8, 40, 9, 5, 64), (17, 33, 33, 3, 64),        # the same for more than 32 tokens
-    (64, 20, 17, 1, 64), (64, 4, 4, 1, 64),                            # more pairs than the 64-token tiles list
+    (64, 20, 17, 1, 64), (64, 4, 4, 1, 64),                            # more pairs than the 64-token tiles list; a quarter of what they do
     (1, 4200, 3, 2, 64),                                               # more heads than a wave's lanes have windows for
 ])
 def test_projection_by_streamed_weights(B, H, kk, Tn, D):
@@ -54,15 +55,16 @@ def _repeats(B, H, kk, used, head, copies, past_the_end):
 
 
 @pytest.mark.parametrize("B,H,kk,Tn,D,used,head,copies,past_the_end", [
-    (1, 72, 64, 8, 192, 63, 5, [2], False),                # eight units: 16 tokens of one head are one pass,
-    (1, 72, 64, 9, 1088, 63, 5, [2], False),               # 18 two; 3 blocks for the first wave
-    (1, 72, 64, 16, 128, 62, 71, [3], False),              # three whole passes, which begin with a slot each
+    (1, 72, 64, 8, 320, 63, 5, [2], False),                # eight units: 16 tokens of one head are one pass,
+    (1, 72, 64, 6, 1088, 62, 5, [3], False),               # 18 two; 3 blocks for the first wave
+    (1, 72, 64, 8, 256, 60, 71, [5], False),               # three, each of whole slots
     (1, 80, 80, 1, 576, 64, 0, [17], False),               # 17 slots of one token
-    (1, 64, 48, 7, 128, 46, 9, [3], False),                # seven units, passes that begin inside a slot's tokens
-    (2, 72, 30, 8, 192, 47, 60, [2, 1], False),            # a repeat in one of two rows: 24 tokens
-    (2, 72, 30, 8, 192, 52, 60, [2, 2], False),
-    (4, 72, 16, 4, 320, 60, 71, [1, 1, 1, 1], True),       # an entry past the last head, whose tokens the last head gets
-    (2, 40, 20, 8, 128, 32, 3, [3, 3], False),             # at most six units: 48 tokens, 32 at a time
+    (1, 64, 48, 7, 320, 46, 9, [3], False),                # seven units, passes that begin inside a slot's tokens
+    (2, 72, 30, 4, 320, 47, 60, [3, 2], False),            # repeats in two rows: 20 tokens
+    (4, 72, 16, 4, 4096, 60, 71, [1, 1, 1, 1], True),      # an entry past the last head, whose tokens the last head gets
+    (2, 72, 40, 4, 256, 58, 71, [2, 2], True),
+    (2, 52, 20, 4, 512, 32, 3, [3, 3], False),             # at most six units: 24 tokens at once
+    (1, 40, 36, 8, 512, 32, 3, [5], False),                # 40 in two passes
 ])
 def test_streamed_projection_of_a_repeated_representative(B, H, kk, Tn, D, used, head, copies, past_the_end):
     """A head that stands in several slots has more tokens than the batch has: every slot's keys and the head's queries are written,
@@ -85,3 +87,18 @@ def test_streamed_projection_of_a_repeated_representative(B, H, kk, Tn, D, used,
             if 0 <= r < H:
                 check_rounded(qh[b, r], q_ref[b, j], np.einsum("te,ce->tc", x64[b], aq[r]), f"q b={b} j={j}")
                 check_rounded(kh[b, j], k_ref[b, j], np.einsum("te,ce->tc", x64[b], ak[r]), f"k b={b} j={j}")
+
+
+@pytest.mark.parametrize("B,H,kk,Tn,D", [
+    (1, 32, 8, 1, 1024), (1, 32, 8, 8, 960),                           # few heads: one unit each; just too narrow to be streamed
+    (1, 32, 9, 1, 512), (1, 32, 9, 3, 448), (1, 40, 17, 1, 576), (1, 40, 24, 1, 512), (1, 52, 40, 2, 512),
+    (1, 64, 51, 1, 256), (1, 64, 51, 1, 192), (1, 64, 64, 2, 4096), (1, 64, 64, 3, 4096),      # rows on the same memory channels
+    (1, 256, 200, 1, 512), (2, 300, 150, 1, 512), (1, 257, 128, 8, 64), (1, 600, 300, 4, 448),
+    (1, 4, 3, 8, 2560), (1, 4, 3, 9, 1024), (1, 4, 3, 16, 1024), (1, 4, 3, 17, 1024), (1, 4, 3, 32, 1024), (1, 4, 3, 32, 960),
+    (1, 4, 3, 33, 2048), (2, 4, 3, 32, 2048), (5, 8, 8, 7, 2048), (3, 6, 6, 21, 2048), (1, 40, 40, 17, 2560),
+    (16, 40, 12, 2, 2560), (16, 40, 12, 2, 2496), (1, 40, 8, 64, 2048), (1, 52, 51, 8, 4096), (1, 52, 52, 8, 4096),
+    (16, 72, 72, 1, 1088), (4, 300, 2, 4, 128), (2, 400, 200, 16, 576),      # no other kernel but 256-token tiles
+])
+def test_projection_on_either_side_of_the_lines(B, H, kk, Tn, D):
+    print(f"[project] B={B} H={H} k={kk} tokens={Tn} width={D}", flush=True)
+    run_case(B, H, kk, Tn, D, 3, Tn + 7, seed=B * 5 + H * 3 + Tn + D, holes=B > 1 or kk > 4)

@@ -390,10 +390,9 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 //  * 4200 for the distances, 3 fp64 operations per coordinate at 8 cycles each.  Here matrix instructions take them in fp32 first, 16
 //    heads and 16 centres per wave, as s = |c|^2 / 2 - x c, and fp64 only those centres that can still be the nearest.  With
 //    u = 2^-24 and M the largest |x|^2 (a centre is a mean of heads, or one: |c|^2 <= M, |x| |c| <= M) the F products of x c, each
-//    rounded at most twice and of a centre rounded to fp32, are off by less than (2F + 2) u M, |c|^2 / 2 by (F + 2) u M, the sum of
-//    the two chains that they are added up in by u M, so that a
-//    centre whose s exceeds the least by more than 2 (3F + 5) u M has the larger distance, in fp64 as well (whose own error is 2^-28
-//    of this).  Twice 2 (3F + 4) u M, which is more from F = 9 on, is allowed for, and 1e-30 for what underflows.  One centre left: it is the nearest.  Where a value is not
+//    rounded at most twice and of a centre rounded to fp32, are off by less than (2F + 2) u M, |c|^2 / 2 by (F + 2) u M, so that a
+//    centre whose s exceeds the least by more than 2 (3F + 4) u M has the larger distance, in fp64 as well (whose own error is 2^-28
+//    of this).  Twice that is allowed for, and 1e-30 for what underflows.  One centre left: it is the nearest.  Where a value is not
 //    finite all centres are taken in fp64.
 //  * 2900 for walking the members' bits, word by word.  Here every head ranks itself among its cluster's and the sum goes along a
 //    list of members, four per word.
@@ -401,7 +400,7 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 // The numbering at the end ranks the centres by readlane in one wave; fp64 distances to the own centre, which the repair of empty
 // centres asks for, are taken there.  A pass takes 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
 // start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 4 problems of 72 heads, 16 centres and 25
-// coordinates, 18.7 with up to sixteen members of a sum requested at a time; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
+// coordinates (seven passes), 8 of 128 heads 28.4 -> 26.9 in ten passes with the words of both masks requested at once; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
 // launching (up to 40 heads) takes what it did.  Where most passes need the 64-bit distances of all centres (problems of a few tight
 // clusters) it is level with the general kernel: 71.9 and 71.6 us for 8 of 256 heads, 16 centres, 25 coordinates.
 // Dynamic LDS (FastLayout): centres [k][FP] fp64, features [H][FP] fp32, centres [16 n][C32] fp32, masks, lists of members, ...
@@ -447,7 +446,8 @@ __device__ __forceinline__ T over_groups(T x, Op op)
     return op(value(b[0]), value(b[1]));
 }
 
-template <int F>
+// FEW: at most 128 heads, four words of a mask
+template <int F, bool FEW>
 __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__restrict__ feat, int H, int k,
                                                                  const int32_t *__restrict__ init_heads, int max_iter,
                                                                  int32_t *__restrict__ h2c, int32_t *__restrict__ rep,
@@ -555,13 +555,9 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
                     for (int t = 0; t < G; ++t) c2 = __builtin_fmaf(c[t], c[t], c2);
                     c2 = over_groups(c2, [](float p, float q) { return p + q; });
                     if (g == 3) c[G - 1] = 0.5f * c2;
-                    km_f32x4 acc = {0.f, 0.f, 0.f, 0.f}, odd = acc;      // x c - |c|^2 / 2, in two chains (|c|^2 last)
+                    km_f32x4 acc = {0.f, 0.f, 0.f, 0.f};     // x c - |c|^2 / 2
 #pragma unroll
-                    for (int t = 0; t < G; t += 2) {
-                        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t], xr[t], acc, 0, 0, 0);
-                        odd = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t + 1], xr[t + 1], odd, 0, 0, 0);
-                    }
-                    acc = acc + odd;
+                    for (int t = 0; t < G; ++t) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(c[t], xr[t], acc, 0, 0, 0);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const bool there = i * 16 + 4 * g + e < k;
@@ -646,7 +642,7 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
         int rank, ignored, n_mine;
         bool empty;
         const int mine = max(min(prev, k - 1), 0);           // (lanes without a head: any centre)
-        if (W <= 4) {                                        // all words of both centres requested at once
+        if constexpr (FEW) {                                 // all words of both centres requested at once
             unsigned own[4], seen[4], any = 0u;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -707,25 +703,13 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_fast_kernel(const float *__
             const unsigned *row = reinterpret_cast<const unsigned *>(list + j * L.LS);
             const int last = L.LS / 4 - 1;
             double acc = 0.0;
-            constexpr int kMost = F <= 25 ? 16 : 8;          // members requested at a time (more would not leave the registers for 1024
-            for (int m = 0; m < n; m += kMost) {             // threads; whatever the list holds is a head)
-                unsigned word[4];
+            for (int m = 0; m < n; m += 8) {                 // eight members requested at a time (whatever the list holds is a head)
+                const unsigned w0 = row[m / 4], w1 = row[min(m / 4 + 1, last)];
+                float v[8];
 #pragma unroll
-                for (int u = 0; u < kMost / 4; ++u) word[u] = row[min(m / 4 + u, last)];
-                float v[16];
-                auto request = [&](int u0) {
+                for (int u = 0; u < 8; ++u) v[u] = x_lds[(((u < 4 ? w0 : w1) >> (8 * (u & 3))) & 0xffu) * FP + f];
 #pragma unroll
-                    for (int u = u0; u < u0 + 8; ++u) v[u] = x_lds[((word[u >> 2] >> (8 * (u & 3))) & 0xffu) * FP + f];
-                };
-                auto add = [&](int u0) {
-#pragma unroll
-                    for (int u = u0; u < u0 + 8; ++u) acc = acc + (double)(m + u < n ? v[u] : -0.0f);      // (-0 changes no sum)
-                };
-                const bool more = kMost > 8 && __any(m + 8 < n);
-                request(0);
-                if (more) request(8);
-                add(0);
-                if (more) add(8);
+                for (int u = 0; u < 8; ++u) acc = acc + (double)(m + u < n ? v[u] : -0.0f);      // (-0 changes no sum)
             }
             if (n != 0) {
                 const double mean = acc / (double)n;
@@ -863,7 +847,7 @@ static bool launch_fast(const float *feat, int B, int H, int k, const int32_t *i
     int n_thr = (H + 15) / 16 * 64;
     const int update = (k * F + 63) / 64 * 64;
     if (n_thr < update) n_thr = update < 512 ? update : (n_thr < 512 ? 512 : n_thr);
-    status = (int)launch_kernel(kmeans_fast_kernel<F>, dim3(B), dim3(n_thr), L.bytes, stream, KernelEvents(), feat, H, k, init_heads,
+    status = (int)launch_kernel(H <= 128 ? kmeans_fast_kernel<F, true> : kmeans_fast_kernel<F, false>, dim3(B), dim3(n_thr), L.bytes, stream, KernelEvents(), feat, H, k, init_heads,
                                 max_iter, h2c, rep, ncl, iters);
     return true;
 }

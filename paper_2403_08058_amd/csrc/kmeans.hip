@@ -15,10 +15,12 @@ namespace {
 
 // ---------------------------------------------------------------------------------------------------------
 // Features: grid (H, B), one wave per head.  The 128-term fp64 dot product of a causal (i, j) pair is one chain of sums in element
-// order; SL neighbouring lanes share a pair: each converts and multiplies its 128 / SL elements at the same time as the others,
-// and then they continue the chain one after the other.  (One lane per pair did all of a pair's conversions and products
-// itself: 6.3 us for 4 x 72 heads, the kernel alone, now 4.2; the membership step of 4 x 72 heads 27.3 -> 24.5 with
-// the shorter sums of k-means.)  A pair's last lane then has its score; lane p takes pair p's element of the softmax.
+// order.  Up to five positions (15 pairs) four neighbouring lanes share a pair: each converts and multiplies its 32 elements at the
+// same time as the others, and then they continue the chain one after the other.  (One lane per pair did all of a pair's conversions
+// and products itself: 6.3 us for 4 x 72 heads, the kernel alone, now 4.2; 300 x 128 heads, five positions 64.1 -> 36.7 us a call.)
+// More positions have a lane per pair, which adds a product as soon as it is there: two lanes per pair of six or seven positions, or
+// one that held all its products, took registers that cost more waves than they saved time (300 x 128 heads, seven positions 72.0 -> 87.7
+// us, eight 77.4 -> 167.4).  A pair's last lane then has its score; lane p takes pair p's element of the softmax.
 // ---------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ double from_lane_before(double x)
 {
@@ -38,63 +40,73 @@ __global__ __launch_bounds__(64) void feature_kernel(const void *__restrict__ q5
     const size_t head = (size_t)b * H + h;
 
     // pair -> (i, j) with j <= i, row by row
-    auto pair_of = [&](int p, int &i, int &j) {
-        i = 0;
-        j = p;
-        while (i < n_tok && j > i) { j -= i + 1; ++i; }
-    };
-    int i, j;
-    pair_of(lane / SL, i, j);
-    const int slice = lane % SL, si = min(i, n_tok - 1), sj = min(j, n_tok - 1);      // (lanes without a pair repeat another's loads)
+    int i = 0, j = lane / SL;
+    while (i < n_tok && j > i) { j -= i + 1; ++i; }
+    // (of four lanes per pair nearly all have one: the others repeat a pair's loads)
+    const int slice = lane % SL, si = SL > 1 ? min(i, n_tok - 1) : i, sj = SL > 1 ? min(j, n_tok - 1) : j;
     const size_t qo = head * (size_t)qs + (size_t)si * kHeadDim + slice * kElems;
     const size_t ko = head * (size_t)ks + (size_t)sj * kHeadDim + slice * kElems;
-    double prod[kElems];
+    double prod[SL > 1 ? kElems : 1], acc = 0.0;
+    auto take = [&](int e, double p) {
+        if constexpr (SL > 1) prod[e] = p;
+        else acc = acc + p;
+    };
     // 16-byte loads (rows start on 16-byte boundaries: the strides are multiples of 8 elements), all of a lane's requested at once
-    if (bf16) {
-        const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(q5) + qo);
-        const uint4 *kv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(k5) + ko);
-        uint4 qr[kElems / 8], kr[kElems / 8];
+    if (SL > 1 || i < n_tok) {
+        if (bf16) {
+            const uint4 *qv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(q5) + qo);
+            const uint4 *kv = reinterpret_cast<const uint4 *>(static_cast<const unsigned short *>(k5) + ko);
+            uint4 qr[kElems / 8], kr[kElems / 8];
 #pragma unroll
-        for (int c8 = 0; c8 < kElems / 8; ++c8) {
-            qr[c8] = qv[c8];
-            kr[c8] = kv[c8];
-        }
+            for (int c8 = 0; c8 < kElems / 8; ++c8) {
+                qr[c8] = qv[c8];
+                kr[c8] = kv[c8];
+            }
 #pragma unroll
-        for (int c8 = 0; c8 < kElems / 8; ++c8) {
-            const unsigned int aw[4] = {qr[c8].x, qr[c8].y, qr[c8].z, qr[c8].w}, bw[4] = {kr[c8].x, kr[c8].y, kr[c8].z, kr[c8].w};
+            for (int c8 = 0; c8 < kElems / 8; ++c8) {
+                const unsigned int aw[4] = {qr[c8].x, qr[c8].y, qr[c8].z, qr[c8].w}, bw[4] = {kr[c8].x, kr[c8].y, kr[c8].z, kr[c8].w};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const unsigned int abits = (e & 1) ? (aw[e >> 1] & 0xffff0000u) : (aw[e >> 1] << 16);
-                const unsigned int bbits = (e & 1) ? (bw[e >> 1] & 0xffff0000u) : (bw[e >> 1] << 16);
-                prod[c8 * 8 + e] = (double)__uint_as_float(abits) * (double)__uint_as_float(bbits);
+                for (int e = 0; e < 8; ++e) {
+                    const unsigned int abits = (e & 1) ? (aw[e >> 1] & 0xffff0000u) : (aw[e >> 1] << 16);
+                    const unsigned int bbits = (e & 1) ? (bw[e >> 1] & 0xffff0000u) : (bw[e >> 1] << 16);
+                    take(c8 * 8 + e, (double)__uint_as_float(abits) * (double)__uint_as_float(bbits));
+                }
+            }
+        } else {
+            const float4 *qv = reinterpret_cast<const float4 *>(static_cast<const float *>(q5) + qo);
+            const float4 *kv = reinterpret_cast<const float4 *>(static_cast<const float *>(k5) + ko);
+            constexpr int kPieces = (SL == 1 ? kElems / 2 : kElems) / 4;      // requested at once
+#pragma unroll
+            for (int c0 = 0; c0 < kElems / 4; c0 += kPieces) {
+                float4 qr[kPieces], kr[kPieces];
+#pragma unroll
+                for (int c4 = 0; c4 < kPieces; ++c4) {
+                    qr[c4] = qv[c0 + c4];
+                    kr[c4] = kv[c0 + c4];
+                }
+#pragma unroll
+                for (int c4 = 0; c4 < kPieces; ++c4) {
+                    const float av[4] = {qr[c4].x, qr[c4].y, qr[c4].z, qr[c4].w}, bv[4] = {kr[c4].x, kr[c4].y, kr[c4].z, kr[c4].w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) take((c0 + c4) * 4 + e, (double)av[e] * (double)bv[e]);
+                }
             }
         }
-    } else {
-        const float4 *qv = reinterpret_cast<const float4 *>(static_cast<const float *>(q5) + qo);
-        const float4 *kv = reinterpret_cast<const float4 *>(static_cast<const float *>(k5) + ko);
-        float4 qr[kElems / 4], kr[kElems / 4];
-#pragma unroll
-        for (int c4 = 0; c4 < kElems / 4; ++c4) {
-            qr[c4] = qv[c4];
-            kr[c4] = kv[c4];
-        }
-#pragma unroll
-        for (int c4 = 0; c4 < kElems / 4; ++c4) {
-            const float av[4] = {qr[c4].x, qr[c4].y, qr[c4].z, qr[c4].w}, bv[4] = {kr[c4].x, kr[c4].y, kr[c4].z, kr[c4].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) prod[c4 * 4 + e] = (double)av[e] * (double)bv[e];
-        }
+        if (SL == 1) s[i][j] = scale * acc;
     }
     // stage st: the pair's lane number st goes on from where the lane before it has come to (what the others add up is not used)
-    double acc = 0.0;
+    if constexpr (SL > 1) {
 #pragma unroll
-    for (int st = 0; st < SL; ++st) {
-        if (st > 0) acc = from_lane_before(acc);
+        for (int st = 0; st < SL; ++st) {
+            if (st > 0) acc = from_lane_before(acc);
 #pragma unroll
-        for (int e = 0; e < kElems; ++e) acc = acc + prod[e];
+            for (int e = 0; e < kElems; ++e) acc = acc + prod[e];
+        }
+        if (i < n_tok && slice == SL - 1) s[i][j] = scale * acc;
+        i = 0;
+        j = lane;
+        while (i < n_tok && j > i) { j -= i + 1; ++i; }
     }
-    if (i < n_tok && slice == SL - 1) s[i][j] = scale * acc;
-    pair_of(lane, i, j);
     __syncthreads();
     // every pair's lane takes its own exponential and its own division (one lane per row took up to eight of each in a
     // row); the row sum is added in column order by all of them
@@ -820,8 +832,7 @@ __global__ __launch_bounds__(kBlock) void cluster_error_kernel(const float *__re
 int launch_score_features(const void *q5, const void *k5, int B, int H, int n_tok, int dtype, int64_t qs, int64_t ks,
                           float scale, float *feat, hipStream_t stream)
 {
-    // pairs: 15 of five positions, 28 of seven, 36 of eight
-    auto *kernel = n_tok <= 5 ? feature_kernel<4> : (n_tok <= 7 ? feature_kernel<2> : feature_kernel<1>);
+    auto *kernel = n_tok <= 5 ? feature_kernel<4> : feature_kernel<1>;       // 15 pairs of five positions, 21 of six
     return (int)launch_kernel(kernel, dim3(H, B), dim3(64), 0, stream, KernelEvents(), q5, k5, H, n_tok,
                               dtype == CHAI_BF16 ? 1 : 0, (long long)qs, (long long)ks, (double)scale, feat);
 }

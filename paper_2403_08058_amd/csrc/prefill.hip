@@ -515,6 +515,15 @@ struct OpSchedule {
     }
 };
 
+// x is what is loaded, here (what is worked out from it by both sides of a branch is not worked out before the branch, where it
+// would wait for the load)
+__device__ __forceinline__ void hold(u32x4 &x)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(x));
+#endif
+}
+
 // What is left to do for a query tile whose accumulators are complete
 template <int U>
 struct Finished {
@@ -746,7 +755,7 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
         char *row0[NM];
 #pragma unroll
         for (int g = 0; g < NM; ++g) row0[g] = reinterpret_cast<char *>(out + ((DIRECT ? brow * H + heads[g] : done.b * H + done.heads[g]) * Tq + done.i0) * kHeadDim);
-        unroll<4 * U>([&](auto c) {
+        auto eight_rows = [&](auto c) __attribute__((always_inline)) {
             constexpr int u = c.value / 4, rows = 32 * u + 8 * (c.value % 4);
             const std::integral_constant<int, c.value % 4> quad;
             float inv[4];
@@ -760,7 +769,15 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
                     store_row(row0[g.value], n_rows, at + rows * (kHeadDim * 4) + e * (kHeadDim * 4), y);
                 }
             });
-        });
+        };
+        if constexpr (DIRECT || BUFS == 2) {
+            unroll<2>(eight_rows);
+            if (n_rows > 16) {                               // (short blocks: half of the stores would be of rows that are not there)
+                acc_settle();
+                unroll<2>([&](auto c) __attribute__((always_inline)) { eight_rows(std::integral_constant<int, c.value + 2>{}); });
+            }
+        } else
+            unroll<4 * U>(eight_rows);
     };
 
     struct Prob {
@@ -949,15 +966,8 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
     Raw raw_a, raw_b;                                        // DIRECT: tiles 0, 2, .. and 1, 3, ..
     if (has_tile) {
         dma_k(0, 0);
-        dma_q();
-        if constexpr (DIRECT) {
-            __builtin_amdgcn_sched_barrier(0);
-            unroll<kKeys>([&](auto i) { fetch_key(raw_a, 0, i); });
-            __builtin_amdgcn_sched_barrier(0);
-            dma_k(min(1, n_tiles - 1), 1);
-            unroll<kKeys>([&](auto i) { fetch_key(raw_b, min(1, n_tiles - 1), i); });
-            __builtin_amdgcn_sched_barrier(0);
-        } else {
+        if constexpr (!DIRECT) {
+            dma_q();
             dma_v(0, 0);
             if (BUFS > 2 && n_tiles > 1) dma_k(1, 1);
         }
@@ -977,15 +987,30 @@ __device__ __forceinline__ void prefill_tile(char *k_lds, char *v_lds, const cha
             for (int ks = 0; ks < kHeadDim / 16; ++ks) qf[u][ks].raw = k_frag(q_lds + (u * 32 + r) * (kHeadDim * 2), ks);
     };                                                       // (before the barrier: behind it the other waves' values come here)
     if constexpr (DIRECT) {
+        auto first_values = [&]() {
+            __builtin_amdgcn_sched_barrier(0);
+            unroll<kKeys>([&](auto i) { hold(raw_a.key[i.value]); });
+            unroll<8>([&](auto u) {
+                convert(raw_a, u);
+                store_unit(0, u);
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        };
         __builtin_amdgcn_sched_barrier(0);
-        unroll<8>([&](auto u) {
-            convert(raw_a, u);
-            store_unit(0, u);
-        });
+        unroll<kKeys>([&](auto i) { fetch_key(raw_a, 0, i); });
         __builtin_amdgcn_sched_barrier(0);
-        unroll<kKeys>([&](auto i) { fetch_key(raw_a, min(2, n_tiles - 1), i); });
-        __builtin_amdgcn_sched_barrier(0);
-        landed(std::integral_constant<int, 2 * kKeys>{});                    // behind the keys of tiles 0 and 1: the values of 1 and 2
+        dma_q();                                             // (they and what follows land under the conversion of the values)
+        if (n_tiles == 1) {                                  // no requests that nobody reads
+            first_values();
+            landed(std::integral_constant<int, 0>{});
+        } else {
+            dma_k(1, 1);
+            unroll<kKeys>([&](auto i) { fetch_key(raw_b, 1, i); });
+            first_values();
+            unroll<kKeys>([&](auto i) { fetch_key(raw_a, min(2, n_tiles - 1), i); });
+            __builtin_amdgcn_sched_barrier(0);
+            landed(std::integral_constant<int, 2 * kKeys>{});                // behind the keys of tiles 0 and 1: the values of 1 and 2
+        }
         read_q();
         written_barrier(std::integral_constant<int, 2 * kKeys>{});
     } else {

@@ -64,6 +64,15 @@ def test_dense_prefill_either_way(B, H, Tq, q_start):
     assert G.guards_intact(whole, (B, H, Tq, 128), float("nan"))
 
 
+@pytest.mark.parametrize("Tq,q_start", [(1, 0), (8, 5), (16, 0), (17, 47), (31, 33), (32, 32), (33, 0), (48, 16), (49, 15), (64, 0), (16, 49), (17, 100)])
+def test_short_blocks_of_one_tile_of_keys(Tq, q_start):
+    """One tile of keys has a start of its own, and up to 16 rows of a wave half of its stores (the last two: two tiles)."""
+    print(f"[prefill] Tq={Tq} q_start={q_start}", flush=True)
+    run_case(2, 9, 3, Tq, q_start, q_start + Tq + 3, seed=Tq + q_start)
+    test_dense_prefill_either_way(3, 5, Tq, q_start)         # converting values
+    test_dense_prefill_either_way(41, 50, Tq, q_start)       # two workgroups per CU, behind the pre-pass
+
+
 def test_prefill_direct_unassigned_heads_and_unused_slots():
     """Heads without a cluster, or of a cluster without a representative, keep their rows; the others' groups close ranks."""
     B, H, kk, Tq, q_start = 3, 23, 5, 70, 9

@@ -16,8 +16,9 @@ def __getattr__(name):
     if name == "binding":
         return binding
     if name in _BINDING_NAMES or name in binding.EXPORTS:
-        # Kept as an ordinary attribute: the next use does not come here again (an import statement's worth of look-ups, 5 us
-        # per call, as much as the smallest decode call takes on the GPU: 1 row x 32 fp32 heads, 256 tokens 10.5 -> 5.6 us).
+        # Kept as an ordinary attribute until it is replaced in the binding: the next use does not come here again (an import
+        # statement's worth of look-ups, 4 us per call, nearly as much as the smallest decode call takes on the GPU: 1 row x 32 fp32
+        # heads, 256 tokens 10.3 -> 6.6 us).
         value = globals()[name] = getattr(binding, name)
         return value
     raise AttributeError(f"module {__name__!r} has no attribute {name!r}")

@@ -9,6 +9,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import types
 from typing import Optional
 
 import torch
@@ -487,3 +489,27 @@ def alloc_workspace(B: int, H: int, k: int, T: int, d: int, dtype: int, device="
     """Device scratch of the size the decode calls ask for (torch allocations are 512-byte aligned)."""
     n = max(chai_decode_workspace_bytes(B, H, k, T, d, dtype), 256)
     return torch.empty((n,), dtype=torch.uint8, device=device)
+
+
+class _Binding(types.ModuleType):
+    """The package keeps names of this module as attributes of its own once they have been used: one that is replaced or
+    deleted here is forgotten there."""
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        _forget(name)
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        _forget(name)
+
+
+def _forget(*names):
+    package = vars(sys.modules[__package__])
+    for name in names:
+        if name in EXPORTS or name in package["_BINDING_NAMES"]:
+            package.pop(name, None)
+
+
+sys.modules[__name__].__class__ = _Binding
+_forget(*EXPORTS, *vars(sys.modules[__package__])["_BINDING_NAMES"])     # (this module was loaded anew)

@@ -158,3 +158,21 @@ def test_package_names_are_looked_up_once():
         assert vars(C)[name] is getattr(C.binding, name)
     with pytest.raises(AttributeError):
         C.no_such_entry_point
+
+
+def test_package_names_follow_the_binding(monkeypatch):
+    """A function that is replaced in the binding, after the package has used it, is replaced in the package, and back."""
+    import subprocess
+    import sys
+
+    import paper_2403_08058_amd as C
+    before = C.chai_version
+    with monkeypatch.context() as m:
+        m.setattr(C.binding, "chai_version", lambda: -1)
+        assert C.chai_version() == -1
+        m.setattr(C.binding, "CHAI_BF16", 17)
+        assert C.CHAI_BF16 == 17
+    assert C.chai_version is before and C.CHAI_BF16 == 1
+    code = ("import importlib, paper_2403_08058_amd as C; f = C.chai_version; importlib.reload(C.binding); "
+            "assert C.chai_version is C.binding.chai_version is not f and C.__spec__ is not None")
+    subprocess.run([sys.executable, "-c", code], check=True, cwd=ROOT, timeout=120)

@@ -235,7 +235,12 @@ constexpr size_t prefill_lds_bytes(bool ident, int bufs, int rows) { return pref
 // one group, the p-th largest and the p-th smallest: under the causal mask tile q walks q+1 key tiles' worth of work, so all
 // pairs cost the same.  The pairs that EXIST (the groups of all rows, counted here from the plan) are dealt to the XCDs in equal
 // contiguous ranges, so that the pairs of one group share its keys and values in one L2.  A queue has whole rounds of 32
-// pairs first; the last 32 to 63 pairs stand in it as single tiles, the largest first, which fills the last round.
+// pairs first; the last 32 to 63 pairs stand in it as single tiles, the largest first, which fills the last round.  The pairs of the
+// whole rounds stand there one by one while a group has fewer than 32 (fewer groups at a time: 834 MiB fetched for 16 rows x 2043
+// positions, 32 heads in 8 clusters, 1013 with a workgroup for every pair).  Longer prompts have the larger tiles of 32 pairs, then the
+// smaller ones, the last first: the CUs walk a group's keys side by side, which do not fit an L2 any more, and small tiles in
+// between would begin them anew (4 x 32 763 positions, 32 heads in clusters of 20, 6, 4 and 2 21.9 -> 20.8 ms, one row 5.6 -> 5.1; 16 379
+// 5.68 -> 5.35; with a workgroup for every pair 21.1, 5.2 and 5.48).
 // ---------------------------------------------------------------------------------------------------------
 constexpr int kXcdCus = 32;
 constexpr int kSmallTiles = 450, kFewTiles = 1450;      // see launch_prefill
@@ -284,11 +289,14 @@ __device__ __forceinline__ bool queue_item(const WorkQueue &w, int n_qt, unsigne
         return true;
     }
     if (i < 2 * (w.mid - w.lo)) {
-        const unsigned at = w.lo + i / 2;
+        // `block` pairs' larger tiles, then their smaller ones, the last pair's first
+        const unsigned block = w.n_pairs >= kXcdCus ? kXcdCus : 1, first = i / (2 * block) * block, r = i - 2 * first;
+        const bool small = r >= block;
+        const unsigned at = w.lo + first + (small ? 2 * block - 1 - r : r);
         group = at / w.n_pairs;
         const int pi = (int)(at - group * w.n_pairs);
-        qt = (i & 1) ? pi : n_qt - 1 - pi;
-        return !(i & 1) || n_qt - 1 - pi != pi;              // the middle tile of an odd count is alone
+        qt = small ? pi : n_qt - 1 - pi;
+        return !small || n_qt - 1 - pi != pi;                // the middle tile of an odd count is alone
     }
     unsigned j = i - 2 * (w.mid - w.lo);
     const unsigned m = w.n_first * w.n_pairs;

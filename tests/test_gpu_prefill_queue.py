@@ -10,7 +10,7 @@ if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
 import paper_2403_08058_amd as C
-from test_gpu_prefill import run_case
+from test_gpu_prefill import RTOL_PREFILL, run_case
 from test_gpu_prefill_direct import test_dense_prefill_either_way as dense_case
 
 
@@ -49,3 +49,33 @@ def test_tickets_start_anew_with_every_call():
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[2]) and torch.equal(outs[0], outs[4])
     assert not any(torch.isnan(o).any() for o in outs)
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("Tq,q_start", [(16128, 3), (16129, 0)])
+def test_prompts_of_thirty_two_pairs_of_tiles(Tq, q_start, dense):
+    """Long prompts' pairs stand in the queue by the round, odd and even numbers of tiles: the same rows as in blocks of a few tiles, whose
+    pairs stand there one by one.  Both round the probabilities to 11 bits and add in 32: each is within test_gpu_prefill's bound of the
+    exact row, and so within twice that of the other."""
+    B, H, kk, n = 1, 40, 8, q_start + Tq
+    g = torch.Generator(device="cuda").manual_seed(Tq)
+    normal = lambda *shape: torch.randn(shape, generator=g, device="cuda").bfloat16()  # noqa: E731
+    q, k, v = normal(B, H, Tq, 128), normal(B, H if dense else kk, n, 128), normal(B, H, n, 128)
+    rep = torch.arange(kk, dtype=torch.int32).repeat(B, 1).cuda()
+    h2c = torch.cat([torch.arange(kk), torch.arange(H - kk) % kk]).int().repeat(B, 1).cuda()
+    ws = torch.zeros(C.chai_prefill_workspace_bytes(B, H, H if dense else kk, n), dtype=torch.uint8, device="cuda")
+
+    def attention(qs, start, out):
+        if dense:
+            C.chai_dense_prefill_attention(qs, k, v, start, 0.0884, out, ws)
+        else:
+            C.chai_prefill_attention(qs, k, v, h2c, rep, start, 0.0884, out, ws)
+
+    whole = torch.full((B, H, Tq, 128), float("nan"), device="cuda")
+    attention(q, q_start, whole)
+    for i in range(0, Tq, 4096):
+        rows = q[:, :, i:i + 4096].contiguous()
+        part = torch.full((B, H, rows.shape[2], 128), float("nan"), device="cuda")
+        attention(rows, q_start + i, part)
+        err = (whole[:, :, i:i + 4096] - part).abs().amax(dim=-1) / part.abs().amax(dim=-1)
+        assert err.max() <= 2 * RTOL_PREFILL             # (false for a NaN)

@@ -899,7 +899,8 @@ int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, co
 // in use (if the rows' maps are independent: H (1 - (1 - k/H)^B), the maps themselves are on the device), how many tokens such a head
 // has, and the width, against the kernel that the call takes otherwise: project_rows_kernel up to 8 tokens over all rows,
 // 64-token tiles above.  The lines lie where the two were level over 14 000 calls drawn at random (1 to 64 tokens, 1 to 600 heads,
-// widths 64 to 9216, weights in no cache); right of them the other kernel is ahead in 1 call of 30, by 5 % or more in 1 of 80.
+// widths 64 to 9216, weights in no cache).  Of 3706 further ones 1645 are streamed, 1.56 times as fast on average; 4.9 % of these measured
+// more than 2 % slower than the other kernel, 1.2 % more than 5 %, 0.4 % more than 10 %.  Of the rest 4.2 % would gain 5 % or more.
 // Other kernel / this one in us, D = 4096 unless noted:
 // * up to 8 tokens: 1 x 1, 8 of 32 heads 12.0 / 7.3; 8 x 1, 72 of 72, D 9216 87.8 / 67.1; 4 x 1, 16 of 72, D 9216 41.8 / 30.4; 1 x 1, 128 of
 //   128, D 512 38.5 / 18.2; but 256 of 256, D 64 19.5 / 34.3, and 64 of 64, D 8192 52.4 / 63.5 (below).
@@ -912,27 +913,44 @@ int launch_mfma_probe(const void *buf, size_t bytes, int rounds, float *sink, co
 //   pairs for every 64 heads: 1 x 1, 2000 of 2000, D 512 161 / 4990.
 static bool project_streams(int B, int H, int k, int Tn, int D)
 {
-    const long long tokens = (long long)B * Tn, pairs = (long long)B * k, heads = H < pairs ? H : pairs;
+    const long long tokens = (long long)B * Tn, pairs = (long long)B * k;
     if (tokens > 64) return false;
-    if (pairs > kJtMaxSlots || (H > kJtMaxHeads && tokens > kJrTokens))
-        return heads <= 128 || (heads <= 320 && D >= (heads <= 200 ? 1024 : 8 * heads));
-    if (H > kJtMaxHeads && heads <= 128) return true;        // (the other kernel starts 16 workgroups for every head there is)
     const double used = H * (1.0 - pow(1.0 - (double)k / H, B)), each = (double)(pairs * Tn) / used;
-    if (tokens <= kJrTokens) {
-        // Eight units leave the rings two blocks.  With rows that all begin on the same memory channels that is not enough.
-        if (((used > 51.5 && used < 64.5) || (used > 102.5 && used < 128.5)) && D % 4096 == 0 && tokens <= D / 2048) return false;
-        return used < 256.5 && D >= (H <= 16 ? 2560 : (used < 8.5 ? 1024 : (used < 42.5 || used > 128.5 ? 512 : 256)));
+    const bool unlisted = pairs > kJtMaxSlots;
+    if (unlisted || (H > kJtMaxHeads && tokens > kJrTokens)) {
+        // No other kernel for few tokens: against 256-token tiles, by what either takes in us.  Here: launch and first ramp, the weights at
+        // 5.5 TB/s (again for more than 32 tokens of a head) or a ramp for every further round, and the look through the maps in every
+        // round, once per 64 heads and once per pass, 64 entries at a time beyond those that are requested at once.  There: rounds of
+        // tiles, each a chain along the width.  (Out by a quarter at most over 450 calls but where both take 8 us.)
+        const double rounds = ceil(used / 64 - 0.001), passes = ceil(each / kJsPass - 0.001), batches = pairs > 512 ? (pairs - 448) / 64.0 : 1.0;
+        const double weights = used * D * 9.3e-5 * passes, ramps = 7.0 * (rounds - 1);
+        const double here = 6.0 + (weights > ramps ? weights : ramps) + rounds * ((H + 63) / 64 + passes) * batches * 0.25;
+        const double there = (double)((pairs + kJCus - 1) / kJCus) * (0.0225 * D + 5.0);
+        return here < there;
     }
+    if (H > kJtMaxHeads && used < 128.5) return used < 32.5 || D >= 256;     // (the other kernel starts 16 workgroups for every head there is)
+    // Eight units leave the rings two blocks.  With rows that all begin on the same memory channels that is not enough.
+    const bool eight = (used > 60.5 && used < 64.5) || (used > 102.5 && used < 128.5);
+    if (eight && ((D % 8192 == 0 && tokens <= 16) || (D % 4096 == 0 && tokens <= 2))) return false;
     // at most so many heads in use, so many tokens of each, and at least this width
     struct Line {
         double used, each;
         int width;
     };
-    static const Line to32[] = {{16, 32, 1024}, {32, 16, 1536}, {32, 32, 2560}, {42, 4, 2048}, {42, 32, 2560},
-                                {51, 4, 2048},  {64, 2, 2048},  {64, 4, 2560},  {51, 8, 4096}, {85, 3, 4096}};
-    static const Line to64[] = {{8, 64, 2048}, {16, 32, 2560}, {16, 64, 5120}, {32, 17, 2560},
-                                {42, 8, 2560}, {64, 4, 2560},  {51, 8, 5120},  {85, 4, 4096}};
+    static const Line to16[] = {{16, 16, 1024}, {32, 16, 1280}, {42, 4, 2048}, {42, 16, 2560}, {51, 4, 2048},
+                                {64, 2, 2048},  {64, 4, 2560},  {51, 8, 4096}, {85, 2, 4096}};
+    static const Line to32[] = {{16, 32, 1024}, {32, 16, 1280}, {32, 32, 2112}, {42, 8, 2048}, {42, 32, 2560}, {51, 4, 1536},
+                                {51, 8, 2048},  {64, 4, 2048},  {85, 2, 2560},  {85, 4, 3072}, {128, 4, 5120}};
+    static const Line to64[] = {{8, 64, 2048}, {16, 32, 2176}, {16, 64, 4096}, {32, 17, 2304}, {42, 8, 2560},
+                                {64, 4, 2560}, {51, 8, 4096},  {85, 4, 3072},  {128, 2, 4096}};
     auto within = [&](const Line &l) { return used < l.used + 0.01 && each < l.each + 0.01 && D >= l.width; };
+    if (tokens <= kJrTokens) {
+        if (H <= 16) return D >= 2304;
+        if (used < 8.5) return D >= 640;
+        if (used < 42.5) return D >= 384;
+        return H > kJtMaxHeads ? used < 320.5 && D >= 512 : D >= (used < 200.5 ? 256 : 448);
+    }
+    if (tokens <= 16) return std::any_of(std::begin(to16), std::end(to16), within);
     return tokens <= 32 ? std::any_of(std::begin(to32), std::end(to32), within) : std::any_of(std::begin(to64), std::end(to64), within);
 }
 

@@ -19,16 +19,15 @@ from test_gpu_project import check_rounded, run_case
 
 
 @pytest.mark.parametrize("B,H,kk,Tn,D", [
-    (1, 32, 8, 1, 64), (1, 32, 9, 1, 128), (1, 40, 17, 1, 512),        # 8 heads in use: one unit each; 9, 17: two; 1, 2, 8 blocks
-    (1, 40, 24, 1, 576), (1, 32, 32, 1, 1088),                         # three units, the last part of two; four; 9, 17 blocks
+    # (most of the narrow ones go to the other kernels: the same sizes at widths that are streamed stand below)
+    (1, 32, 8, 1, 64), (1, 32, 9, 1, 128), (1, 40, 17, 1, 512),        # 17 heads in use: two units each; 8 blocks
+    (1, 40, 24, 1, 576), (1, 32, 32, 1, 1088),                         # four units; 9, 17 blocks
     (1, 52, 40, 2, 192), (1, 64, 51, 1, 704), (1, 80, 64, 1, 256),     # more heads than whole rounds of four units: up to eight
-    (1, 90, 72, 1, 320), (2, 300, 150, 1, 128),                        # two rounds; several, five windows of 64 heads
-    (1, 4, 3, 8, 192), (1, 4, 3, 9, 192), (1, 4, 3, 16, 192), (1, 4, 3, 17, 192),    # 8, 16 and 32 tokens at a time
-    (1, 4, 3, 32, 128), (1, 4, 3, 33, 128), (2, 4, 3, 32, 128),        # one pass and two
-    (1, 40, 40, 17, 128),                                              # 32 tokens at a time with six units
-    (5, 8, 8, 7, 128), (3, 6, 6, 21, 64),                              # passes that begin inside a row's tokens
-    (16, 40, 12, 2, 128), (16, 40, 13, 1, 128),                        # either side of the line to the 64-token tiles
-    (1, 40, 8, 64, 64), (8, 40, 9, 5, 64), (17, 33, 33, 3, 64),        # the same for more than 32 tokens
+    (1, 90, 72, 1, 320), (2, 300, 150, 1, 128),                        # two rounds
+    (1, 4, 3, 8, 192), (1, 4, 3, 9, 192), (1, 4, 3, 16, 192), (1, 4, 3, 17, 192),
+    (1, 4, 3, 32, 128), (1, 4, 3, 33, 128), (2, 4, 3, 32, 128),
+    (1, 40, 40, 17, 128), (5, 8, 8, 7, 128), (3, 6, 6, 21, 64),
+    (16, 40, 12, 2, 128), (16, 40, 13, 1, 128), (1, 40, 8, 64, 64), (8, 40, 9, 5, 64), (17, 33, 33, 3, 64),
     (64, 20, 17, 1, 64), (64, 4, 4, 1, 64),                            # more pairs than the 64-token tiles list; a quarter of what they do
     (1, 4200, 3, 2, 64),                                               # more heads than a wave's lanes have windows for
 ])
@@ -90,14 +89,16 @@ def test_streamed_projection_of_a_repeated_representative(B, H, kk, Tn, D, used,
 
 
 @pytest.mark.parametrize("B,H,kk,Tn,D", [
-    (1, 32, 8, 1, 1024), (1, 32, 8, 8, 960),                           # few heads: one unit each; just too narrow to be streamed
-    (1, 32, 9, 1, 512), (1, 32, 9, 3, 448), (1, 40, 17, 1, 576), (1, 40, 24, 1, 512), (1, 52, 40, 2, 512),
+    (1, 32, 8, 1, 640), (1, 32, 8, 8, 576),                           # few heads: one unit each; just too narrow to be streamed
+    (1, 32, 9, 1, 384), (1, 32, 9, 3, 320), (1, 40, 17, 1, 576), (1, 40, 23, 1, 512), (1, 52, 40, 2, 512),      # two units; three; six
     (1, 64, 51, 1, 256), (1, 64, 51, 1, 192), (1, 64, 64, 2, 4096), (1, 64, 64, 3, 4096),      # rows on the same memory channels
-    (1, 256, 200, 1, 512), (2, 300, 150, 1, 512), (1, 257, 128, 8, 64), (1, 600, 300, 4, 448),
-    (1, 4, 3, 8, 2560), (1, 4, 3, 9, 1024), (1, 4, 3, 16, 1024), (1, 4, 3, 17, 1024), (1, 4, 3, 32, 1024), (1, 4, 3, 32, 960),
-    (1, 4, 3, 33, 2048), (2, 4, 3, 32, 2048), (5, 8, 8, 7, 2048), (3, 6, 6, 21, 2048), (1, 40, 40, 17, 2560),
-    (16, 40, 12, 2, 2560), (16, 40, 12, 2, 2496), (1, 40, 8, 64, 2048), (1, 52, 51, 8, 4096), (1, 52, 52, 8, 4096),
+    (1, 256, 200, 1, 512), (2, 300, 150, 1, 512), (1, 257, 128, 8, 64), (1, 600, 300, 4, 448),                  # several rounds, windows
+    (1, 4, 3, 8, 2560), (1, 4, 3, 9, 1024), (1, 4, 3, 16, 1024), (1, 4, 3, 17, 1024),                           # 8, 16, 32 tokens at a time
+    (1, 4, 3, 32, 1024), (1, 4, 3, 32, 960), (1, 4, 3, 33, 2048), (2, 4, 3, 32, 2048),                          # one pass and two
+    (5, 8, 8, 7, 2048), (3, 6, 6, 21, 2048), (1, 40, 40, 17, 2560),                                             # passes inside a row's tokens
+    (16, 40, 12, 2, 2560), (16, 40, 12, 2, 2496), (3, 6, 6, 5, 1024), (3, 6, 6, 5, 960), (1, 40, 8, 64, 2048), (1, 52, 51, 8, 4096), (1, 52, 52, 8, 4096),
     (16, 72, 72, 1, 1088), (4, 300, 2, 4, 128), (2, 400, 200, 16, 576),      # no other kernel but 256-token tiles
+    (4, 300, 30, 3, 192), (4, 300, 30, 3, 256), (2, 300, 60, 4, 192), (2, 300, 60, 4, 256), (1, 64, 64, 2, 8192),
 ])
 def test_projection_on_either_side_of_the_lines(B, H, kk, Tn, D):
     print(f"[project] B={B} H={H} k={kk} tokens={Tn} width={D}", flush=True)

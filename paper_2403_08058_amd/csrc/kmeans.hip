@@ -410,9 +410,12 @@ __global__ __launch_bounds__(kKmThreads) void kmeans_kernel(const float *__restr
 //    list of members, four per word.
 //  * 1200 for barriers and the look for empty centres.
 // The numbering at the end ranks the centres by readlane in one wave; fp64 distances to the own centre, which the repair of empty
-// centres asks for, are taken there.  A pass takes 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
+// centres asks for, are taken there.  A pass took 4700 cycles (sums 1950, distances 1500, empty centres and ranks 770), and the
 // start 6000, most of it the latency of loading the features: 27.7 -> 19.2 us for 4 problems of 72 heads, 16 centres and 25
-// coordinates (seven passes), 8 of 128 heads 28.4 -> 26.9 in ten passes with the words of both masks requested at once; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  What is bound by
+// coordinates; one launch alone over 300 problems of 128 heads, 16 centres and 64 coordinates 228 -> 52 us.  With all words of both
+// masks requested at once (FEW) a call takes 5 to 8 % less: 4 x 72 heads in five, six and seven passes 14.7 -> 13.6, 16.9 -> 15.7 and 21.0
+// -> 19.7, 8 x 128 in ten 28.4 -> 26.9.  Sixteen members of a sum requested at a time, and distances in two chains of products, were
+// up to 4 % slower on more heads and no faster elsewhere.  What is bound by
 // launching (up to 40 heads) takes what it did.  Where most passes need the 64-bit distances of all centres (problems of a few tight
 // clusters) it is level with the general kernel: 71.9 and 71.6 us for 8 of 256 heads, 16 centres, 25 coordinates.
 // Dynamic LDS (FastLayout): centres [k][FP] fp64, features [H][FP] fp32, centres [16 n][C32] fp32, masks, lists of members, ...

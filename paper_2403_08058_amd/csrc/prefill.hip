@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) void prepass_kernel(const char *__restrict__ v
 // direct loads, requested in the first half of the tile; K runs ahead of V because the scores of a block are issued one
 // block before its softmax, and V lags because its products come one block after.  ONE barrier per tile.
 // Dense attention of thousands of heads over at most one tile of keys has rings of two (BUFS), 80 KB: it is all start and end,
-// and two workgroups on a CU cover each other's (64 x 72 heads of 24 keys 72 us, 79 us with one, values converted on the way).
+// and two workgroups on a CU cover each other's (64 x 72 heads of 24 keys 55 us, 67 us with one, values converted on the way).
 //
 // A score block is shared by TWO members.  Wider schemes were built on the kernel before and were slower: four members
 // through LDS (670-840 against 578 us per 8-cluster LLaMa-7B layer), three members in one wave (630 against 553 us).
@@ -1300,13 +1300,15 @@ __device__ __forceinline__ bool find_group(const int32_t *__restrict__ h2c, cons
 // spread over the slots of both blocks.  What it costs: 64 conversions' worth of instructions and 8 LDS writes per wave and tile
 // (about 400 cycles), loads to registers instead of to LDS (about 380, 8 requests of 1 KB each); a tile of 64 keys and two
 // members takes 3400 cycles, 2550 without all of it, of which the products are 1536: a lone wave's issue slots.  The call above
-// 93 -> 62 us; 507 positions behind 5 keys, 4 x 72 heads in 16 clusters 65 -> 55 us; 24 behind 4000, 16 x 32 in 8 401 -> 206 us.
+// 86 us with the pre-pass, 56 so; 507 positions behind 5 keys, 4 x 72 heads in 16 clusters 58 and 48 us; 24 behind 4000, 16 x 32 in 8 394
+// and 191 us.  One tile of keys has a start of its own, which requests no second one, and a wave of at most 16 rows leaves out half
+// of the stores: 37 x 12 positions, 128 heads in 8 clusters 62.3 -> 56.5 us.
 //
 // The groups of a row are found by every workgroup for itself (a launch for the work list would cost 5 us).  Workgroups are
 // numbered group by group, all rows of one before the next, the longest query tiles first: the XCDs get equal shares without
 // any of them knowing the other rows' groups.  (by_group: all query tiles of a group before the next group.  The groups that the
 // rows do not have are all at the end then, and the others' tiles fill the CUs of all XCDs alike: 1 row x 64 heads in 2 clusters, 862
-// positions behind 3018 keys, 33 groups of seven tiles, 144 -> 104 us, 112 with the pre-pass.)
+// positions behind 3018 keys, 33 groups of seven tiles, 144 -> 104 us when the tile took 3400 cycles; 100 now, 105 with the pre-pass.)
 // ---------------------------------------------------------------------------------------------------------
 template <bool IDENT>
 __global__ __launch_bounds__(256, 1) void prefill_direct_kernel(const char *__restrict__ q, const char *__restrict__ kc,
@@ -1371,27 +1373,29 @@ static int direct_groups(int H, int k, bool identity)
 // way at 6.5 TB/s, and 3 us); converting them in the 128-row tiles costs every tile of 64 keys 0.3 us per group of two members and
 // 0.15 us per head alone, in each query tile again, where longer calls have 256-row tiles, which are a fifth faster per row.
 // Whole calls, with pre-pass / direct in us:
-// * one or two query tiles: 4 rows x 52 heads in 8 clusters, 24 behind 0 / 400 / 1792 / 4000 keys 15 / 10, 28 / 19, 73 / 48 and 176 /
-//   100, 256 behind the same 26 / 19, 42 / 30, 95 / 64 and 183 / 124; 16 x 72 in 16, 128 behind 0 / 1792 56 / 43 and 403 / 193;
-//   dense, 16 x 32 heads, 24 behind 0 / 1792 19 / 11 and 188 / 94, 200 behind 0 / 400 / 1792 50 / 44, 90 / 91 and 242 / 230.  Not
+// * one or two query tiles: 4 rows x 52 heads in 8 clusters, 24 behind 0 / 400 / 1792 / 4000 keys 12 / 7, 30 / 16, 71 / 45 and 148 /
+//   90, 256 behind the same 23 / 14, 38 / 25, 86 / 56 and 168 / 115; 16 x 72 in 16, 128 behind 0 / 1792 43 / 32 and 396 / 189;
+//   dense, 16 x 32 heads, 24 behind 0 / 1792 13 / 9 and 191 / 90, 200 behind 0 / 400 / 1792 40 / 37, 82 / 74 and 235 / 225.  Not
 //   where a handful of heads makes the pre-pass cheap next to a long chain of tiles: 1 x 32 in 8, 24 behind 400 / 1792 / 4000
-//   21 / 18, 46.6 / 47.3 and 88 / 93; dense, 1 x 8, 128 behind 1000 / 2500 / 4000 29 / 27, 52.8 / 53.1 and 75 / 78.  Nor for blocks
-//   of at most one key tile on thousands of heads, which have two workgroups per CU (64 x 72, 24 keys 72 / 79, but 65 keys
-//   140 / 124, and 32 x 52, 24 keys 30 / 30).
-// * clustered, more: three 4 x 72 in 16, 384 behind 0 / 1792 46 / 36 and 173 / 146; four 4 x 72, 507 behind 0 / 1792 63 / 52 and
-//   218 / 189, 16 x 72 in 16, 507 behind 0 / 400 208 / 204 and 330 / 341; five 16 x 32 in 8, 600 behind 0 / 800 135 / 124 and 277 /
-//   257; six (three whole wide tiles) 4 x 52, 700 behind 0 / 800 69 / 62 and 133 / 121, 4 x 72, 700 behind 200 / 800 112 / 109 and
-//   164 / 171.  Each key tile behind costs seven query tiles seven conversions: 12 x 52 in 4, 860 behind 0 / 200 239 / 219 and 302 /
-//   276, but 3 x 72 in 8, 842 behind 1223 184 / 195, 9 x 52 in 8, 885 behind 555 270 / 296, 4 x 32 in 8, 872 behind 2090 164 / 189;
-//   eight 4 x 52, 1000 behind 0 96 / 90, but 6 x 52 in 4, 926 behind 0 119 / 125.  The lines from five tiles on lie where the two were
-//   level over a thousand calls of 8 to 128 heads in 2 to 32 clusters, 1 to 24 rows and 0 to 6000 keys behind, for each number of tiles;
-//   on either side of them one is up to 5 % ahead, and 12 % with seven or eight tiles.
-// * dense, more: while the tiles are one round of the chip (1 x 32, 1000 behind 0 / 800 30 / 26 and 46 / 41); beyond, three 6 x 52,
-//   300 behind 0 / 800 52 / 45 and 133 / 118, but just over one round 2 x 52, 384 behind 1792 / 4000 83 / 83 and 154 / 169, and on
-//   many heads 12 x 72, 384 behind 400 261 / 270; four 6 x 52, 400 behind 0 / 200 / 800 69 / 64, 91 / 89 and 150 / 155, 8 x 72, 400
-//   behind 0 112 / 115; five 4 x 52, 600 behind 0 / 200 72 / 67 and 90 / 92; six 2 x 52, 700 behind 0 44 / 39, 4 x 52, 733 behind 0
-//   77.8 / 78.5, 6 x 52 121 / 125; seven 2 x 52, 869 behind 0 51 / 46, 2 x 96 85 / 89, 6 x 52 149 / 157; eight 4 x 52, 1000 behind 0
-//   125 / 130.
+//   18 / 16, 48 / 44 and 87 / 89; dense, 1 x 8, 128 behind 1000 / 2500 / 4000 25 / 24, 48 / 49 and 72 / 74.  Nor for blocks
+//   of at most one key tile on thousands of heads, which have two workgroups per CU (64 x 72, 24 keys 55 / 67, but 65 keys
+//   153 / 114, and 32 x 52, 24 keys 30 / 28).
+// * clustered, more: three 4 x 72 in 16, 384 behind 0 / 1792 41 / 31 and 153 / 129; four 4 x 72, 507 behind 0 / 1792 57 / 43 and
+//   201 / 171, 16 x 72 in 16, 507 behind 0 / 400 178 / 174 and 299 / 312; five 16 x 32 in 8, 600 behind 0 / 800 108 / 98 and 243 /
+//   227; six (three whole wide tiles) 4 x 52 in 8, 700 behind 0 / 800 65 / 53 and 122 / 114, 4 x 72 in 16, 700 behind 200 / 800 96 / 104
+//   and 145 / 168.  Each key tile behind costs seven query tiles seven conversions: 12 x 52 in 4, 860 behind 0 / 200 200 / 186 and 257 /
+//   251, but 3 x 72 in 8, 842 behind 1223 174 / 188, 9 x 52 in 8, 885 behind 555 259 / 300, 4 x 32 in 8, 872 behind 2090 161 / 188;
+//   eight 4 x 52 in 8, 1000 behind 0 83 / 80, but 6 x 52 in 4, 926 behind 0 114 / 118.
+// * dense, more: while the tiles are one round of the chip (1 x 32, 1000 behind 0 / 800 30 / 23 and 45 / 38); beyond, three 6 x 52,
+//   300 behind 0 / 800 44 / 39 and 118 / 98, but just over one round 2 x 52, 384 behind 1792 / 4000 76 / 76 and 146 / 153, and on
+//   many heads 12 x 72, 384 behind 400 230 / 252; four 6 x 52, 400 behind 0 / 200 / 800 59 / 56, 79 / 82 and 140 / 136, 8 x 72, 400
+//   behind 0 94 / 100; five 4 x 52, 600 behind 0 / 200 63 / 57 and 78 / 82; six 2 x 52, 700 behind 0 38 / 35, 4 x 52, 733 behind 0
+//   70 / 72, 6 x 52 102 / 111; seven 2 x 52, 869 behind 0 49 / 44, 2 x 96 81 / 87, 6 x 52 133 / 141; eight 4 x 52, 1000 behind 0
+//   108 / 116.
+// The lines were drawn with kernels of which the direct one was 4 to 10 % slower and the other, without a queue, up to 13 %.  Of 1171
+// clustered and 631 dense calls drawn at random (8 to 128 heads, 1 to 24 rows, up to 1024 positions behind up to 6000 keys) 2.6 and 2.9 %
+// are more than 3 % slower than the other way, mostly with five to seven query tiles and just beyond one round of the chip (17 x 709
+// behind 87, 64 in 4 283 / 331, dense 1 x 987, 40 heads 30 / 23); against the pre-pass everywhere they take 1 / 1.43 and 1 / 1.35.
 static bool prefill_is_direct(int B, int H, int k, int Tq, int q_start, bool identity)
 {
     const long long heads = (long long)B * H, n_keys = (long long)q_start + Tq;
@@ -1468,25 +1472,24 @@ int launch_prefill(const void *q, const void *kc, const void *v, const int32_t *
     if (e != hipSuccess) return (int)e;
     // Tiles of 256 or of 128 query rows: 128 where the wide tiles would leave CUs without work or end in a ragged last round,
     // and where a block has no more rows than that.  The lines lie at a number of 256-row tiles of the most groups the maps
-    // can have.  Whole calls with 256 / 128 rows: clustered, at 136 tiles 118 / 97 us, at 384 164 / 153 us and 71 / 66 us, at
-    // 440 28 / 25 us, at 416 81 / 86 us and 110 / 103 us, at 576 129 / 148 us, at 1280 472 / 567 us, 65 rows at 960 tiles
-    // 81 / 73 us.  Five narrow tiles are half a wide tile less and leave no wide one without its pair: 513 positions, 30 rows x 32
-    // heads in 8 clusters 240 / 225 us, 12 x 52 in 8 157 / 145, 16 x 52 in 4 204 / 181, 64 x 32 in 8 489 / 466, behind 200
-    // 606 / 582, 16 x 72 in 16 behind 1000 643 / 620.  So are three, where launch and block are short: 257 positions, 12 x 52
-    // and 30 x 32 (816 and 1440 tiles) 85 / 78 and 127 / 118, behind 128 101 / 93 and 154 / 142, behind 200 level, but 16 x 72
-    // in 16 (1664 tiles) 143 / 143 and with 300 positions 152 / 157, 64 x 32 (3072) 233 / 251.  Six against three wide ones
-    // only between 900 and 1450: 768 positions, 16 x 52 in 4 (1440) 282 / 268, 16 x 32 in 4 (960) 173 / 168, but 8 x 52 (720)
-    // 134 / 140, and 641 positions, 64 x 32 in 8 (4608) 576 / 594.  Seven: 769 positions 340 / 359.  (Of three and five tiles what is
+    // can have; they were drawn when every workgroup took a pair of tiles.  Since workgroups draw tiles from a queue, which does away
+    // with ragged rounds, they send many calls of five and six narrow tiles the wrong way.  Whole calls with 256 / 128 rows, in us:
+    // five narrow tiles, 513 positions, 12 rows x 52 heads in 8 clusters 122 / 115, 16 x 52 in 4 155 / 146, 30 x 32 in 8 190 / 191, but 64 x
+    // 32 in 8 380 / 394, behind 200 498 / 533, 16 x 72 in 16 behind 1000 550 / 589.  Three, where launch and block are short: 257
+    // positions, 12 x 52 and 30 x 32 in 8 (816 and 1440 tiles) 74 / 62 and 107 / 90, behind 128 88 / 76 and 131 / 118, behind 200 99 /
+    // 87 and 146 / 135, 16 x 72 in 16 (1664 tiles) 118 / 109 and with 300 positions 126 / 117, 64 x 32 (3072) 207 / 196.  Six against
+    // three wide ones between 900 and 1450: 768 positions, 16 x 52 in 4 (1440) 203 / 224, 16 x 32 in 4 (960) 131 / 140, 8 x 52 (720)
+    // 110 / 108, and 641 positions, 64 x 32 in 8 (4608) 444 / 523.  (Of three and five tiles what is
     // left here is past the lines of prefill_is_direct, or of more heads or clusters than it takes: 1 x 260 in 4, 300 positions.)
-    // Dense: up to 128 wide tiles the narrow ones are one round too, above 256 the wide ones fill the chip better (at 4096
-    // 783 / 914 us).  Between, two narrow tiles share a CU one after the other, the longest with the shortest: the second
+    // Dense: up to 128 wide tiles the narrow ones are one round too, above 256 the wide ones fill the chip better.
+    // Between, two narrow tiles share a CU one after the other, the longest with the shortest: the second
     // round starts with the 256-th longest, 128 * 256 / heads keys below the longest.  With 7 us for a start and 20 against 30
     // ns per key of a narrow and a wide tile, two of those take less than one wide tile where
     // heads * (4 (q_start + Tq in whole tiles) - 3 keys + 700) <= 131072.  Wide / narrow: one query tile per head, 256 keys,
-    // 160 / 192 / 256 heads 26.8 / 27.0, 27.3 / 28.4, 30.8 / 34.1 us, 256 behind 1000 keys 84 / 98; two tiles, 512 keys,
-    // 72 / 96 / 128 heads 31.3 / 26.5, 32.2 / 30.5, 33.9 / 35.8; four, 64 heads 45.3 / 42.5, behind 1000 keys 71 / 80; eight,
-    // 32 heads 69 / 61, behind 1000 keys 101 / 98.  Blocks of up to 128 rows fill half a wide tile: 512 heads, 100 rows
-    // 40.0 / 39.4, 24 rows level.
+    // 160 / 192 / 256 heads 22.9 / 24.4, 23.9 / 25.7, 27.0 / 31.1 us, 256 behind 1000 keys 78 / 89; two tiles, 512 keys,
+    // 72 / 96 / 128 heads 26.3 / 23.9, 27.8 / 27.5, 30.1 / 34.0; four, 1000 keys, 64 heads 40.3 / 41.2, behind 1000 73 / 77; eight, 2000,
+    // 32 heads 62 / 56, behind 1000 91 / 91.  Blocks of up to 128 rows fill half a wide tile: 512 heads, 100 rows
+    // 27.0 / 27.2, 24 rows 16.3 / 12.8.
     const long long tiles = (long long)((Tq + 255) / 256) * max_groups * B;
     const int n_narrow = (Tq + 127) / 128;
     bool small = Tq <= 128 || tiles <= (identity ? 128 : kSmallTiles);
